@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256) void route_topk_keys_kernel(const float *__res
 
 // WAVES: resident wavefronts per SIMD the register allocation is held to.
 // FULL: E == LANES * VPL, every load is in range (rows beyond the last repeat the last row and are not stored).
-template <int LANES, int VPL, int L, int WAVES, bool FULL>
+template <int LANES, int VPL, int L, int KM, int WAVES, bool FULL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8))) void route_topk_insert_kernel(
     const float *__restrict__ logits, int64_t rows, int E, int k, int32_t *__restrict__ topk_idx, int wide_store)
 {
@@ -257,12 +257,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
 
     float4 x[VPL / 4];
     row_load<LANES, VPL, FULL>(logits + (live ? row : rows - 1) * E, E, q, x);
-    float own[L];
-    lane_best<LANES, VPL, L>(x, q, own);
-    unsigned u[8];
-    const bool bad = row_best8<LANES, VPL, L>(own, k, u);
+    int own[L];
+    unsigned bits;
+    lane_best<LANES, VPL, L, FULL>(x, E, q, own, bits);
+    unsigned u[KM];
+    const bool bad = row_best<LANES, VPL, L, KM>(own, bits, k, u);
     if (__ballot(live && bad) == 0ull) {
-        store_best8<LANES, MASK>(topk_idx, row, k, q, live, wide_store, u);
+        store_best<LANES, MASK, KM>(topk_idx, row, k, q, live, wide_store, u);
         return;
     }
     // rare: the wavefront's rows are read again and picked by full comparisons
@@ -271,7 +272,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
     });
 }
 
-template <int LANES, int VPL, int L, int WAVES>
+template <int LANES, int VPL, int L, int KM, int WAVES>
 static int launch_topk_insert(const float *logits, int64_t rows, int E, int k, int32_t *out, hipStream_t st)
 {
     constexpr int ROWS_PER_BLOCK = 4 * (64 / LANES);
@@ -279,9 +280,9 @@ static int launch_topk_insert(const float *logits, int64_t rows, int E, int k, i
     if (blocks > 0x7FFFFFFFll) return RAILSCHED_ERR_UNSUPPORTED;
     const int wide_store = reinterpret_cast<uintptr_t>(out) % 16 == 0 ? 1 : 0;
     if (E == LANES * VPL)
-        hipLaunchKernelGGL((route_topk_insert_kernel<LANES, VPL, L, WAVES, true>), dim3((unsigned)blocks), dim3(256), 0, st, logits, rows, E, k, out, wide_store);
+        hipLaunchKernelGGL((route_topk_insert_kernel<LANES, VPL, L, KM, WAVES, true>), dim3((unsigned)blocks), dim3(256), 0, st, logits, rows, E, k, out, wide_store);
     else
-        hipLaunchKernelGGL((route_topk_insert_kernel<LANES, VPL, L, WAVES, false>), dim3((unsigned)blocks), dim3(256), 0, st, logits, rows, E, k, out, wide_store);
+        hipLaunchKernelGGL((route_topk_insert_kernel<LANES, VPL, L, KM, WAVES, false>), dim3((unsigned)blocks), dim3(256), 0, st, logits, rows, E, k, out, wide_store);
     return launch_status();
 }
 
@@ -322,12 +323,21 @@ extern "C" int railsched_route_topk(const float *logits, int64_t rows, int32_t E
     if (!logits || !topk_idx) return RAILSCHED_ERR_NULL_PTR;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool vec4 = (E % 4 == 0) && (reinterpret_cast<uintptr_t>(logits) % 16 == 0);
-    if (vec4 && E > 32 && E <= 64 && k <= 8) return launch_topk_insert<4, 16, 8, 6>(logits, rows, E, k, topk_idx, st);
+    // Insertion lists up to k = 8 (k = 16 where a row has more than 256 logits), 16 logits per lane up to 256 and whole rows of 16 lanes
+    // above: fewer logits per lane are more wavefronts with less in flight each.  Lists are as short as leave a lane whose list
+    // is all winners rare (under one row in a thousand on shuffled logits).  us for 8 388 608 x 128 top-8: 843 with 32 logits per lane, 716
+    // with 16, 1000 with 8; 4 194 304 x 256 top-8: 745 / 704; 524 288 x 512 top-10: 640 by rounds, 210 with 64 per lane, 198 with 32;
+    // top-8 540 / 190 / 179; top-16 990 / 263 / 247; 262 144 x 1024 top-10: 457 by rounds, 207.  Larger k stays with the rounds.
+    if (vec4 && E > 32 && E <= 64 && k <= 8) return launch_topk_insert<4, 16, 8, 8, 6>(logits, rows, E, k, topk_idx, st);
     if (vec4 && E > 32 && E <= 64 && k <= 16) return launch_topk_keys<16, 4>(logits, rows, E, k, topk_idx, st);
-    if (vec4 && E > 64 && E <= 128 && k <= 8) return launch_topk_insert<4, 32, 8, 6>(logits, rows, E, k, topk_idx, st);
+    if (vec4 && E > 64 && E <= 128 && k <= 8) return launch_topk_insert<8, 16, 6, 8, 6>(logits, rows, E, k, topk_idx, st);
     if (vec4 && E > 64 && E <= 128 && k <= 32) return launch_topk_keys<32, 4>(logits, rows, E, k, topk_idx, st);
-    if (vec4 && E > 128 && E <= 256 && k <= 8) return launch_topk_insert<8, 32, 6, 5>(logits, rows, E, k, topk_idx, st);
+    if (vec4 && E > 128 && E <= 256 && k <= 8) return launch_topk_insert<16, 16, 5, 8, 6>(logits, rows, E, k, topk_idx, st);
     if (vec4 && E > 128 && E <= 256 && k <= 64) return launch_topk_keys<64, 4>(logits, rows, E, k, topk_idx, st);
+    if (vec4 && E > 256 && E <= 512 && k <= 8) return launch_topk_insert<16, 32, 5, 8, 4>(logits, rows, E, k, topk_idx, st);
+    if (vec4 && E > 256 && E <= 512 && k <= 16) return launch_topk_insert<16, 32, 7, 16, 4>(logits, rows, E, k, topk_idx, st);
+    if (vec4 && E > 512 && k <= 8) return launch_topk_insert<16, 64, 5, 8, 4>(logits, rows, E, k, topk_idx, st);
+    if (vec4 && E > 512 && k <= 16) return launch_topk_insert<16, 64, 7, 16, 4>(logits, rows, E, k, topk_idx, st);
     if (E <= 4) return launch_topk<1, 4>(logits, rows, E, k, topk_idx, st);
     if (E <= 8) return launch_topk<1, 8>(logits, rows, E, k, topk_idx, st);
     if (E <= 16) return launch_topk<4, 4>(logits, rows, E, k, topk_idx, st);

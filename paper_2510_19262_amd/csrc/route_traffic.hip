@@ -12,9 +12,9 @@
 // insertion kernel of stage 1 with the same addition - once the lanes of a row hold its winners, lane j looks up
 // the destination of winner j and bumps its bin.  A workgroup walks a few hundred consecutive tokens of one pair
 // so that its G counts are a small share of the logits it read.  When the indices are wanted the two stages run
-// back to back instead: measured on 4 194 304 rows of 256 logits, top-8, the one-pass kernel takes 0.74 ms without
+// back to back instead: measured on 4 194 304 rows of 256 logits, top-8, the one-pass kernel takes 0.72 ms without
 // and 0.80 ms with the index stores (its workgroups live eight times longer than stage 1's, which ends the launch
-// on a longer tail), the two separate kernels 0.72 + 0.04 ms.  Other shapes always run the two stages.
+// on a longer tail), the two separate kernels 0.70 + 0.03 ms.  Other shapes always run the two stages.
 //
 // Short-lived workgroups of one or a few rounds of 512 tokens stream best, so a pair's tokens are cut
 // into many slices; each slice leaves its G counts in the workspace with plain stores and a second,
@@ -261,19 +261,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
                 if ((unsigned)d < (unsigned)a.G) atomicAdd(&bins[d], 1u);
             }
         };
-        float own[L];
-        lane_best<LANES, VPL, L>(x, q, own);
+        int own[L];
+        unsigned bits;
+        lane_best<LANES, VPL, L, FULL>(x, a.E, q, own, bits);
         // the next row group's logits are requested as soon as this one's are consumed
         if (it + 1 < a.iters) row_load<LANES, VPL, FULL>(pair_logits + clamp_token(t + RPB) * a.E, a.E, q, x);
         unsigned u[8];
-        const bool bad = row_best8<LANES, VPL, L>(own, a.k, u);
+        const bool bad = row_best<LANES, VPL, L, 8>(own, bits, a.k, u);
         if (__ballot(live && bad) == 0ull) {
 #pragma unroll
             for (int r = 0; r < (8 + LANES - 1) / LANES; ++r) {          // winners q, q+LANES, ... are counted by this lane
                 unsigned sel = 0;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) sel = (j == q + r * LANES) ? u[j] : sel;
-                if (live && q + r * LANES < a.k) count((int)(sel & MASK));
+                if (live && q + r * LANES < a.k) count((int)key_index<MASK>(sel));
             }
         } else {
             // rare: the wavefront's rows are read again and picked by full comparisons
@@ -290,11 +291,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
     }
 }
 
-// row groups per workgroup: enough tokens that the G counts a workgroup leaves behind are under a hundredth of the logits it read
+// row groups per workgroup: enough tokens that the G counts a workgroup leaves behind are under a two-hundredth of the logits it read (twice that share: 2-6 % slower)
 static int rw_iters(int64_t tokens_per_gpu, int64_t G, int E, int rows_per_group)
 {
     int64_t it = 1;
-    while (it * rows_per_group * E < 128 * G && it * rows_per_group < tokens_per_gpu) it *= 2;
+    while (it * rows_per_group * E < 256 * G && it * rows_per_group < tokens_per_gpu) it *= 2;
     return (int)it;
 }
 
@@ -313,13 +314,16 @@ static int launch_route_traffic_insert(RwArgs a, int64_t pairs, hipStream_t st)
     return launch_status();
 }
 
+// lanes per row of the one-pass kernel: 16 logits per lane, as in stage 1
+static int rw_lanes(int E) { return E <= 64 ? 4 : E <= 128 ? 8 : 16; }
+
 // shape of the one-pass kernel for rows of 33..256 logits; false: the two stages run back to back
 static bool rw_shape(const float *logits, int32_t E, int32_t k, int64_t G, int *lanes)
 {
     const bool vec4 = (E % 4 == 0) && (reinterpret_cast<uintptr_t>(logits) % 16 == 0);
     if (!vec4 || E <= 32 || E > 256 || k > 8) return false;
     if (4 * G > 16 * 1024) return false;            // the destination counts of a workgroup live in LDS
-    *lanes = E <= 128 ? 4 : 8;
+    *lanes = rw_lanes(E);
     return true;
 }
 
@@ -349,7 +353,7 @@ extern "C" size_t railsched_route_traffic_workspace_bytes(int32_t batch, int64_t
     if (E > 8) {
         // the larger of what the one-pass kernel for 33..256 logits and the two-stage path would need
         size_t need = railsched_traffic_matrix_workspace_bytes(batch, tokens_per_gpu, k, h_topo);
-        const int rpg = 4 * (64 / (E <= 128 ? 4 : 8));
+        const int rpg = 4 * (64 / rw_lanes(E));
         if (E > 32 && E <= 256 && k <= 8 && pairs > 0 && 4 * G <= 16 * 1024) {
             const int64_t rb = (int64_t)rw_iters(tokens_per_gpu, G, E, rpg) * rpg;
             const int64_t splits = (tokens_per_gpu + rb - 1) / rb;
@@ -402,8 +406,8 @@ extern "C" int railsched_route_traffic(const float *logits, int32_t batch, int64
         hipStream_t st = static_cast<hipStream_t>(stream);
         int rc;
         if (E <= 64) rc = launch_route_traffic_insert<4, 16, 8, 6>(a, pairs, st);
-        else if (E <= 128) rc = launch_route_traffic_insert<4, 32, 8, 4>(a, pairs, st);
-        else rc = launch_route_traffic_insert<8, 32, 6, 4>(a, pairs, st);
+        else if (E <= 128) rc = launch_route_traffic_insert<8, 16, 6, 6>(a, pairs, st);
+        else rc = launch_route_traffic_insert<16, 16, 5, 6>(a, pairs, st);
         if (rc) return rc;
         if (splits > 1) return launch_count_reduce(a.partial, D1, pairs * G, (int)G, (int)splits, payload_bytes, st);
         return RAILSCHED_OK;

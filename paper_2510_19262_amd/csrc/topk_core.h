@@ -55,93 +55,115 @@ __device__ __forceinline__ void group_argmax(float &bv, int &bi)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Insertion kernels for k <= 8 and rows of 64..256 logits: no rounds and no sorting networks.
+// Insertion kernels for rows of 33..1024 logits and k <= KM (8 or 16): no rounds and no sorting networks.
 //
-// Keys are floats.  A logit keeps its sign, exponent and upper mantissa bits and takes its expert index into the
-// low IDXBITS bits of the mantissa, so every key of a row is a different finite float, ordinary float comparison
-// orders keys by their "cut" value, and the index comes back with one AND.  (-0 becomes +0 first, by adding +0.)
-// The index bits are never trusted to order two logits of the same cut value: such rows are found and redone
-// exactly, see below.  Two instructions per logit.
+// Keys are signed integers.  The order-preserving integer image of a logit keeps its upper bits and takes
+// MASK - (expert index) into its low IDXBITS bits, so every key of a row is different, larger keys are larger cut values
+// and, between equal cut values, lower expert indices, and the index comes back with one AND.  Four instructions per logit.
+// The cut loses nothing when the bits it drops are zero in the whole row - logits that a gate computed in bf16 (16 zero
+// bits) or any other short format - and then key order IS the exact order, ties included.  Otherwise the index bits are
+// not trusted to order two logits of the same cut value: such rows are found and redone exactly, see below.
 // A lane keeps the L largest keys it has seen as a descending list in registers.  Inserting x into a >= b >= c...
 // is one instruction per entry: the new i-th entry is the median of (old entry i-1, old entry i, x), the new head
-// max(head, x).  Then the LANES lanes of a row merge pairwise, log2(LANES) times, each keeping the 8 largest of
-// its own and its partner's list (max(a[i], b[7-i]) is that set as a bitonic sequence; three exchange layers sort
-// it); both partners end with the same list, so finally every lane of the row holds the row's 8 largest keys.
-// The result is exact unless (a) two of those 8, or the k-th winner and a key that lost, share a cut value, or
-// (b) a lane's whole list ended up among the winners, so that a key it dropped might have belonged there too (or
-// be the best loser).  Both are tested on L + 8 registers; a wavefront with such a row re-reads its rows and picks
-// by full (value, index) comparisons - rows full of exact ties take that path, continuous logits almost never do.
+// max(head, x).  Then the LANES lanes of a row merge pairwise, log2(LANES) times, each keeping the KM largest of
+// its own and its partner's list (max(a[i], b[KM-1-i]) is that set as a bitonic sequence; log2(KM) exchange layers sort
+// it); both partners end with the same list, so finally every lane of the row holds the row's KM largest keys.
+// The result is exact unless (a) the cut lost something and two neighbours among the k winners and the best loser share a
+// cut value, or (b) a lane's whole list ended up among the winners, so that a key it dropped might have belonged there too.
+// (A dropped key that shares the k-th winner's cut value is below the lane's last entry, which then shares it as well,
+// and so does the best loser.)  A wavefront with such a row re-reads its rows and picks by full (value, index) comparisons.
+// 4 194 304 rows of 64 logits from a bf16 gate, top-6, where most wavefronts hold a tie: 0.39 ms when every tie took the full
+// comparisons, 0.21 now.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ float fmed3(float a, float b, float c) { return __builtin_amdgcn_fmed3f(a, b, c); }
+__device__ __forceinline__ int imed3(int a, int b, int c)
+{
+    int r;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
 
 // x into the descending list a[0..HAVE) (a[0..L) once it is full)
 template <int L, int HAVE>
-__device__ __forceinline__ void list_insert(float (&a)[L], float x)
+__device__ __forceinline__ void list_insert(int (&a)[L], int x)
 {
     if constexpr (HAVE == 0) {
         a[0] = x;
     } else {
-        if constexpr (HAVE < L) a[HAVE] = fminf(a[HAVE - 1], x);
+        if constexpr (HAVE < L) a[HAVE] = min(a[HAVE - 1], x);
 #pragma unroll
-        for (int i = (HAVE < L ? HAVE - 1 : L - 1); i >= 1; --i) a[i] = fmed3(a[i - 1], a[i], x);   // old a[i-1]: bottom first
-        a[0] = fmaxf(a[0], x);
+        for (int i = (HAVE < L ? HAVE - 1 : L - 1); i >= 1; --i) a[i] = imed3(a[i - 1], a[i], x);   // old a[i-1]: bottom first
+        a[0] = max(a[0], x);
     }
 }
 
-__device__ __forceinline__ void fsort2_desc(float &a, float &b)
+// a bitonic sequence of N (a power of two) into descending order
+template <int N>
+__device__ __forceinline__ void bitonic_desc(int (&a)[N])
 {
-    const float hi = fmaxf(a, b), lo = fminf(a, b);
-    a = hi; b = lo;
-}
-
-// a bitonic sequence of 8 into descending order
-__device__ __forceinline__ void bitonic8_desc(float (&a)[8])
-{
-    fsort2_desc(a[0], a[4]); fsort2_desc(a[1], a[5]); fsort2_desc(a[2], a[6]); fsort2_desc(a[3], a[7]);
-    fsort2_desc(a[0], a[2]); fsort2_desc(a[1], a[3]); fsort2_desc(a[4], a[6]); fsort2_desc(a[5], a[7]);
-    fsort2_desc(a[0], a[1]); fsort2_desc(a[2], a[3]); fsort2_desc(a[4], a[5]); fsort2_desc(a[6], a[7]);
+#pragma unroll
+    for (int d = N / 2; d >= 1; d /= 2)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if ((i & d) == 0) {
+                const int hi = max(a[i], a[i + d]), lo = min(a[i], a[i + d]);
+                a[i] = hi; a[i + d] = lo;
+            }
 }
 
 template <int OFF>
-__device__ __forceinline__ float from_partner(float v)
+__device__ __forceinline__ int from_partner(int v)
 {
     constexpr int CTRL = OFF == 1 ? 0xB1 : OFF == 2 ? 0x4E : OFF == 4 ? 0x141 : 0x140;
-    return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, true));
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
 }
 
-// the 8 largest of this lane's and its partner's descending lists of LEN entries (entries LEN..7 count as lowest);
+constexpr int kNoKey = INT_MIN;                     // below the key of every logit
+
+// the KM largest of this lane's and its partner's descending lists of LEN entries (entries LEN..KM-1 count as lowest);
 // both partners end with the same list
-template <int OFF, int LEN>
-__device__ __forceinline__ void merge_lists(const float (&a)[LEN], float (&out)[8])
+template <int OFF, int LEN, int KM>
+__device__ __forceinline__ void merge_lists(const int (&a)[LEN], int (&out)[KM])
 {
     static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8, "exchanges inside a row of 16 lanes");
-    static_assert(LEN >= 4 && LEN <= 8, "lists of 4..8 keys");
+    static_assert(LEN <= KM, "lists of at most KM keys");
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        if (i < 8 - LEN) out[i] = a[i];                               // the partner has nothing to set against it
-        else if (i >= LEN) out[i] = from_partner<OFF>(a[7 - i]);     // nor this lane against the partner's
-        else out[i] = fmaxf(a[i], from_partner<OFF>(a[7 - i]));      // folds into one v_max_f32 with a DPP operand
+    for (int i = 0; i < KM; ++i) {
+        const bool own = i < LEN, theirs = KM - 1 - i < LEN;
+        if (own && theirs) out[i] = max(a[i], from_partner<OFF>(a[KM - 1 - i]));   // folds into one v_max_i32 with a DPP operand
+        else if (own) out[i] = a[i];                                  // the partner has nothing to set against it
+        else if (theirs) out[i] = from_partner<OFF>(a[KM - 1 - i]);  // nor this lane against the partner's
+        else out[i] = kNoKey;
     }
-    bitonic8_desc(out);
+    bitonic_desc<KM>(out);
 }
 
-// key of a logit: cut value in the upper bits, expert index below.  lane_field has ones above the index bits and
-// the lane's share of the index inside them; SLOT (a constant) likewise with the slot's share; the two never
-// have an index bit in common.  One bit operation: (v & lane & slot) | (lane ^ slot).
+// key of a logit whose bits (-0 made +0) are c: lane_field has ones above the index bits and the lane's share of the index
+// inside them; SLOT (a constant) likewise with the slot's share; the two never have an index bit in common.
 template <unsigned SLOT>
-__device__ __forceinline__ float make_fkey(float f, unsigned lane_field)
+__device__ __forceinline__ int make_ikey(unsigned c, unsigned lane_field)
 {
-    return __uint_as_float(__builtin_amdgcn_bitop3_b32(__float_as_uint(f + 0.0f), lane_field, SLOT, 0xE6));
+    const unsigned sign = (unsigned)((int)c >> 31);
+    const unsigned ord = __builtin_amdgcn_bitop3_b32(c, sign, 0x7FFFFFFFu, 0x78);       // c ^ (sign & 0x7FFFFFFF): monotone
+    return (int)__builtin_amdgcn_bitop3_b32(ord, lane_field, SLOT, 0x91);               // (ord & lane & slot) | ~(lane | slot)
 }
+// expert index of a key
+template <unsigned MASK>
+__device__ __forceinline__ unsigned key_index(unsigned u) { return ~u & MASK; }
 
-template <int LANES, int VPL, int L, unsigned MASK, int C, int J>
-__device__ __forceinline__ void insert_loaded(const float4 (&x)[VPL / 4], unsigned lane_field, float (&lst)[L])
+// has(C): the row has logits at float4 C of this lane (false only where E < LANES * VPL)
+template <int LANES, int VPL, int L, unsigned MASK, bool FULL, int C, int J>
+__device__ __forceinline__ void insert_loaded(const float4 (&x)[VPL / 4], unsigned lane_field, int E, int q, int (&lst)[L], unsigned &bits)
 {
     if constexpr (C < VPL / 4) {
         constexpr unsigned SLOT = ~MASK | (unsigned)(4 * LANES * C + J);
         const float v = J == 0 ? x[C].x : J == 1 ? x[C].y : J == 2 ? x[C].z : x[C].w;
-        list_insert<L, (4 * C + J < L ? 4 * C + J : L)>(lst, make_fkey<SLOT>(v, lane_field));
-        insert_loaded<LANES, VPL, L, MASK, (J == 3 ? C + 1 : C), (J == 3 ? 0 : J + 1)>(x, lane_field, lst);
+        const unsigned c = __float_as_uint(v + 0.0f);
+        bits |= c;
+        int key = make_ikey<SLOT>(c, lane_field);
+        if constexpr (!FULL) key = 4 * (q + LANES * C) < E ? key : kNoKey;
+        list_insert<L, (4 * C + J < L ? 4 * C + J : L)>(lst, key);
+        if constexpr (J == 3 && VPL >= 32) __builtin_amdgcn_sched_barrier(0);   // keys of later logits made early would only take registers
+        insert_loaded<LANES, VPL, L, MASK, FULL, (J == 3 ? C + 1 : C), (J == 3 ? 0 : J + 1)>(x, lane_field, E, q, lst, bits);
     }
 }
 
@@ -156,77 +178,88 @@ __device__ __forceinline__ unsigned min_xor_dist(unsigned m, unsigned a, unsigne
 template <int LANES, int VPL, bool FULL>
 __device__ __forceinline__ void row_load(const float *__restrict__ row_logits, int E, int q, float4 (&x)[VPL / 4])
 {
-    const float lowest = -FLT_MAX;                  // stands in for logits that do not exist (E < LANES * VPL)
 #pragma unroll
     for (int c = 0; c < VPL / 4; ++c) {
         const int e0 = 4 * (q + LANES * c);
         if constexpr (FULL) x[c] = load_stream4(row_logits + e0);
-        else x[c] = e0 < E ? load_stream4(row_logits + e0) : make_float4(lowest, lowest, lowest, lowest);
+        else x[c] = e0 < E ? load_stream4(row_logits + e0) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // their keys become kNoKey
     }
 }
 
-// The L largest keys among this lane's logits, descending.  The logits are not needed afterwards.
-template <int LANES, int VPL, int L>
-__device__ __forceinline__ void lane_best(const float4 (&x)[VPL / 4], int q, float (&own)[L])
+// The L largest keys among this lane's logits, descending.  The logits are not needed afterwards.  bits: the union of their bit patterns.
+template <int LANES, int VPL, int L, bool FULL>
+__device__ __forceinline__ void lane_best(const float4 (&x)[VPL / 4], int E, int q, int (&own)[L], unsigned &bits)
 {
     constexpr unsigned MASK = (unsigned)(LANES * VPL) - 1u;   // expert index bits of a key
-    static_assert(VPL % 4 == 0 && VPL >= 8 && LANES >= 2 && LANES <= 16 && L >= 4 && L <= 8 && L <= VPL, "shape");
-    insert_loaded<LANES, VPL, L, MASK, 0, 0>(x, ~MASK | (unsigned)(4 * q), own);
+    static_assert(VPL % 4 == 0 && VPL >= 8 && LANES >= 2 && LANES <= 16 && L >= 4 && L <= VPL, "shape");
+    bits = 0;
+    insert_loaded<LANES, VPL, L, MASK, FULL, 0, 0>(x, ~MASK | (unsigned)(4 * q), E, q, own, bits);
 }
 
-// The 8 largest keys of the row from the lists of its LANES lanes, as bit patterns in u[0..8), the same in all lanes of the
+// The KM largest keys of the row from the lists of its LANES lanes, as bit patterns in u[0..KM), the same in all lanes of the
 // row.  Returns true when the result cannot be trusted (see above): the caller then picks the row's winners by full comparisons.
-template <int LANES, int VPL, int L>
-__device__ __forceinline__ bool row_best8(const float (&own)[L], int k, unsigned (&u)[8])
+template <int LANES, int VPL, int L, int KM>
+__device__ __forceinline__ bool row_best(const int (&own)[L], unsigned bits, int k, unsigned (&u)[KM])
 {
     constexpr unsigned MASK = (unsigned)(LANES * VPL) - 1u;
-    float lst[8];
-    merge_lists<1, L>(own, lst);
-    if constexpr (LANES >= 4) { float t[8]; merge_lists<2, 8>(lst, t);
+    int lst[KM];
+    merge_lists<1, L, KM>(own, lst);
+    if constexpr (LANES >= 4) { int t[KM]; merge_lists<2, KM, KM>(lst, t);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) lst[i] = t[i]; }
-    if constexpr (LANES >= 8) { float t[8]; merge_lists<4, 8>(lst, t);
+        for (int i = 0; i < KM; ++i) lst[i] = t[i]; }
+    if constexpr (LANES >= 8) { int t[KM]; merge_lists<4, KM, KM>(lst, t);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) lst[i] = t[i]; }
-    if constexpr (LANES >= 16) { float t[8]; merge_lists<8, 8>(lst, t);
+        for (int i = 0; i < KM; ++i) lst[i] = t[i]; }
+    if constexpr (LANES >= 16) { int t[KM]; merge_lists<8, KM, KM>(lst, t);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) lst[i] = t[i]; }
+        for (int i = 0; i < KM; ++i) lst[i] = t[i]; }
 
     // lst[j] = j-th largest key of the row (if no lane dropped one of them), the same in all its lanes
 #pragma unroll
-    for (int j = 0; j < 8; ++j) u[j] = __float_as_uint(lst[j]);
-    const float kth = k >= 8 ? lst[7] : k == 7 ? lst[6] : k == 6 ? lst[5] : k == 5 ? lst[4] : k == 4 ? lst[3] : k == 3 ? lst[2]
-                    : k == 2 ? lst[1] : lst[0];
-    const unsigned ukth = __float_as_uint(kth);
+    for (int j = 0; j < KM; ++j) u[j] = (unsigned)lst[j];
+    int kth = lst[KM - 1];
     unsigned close = 0xFFFFFFFFu;                   // (a ^ b) - 1 < MASK: a and b are different keys of one cut value
 #pragma unroll
-    for (int j = 1; j < 8; ++j) close = min_xor_dist(close, u[j], u[j - 1]);                  // neighbours among the row's best 8
+    for (int j = 1; j < KM; ++j) {
+        if (j <= k) close = min_xor_dist(close, u[j], u[j - 1]);     // neighbours among the winners and the best loser (k is uniform)
+        if (j == k) kth = lst[j - 1];
+    }
+    if (k == KM) {                                  // the best loser is not in the list: this lane's keys against the last winner
 #pragma unroll
-    for (int i = 0; i < L; ++i) close = min_xor_dist(close, __float_as_uint(own[i]), ukth);   // this lane's keys against the k-th winner
-    return close < MASK || own[L - 1] >= kth;       // ... or every key this lane kept is a winner
+        for (int i = 0; i < L; ++i) close = min_xor_dist(close, (unsigned)own[i], u[KM - 1]);
+    }
+    bool bad = close < MASK;
+    if (__ballot(bad) != 0ull) {                    // did the cut lose anything in this row?
+        bits |= (unsigned)from_partner<1>((int)bits);
+        if constexpr (LANES >= 4) bits |= (unsigned)from_partner<2>((int)bits);
+        if constexpr (LANES >= 8) bits |= (unsigned)from_partner<4>((int)bits);
+        if constexpr (LANES >= 16) bits |= (unsigned)from_partner<8>((int)bits);
+        bad = bad && (bits & MASK) != 0u;
+    }
+    return bad || own[L - 1] >= kth;                // ... or every key this lane kept is a winner
 }
 
-// expert indices of the row's k winners to topk_idx[row][0..k)
-template <int LANES, unsigned MASK>
-__device__ __forceinline__ void store_best8(int32_t *__restrict__ topk_idx, int64_t row, int k, int q, bool live, int wide_store,
-                                            const unsigned (&u)[8])
+// expert indices of the row's k winners to topk_idx[row][0..k); streaming stores (4 194 304 rows of 64 logits, top-6: 0.209 ms, plain 0.227)
+template <int LANES, unsigned MASK, int KM>
+__device__ __forceinline__ void store_best(int32_t *__restrict__ topk_idx, int64_t row, int k, int q, bool live, int wide_store,
+                                           const unsigned (&u)[KM])
 {
-    if (wide_store && k == 8) {                     // one lane stores the row's eight indices: two 16-byte stores
+    if (KM == 8 && wide_store && k == 8) {          // one lane stores the row's eight indices: two 16-byte stores
         if (live && q == 0) {
             i32x4 lo, hi;
-            lo.x = (int)(u[0] & MASK); lo.y = (int)(u[1] & MASK); lo.z = (int)(u[2] & MASK); lo.w = (int)(u[3] & MASK);
-            hi.x = (int)(u[4] & MASK); hi.y = (int)(u[5] & MASK); hi.z = (int)(u[6] & MASK); hi.w = (int)(u[7] & MASK);
+            lo.x = (int)key_index<MASK>(u[0]); lo.y = (int)key_index<MASK>(u[1]); lo.z = (int)key_index<MASK>(u[2]); lo.w = (int)key_index<MASK>(u[3]);
+            hi.x = (int)key_index<MASK>(u[4]); hi.y = (int)key_index<MASK>(u[5]); hi.z = (int)key_index<MASK>(u[6]); hi.w = (int)key_index<MASK>(u[7]);
             i32x4 *dst = reinterpret_cast<i32x4 *>(topk_idx + row * 8);
             __builtin_nontemporal_store(lo, dst);
             __builtin_nontemporal_store(hi, dst + 1);
         }
     } else {
 #pragma unroll
-        for (int r = 0; r < (8 + LANES - 1) / LANES; ++r) {          // winners q, q+LANES, ... of this lane
+        for (int r = 0; r < (KM + LANES - 1) / LANES; ++r) {         // winners q, q+LANES, ... of this lane
             unsigned sel = 0;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) sel = (j == q + r * LANES) ? u[j] : sel;
-            if (live && q + r * LANES < k) topk_idx[row * k + q + r * LANES] = (int)(sel & MASK);
+            for (int j = r * LANES; j < KM && j < (r + 1) * LANES; ++j) sel = (j == q + r * LANES) ? u[j] : sel;
+            if (live && q + r * LANES < k) __builtin_nontemporal_store((int)key_index<MASK>(sel), topk_idx + row * k + q + r * LANES);
         }
     }
 }
@@ -244,17 +277,21 @@ __device__ __forceinline__ void row_exact(const float *__restrict__ row_logits, 
         v[4 * c + 0] = cur.x; v[4 * c + 1] = cur.y; v[4 * c + 2] = cur.z; v[4 * c + 3] = cur.w;
     }
     for (int sel = 0; sel < k; ++sel) {
+        // places inside the lane (constants) while scanning and removing: expert indices of all VPL places would be kept in registers
         float bv = -INFINITY;
-        int bi = INT_MAX;
+        int bj = -1;
 #pragma unroll
         for (int j = 0; j < VPL; ++j) {
             const bool better = v[j] > bv;
             bv = better ? v[j] : bv;
-            bi = better ? slot_index<LANES, VPL, true>(q, j) : bi;
+            bj = better ? j : bj;
         }
+        int bi = bj < 0 ? INT_MAX : 4 * (q + LANES * (bj >> 2)) + (bj & 3);
+        const int mine = bi;
         group_argmax<LANES>(bv, bi);
+        const int gone = bi == mine ? bj : -1;      // only the winner's lane loses an entry
 #pragma unroll
-        for (int j = 0; j < VPL; ++j) v[j] = (slot_index<LANES, VPL, true>(q, j) == bi) ? -INFINITY : v[j];
+        for (int j = 0; j < VPL; ++j) v[j] = (j == gone) ? -INFINITY : v[j];
         emit(sel, bi);
     }
 }

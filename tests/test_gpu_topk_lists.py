@@ -1,0 +1,46 @@
+"""The insertion kernels of stage 1 at the edges of their shapes (33..1024 logits, k up to 16), against the CPU oracle, exactly:
+whole-number outputs, so there is no tolerance."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_19262_amd as rs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _bf16(x):
+    return torch.from_numpy(x).to(torch.bfloat16).to(torch.float32).numpy()
+
+
+def _rows(kind, rows, E, rng):
+    x = rng.standard_normal((rows, E)).astype(np.float32)
+    if kind == "bf16":                               # ties of both signs, nothing lost by the cut
+        x = _bf16(x)
+    elif kind == "negative":
+        x = _bf16(-np.abs(x) - 1)
+    elif kind == "close":                            # equal but for the last bits: the cut loses what decides
+        base = rng.choice(np.array([2.5, -2.5, 1e-30, -0.0], np.float32), size=(rows, 1))
+        x = (base.view(np.int32) + rng.integers(0, 5, size=(rows, E)).astype(np.int32)).view(np.float32)
+        x[::2] = rng.standard_normal(x[::2].shape)
+    elif kind == "one_lane":                         # all leaders in the places of one lane (float4s E/stride apart)
+        for r in range(rows):
+            lane = 4 * int(rng.integers(0, 4))
+            for c in range(lane, E, 32):
+                x[r, c:c + 4] += 10.0
+    elif kind == "lowest":                           # masked experts
+        x[rng.random((rows, E)) < 0.9] = np.finfo(np.float32).min
+    return x
+
+
+@pytest.mark.parametrize("kind", ["normal", "bf16", "negative", "close", "one_lane", "lowest"])
+@pytest.mark.parametrize("E,k", [(36, 1), (64, 6), (64, 8), (68, 7), (128, 8), (132, 8), (256, 8), (256, 3), (260, 1), (260, 9), (512, 8),
+                                 (512, 10), (512, 16), (508, 16), (516, 8), (516, 16), (1024, 8), (1024, 10), (1024, 16), (512, 17), (514, 10)])
+def test_topk_lists(E, k, kind):
+    rng = np.random.default_rng(E * 31 + k)
+    for rows in (1, 517):
+        x = _rows(kind, rows, E, rng)
+        got = rs.route_topk(torch.from_numpy(x).to(DEV), k).cpu().numpy()
+        assert np.array_equal(got, oracle.route_topk(x, k))
