@@ -44,3 +44,14 @@ def test_topk_lists(E, k, kind):
         x = _rows(kind, rows, E, rng)
         got = rs.route_topk(torch.from_numpy(x).to(DEV), k).cpu().numpy()
         assert np.array_equal(got, oracle.route_topk(x, k))
+
+
+@pytest.mark.parametrize("k,R,tok", [(6, 1, 4096), (6, 4, 1021), (3, 3, 1000), (10, 1, 77), (5, 2, 4099), (8, 1, 512), (8, 5, 300)])
+def test_traffic_matrix_replicas(k, R, tok):
+    # slots whose token index needs a division, whose replica index does not, and both
+    rng = np.random.default_rng(k * 100 + R)
+    E, M, N = 24, 3, 4
+    idx = rng.integers(0, E, size=(2 * M * N * tok, k)).astype(np.int32)
+    eg = rng.integers(0, M * N, size=(E, R)).astype(np.int32)
+    got = rs.traffic_matrix(torch.from_numpy(idx).to(DEV), 2, tok, torch.from_numpy(eg).to(DEV), 2048, rs.Topo(M, N, 65536))
+    assert np.array_equal(got.cpu().numpy(), oracle.traffic_matrix(idx, 2, tok, eg, 2048, M, N))
