@@ -55,3 +55,33 @@ def test_traffic_matrix_replicas(k, R, tok):
     eg = rng.integers(0, M * N, size=(E, R)).astype(np.int32)
     got = rs.traffic_matrix(torch.from_numpy(idx).to(DEV), 2, tok, torch.from_numpy(eg).to(DEV), 2048, rs.Topo(M, N, 65536))
     assert np.array_equal(got.cpu().numpy(), oracle.traffic_matrix(idx, 2, tok, eg, 2048, M, N))
+
+
+@pytest.mark.parametrize("kind", ["normal", "bf16", "close", "lowest"])
+@pytest.mark.parametrize("E,k", [(12, 1), (12, 4), (16, 4), (16, 5), (16, 8), (20, 2), (28, 8), (32, 3), (32, 8), (32, 9), (18, 4)])
+def test_one_pass_routing_of_short_rows(E, k, kind):
+    rng = np.random.default_rng(E * 17 + k)
+    M, N, B, R = 2, 3, 2, 2
+    G = M * N
+    topo = rs.Topo(M, N, 65536)
+    eg = rng.integers(0, G, size=(E, R)).astype(np.int32)
+    for tok in (1, 255, 511, 1025):
+        x = _rows(kind, B * G * tok, E, rng)
+        idx, D1 = rs.route_traffic(torch.from_numpy(x).to(DEV), k, B, tok, torch.from_numpy(eg).to(DEV), 512, topo)
+        want = oracle.route_topk(x, k)
+        assert np.array_equal(idx.cpu().numpy(), want)
+        assert np.array_equal(D1.cpu().numpy(), oracle.traffic_matrix(want, B, tok, eg, 512, M, N))
+
+
+def test_one_pass_routing_without_room_for_slice_counts():
+    # rows of 16 logits with a workspace that only the two stages fit: the same outputs
+    rng = np.random.default_rng(5)
+    M, N, B, E, k, tok = 2, 2, 1, 16, 2, 1100
+    topo = rs.Topo(M, N, 65536)
+    x = rng.standard_normal((B * M * N * tok, E)).astype(np.float32)
+    eg = rng.integers(0, M * N, size=(E, 1)).astype(np.int32)
+    ws = torch.empty(16, dtype=torch.uint8, device=DEV)
+    idx, D1 = rs.route_traffic(torch.from_numpy(x).to(DEV), k, B, tok, torch.from_numpy(eg).to(DEV), 512, topo, ws=ws)
+    want = oracle.route_topk(x, k)
+    assert np.array_equal(idx.cpu().numpy(), want)
+    assert np.array_equal(D1.cpu().numpy(), oracle.traffic_matrix(want, B, tok, eg, 512, M, N))
