@@ -238,3 +238,22 @@ def test_whole_path_replays_from_a_hip_graph(fused):
         assert all(torch.equal(a, b) for a, b in zip(want, got)), f"replay {rnd}"
         got_rec = (plan.chunk_w, plan.chunk_flow, plan.perm, plan.rail)
         assert all(torch.equal(a, b[:n]) for a, b in zip(want_rec, got_rec)), f"replay {rnd} records"
+
+
+@pytest.mark.parametrize("N,P", [(1, 8), (3, 1), (5, 8), (8, 8), (8, 128), (8, 256), (8, 6), (9, 16), (12, 8), (16, 128), (24, 8)])
+def test_port_round_robin_of_any_rails(N, P):
+    # rails in no order, instances of every length around a tile and of none
+    rng = np.random.default_rng(N * 1000 + P)
+    M, B = 5, 3
+    sizes = np.array([0, 1, 15, 16, 17, 4095, 4096, 4097, 4111, 8192, 12300, 3, 0, 5000, 33])
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n = int(off[-1])
+    rail = rng.integers(0, N, size=n).astype(np.uint8)
+    topo = rs.Topo(M, N, 4096)
+    want = oracle.port_round_robin(off, rail, B, M, N, P)
+    d_off, d_rail = torch.from_numpy(off).to(DEV), torch.from_numpy(rail).to(DEV)
+    got = rs.port_round_robin(d_off, d_rail, B, topo, P)
+    assert np.array_equal(got.cpu().numpy()[:n], want)
+    shifted = torch.empty(n + 16, dtype=torch.uint8, device=DEV)[3:3 + n]           # not aligned for the wide loads
+    shifted.copy_(d_rail)
+    assert np.array_equal(rs.port_round_robin(d_off, shifted, B, topo, P).cpu().numpy()[:n], want)
