@@ -70,10 +70,6 @@ __global__ __launch_bounds__(kEvThreads) void eval_partial_kernel(EvArgs a)
     if (threadIdx.x == 0) slot[a.G] = (int64_t)ev_wmax;
 }
 
-// One workgroup of THREADS/64 wavefronts per matrix (1024 threads, or 256 when the matrix is small: fewer
-// wavefronts make cheaper barriers).  Receive bins: a wavefront covers 64 consecutive bins (or, when G < 64,
-// several slices side by side), the wavefronts split the slices, LDS joins them.  The six statistics are
-// reduced together: shuffles inside the wavefronts, one exchange through LDS.
 // R[b][base..base+63] = sum over the matrix's slots, for matrices with so many slots that one workgroup per matrix
 // would read megabytes alone: grid (ceil(G/64), batch), four wavefronts split the slots.
 __global__ __launch_bounds__(256) void eval_sum_kernel(EvArgs a)
@@ -100,65 +96,85 @@ __global__ __launch_bounds__(256) void eval_sum_kernel(EvArgs a)
 }
 
 // SUM: the receive bins are summed here; otherwise eval_sum_kernel has already written R.
+// Latency bound (one workgroup per matrix): bins are taken in chunks of whole nodes, a chunk's slots are read with all
+// threads' loads in flight (groups of threads take every groups-th slot, eight at a time), and the per-node sums come
+// from LDS.  64 slots of 512 bins, one matrix: 20-26 us when 64 bins at a time were summed between two barriers and the
+// nodes read back one load after the other, 12 now.
 template <int THREADS, bool SUM>
 __global__ __launch_bounds__(THREADS) void eval_reduce_kernel(EvArgs a)
 {
     constexpr int WAVES = THREADS / 64;
-    __shared__ int64_t part[WAVES][64];
+    __shared__ int64_t sum[THREADS], shR[THREADS], shS[THREADS];
     __shared__ int64_t sh[6][WAVES];
-    const int b = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
     const int64_t *slots = a.partial + (int64_t)b * a.slices * (a.G + 1);
     int64_t *Rb = a.R + (int64_t)b * a.G;
     const int64_t *Sb = a.S + (int64_t)b * a.G;
     if (a.chunk_off[a.n_inst] > a.capacity) {         // more chunks than the record arrays hold: nothing was read, say so
-        for (int i = threadIdx.x; i < a.G; i += THREADS) Rb[i] = -1;
-        if (threadIdx.x < 8) a.stats[(int64_t)b * 8 + threadIdx.x] = -1;
+        for (int i = tid; i < a.G; i += THREADS) Rb[i] = -1;
+        if (tid < 8) a.stats[(int64_t)b * 8 + tid] = -1;
         return;
     }
-
-    int width = 64;                                   // lanes per slice row: 64, or the power of two >= G
-    while (width / 2 >= a.G) width /= 2;
-    const int sub = 64 / width;                       // slices a wavefront reads side by side
-    const int ts = lane / width, li = lane % width;
-    for (int base = 0; SUM && base < a.G; base += 64) {
-        const int i = base + li;
-        int64_t acc = 0;
-        if (i < a.G)
-            for (int t = wave * sub + ts; t < a.slices; t += WAVES * sub) acc += slots[(int64_t)t * (a.G + 1) + i];
-        __syncthreads();                              // previous round's readers are done
-        part[wave][lane] = acc;
-        __syncthreads();
-        if (wave == 0 && lane < width && base + lane < a.G) {
-            int64_t r = 0;
-            for (int w = 0; w < WAVES; ++w)
-                for (int u = 0; u < sub; ++u) r += part[w][u * width + lane];
-            Rb[base + lane] = r;
-        }
-    }
     int64_t wmax = 0;
-    for (int t = threadIdx.x; t < a.slices; t += THREADS) {
+    for (int t = tid; t < a.slices; t += THREADS) {
         const int64_t x = slots[(int64_t)t * (a.G + 1) + a.G];
         wmax = x > wmax ? x : wmax;
     }
-    __syncthreads();   // R[b] written by this workgroup is read back below
 
+    const int chunk = THREADS / a.N * a.N;            // whole nodes (N <= 64)
     int64_t max_s = 0, max_r = 0, lb = 0, total = 0, spread = 0;
-    for (int k = threadIdx.x; k < a.M; k += THREADS) {
-        int64_t out = 0, in = 0, smin = INT64_MAX, smax = 0;
-        for (int n = 0; n < a.N; ++n) {
-            const int64_t s = Sb[k * a.N + n], r = Rb[k * a.N + n];
-            out += s; in += r;
-            max_s = s > max_s ? s : max_s;
-            max_r = r > max_r ? r : max_r;
-            smin = s < smin ? s : smin;
-            smax = s > smax ? s : smax;
+    for (int base = 0; base < a.G; base += chunk) {
+        const int nb = a.G - base < chunk ? a.G - base : chunk;
+        int64_t s = 0, r = 0;
+        if (tid < nb) s = Sb[base + tid];
+        if constexpr (SUM) {
+            int width = 64;                           // threads per slot row: the power of two >= nb
+            while (width < nb) width *= 2;            // nb <= THREADS, a multiple of 64 that is a power of two
+            const int groups = THREADS / width, g = tid / width, i = tid & (width - 1);
+            int64_t acc = 0;
+            if (i < nb) {
+                const int64_t *p = slots + base + i;
+                const int64_t step = a.G + 1;
+                int t = g;
+                for (; t + 7 * groups < a.slices; t += 8 * groups) {
+                    int64_t v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)(t + u * groups) * step];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) acc += v[u];
+                }
+                for (; t < a.slices; t += groups) acc += p[(int64_t)t * step];
+            }
+            sum[tid] = acc;
+            __syncthreads();
+            if (tid < nb) {
+                for (int j = 0; j < groups; ++j) r += sum[j * width + tid];
+                Rb[base + tid] = r;
+            }
+        } else {
+            if (tid < nb) r = Rb[base + tid];
         }
-        total += out;
-        const int64_t co = (out + a.N - 1) / a.N, ci = (in + a.N - 1) / a.N;
-        lb = co > lb ? co : lb;
-        lb = ci > lb ? ci : lb;
-        spread = (smax - smin) > spread ? (smax - smin) : spread;
+        shR[tid] = r;
+        shS[tid] = s;
+        __syncthreads();
+        if (tid < nb / a.N) {
+            int64_t out = 0, in = 0, smin = INT64_MAX, smax = 0;
+            for (int n = 0; n < a.N; ++n) {
+                const int64_t sv = shS[tid * a.N + n], rv = shR[tid * a.N + n];
+                out += sv; in += rv;
+                max_s = sv > max_s ? sv : max_s;
+                max_r = rv > max_r ? rv : max_r;
+                smin = sv < smin ? sv : smin;
+                smax = sv > smax ? sv : smax;
+            }
+            total += out;
+            const int64_t co = (out + a.N - 1) / a.N, ci = (in + a.N - 1) / a.N;
+            lb = co > lb ? co : lb;
+            lb = ci > lb ? ci : lb;
+            spread = (smax - smin) > spread ? (smax - smin) : spread;
+        }
+        __syncthreads();                              // the nodes have been read
     }
     // five maxima and one sum, together
     int64_t v[6] = {max_s, max_r, lb, wmax, spread, total};
@@ -195,9 +211,12 @@ __global__ __launch_bounds__(THREADS) void eval_reduce_kernel(EvArgs a)
 
 int launch_eval_reduce(const EvArgs &a, int batch, hipStream_t st)
 {
-    if ((int64_t)a.slices * a.G <= 16384 && a.M <= 256) {
+    // a workgroup reads its matrix's slots alone: 256 threads while they are few (cheaper barriers), 1024 up to 64 Ki sums, and
+    // beyond that the slots are summed by G / 64 workgroups per matrix first (128 slots of 1024
+    // bins: 58 us by one workgroup as it was, 5 + 8 in two kernels)
+    if ((int64_t)a.slices * a.G <= 2048) {
         hipLaunchKernelGGL((eval_reduce_kernel<256, true>), dim3((unsigned)batch), dim3(256), 0, st, a);
-    } else if ((int64_t)a.slices * a.G <= 131072) {
+    } else if ((int64_t)a.slices * a.G <= 65536) {
         hipLaunchKernelGGL((eval_reduce_kernel<1024, true>), dim3((unsigned)batch), dim3(1024), 0, st, a);
     } else {
         hipLaunchKernelGGL(eval_sum_kernel, dim3((unsigned)((a.G + 63) / 64), (unsigned)batch), dim3(256), 0, st, a);
