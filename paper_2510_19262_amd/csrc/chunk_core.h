@@ -21,6 +21,7 @@ struct CsArgs {
     uint8_t *rail;       // when set, the fill also writes the rails of every instance's leading run (see cs_fill_kernel)
     int32_t nmask;       // N - 1 when N is a power of two, else -1
     int32_t gmask, nshift;   // G - 1 and log2 N when G / N are powers of two, else -1
+    int64_t *run_end;    // when set, run_end[inst * N] receives the length of every instance's leading run of full chunks
 };
 
 __device__ __forceinline__ void split_bytes(const CsArgs &a, int64_t B, uint32_t &q, uint32_t &r)
@@ -79,64 +80,161 @@ __device__ __forceinline__ void lds_sync()
     else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
-// Tails (B mod C > 0) of the flows of one instance, sorted by weight descending, ties in canonical (flow) order:
-// stable LSD radix sort by one wavefront in LDS, 8-bit digits over the span of key bits that differ at all,
-// ranks inside a batch of 64 from ballot matching.  rem[NF] receives every flow's tail bytes, hist[256] is
-// scratch, idx_a/idx_b[NF] are ping-pong arrays of flow ids; returns the array that holds the sorted ids and
-// their number in nt.
-template <bool ONE_WAVE_BLOCK>
-__device__ __forceinline__ unsigned short *tail_sort_wave(const CsArgs &a, const int64_t *rows, int k, unsigned *rem, unsigned *hist,
-                                                          unsigned short *idx_a, unsigned short *idx_b, int &nt_out)
+// Flows of the 256 positions first .. first + 255, four per lane, for a wavefront that knows the flow j_lo of position `first` or of one
+// before it (the same in all lanes): every flow that starts in the window, or between j_lo and it, leaves its number where it
+// starts (the largest wins: the ones before it are empty) and a running maximum carries them on.  No search: a window costs a few
+// LDS round trips whatever the flows' lengths.  mark[256] is this wavefront's scratch, 16-byte aligned.  Positions beyond `last` (of
+// the last lanes) get the flow of `last`.  Returns the flow of `last`.
+__device__ __forceinline__ int window_flows(const uint32_t *fs, int nf, int j_lo, uint32_t first, uint32_t last, unsigned *mark, uint32_t (&fl)[4])
 {
     const int lane = threadIdx.x & 63;
+    *reinterpret_cast<uint4 *>(mark + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    for (int f = j_lo + 1 + lane;; f += 64) {
+        const uint32_t s = f < nf ? fs[f] : 0xFFFFFFFFu;
+        const bool in = s <= last;
+        if (in) atomicMax(&mark[s > first ? s - first : 0u], (unsigned)f);
+        if (__ballot(!in) != 0ull) break;           // starts ascend: nothing further on starts at or before `last`
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    const uint4 m = *reinterpret_cast<const uint4 *>(mark + 4 * lane);
+    const unsigned m1 = max(m.x, m.y), m2 = max(m1, m.z), m3 = max(m2, m.w);
+    unsigned inc = max(m3, (unsigned)j_lo);         // inclusive maximum over the lanes
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xF, 0xF, false));   // row_shr:1
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xF, 0xF, false));   // row_shr:2
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x114, 0xF, 0xF, false));   // row_shr:4
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xF, 0xF, false));   // row_shr:8
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x142, 0xA, 0xF, false));   // row_bcast15 into rows 1 and 3
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x143, 0xC, 0xF, false));   // row_bcast31 into rows 2 and 3
+    const unsigned left = (unsigned)__builtin_amdgcn_update_dpp(j_lo, (int)inc, 0x138, 0xF, 0xF, false);   // wave_shr:1; lane 0 keeps j_lo
+    fl[0] = max(left, m.x); fl[1] = max(left, m1); fl[2] = max(left, m2); fl[3] = max(left, m3);
+    return __builtin_amdgcn_readlane((int)inc, 63);
+}
+
+constexpr int kTailLoads = 4;       // flows per thread and round of the flow scans: their loads are in flight together
+
+// LDS words tail_sort_block needs beside rem[NF], hist[] and the two index arrays
+template <int T> constexpr int tail_hist_words() { return 256 * (T / 64); }
+constexpr int kTailShared = 64 + 2 + 16;
+constexpr int kRankTails = 256;     // tails up to which places are counted instead of sorted for (a 16-GPU instance: one pass over its neighbours in LDS, no histogram)
+
+// Tails (B mod C > 0) of the flows of one instance, sorted by weight descending, ties in canonical (flow) order:
+// stable LSD radix sort by one workgroup of T threads in LDS, 8-bit digits over the span of key bits that differ at all.
+// A wavefront owns a contiguous share of the order and a histogram of its own, so ranks inside a share need no workgroup
+// barrier (ballot matching in batches of 64); a pass has three.  rem[NF] receives every flow's tail bytes,
+// hist[tail_hist_words<T>()] and sh[kTailShared] are scratch, idx_a/idx_b[NF] are ping-pong arrays of flow ids; returns the
+// array that holds the sorted ids and their number in nt.  Latency bound: one wavefront took 32 us for the 4096 flows of a
+// 512-GPU instance, and four of them per CU (its LDS) 364 us for 3904 such instances; a workgroup of 1024 takes 14 us for 128 instances of 8192 flows (67 before),
+// one of 256 155 us for the 3904.
+template <int T>
+__device__ __forceinline__ unsigned short *tail_sort_block(const CsArgs &a, const int64_t *rows, int k, unsigned *rem, unsigned *hist,
+                                                           unsigned short *idx_a, unsigned short *idx_b, unsigned *sh, int &nt_out)
+{
+    constexpr int W = T / 64, U = kTailLoads;
+    static_assert(U * W <= 64, "one lane per (round, wavefront)");
+    unsigned *sh_cnt = sh, *sh_bits = sh + 64, *sh_tot = sh + 66;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const unsigned long long lt = (1ull << lane) - 1ull;
+    if (tid == 0) { sh_bits[0] = 0u; sh_bits[1] = 0xFFFFFFFFu; }
     // tails in canonical order; which key bits differ at all between them
     int nt = 0;
     unsigned any1 = 0u, all1 = 0xFFFFFFFFu;
-    for (int f0 = 0; f0 < a.NF; f0 += 512) {
-        int64_t bytes[8];                           // eight rounds of loads in flight: one memory round trip, not eight
+    for (int f0 = 0; f0 < a.NF; f0 += U * T) {
+        int64_t bytes[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int f = f0 + 64 * u + lane;
+        for (int u = 0; u < U; ++u) {
+            const int f = f0 + u * T + tid;
             bytes[u] = f < a.NF ? flow_bytes(a, rows, k, f) : 0;
         }
+        unsigned r[U];
+        unsigned long long m[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int f = f0 + 64 * u + lane;
-            if (f0 + 64 * u >= a.NF) break;         // wave-uniform
-            uint32_t q = 0, r = 0;
-            if (f < a.NF) { split_bytes(a, bytes[u], q, r); rem[f] = r; }
-            const unsigned long long m = __ballot(r != 0);
-            if (r) { idx_a[nt + __popcll(m & lt)] = (unsigned short)f; any1 |= r; all1 &= r; }
-            nt += __popcll(m);
+        for (int u = 0; u < U; ++u) {
+            const int f = f0 + u * T + tid;
+            uint32_t q = 0;
+            split_bytes(a, bytes[u], q, r[u]);
+            if (f < a.NF) rem[f] = r[u];
+            m[u] = __ballot(r[u] != 0);
+            if (r[u]) { any1 |= r[u]; all1 &= r[u]; }
+            if (lane == 0) sh_cnt[u * W + wave] = (unsigned)__popcll(m[u]);
         }
+        __syncthreads();
+        unsigned total;
+        const unsigned before = wave_exscan(lane < U * W ? sh_cnt[lane] : 0u, total);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const unsigned at = (unsigned)nt + (unsigned)__shfl((int)before, u * W + wave);
+            if (r[u]) idx_a[at + __popcll(m[u] & lt)] = (unsigned short)(f0 + u * T + tid);
+        }
+        nt += (int)total;
+        __syncthreads();                            // sh_cnt has been read
+    }
+    nt_out = nt;
+    if (nt <= kRankTails) {
+        // few tails: a tail's place is the number of tails that go before it.  Keys side by side in hist, read four at a time;
+        // with T / 256 threads per tail each counts a share of them.
+        constexpr int P = T >= 256 ? T / 256 : 1, STEP = T >= 256 ? 256 : T;
+        const int quads = (nt + 3) >> 2;
+        for (int i = tid; i < 4 * quads; i += T) hist[i] = i < nt ? rem[idx_a[i]] : 0u;   // a tail is at least one byte
+        if constexpr (P > 1) { if (tid < kRankTails) hist[kRankTails + tid] = 0u; }
+        __syncthreads();
+        const int part = tid / 256;
+        for (int i = tid % 256; i < nt; i += STEP) {
+            const unsigned w = hist[i];
+            unsigned rank = 0;
+            for (int g = part; g < quads; g += P) {
+                const uint4 o = *reinterpret_cast<const uint4 *>(hist + 4 * g);
+                const int j = 4 * g;
+                rank += (o.x > w || (o.x == w && j + 0 < i)) ? 1u : 0u;
+                rank += (o.y > w || (o.y == w && j + 1 < i)) ? 1u : 0u;
+                rank += (o.z > w || (o.z == w && j + 2 < i)) ? 1u : 0u;
+                rank += (o.w > w || (o.w == w && j + 3 < i)) ? 1u : 0u;
+            }
+            if constexpr (P > 1) atomicAdd(&hist[kRankTails + i], rank);
+            else idx_b[rank] = idx_a[i];
+        }
+        __syncthreads();
+        if constexpr (P > 1) {
+            if (tid < nt) idx_b[hist[kRankTails + tid]] = idx_a[tid];
+            __syncthreads();
+        }
+        return idx_b;
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) { any1 |= (unsigned)__shfl_xor((int)any1, d); all1 &= (unsigned)__shfl_xor((int)all1, d); }
-    lds_sync<ONE_WAVE_BLOCK>();
+    if (lane == 0) { atomicOr(&sh_bits[0], any1); atomicAnd(&sh_bits[1], all1); }
+    __syncthreads();
     // bits that are equal in every key cannot change the order: sort on the span of differing bits only
     // (token payloads make tails multiples of some power of two, so the span is usually one digit wide)
-    const unsigned diff = any1 ^ all1;
+    const unsigned diff = sh_bits[0] ^ sh_bits[1];
     const int lo_bit = diff ? __ffs((int)diff) - 1 : 0;
     const int n_pass = (nt > 1 && diff) ? (32 - __clz((int)diff) - lo_bit + 7) / 8 : 0;
+    const int share = ((nt + W - 1) / W + 63) & ~63;                     // of one wavefront, whole batches
+    const int i_lo = wave * share, i_hi = i_lo + share < nt ? i_lo + share : nt;
+    unsigned *mine = hist + wave * 256;
 
     for (int pass = 0; pass < n_pass; ++pass) {
         const int shift = lo_bit + 8 * pass;
-        for (int i = lane; i < 256; i += 64) hist[i] = 0;
-        lds_sync<ONE_WAVE_BLOCK>();
-        for (int i = lane; i < nt; i += 64) atomicAdd(&hist[255u - ((rem[idx_a[i]] >> shift) & 255u)], 1u);
-        lds_sync<ONE_WAVE_BLOCK>();
-        {   // exclusive scan of the 256 buckets: four per lane
-            const unsigned h0 = hist[4 * lane], h1 = hist[4 * lane + 1], h2 = hist[4 * lane + 2], h3 = hist[4 * lane + 3];
-            unsigned tot;
-            const unsigned ex = wave_exscan(h0 + h1 + h2 + h3, tot);
-            lds_sync<ONE_WAVE_BLOCK>();
-            hist[4 * lane] = ex; hist[4 * lane + 1] = ex + h0; hist[4 * lane + 2] = ex + h0 + h1; hist[4 * lane + 3] = ex + h0 + h1 + h2;
+        for (int i = lane; i < 256; i += 64) mine[i] = 0;
+        lds_sync<false>();
+        for (int i = i_lo + lane; i < i_hi; i += 64) atomicAdd(&mine[255u - ((rem[idx_a[i]] >> shift) & 255u)], 1u);
+        __syncthreads();
+        {   // exclusive scan over (digit, wavefront): four consecutive entries per thread
+            unsigned h[4], sum = 0, tot;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { const int e = 4 * tid + j; h[j] = hist[(e % W) * 256 + e / W]; sum += h[j]; }
+            unsigned ex = wave_exscan(sum, tot);
+            if (lane == 0) sh_tot[wave] = tot;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < W; ++w) ex += w < wave ? sh_tot[w] : 0u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { const int e = 4 * tid + j; hist[(e % W) * 256 + e / W] = ex; ex += h[j]; }
         }
-        lds_sync<ONE_WAVE_BLOCK>();
-        for (int i0 = 0; i0 < nt; i0 += 64) {                            // batches in order keep the sort stable
+        __syncthreads();
+        for (int i0 = i_lo; i0 < i_hi; i0 += 64) {                       // batches in order keep the sort stable
             const int i = i0 + lane;
-            const bool act = i < nt;
+            const bool act = i < i_hi;
             const unsigned short f = act ? idx_a[i] : 0;
             const unsigned d = act ? 255u - ((rem[f] >> shift) & 255u) : 0u;
             unsigned long long peers = __ballot(act);
@@ -146,16 +244,16 @@ __device__ __forceinline__ unsigned short *tail_sort_wave(const CsArgs &a, const
                 const unsigned long long bm = __ballot(act && one);
                 peers &= one ? bm : ~bm;
             }
-            const unsigned base = act ? hist[d] : 0u;
+            const unsigned base = act ? mine[d] : 0u;
             if (act) idx_b[base + __popcll(peers & lt)] = f;
-            lds_sync<ONE_WAVE_BLOCK>();
-            if (act && (peers >> lane) == 1ull) hist[d] = base + __popcll(peers);   // highest lane of the peer set
-            lds_sync<ONE_WAVE_BLOCK>();
+            lds_sync<false>();
+            if (act && (peers >> lane) == 1ull) mine[d] = base + __popcll(peers);   // highest lane of the peer set
+            lds_sync<false>();
         }
+        __syncthreads();
         unsigned short *t = idx_a; idx_a = idx_b; idx_b = t;
     }
 
-    nt_out = nt;
     return idx_a;
 }
 
@@ -163,9 +261,10 @@ __device__ __forceinline__ unsigned short *tail_sort_wave(const CsArgs &a, const
 // validates, lays the workspace out and launches count, scan, tail sort and fill.  With `rail` set the fill also
 // writes rail[i] = i mod N for the first n_full - n_full mod N positions of every instance - the greedy
 // allocation of a leading run of equal weights from empty rails (Algorithm 2 step 3) in closed form.
+// run_end, if given, receives those runs' lengths n_full at run_end[inst * N], where stage 4's serial kernels look for them.
 // *args_out, if given, receives the argument block (workspace pointers included).
 int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int64_t *chunk_off, uint32_t *chunk_w,
-           uint32_t *chunk_flow, uint32_t *perm, int64_t capacity, uint8_t *rail, void *ws, size_t ws_bytes, hipStream_t st,
+           uint32_t *chunk_flow, uint32_t *perm, int64_t capacity, uint8_t *rail, int64_t *run_end, void *ws, size_t ws_bytes, hipStream_t st,
            CsArgs *args_out);
 
 }  // namespace rs

@@ -6,7 +6,7 @@
 // "weight descending, ties in canonical order" all full chunks therefore come first, in canonical
 // order (their positions follow from an exclusive scan of floor(B/C) over the instance's flows), and
 // only the tails - at most one per flow, N*G per instance - need a real sort.  The tails of one
-// instance are sorted by one wavefront with a stable LSD radix sort held in LDS (8-bit digits,
+// instance are sorted by one workgroup with a stable LSD radix sort held in LDS (8-bit digits,
 // ranks inside a 64-element batch from ballot matching).  Every chunk record is written to HBM
 // exactly once.
 //
@@ -20,45 +20,80 @@ namespace rs {
 constexpr int kTileMin = 1024;      // full-chunk positions per fill tile: a power of two between these two, chosen per call
 constexpr int kTileMax = 16384;     // so that small batches still spread over a few thousand workgroups
 constexpr int kFillThreads = 256;
-constexpr int kFillStage = 2048;    // flow boundaries staged in LDS per span (16 KiB with the canonical starts: 8 workgroups per CU)
+constexpr int kFillStage = 1536;    // flow boundaries staged in LDS per span (16 KiB with the canonical starts and the marks: 8 workgroups per CU)
 constexpr int kFillBlocks = 16384;  // most workgroups of one fill launch: several rounds of the chip, which evens out their ends
 
 // ---- A: per-instance chunk counts and the two exclusive scans over its flows -----------------
-__global__ __launch_bounds__(64) void cs_count_kernel(CsArgs a)
+// One workgroup of T threads per instance, T * kTailLoads flows per round.  Latency bound (a few dependent trips to memory and
+// barriers): with one wavefront per instance the 4096 flows of a 512-GPU instance took 31 us, 7 now.
+template <int T>
+__global__ __launch_bounds__(T) void cs_count_kernel(CsArgs a)
 {
+    constexpr int W = T / 64, U = kTailLoads;
+    static_assert(U * W <= 64, "one lane per (round, wavefront)");
+    __shared__ unsigned sh_q[64], sh_c[64];
+    __shared__ int64_t sh_n[2][W];
     const int inst = blockIdx.x;
     const int b = inst / a.M, k = inst % a.M;
-    const int lane = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
     uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
     uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;
-    unsigned carry_full = 0, carry_all = 0;
+    unsigned carry_q = 0, carry_c = 0;
     int64_t n_full = 0, n_all = 0;
-    for (int f0 = 0; f0 < a.NF; f0 += 256) {
-        int64_t bytes[4];                           // four rounds of loads in flight before the scans, which chain
+    for (int f0 = 0; f0 < a.NF; f0 += U * T) {
+        int64_t bytes[U];                           // all of a round's loads in flight before the scans, which chain
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int f = f0 + 64 * u + lane;
+        for (int u = 0; u < U; ++u) {
+            const int f = f0 + u * T + tid;
             bytes[u] = f < a.NF ? flow_bytes(a, rows, k, f) : 0;
         }
+        unsigned eq[U], ec[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int f = f0 + 64 * u + lane;
-            if (f0 + 64 * u >= a.NF) break;         // wave-uniform
+        for (int u = 0; u < U; ++u) {
             uint32_t q = 0, r = 0;
-            if (f < a.NF) split_bytes(a, bytes[u], q, r);
+            split_bytes(a, bytes[u], q, r);
             const unsigned c = q + (r ? 1u : 0u);
             unsigned tq, tc;
-            const unsigned eq = wave_exscan(q, tq);
-            const unsigned ec = wave_exscan(c, tc);
-            if (f < a.NF) { fs[f] = carry_full + eq; cs[f] = carry_all + ec; }
-            carry_full += tq; carry_all += tc;
+            eq[u] = wave_exscan(q, tq);
+            ec[u] = wave_exscan(c, tc);
+            if (lane == 0) { sh_q[u * W + wave] = tq; sh_c[u * W + wave] = tc; }
             n_full += q; n_all += c;
         }
+        __syncthreads();
+        unsigned total_q, total_c;
+        const unsigned bq = wave_exscan(lane < U * W ? sh_q[lane] : 0u, total_q);
+        const unsigned bc = wave_exscan(lane < U * W ? sh_c[lane] : 0u, total_c);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int f = f0 + u * T + tid;
+            const unsigned oq = carry_q + (unsigned)__shfl((int)bq, u * W + wave) + eq[u];
+            const unsigned oc = carry_c + (unsigned)__shfl((int)bc, u * W + wave) + ec[u];
+            if (f < a.NF) { fs[f] = oq; cs[f] = oc; }
+        }
+        carry_q += total_q; carry_c += total_c;
+        __syncthreads();                            // the totals have been read
     }
     // exact 64-bit totals
+#pragma unroll
     for (int d = 32; d >= 1; d >>= 1) { n_full += __shfl_xor(n_full, d); n_all += __shfl_xor(n_all, d); }
-    if (lane == 0) { a.cnt_all[inst] = n_all; a.cnt_full[inst] = n_full; }
+    if (lane == 0) { sh_n[0][wave] = n_full; sh_n[1][wave] = n_all; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < W; ++w) { n_full += sh_n[0][w]; n_all += sh_n[1][w]; }
+        a.cnt_all[inst] = n_all; a.cnt_full[inst] = n_full;
+        if (a.run_end) a.run_end[(int64_t)inst * a.N] = n_full;
+    }
+}
+
+// Threads per instance of the flow kernels (count, tail sort): four flows each up to 256 flows; then as many as shorten the one
+// instance a CU has, or, with more than four instances per CU, as few as let them overlap (tail sort of 4096 instances of
+// 2048 flows: 57 us with one wavefront, 37 with 256 threads, 106 with 1024; 3904 of 4096: 364, 157, 213)
+static int flow_threads(int64_t n_inst, int64_t NF)
+{
+    if (NF <= 256) return 64;
+    if (NF <= 1024 || n_inst > 1024) return 256;
+    return 1024;
 }
 
 // ---- B: chunk_off = exclusive scan of instance sizes; tile_off = exclusive scan of fill tiles --
@@ -106,35 +141,48 @@ __global__ __launch_bounds__(1024) void cs_scan_kernel(CsArgs a)
     if (tid == 0) { a.chunk_off[a.n_inst] = carry_a; a.tile_off[a.n_inst] = carry_t; }
 }
 
-// ---- C: tails of one instance: stable descending radix sort in LDS, one wavefront -------------
-__global__ __launch_bounds__(64) void cs_tail_kernel(CsArgs a)
+// ---- C: tails of one instance: stable descending radix sort in LDS, one workgroup per instance ----
+template <int T>
+__global__ __launch_bounds__(T) void cs_tail_kernel(CsArgs a)
 {
-    extern __shared__ unsigned cs_lds[];
-    unsigned *rem = cs_lds;                                              // [NF] tail bytes per flow
-    unsigned *hist = cs_lds + a.NF;                                      // [256]
-    unsigned short *idx_a = reinterpret_cast<unsigned short *>(hist + 256);   // [NF] flow ids, ping
+    extern __shared__ __align__(16) unsigned cs_lds[];
+    __shared__ unsigned sh[kTailShared];
+    unsigned *hist = cs_lds;                                             // [tail_hist_words<T>()], read 16 bytes at a time
+    unsigned *rem = hist + tail_hist_words<T>();                         // [NF] tail bytes per flow
+    unsigned short *idx_a = reinterpret_cast<unsigned short *>(rem + a.NF);    // [NF] flow ids, ping
     unsigned short *idx_b = idx_a + a.NF;                                      // [NF] pong
     if (a.chunk_off[a.n_inst] > a.capacity) return;                      // record arrays too small: leave them alone
 
     const int inst = blockIdx.x;
     const int b = inst / a.M, k = inst % a.M;
-    const int lane = threadIdx.x;
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
 
     int nt = 0;
-    unsigned short *sorted = tail_sort_wave<true>(a, rows, k, rem, hist, idx_a, idx_b, nt);
-    idx_a = sorted;
+    const unsigned short *sorted = tail_sort_block<T>(a, rows, k, rem, hist, idx_a, idx_b, sh, nt);
 
     const int64_t out0 = a.chunk_off[inst] + a.cnt_full[inst];
     const uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;
     const uint32_t n_all = (uint32_t)a.cnt_all[inst];
-    for (int i = lane; i < nt; i += 64) {
-        const int f = idx_a[i];
+    for (int i = threadIdx.x; i < nt; i += T) {
+        const int f = sorted[i];
         a.chunk_w[out0 + i] = rem[f];
         a.chunk_flow[out0 + i] = (uint32_t)f;
         // the tail is its flow's last chunk: one before the canonical start of the next flow
         if (a.perm) a.perm[out0 + i] = (f + 1 < a.NF ? cs[f + 1] : n_all) - 1u;
     }
+}
+
+template <int T>
+static int launch_cs_tail(const CsArgs &a, hipStream_t st)
+{
+    const size_t lds = sizeof(unsigned) * (size_t)(a.NF + tail_hist_words<T>()) + 2 * sizeof(unsigned short) * (size_t)a.NF;
+    if (lds > 48 * 1024) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(cs_tail_kernel<T>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds) != hipSuccess)
+            return RAILSCHED_ERR_HIP;
+    }
+    hipLaunchKernelGGL(cs_tail_kernel<T>, dim3((unsigned)a.n_inst), dim3(T), lds, st, a);
+    return launch_status();
 }
 
 // ---- D: full chunks: tiles of consecutive output positions ------------------------------------
@@ -143,13 +191,12 @@ __global__ __launch_bounds__(64) void cs_tail_kernel(CsArgs a)
 // A tile is filled in spans: as many flow boundaries as fit are staged in LDS (in rounds of 512, until they reach
 // the tile's end), and the span ends where the staged flows end.  Inside a span positions are grouped by fours at
 // multiples of four of the global record index (16-byte stores); a wavefront walks a contiguous quarter of the
-// groups, 64 at a time, so the flow of its first group is known from the step before, one ballot over the next 64
-// boundaries bounds the flows its 256 positions can lie in, and each lane finishes with a binary search over that
-// handful.
+// groups, 64 at a time, and finds the flows of its 256 positions from the starts that fall among them (window_flows).
 __global__ __launch_bounds__(kFillThreads) void cs_fill_kernel(CsArgs a, int vec_ok)
 {
     __shared__ uint32_t st_fs[kFillStage + 1];
     __shared__ uint32_t st_cs[kFillStage];
+    __shared__ __align__(16) unsigned marks[kFillThreads / 64][256];
     if (a.chunk_off[a.n_inst] > a.capacity) return;
     const int64_t n_tiles = a.tile_off[a.n_inst];
     const int64_t u0 = n_tiles * blockIdx.x / gridDim.x, u1 = n_tiles * (blockIdx.x + 1) / gridDim.x;
@@ -227,32 +274,14 @@ __global__ __launch_bounds__(kFillThreads) void cs_fill_kernel(CsArgs a, int vec
                         cnt = 64u - ((G0 + gb) & 63u);
                         cnt = cnt < g1 - gb ? cnt : g1 - gb;
                         const bool active = (uint32_t)lane < cnt;
-                        const uint32_t g = active ? gb + lane : gb + cnt - 1;      // idle lanes shadow the step's last group
-                        const uint32_t p = pa + 4 * g;
-                        const uint32_t g_last = gb + cnt - 1;
-                        const uint32_t p_last = pa + 4 * g_last + 3;
-                        // boundaries j_lo+1 .. j_lo+64: those at or below the step's last position form a prefix
-                        const int probe = j_lo + 1 + lane;
-                        const uint32_t pv = probe <= nf ? st_fs[probe] : 0xFFFFFFFFu;
-                        const int inside = __popcll(__ballot(pv <= p_last));
-                        int lo = j_lo, hi = inside < 64 ? j_lo + inside + 1 : nf;   // flow of p lies in [lo, hi)
-                        while (hi - lo > 1) {
-                            const int mid = (lo + hi) >> 1;
-                            if (st_fs[mid] <= p) lo = mid; else hi = mid;
-                        }
-                        int j = lo;
-                        uint32_t nxt = st_fs[j + 1];
-                        uint32_t base = a.perm ? st_cs[j] - st_fs[j] : 0u;       // canonical position = base + p
+                        const uint32_t p = pa + 4 * (gb + lane);
+                        const uint32_t p_last = pa + 4 * (gb + cnt) - 1;
                         uint32_t fl[4], pm[4];
+                        j_lo = window_flows(st_fs, nf, j_lo, pa + 4 * gb, p_last, marks[wave], fl);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            while (p + e >= nxt) {
-                                ++j;
-                                nxt = st_fs[j + 1];
-                                base = a.perm ? st_cs[j] - st_fs[j] : 0u;
-                            }
-                            fl[e] = (uint32_t)(fb + j);
-                            pm[e] = base + p + e;
+                            if (a.perm) pm[e] = st_cs[fl[e]] - st_fs[fl[e]] + p + e;
+                            fl[e] += (uint32_t)fb;
                         }
                         if (active && a.rail) {                      // leading run: rail = position mod N
                             uint32_t r = a.nmask >= 0 ? (p & (uint32_t)a.nmask) : p % (uint32_t)a.N, rr = 0;
@@ -273,7 +302,6 @@ __global__ __launch_bounds__(kFillThreads) void cs_fill_kernel(CsArgs a, int vec
                             *reinterpret_cast<uint4 *>(a.chunk_flow + out0 + p) = make_uint4(fl[0], fl[1], fl[2], fl[3]);
                             if (a.perm) *reinterpret_cast<uint4 *>(a.perm + out0 + p) = make_uint4(pm[0], pm[1], pm[2], pm[3]);
                         }
-                        j_lo = __builtin_amdgcn_readlane(j, 63);         // flow of the step's last position
                     }
                 }
                 // the few positions before the first and behind the last aligned group
@@ -317,7 +345,11 @@ static void ws_layout(int64_t n_inst, int64_t NF, size_t off[6])
 void cs_ws_layout(int64_t n_inst, int64_t NF, size_t off[6]) { ws_layout(n_inst, NF, off); }
 void launch_cs_count(const CsArgs &a, hipStream_t st)
 {
-    hipLaunchKernelGGL(cs_count_kernel, dim3((unsigned)a.n_inst), dim3(64), 0, st, a);
+    const int T = flow_threads(a.n_inst, a.NF);
+    const dim3 grid((unsigned)a.n_inst);
+    if (T == 64) hipLaunchKernelGGL(cs_count_kernel<64>, grid, dim3(64), 0, st, a);
+    else if (T == 256) hipLaunchKernelGGL(cs_count_kernel<256>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(cs_count_kernel<1024>, grid, dim3(1024), 0, st, a);
 }
 
 }  // namespace rs
@@ -334,8 +366,8 @@ extern "C" size_t railsched_chunk_sort_workspace_bytes(int32_t batch, const rail
 
 namespace rs {
 int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int64_t *chunk_off, uint32_t *chunk_w,
-           uint32_t *chunk_flow, uint32_t *perm, int64_t capacity, uint8_t *rail, void *ws, size_t ws_bytes, hipStream_t st,
-           CsArgs *args_out)
+           uint32_t *chunk_flow, uint32_t *perm, int64_t capacity, uint8_t *rail, int64_t *run_end, void *ws, size_t ws_bytes,
+           hipStream_t st, CsArgs *args_out)
 {
     if (int rc = check_topo(h_topo)) return rc;
     if (batch < 0 || capacity < 0) return RAILSCHED_ERR_INVALID_ARG;
@@ -365,27 +397,22 @@ int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int
     a.M = (int32_t)M; a.N = (int32_t)N; a.G = (int32_t)G; a.NF = (int32_t)NF; a.intra = h_topo->include_intra_node;
     a.n_inst = (int32_t)n_inst;
     a.rail = rail;
+    a.run_end = run_end;
     a.nmask = is_pow2(N) ? (int32_t)N - 1 : -1;
     a.gmask = is_pow2(G) ? (int32_t)G - 1 : -1;
     a.nshift = is_pow2(N) ? ilog2(N) : -1;
     if (args_out) *args_out = a;
 
     if (n_inst > 0) {
-        hipLaunchKernelGGL(cs_count_kernel, dim3((unsigned)n_inst), dim3(64), 0, st, a);
+        launch_cs_count(a, st);
         if (int rc = launch_status()) return rc;
     }
     hipLaunchKernelGGL(cs_scan_kernel, dim3(1), dim3(1024), 0, st, a);
     if (int rc = launch_status()) return rc;
     if (!chunk_w || n_inst == 0) return RAILSCHED_OK;
 
-    const size_t lds = sizeof(unsigned) * (size_t)(NF + 256) + 2 * sizeof(unsigned short) * (size_t)NF;
-    if (lds > 48 * 1024) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(cs_tail_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess)
-            return RAILSCHED_ERR_HIP;
-    }
-    hipLaunchKernelGGL(cs_tail_kernel, dim3((unsigned)n_inst), dim3(64), lds, st, a);
-    if (int rc = launch_status()) return rc;
+    const int T = flow_threads(n_inst, NF);
+    if (int rc = T == 64 ? launch_cs_tail<64>(a, st) : T == 256 ? launch_cs_tail<256>(a, st) : launch_cs_tail<1024>(a, st)) return rc;
     const int vec_ok = (reinterpret_cast<uintptr_t>(chunk_w) % 16 == 0 && reinterpret_cast<uintptr_t>(chunk_flow) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(perm) % 16 == 0 && reinterpret_cast<uintptr_t>(rail) % 4 == 0) ? 1 : 0;
     // no launch needs more workgroups than there can be tiles: capacity/tile full ones and one ragged one per instance
@@ -400,6 +427,6 @@ extern "C" int railsched_chunk_sort(const int64_t *D1, int32_t batch, const rail
                                     int64_t *chunk_off, uint32_t *chunk_w, uint32_t *chunk_flow, uint32_t *perm,
                                     int64_t capacity, void *ws, size_t ws_bytes, void *stream)
 {
-    return rs::cs_run(D1, batch, h_topo, chunk_off, chunk_w, chunk_flow, perm, capacity, nullptr, ws, ws_bytes,
+    return rs::cs_run(D1, batch, h_topo, chunk_off, chunk_w, chunk_flow, perm, capacity, nullptr, nullptr, ws, ws_bytes,
                       static_cast<hipStream_t>(stream), nullptr);
 }

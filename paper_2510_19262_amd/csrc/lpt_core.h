@@ -349,6 +349,66 @@ __device__ __forceinline__ void lpt_wide_body_sorted(const uint32_t *__restrict_
     }
 }
 
+// The same function for `n` chunks in LDS that are mostly runs of one weight (N <= 16; no weight above WideLimit; the 64 words behind the
+// last weight are readable).  The chain goes from run to run: with all loads within one weight of each other the rest of the
+// run, up to 64 chunks, is closed form (see closed_period: the list is visited front to back, round after round, and then
+// rotated by the run's length mod N); 16 ordinary steps when they are further apart or the run is shorter than that.  After N steps of
+// one weight from loads a little over it apart - what the heavier run before leaves - they are within it.
+// An iteration is about 700 cycles where a step of the plain chain is 33, so runs have to hold about 24 chunks on average: decode layer
+// of 512 GPUs, 966 tails of 9 values: 33 iterations, the instance kernel 29 -> 24 us; 867 tails of 16 values: 28 -> 21.
+template <int GW>
+__device__ __forceinline__ void lpt_runs_body(const uint32_t *__restrict__ w, uint8_t *__restrict__ rails, int n, unsigned long long base,
+                                              int N, int64_t *__restrict__ S_row)
+{
+    static_assert(GW <= 16, "the list fits a row");
+    constexpr int S = GroupBits<GW>::S;
+    constexpr unsigned MASK = (unsigned)GW - 1u;
+    const int lane = threadIdx.x & 63;
+    const unsigned r = (unsigned)lane & 15u;        // place in the list; the four rows carry copies
+    const bool in_list = (int)r < N;
+    const unsigned inv = (65536u + (unsigned)N - 1u) / (unsigned)N;   // x * inv >> 16 == x / N for x <= 64
+    const int place = (lane & 48) | (int)((unsigned)lane % (unsigned)N);   // lane whose entry takes chunk `lane` of a closed run
+    unsigned t = in_list ? ~r : 0u;
+    for (int pos = 0; pos < n;) {
+        const unsigned wv = w[pos + lane];
+        const unsigned w0 = (unsigned)__builtin_amdgcn_readfirstlane((int)wv);
+        const unsigned long long other = __ballot(wv != w0);
+        int run = other ? (int)__builtin_ctzll(other) : 64;
+        run = run < n - pos ? run : n - pos;
+        const unsigned dmin = (~(unsigned)__builtin_amdgcn_readfirstlane((int)t)) >> S;
+        const unsigned dmax = (~(unsigned)__builtin_amdgcn_readlane((int)t, N - 1)) >> S;
+        if (run >= 16 && dmax - dmin < w0) {
+            const unsigned took = (unsigned)__shfl((int)t, place);
+            const unsigned per = ((unsigned)run * inv) >> 16, extra = (unsigned)run - per * (unsigned)N;
+            const unsigned grown = t - ((w0 * (per + (r < extra ? 1u : 0u))) << S);
+            unsigned from = r + extra;              // the list rotates by `extra`
+            from = from >= (unsigned)N ? from - (unsigned)N : from;
+            const unsigned moved = (unsigned)__shfl((int)grown, (lane & 48) | (int)(from & 15u));
+            t = in_list ? moved : 0u;
+            if (lane < run) rails[pos + lane] = (uint8_t)(~took & MASK);
+            pos += run;
+        } else {
+            // a run: one chunk for every rail that stays at or below the fullest with it, which brings the loads within w0 (or closer);
+            // whole rounds of a run would leave ties a full w0 apart as they are
+            int left = 16;
+            if (run >= 16) left = (int)__popcll(__ballot(in_list && ((~t) >> S) + w0 <= dmax) & 0xFFFFull);
+            left = n - pos < left ? n - pos : left;
+            unsigned won = 0;
+            sorted_steps<true, 0>(t, won, (lane < left ? wv : 0u) << S);   // weight 0 changes nothing (blocks of 4 and 8 steps: no faster)
+            if (lane >= 48 && lane - 48 < left) rails[pos + lane - 48] = (uint8_t)(~won & MASK);
+            pos += left;
+        }
+        // the emptiest rail's delta moves into the base, so deltas stay below the packing limit
+        const unsigned adv = (~(unsigned)__builtin_amdgcn_readfirstlane((int)t)) >> S;
+        if (in_list) t += adv << S;
+        base += adv;
+    }
+    if (lane < N) {
+        const unsigned key = ~t;
+        S_row[key & MASK] = (int64_t)(base + (unsigned long long)(key >> S));
+    }
+}
+
 template <int GW, bool RUNS>
 __device__ __forceinline__ void lpt_wide_body(const uint32_t *__restrict__ wsrc, uint8_t *__restrict__ rdst, int64_t len,
                                               unsigned long long base, int N, int64_t *__restrict__ S_row,

@@ -10,9 +10,9 @@
 // of HBM traffic per chunk in all instead of 27.  Small ones - up to 1024 instances of a few thousand chunks, the
 // shape of one training step's MoE layers - are bound by the latency of nine dependent launches, so they take
 // three: the per-instance counts (stage 3's count kernel), then ONE workgroup per instance that does everything
-// the instance needs, then the per-matrix reduction of stage 5.  Inside the workgroup, wavefront 0 sorts the
-// tails and runs the serial LPT chain on them - weights and rails in LDS, the chain being what bounds the time -
-// while the other wavefronts write the full-chunk records, the round-robin rails of the leading run (closed
+// the instance needs, then the per-matrix reduction of stage 5.  Inside the workgroup all wavefronts sort the
+// tails; then wavefront 0 runs the serial LPT chain on them - weights and rails in LDS, the chain being what bounds the
+// time - while the other wavefronts write the full-chunk records, the round-robin rails of the leading run (closed
 // form: from empty rails a run of one weight is rail = i mod N) and the receive loads those imply.
 #include "chunk_core.h"
 #include "eval_core.h"
@@ -50,11 +50,13 @@ int lpt_serial_after_leading_runs(const int64_t *chunk_off, const uint32_t *chun
                                   int64_t *S, int64_t capacity, hipStream_t st);   // lpt_spray.hip
 void cs_ws_layout(int64_t n_inst, int64_t NF, size_t off[6]);  // chunk_sort.hip
 
-constexpr int kSsThreads = 512;         // one wavefront on the chain, seven on the records (three: 6 us more per call on 256 instances of 7 K chunks)
 constexpr int kSlThreads = 256;         // closed-form receive loads of large batches
+constexpr int kSsRun = 24;              // late chunks per run of one weight from which the chain goes run by run (lpt_runs_body)
 constexpr int kSsMaxInst = 1024;        // instances whose counts one workgroup adds up
-constexpr int kSsMaxFlows = 2048;       // N*G of an instance held in LDS
-constexpr int kSsMaxAvg = 32768;        // chunks per instance (capacity / instances) above which one workgroup is too few
+constexpr int kSsMaxFlows = 4096;       // N*G of an instance held in LDS
+constexpr int kSsWideFlows = 1024;      // N*G above which an instance's workgroup has 1024 threads instead of 512: 16 flows a thread of the sort at most
+constexpr int kSsMaxInstWide = 256;     // instances of more than 2048 flows: one workgroup per CU, one round of them
+constexpr int kSsMaxAvg = 65536;        // chunks per instance (capacity / instances) above which one workgroup is too few
 
 struct SsArgs {
     uint8_t *rail;
@@ -70,21 +72,51 @@ __device__ __forceinline__ int ss_dst_node(const CsArgs &a, const SsArgs &x, uin
     return (int)((flow % (uint32_t)a.G) / (uint32_t)a.N);
 }
 
-template <int GW>
+// Receive loads of the leading run (positions below `lead`, rails i mod N) into bins[G], in closed form.  The flows of one source
+// GPU to the N GPUs of one node are neighbours in canonical order, so their full chunks are one range of positions:
+// NF / N ranges of N rails each, dealt to the threads t, t + T, ... (per flow, as before, it was N times the atomics).
+__device__ __forceinline__ void add_leading_run(const CsArgs &a, const SsArgs &x, const uint32_t *fs, uint32_t n_full, uint32_t lead,
+                                                unsigned long long *bins, int t, int T)
+{
+    const int N = a.N, ranges = a.NF / N;
+    const uint32_t cw = (uint32_t)a.C;
+    for (int i = t; i < ranges; i += T) {
+        const uint32_t s = fs[i * N];
+        uint32_t e = i + 1 < ranges ? fs[(i + 1) * N] : n_full;
+        e = e < lead ? e : lead;
+        if (s >= e) continue;
+        const int node = i % a.M;
+        for (int n = 0; n < N; ++n) {
+            // positions i < v with i mod N == n number (v + N - 1 - n) / N
+            const uint32_t up = (uint32_t)(N - 1 - n);
+            const uint32_t c = x.nshift >= 0 ? ((e + up) >> x.nshift) - ((s + up) >> x.nshift) : (e + up) / (uint32_t)N - (s + up) / (uint32_t)N;
+            if (c) atomicAdd(&bins[node * N + n], (unsigned long long)c * (unsigned long long)cw);
+        }
+    }
+}
+
+// LDS words of hist, which the late chunks' weights take over once the tails are sorted
+template <int T>
+__host__ __device__ constexpr int ss_hist_words(int NF) { return tail_hist_words<T>() > NF + 128 ? tail_hist_words<T>() : (NF + 128 + 3) / 4 * 4; }
+// LDS words of rem, where the wavefronts that write records then mark flow starts
+template <int T>
+__host__ __device__ constexpr int ss_rem_words(int NF) { return 256 * (T / 64 - 1) > NF ? 256 * (T / 64 - 1) : (NF + 3) / 4 * 4; }
+
+template <int GW, int kSsThreads>
 __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArgs x)
 {
-    extern __shared__ unsigned long long ss_lds64[];
+    extern __shared__ __align__(16) unsigned long long ss_lds64[];
     __shared__ int64_t sh_red[2][kSsThreads / 64];
-    __shared__ unsigned sh_wmax;
-    __shared__ int sh_nt, sh_sorted_in_b;                                // wavefront 0's sort result, for the others
-    // LDS: bins[G] u64 | st_fs[NF+1] | st_cs[NF] | rem[NF] | hist[256] | late_w[NF+64] | idx_a[NF] idx_b[NF] u16 | late_rail[NF+64] u8
-    unsigned long long *bins = ss_lds64;
+    __shared__ unsigned sh_runs;
+    __shared__ unsigned sh_sort[kTailShared];
+    // LDS: hist / late_w | rem[NF] / marks | bins[G] u64 | st_fs[NF+1] | st_cs[NF] | idx_a[NF] idx_b[NF] u16 | late_rail[NF+64] u8
+    unsigned *hist = reinterpret_cast<unsigned *>(ss_lds64);             // read 16 bytes at a time
+    unsigned *late_w = hist;
+    unsigned *rem = hist + ss_hist_words<kSsThreads>(a.NF);              // later the record writers' marks, 16-byte aligned
+    unsigned long long *bins = reinterpret_cast<unsigned long long *>(rem + ss_rem_words<kSsThreads>(a.NF));
     unsigned *st_fs = reinterpret_cast<unsigned *>(bins + a.G);
     unsigned *st_cs = st_fs + a.NF + 1;
-    unsigned *rem = st_cs + a.NF;
-    unsigned *hist = rem + a.NF;
-    unsigned *late_w = hist + 256;
-    unsigned short *idx_a = reinterpret_cast<unsigned short *>(late_w + a.NF + 64);
+    unsigned short *idx_a = reinterpret_cast<unsigned short *>(st_cs + a.NF);
     unsigned short *idx_b = idx_a + a.NF;
     uint8_t *late_rail = reinterpret_cast<uint8_t *>(idx_b + a.NF);
 
@@ -93,41 +125,30 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int N = a.N;
 
-    // ---- wavefront 0 starts on the tails at once; the others add up the offsets (chunks of the instances before
-    // this one, and of all) and stage this instance's flow starts
-    int nt = 0;
-    const unsigned short *sorted = idx_a;
+    // ---- offsets (chunks of the instances before this one, and of all), this instance's flow starts, then the tails
     int64_t before = 0, total = 0;
-    if (wave == 0) {
-        const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
-        sorted = tail_sort_wave<false>(a, rows, k, rem, hist, idx_a, idx_b, nt);
-        if (lane == 0) { sh_nt = nt; sh_sorted_in_b = sorted == idx_b ? 1 : 0; }
-    } else {
-        constexpr int T = kSsThreads - 64;
-        const int t = tid - 64;
-        for (int i = t; i < a.n_inst; i += T) {
-            const int64_t c = a.cnt_all[i];
-            total += c;
-            before += i < inst ? c : 0;
-        }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) { before += __shfl_xor(before, d); total += __shfl_xor(total, d); }
-        for (int i = t; i < a.G; i += T) bins[i] = 0;
-        const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
-        const uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;
-        for (int i = t; i < a.NF; i += T) { st_fs[i] = fs[i]; st_cs[i] = cs[i]; }
-        if (t == 0) st_fs[a.NF] = 0xFFFFFFFFu;                           // nothing starts behind the last flow
+    for (int i = tid; i < a.n_inst; i += kSsThreads) {
+        const int64_t c = a.cnt_all[i];
+        total += c;
+        before += i < inst ? c : 0;
     }
-    if (lane == 0) { sh_red[0][wave] = before; sh_red[1][wave] = total; }
+    for (int i = tid; i < a.G; i += kSsThreads) bins[i] = 0;
+    const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
+    const uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;
+    for (int i = tid; i < a.NF; i += kSsThreads) { st_fs[i] = fs[i]; st_cs[i] = cs[i]; }
+    if (tid == 0) { st_fs[a.NF] = 0xFFFFFFFFu; sh_runs = 0; }            // nothing starts behind the last flow
     const uint32_t n_full = (uint32_t)a.cnt_full[inst];
     const uint32_t n_all = (uint32_t)a.cnt_all[inst];
-    __syncthreads();
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) { before += __shfl_xor(before, d); total += __shfl_xor(total, d); }
+    if (lane == 0) { sh_red[0][wave] = before; sh_red[1][wave] = total; }
+    int nt = 0;
+    const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
+    const unsigned short *sorted = tail_sort_block<kSsThreads>(a, rows, k, rem, hist, idx_a, idx_b, sh_sort, nt);   // its barriers cover the above
     before = 0; total = 0;
 #pragma unroll
     for (int w = 0; w < kSsThreads / 64; ++w) { before += sh_red[0][w]; total += sh_red[1][w]; }
     const int64_t out0 = before;
-    nt = sh_nt;
-    sorted = sh_sorted_in_b ? idx_b : idx_a;
     if (tid == 0) {
         a.chunk_off[inst] = out0;
         if (inst == a.n_inst - 1) a.chunk_off[a.n_inst] = total;
@@ -142,23 +163,32 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
     const uint32_t skip = n_full - n_full % (uint32_t)N;
     const uint32_t late_full = n_full - skip;                            // full chunks left to the chain (< N)
 
-    if (wave == 0) {
-        // ---- the serial chain over [late full chunks | sorted tails]; the others write the tails' records
-        for (int i = lane; i < nt; i += 64) late_w[late_full + i] = rem[sorted[i]];
-        if (lane < (int)late_full) late_w[lane] = cw;
-        if (lane == 0) sh_wmax = n_full ? cw : (nt ? rem[sorted[0]] : 0u);
-        lds_sync<false>();
-        const int64_t n_late = (int64_t)late_full + nt;
-        lpt_wide_body<GW, true>(late_w, late_rail, n_late, (unsigned long long)cw * (unsigned long long)(skip / (uint32_t)N), N,
-                                x.S + (int64_t)inst * N, late_w);
-        lds_sync<false>();
-        // rails of the late chunks to memory, and their bytes to the receive bins
-        for (int i = lane; i < (int)n_late; i += 64) {
-            const unsigned r = late_rail[i];
-            x.rail[out0 + skip + i] = (uint8_t)r;
-            const uint32_t f = i < (int)late_full ? (uint32_t)last_le<uint32_t>(st_fs, a.NF, skip + i) : (uint32_t)sorted[i - late_full];
-            atomicAdd(&bins[ss_dst_node(a, x, f) * N + r], (unsigned long long)late_w[i]);
+    const int n_late = (int)late_full + nt;
+    {   // the late chunks' weights, and how many runs of one weight they are
+        unsigned starts = 0, total_starts;
+        for (int i = tid; i < nt; i += kSsThreads) {
+            const unsigned w = rem[sorted[i]];
+            late_w[late_full + i] = w;
+            starts += (i == 0 || rem[sorted[i - 1]] != w) ? 1u : 0u;
         }
+        if (tid < (int)late_full) late_w[tid] = cw;
+        if (tid < 64) late_w[n_late + tid] = 0;
+        wave_exscan(starts, total_starts);
+        if (lane == 0 && total_starts) atomicAdd(&sh_runs, total_starts);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        // ---- the serial chain over [late full chunks | sorted tails]; the others write the records
+        __builtin_amdgcn_s_setprio(3);              // it is what the workgroup waits for
+        const unsigned long long base = (unsigned long long)cw * (unsigned long long)(skip / (uint32_t)N);
+        int64_t *S_row = x.S + (int64_t)inst * N;
+        bool runs = false;
+        if constexpr (GW <= 16) {
+            runs = n_late >= kSsRun * (int)(sh_runs + 1u);
+            if (runs) lpt_runs_body<GW>(late_w, late_rail, n_late, base, N, S_row);
+        }
+        if (!runs) lpt_wide_body<GW, true>(late_w, late_rail, n_late, base, N, S_row, late_w);
+        __builtin_amdgcn_s_setprio(0);
     } else {
         // ---- full chunks: records, rails of the leading run, receive loads of the leading run
         const int t = tid - 64;
@@ -166,7 +196,7 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
         const int64_t tail0 = out0 + n_full;
         for (int i = t; i < nt; i += T) {
             const int f = sorted[i];
-            a.chunk_w[tail0 + i] = rem[f];
+            a.chunk_w[tail0 + i] = late_w[late_full + i];
             a.chunk_flow[tail0 + i] = (uint32_t)f;
             // the tail is its flow's last chunk: one before the canonical start of the next flow
             if (a.perm) a.perm[tail0 + i] = (f + 1 < a.NF ? st_cs[f + 1] : n_all) - 1u;
@@ -176,23 +206,31 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
             const uint32_t pa = n_full < head ? n_full : head;
             const uint32_t groups = (n_full - pa) / 4;
             const uint32_t pb = pa + groups * 4;
-            // lane l of a wavefront takes a group whose global index is l mod 64, so the 64 lanes store one whole
-            // kilobyte on a 1 KiB boundary of each record array
-            const uint32_t lead_in = (uint32_t)(((out0 + pa) >> 2) & 63);
-            for (uint32_t gs = t; gs < groups + lead_in; gs += T) {
-                if (gs < lead_in) continue;
-                const uint32_t g = gs - lead_in;
-                const uint32_t p = pa + 4 * g;
-                int j = last_le<uint32_t>(st_fs, a.NF, p);
-                uint32_t nxt = st_fs[j + 1];
-                uint32_t base = st_cs[j] - st_fs[j];                     // canonical position = base + p
+            // A wavefront streams a contiguous share of the groups, 64 at a time: shares and steps end where the global group index is
+            // a multiple of 64, so the 64 lanes store one whole kilobyte on a 1 KiB boundary of each record array.
+            constexpr int kFill = kSsThreads / 64 - 1;
+            const uint32_t G0 = (uint32_t)(((out0 + pa) >> 2) & 63);      // global group index of group 0, mod 64
+            auto share = [&](int w) {
+                if (w <= 0) return 0u;
+                if (w >= kFill) return groups;
+                const uint32_t cut = ((G0 + (uint32_t)((uint64_t)groups * w / kFill)) & ~63u);
+                return cut > G0 ? cut - G0 : 0u;
+            };
+            const uint32_t g0 = share(wave - 1), g1 = share(wave);
+            unsigned *mark = rem + (wave - 1) * 256;                      // the tails' bytes are in late_w by now
+            int j_lo = g0 < g1 ? last_le<uint32_t>(st_fs, a.NF, pa + 4 * g0) : 0;
+            uint32_t cnt = 0;
+            for (uint32_t gb = g0; gb < g1; gb += cnt) {
+                cnt = 64u - ((G0 + gb) & 63u);
+                cnt = cnt < g1 - gb ? cnt : g1 - gb;
+                const uint32_t p = pa + 4 * (gb + lane);
                 uint32_t fl[4], pm[4], rr = 0;
+                j_lo = window_flows(st_fs, a.NF, j_lo, pa + 4 * gb, pa + 4 * (gb + cnt) - 1, mark, fl);
+                if ((uint32_t)lane >= cnt) continue;
                 uint32_t r = x.nshift >= 0 ? (p & ((1u << x.nshift) - 1u)) : p % (uint32_t)N;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    while (p + e >= nxt) { ++j; nxt = st_fs[j + 1]; base = st_cs[j] - st_fs[j]; }
-                    fl[e] = (uint32_t)j;
-                    pm[e] = base + p + e;
+                    if (a.perm) pm[e] = st_cs[fl[e]] - st_fs[fl[e]] + p + e;
                     rr |= r << (8 * e);
                     r = (r + 1 == (uint32_t)N) ? 0u : r + 1;
                 }
@@ -224,34 +262,23 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
                 if (p < skip) x.rail[out0 + p] = (uint8_t)(p % (uint32_t)N);
             }
         }
-        // receive loads of the leading run, flow by flow: positions [s, e) below `skip` take rails s mod N, s+1 mod N, ...
-        for (int f = t; f < a.NF; f += T) {
-            const uint32_t s = st_fs[f];
-            uint32_t e = f + 1 < a.NF ? st_fs[f + 1] : n_full;
-            e = e < skip ? e : skip;
-            if (s >= e) continue;
-            const int node = ss_dst_node(a, x, (uint32_t)f);
-            for (int n = 0; n < N; ++n) {
-                // positions i < v with i mod N == n number (v + N - 1 - n) / N
-                const uint32_t up = (uint32_t)(N - 1 - n);
-                const uint32_t c = x.nshift >= 0 ? ((e + up) >> x.nshift) - ((s + up) >> x.nshift) : (e + up) / (uint32_t)N - (s + up) / (uint32_t)N;
-                if (c) atomicAdd(&bins[node * N + n], (unsigned long long)c * (unsigned long long)cw);
-            }
-        }
+        add_leading_run(a, x, st_fs, n_full, skip, bins, t, T);
+    }
+    __syncthreads();
+    // rails of the late chunks to memory, and their bytes to the receive bins
+    for (int i = tid; i < n_late; i += kSsThreads) {
+        const unsigned r = late_rail[i];
+        x.rail[out0 + skip + i] = (uint8_t)r;
+        const uint32_t f = i < (int)late_full ? (uint32_t)last_le<uint32_t>(st_fs, a.NF, skip + i) : (uint32_t)sorted[i - late_full];
+        atomicAdd(&bins[ss_dst_node(a, x, f) * N + r], (unsigned long long)late_w[i]);
     }
     __syncthreads();
     int64_t *slot = x.partial + (int64_t)inst * (a.G + 1);               // [b][k][G + 1]
     for (int i = tid; i < a.G; i += kSsThreads) slot[i] = (int64_t)bins[i];
-    if (tid == 0) slot[a.G] = (int64_t)sh_wmax;
+    if (tid == 0) slot[a.G] = n_full ? (int64_t)cw : nt ? (int64_t)late_w[0] : 0;   // no full chunk: the first tail is the largest
 }
 
 // ---------------------------------------------------------------------------------------------- large batches
-// S[inst*N] = length of the instance's leading run of full chunks, where stage 4's serial kernels look for it
-__global__ void sl_run_end_kernel(CsArgs a, int64_t *S)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < a.n_inst; i += gridDim.x * blockDim.x) S[(int64_t)i * a.N] = a.cnt_full[i];
-}
-
 // Receive loads of one instance into its workspace slot [G + 1]: the leading run (positions below
 // n_full - n_full mod N, rails i mod N) flow by flow in closed form, the chunks behind it from their records.
 __global__ __launch_bounds__(kSlThreads) void sl_recv_kernel(CsArgs a, SsArgs x)
@@ -263,22 +290,9 @@ __global__ __launch_bounds__(kSlThreads) void sl_recv_kernel(CsArgs a, SsArgs x)
     __syncthreads();
     const uint32_t n_full = (uint32_t)a.cnt_full[inst], n_all = (uint32_t)a.cnt_all[inst];
     const uint32_t lead = n_full - n_full % (uint32_t)N;
-    const uint32_t cw = (uint32_t)a.C;
     const int64_t out0 = a.chunk_off[inst];
     const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
-    for (int f = tid; f < a.NF; f += kSlThreads) {
-        const uint32_t s = fs[f];
-        uint32_t e = f + 1 < a.NF ? fs[f + 1] : n_full;
-        e = e < lead ? e : lead;
-        if (s >= e) continue;
-        const int node = ss_dst_node(a, x, (uint32_t)f);
-        for (int n = 0; n < N; ++n) {
-            // positions i < v with i mod N == n number (v + N - 1 - n) / N
-            const uint32_t up = (uint32_t)(N - 1 - n);
-            const uint32_t c = x.nshift >= 0 ? ((e + up) >> x.nshift) - ((s + up) >> x.nshift) : (e + up) / (uint32_t)N - (s + up) / (uint32_t)N;
-            if (c) atomicAdd(&sl_bins[node * N + n], (unsigned long long)c * (unsigned long long)cw);
-        }
-    }
+    add_leading_run(a, x, fs, n_full, lead, sl_bins, tid, kSlThreads);
     for (uint32_t p = lead + tid; p < n_all; p += kSlThreads) {
         const unsigned r = x.rail[out0 + p];
         const int node = ss_dst_node(a, x, a.chunk_flow[out0 + p]);
@@ -290,18 +304,24 @@ __global__ __launch_bounds__(kSlThreads) void sl_recv_kernel(CsArgs a, SsArgs x)
     if (tid == 0) slot[a.G] = n_all ? (int64_t)a.chunk_w[out0] : 0;      // records are sorted: the first is the largest
 }
 
-template <int GW>
-static int launch_ss(const CsArgs &a, const SsArgs &x, hipStream_t st)
+template <int GW, int T>
+static int launch_ss_t(const CsArgs &a, const SsArgs &x, hipStream_t st)
 {
-    const size_t lds = sizeof(unsigned long long) * (size_t)a.G + sizeof(unsigned) * (size_t)(4 * a.NF + 1 + 256 + 64) +
+    const size_t lds = sizeof(unsigned long long) * (size_t)a.G + sizeof(unsigned) * (size_t)(2 * a.NF + 1 + ss_rem_words<T>(a.NF) + ss_hist_words<T>(a.NF)) +
                        2 * sizeof(unsigned short) * (size_t)a.NF + (size_t)a.NF + 64 + 16;
     if (lds > 48 * 1024) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(ss_instance_kernel<GW>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(ss_instance_kernel<GW, T>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds) != hipSuccess)
             return RAILSCHED_ERR_HIP;
     }
-    hipLaunchKernelGGL((ss_instance_kernel<GW>), dim3((unsigned)a.n_inst), dim3(kSsThreads), lds, st, a, x);
+    hipLaunchKernelGGL((ss_instance_kernel<GW, T>), dim3((unsigned)a.n_inst), dim3(T), lds, st, a, x);
     return launch_status();
+}
+
+template <int GW>
+static int launch_ss(const CsArgs &a, const SsArgs &x, hipStream_t st)
+{
+    return a.NF > kSsWideFlows ? launch_ss_t<GW, 1024>(a, x, st) : launch_ss_t<GW, 512>(a, x, st);
 }
 
 }  // namespace rs
@@ -338,7 +358,7 @@ static int schedule_run(const int64_t *D1, int32_t batch, const railsched_topo_t
     const int GW = N <= 4 ? 4 : N <= 8 ? 8 : N <= 16 ? 16 : N <= 32 ? 32 : 64;
     const unsigned w_limit = GW == 4 ? WideLimit<4>::value : GW == 8 ? WideLimit<8>::value : GW == 16 ? WideLimit<16>::value
                            : GW == 32 ? WideLimit<32>::value : WideLimit<64>::value;
-    const bool small = n_inst <= kSsMaxInst && NF <= kSsMaxFlows && capacity <= n_inst * (int64_t)kSsMaxAvg &&
+    const bool small = n_inst <= (NF <= 2048 ? kSsMaxInst : kSsMaxInstWide) && NF <= kSsMaxFlows && capacity <= n_inst * (int64_t)kSsMaxAvg &&
                        (uint64_t)h_topo->chunk_bytes <= (uint64_t)w_limit;
     SsArgs x;
     x.rail = rail; x.S = S; x.partial = reinterpret_cast<int64_t *>(w8 + ws_sort);
@@ -354,9 +374,7 @@ static int schedule_run(const int64_t *D1, int32_t batch, const railsched_topo_t
 
     if (!small) {
         CsArgs a;
-        if (int rc = cs_run(D1, batch, h_topo, chunk_off, chunk_w, chunk_flow, perm, capacity, rail, w8, ws_sort, st, &a)) return rc;
-        hipLaunchKernelGGL(sl_run_end_kernel, dim3((unsigned)((n_inst + 255) / 256 > 1024 ? 1024 : (n_inst + 255) / 256)), dim3(256), 0, st, a, S);
-        if (int rc = launch_status()) return rc;
+        if (int rc = cs_run(D1, batch, h_topo, chunk_off, chunk_w, chunk_flow, perm, capacity, rail, S, w8, ws_sort, st, &a)) return rc;
         if (int rc = lpt_serial_after_leading_runs(chunk_off, chunk_w, n_inst, (int)N, rail, S, capacity, st)) return rc;
         const size_t lds = sizeof(unsigned long long) * (size_t)G;
         if (lds > 48 * 1024) {
@@ -384,7 +402,7 @@ static int schedule_run(const int64_t *D1, int32_t batch, const railsched_topo_t
     a.cshift = is_pow2(a.C) ? ilog2(a.C) : -1;
     a.M = (int32_t)M; a.N = (int32_t)N; a.G = (int32_t)G; a.NF = (int32_t)NF; a.intra = h_topo->include_intra_node;
     a.n_inst = (int32_t)n_inst;
-    a.rail = nullptr; a.nmask = -1;                 // unused by the count kernel
+    a.rail = nullptr; a.nmask = -1; a.run_end = nullptr;   // unused by the count kernel
     a.gmask = is_pow2(G) ? (int32_t)G - 1 : -1;
     a.nshift = is_pow2(N) ? ilog2(N) : -1;
     launch_cs_count(a, st);
