@@ -126,9 +126,10 @@ constexpr int kRankTails = 256;     // tails up to which places are counted inst
 // array that holds the sorted ids and their number in nt.  Latency bound: one wavefront took 32 us for the 4096 flows of a
 // 512-GPU instance, and four of them per CU (its LDS) 364 us for 3904 such instances; a workgroup of 1024 takes 14 us for 128 instances of 8192 flows (67 before),
 // one of 256 155 us for the 3904.
-template <int T>
+// stage() is called once with the first flows' loads in flight, for what the caller has to fetch as well.
+template <int T, typename F>
 __device__ __forceinline__ unsigned short *tail_sort_block(const CsArgs &a, const int64_t *rows, int k, unsigned *rem, unsigned *hist,
-                                                           unsigned short *idx_a, unsigned short *idx_b, unsigned *sh, int &nt_out)
+                                                           unsigned short *idx_a, unsigned short *idx_b, unsigned *sh, int &nt_out, F stage)
 {
     constexpr int W = T / 64, U = kTailLoads;
     static_assert(U * W <= 64, "one lane per (round, wavefront)");
@@ -146,6 +147,7 @@ __device__ __forceinline__ unsigned short *tail_sort_block(const CsArgs &a, cons
             const int f = f0 + u * T + tid;
             bytes[u] = f < a.NF ? flow_bytes(a, rows, k, f) : 0;
         }
+        if (f0 == 0) stage();
         unsigned r[U];
         unsigned long long m[U];
 #pragma unroll

@@ -57,9 +57,16 @@ __global__ __launch_bounds__(T) void cs_count_kernel(CsArgs a)
             unsigned tq, tc;
             eq[u] = wave_exscan(q, tq);
             ec[u] = wave_exscan(c, tc);
-            if (lane == 0) { sh_q[u * W + wave] = tq; sh_c[u * W + wave] = tc; }
+            if constexpr (W == 1) {                 // a wavefront by itself carries its totals along
+                const int f = f0 + u * T + tid;
+                if (f < a.NF) { fs[f] = carry_q + eq[u]; cs[f] = carry_c + ec[u]; }
+                carry_q += tq; carry_c += tc;
+            } else if (lane == 0) {
+                sh_q[u * W + wave] = tq; sh_c[u * W + wave] = tc;
+            }
             n_full += q; n_all += c;
         }
+        if constexpr (W == 1) continue;
         __syncthreads();
         unsigned total_q, total_c;
         const unsigned bq = wave_exscan(lane < U * W ? sh_q[lane] : 0u, total_q);
@@ -77,8 +84,10 @@ __global__ __launch_bounds__(T) void cs_count_kernel(CsArgs a)
     // exact 64-bit totals
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) { n_full += __shfl_xor(n_full, d); n_all += __shfl_xor(n_all, d); }
-    if (lane == 0) { sh_n[0][wave] = n_full; sh_n[1][wave] = n_all; }
-    __syncthreads();
+    if constexpr (W > 1) {
+        if (lane == 0) { sh_n[0][wave] = n_full; sh_n[1][wave] = n_all; }
+        __syncthreads();
+    }
     if (tid == 0) {
         for (int w = 1; w < W; ++w) { n_full += sh_n[0][w]; n_all += sh_n[1][w]; }
         a.cnt_all[inst] = n_all; a.cnt_full[inst] = n_full;
@@ -158,7 +167,7 @@ __global__ __launch_bounds__(T) void cs_tail_kernel(CsArgs a)
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
 
     int nt = 0;
-    const unsigned short *sorted = tail_sort_block<T>(a, rows, k, rem, hist, idx_a, idx_b, sh, nt);
+    const unsigned short *sorted = tail_sort_block<T>(a, rows, k, rem, hist, idx_a, idx_b, sh, nt, [] {});
 
     const int64_t out0 = a.chunk_off[inst] + a.cnt_full[inst];
     const uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;

@@ -125,26 +125,29 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int N = a.N;
 
-    // ---- offsets (chunks of the instances before this one, and of all), this instance's flow starts, then the tails
+    // ---- the tails; while their flows are on the way, the offsets (chunks of the instances before this one, and of all) and this
+    // instance's flow starts
     int64_t before = 0, total = 0;
-    for (int i = tid; i < a.n_inst; i += kSsThreads) {
-        const int64_t c = a.cnt_all[i];
-        total += c;
-        before += i < inst ? c : 0;
-    }
-    for (int i = tid; i < a.G; i += kSsThreads) bins[i] = 0;
-    const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
-    const uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;
-    for (int i = tid; i < a.NF; i += kSsThreads) { st_fs[i] = fs[i]; st_cs[i] = cs[i]; }
-    if (tid == 0) { st_fs[a.NF] = 0xFFFFFFFFu; sh_runs = 0; }            // nothing starts behind the last flow
-    const uint32_t n_full = (uint32_t)a.cnt_full[inst];
-    const uint32_t n_all = (uint32_t)a.cnt_all[inst];
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) { before += __shfl_xor(before, d); total += __shfl_xor(total, d); }
-    if (lane == 0) { sh_red[0][wave] = before; sh_red[1][wave] = total; }
+    uint32_t n_full = 0, n_all = 0;
     int nt = 0;
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
-    const unsigned short *sorted = tail_sort_block<kSsThreads>(a, rows, k, rem, hist, idx_a, idx_b, sh_sort, nt);   // its barriers cover the above
+    const unsigned short *sorted = tail_sort_block<kSsThreads>(a, rows, k, rem, hist, idx_a, idx_b, sh_sort, nt, [&] {
+        for (int i = tid; i < a.n_inst; i += kSsThreads) {
+            const int64_t c = a.cnt_all[i];
+            total += c;
+            before += i < inst ? c : 0;
+        }
+        n_full = (uint32_t)a.cnt_full[inst];
+        n_all = (uint32_t)a.cnt_all[inst];
+        const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
+        const uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;
+        for (int i = tid; i < a.NF; i += kSsThreads) { st_fs[i] = fs[i]; st_cs[i] = cs[i]; }
+        for (int i = tid; i < a.G; i += kSsThreads) bins[i] = 0;
+        if (tid == 0) { st_fs[a.NF] = 0xFFFFFFFFu; sh_runs = 0; }        // nothing starts behind the last flow
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) { before += __shfl_xor(before, d); total += __shfl_xor(total, d); }
+        if (lane == 0) { sh_red[0][wave] = before; sh_red[1][wave] = total; }
+    });                                                                  // its barriers cover the above
     before = 0; total = 0;
 #pragma unroll
     for (int w = 0; w < kSsThreads / 64; ++w) { before += sh_red[0][w]; total += sh_red[1][w]; }

@@ -1,0 +1,70 @@
+"""Stages 3-5 at the edges of the per-instance kernels (threads per instance, tails counted or sorted, chains by runs, one workgroup per
+instance or separate kernels), against the CPU oracle: whole numbers, compared exactly."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_19262_amd as rs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _matrix(kind, B, G, C, rng):
+    if kind == "payload":                            # few tail values, long runs of them, ties a full weight apart
+        m = rng.poisson(3.0, size=(B, G, G)) * (C * 7 // 64)
+    elif kind == "tokens":                           # most flows shorter than a chunk, many of none
+        m = rng.poisson(0.7, size=(B, G, G)) * (C // 9 + 1)
+    elif kind == "any":                              # every tail different
+        m = rng.integers(0, 5 * C, size=(B, G, G))
+    elif kind == "sparse":                           # long stretches of flows without full chunks between long flows
+        m = np.where(rng.random((B, G, G)) < 0.01, rng.integers(20 * C, 90 * C, size=(B, G, G)), rng.integers(0, 3, size=(B, G, G)))
+    else:                                            # "two": runs of two weights, the lighter far below the spread the heavier leaves
+        m = np.where(rng.random((B, G, G)) < 0.5, C - 1, 3)
+    return m.astype(np.int64)
+
+
+@pytest.mark.parametrize("kind", ["payload", "tokens", "any", "sparse", "two"])
+@pytest.mark.parametrize("M,N,B,C", [(4, 4, 1, 65536),            # 64 flows
+                                     (3, 9, 2, 100_000),          # 243, nothing a power of two
+                                     (4, 8, 2, 65536),            # 256
+                                     (5, 8, 3, 4096),             # 320
+                                     (16, 8, 2, 131072),          # 1024
+                                     (17, 8, 1, 131072),          # 1088: 1024 threads
+                                     (8, 16, 2, 65536),           # 2048, 16 rails
+                                     (2, 32, 3, 65536),           # 2048, the list spans the wavefront
+                                     (64, 8, 1, 131072),          # 4096: the largest in one workgroup
+                                     (65, 8, 1, 131072),          # 4160: separate kernels
+                                     (28, 12, 1, 262144),         # 4032, 12 rails
+                                     (4, 2, 300, 4096),           # 1200 instances
+                                     (16, 8, 66, 65536)])         # 1056 instances of 1024 flows
+def test_instances(M, N, B, C, kind):
+    G = M * N
+    rng = np.random.default_rng(M * 1000 + N * 10 + B)
+    D1n = _matrix(kind, B, G, C, rng)
+    topo = rs.Topo(M, N, C)
+    off, w, flow, perm = oracle.chunk_sort_batch(D1n, M, N, C)
+    rail, S = oracle.lpt_batch(off, w, B, M, N)
+    _, R, stats = oracle.eval_batch(off, w, flow, rail, B, M, N)
+    n = int(off[-1])
+    want = dict(off=off, w=w, flow=flow, perm=perm, rail=rail, S=S, R=R, stats=stats)
+    D1 = torch.from_numpy(D1n).to(DEV)
+    u32 = lambda t: t.cpu().numpy().view(np.uint32)[:n]
+
+    def check(got, what):
+        o, gw, gf, gp, gr, gS, gR, gst = got
+        have = dict(off=o.cpu().numpy(), w=u32(gw), flow=u32(gf), perm=u32(gp), rail=gr.cpu().numpy()[:n], S=gS.cpu().numpy(),
+                    R=gR.cpu().numpy(), stats=gst.cpu().numpy())
+        for key, value in want.items():
+            assert np.array_equal(have[key], value), f"{what} {key}"
+
+    check(rs.schedule(D1, topo, n), "one call")
+    o, gw, gf, gp = rs.chunk_sort(D1, topo)
+    gr, gS = rs.lpt_spray(o, gw, B, topo)
+    check((o, gw, gf, gp, gr, gS, *rs.eval(o, gw, gf, gr, gS, B, topo)), "three calls")
+    # too little room by one record: the loads say so and no record is touched
+    if n:
+        out = rs.schedule(D1, topo, n - 1)
+        assert (out[5].cpu().numpy() == -1).all() and (out[6].cpu().numpy() == -1).all() and (out[7].cpu().numpy() == -1).all()
+        assert np.array_equal(out[0].cpu().numpy(), off)
