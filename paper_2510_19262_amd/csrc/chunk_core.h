@@ -69,16 +69,10 @@ __device__ __forceinline__ unsigned wave_exscan(unsigned v, unsigned &total)
     return inc - v;
 }
 
-// Ordering point between LDS accesses of the lanes of ONE wavefront.  When the wavefront is the whole
-// workgroup a workgroup barrier does; when other wavefronts of the workgroup are busy elsewhere, waiting
+// Ordering point between LDS accesses of the lanes of ONE wavefront, whatever the others of the workgroup are at: waiting
 // for the wavefront's own LDS operations is enough (LDS executes a wavefront's operations in order) and
 // the asm statement keeps the compiler from moving LDS accesses across it.
-template <bool ONE_WAVE_BLOCK>
-__device__ __forceinline__ void lds_sync()
-{
-    if constexpr (ONE_WAVE_BLOCK) __syncthreads();
-    else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-}
+__device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // Flows of the 256 positions first .. first + 255, four per lane, for a wavefront that knows the flow j_lo of position `first` or of one
 // before it (the same in all lanes): every flow that starts in the window, or between j_lo and it, leaves its number where it
@@ -89,14 +83,14 @@ __device__ __forceinline__ int window_flows(const uint32_t *fs, int nf, int j_lo
 {
     const int lane = threadIdx.x & 63;
     *reinterpret_cast<uint4 *>(mark + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    lds_sync();
     for (int f = j_lo + 1 + lane;; f += 64) {
         const uint32_t s = f < nf ? fs[f] : 0xFFFFFFFFu;
         const bool in = s <= last;
         if (in) atomicMax(&mark[s > first ? s - first : 0u], (unsigned)f);
         if (__ballot(!in) != 0ull) break;           // starts ascend: nothing further on starts at or before `last`
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    lds_sync();
     const uint4 m = *reinterpret_cast<const uint4 *>(mark + 4 * lane);
     const unsigned m1 = max(m.x, m.y), m2 = max(m1, m.z), m3 = max(m2, m.w);
     unsigned inc = max(m3, (unsigned)j_lo);         // inclusive maximum over the lanes
@@ -218,7 +212,7 @@ __device__ __forceinline__ unsigned short *tail_sort_block(const CsArgs &a, cons
     for (int pass = 0; pass < n_pass; ++pass) {
         const int shift = lo_bit + 8 * pass;
         for (int i = lane; i < 256; i += 64) mine[i] = 0;
-        lds_sync<false>();
+        lds_sync();
         for (int i = i_lo + lane; i < i_hi; i += 64) atomicAdd(&mine[255u - ((rem[idx_a[i]] >> shift) & 255u)], 1u);
         __syncthreads();
         {   // exclusive scan over (digit, wavefront): four consecutive entries per thread
@@ -248,9 +242,9 @@ __device__ __forceinline__ unsigned short *tail_sort_block(const CsArgs &a, cons
             }
             const unsigned base = act ? mine[d] : 0u;
             if (act) idx_b[base + __popcll(peers & lt)] = f;
-            lds_sync<false>();
+            lds_sync();
             if (act && (peers >> lane) == 1ull) mine[d] = base + __popcll(peers);   // highest lane of the peer set
-            lds_sync<false>();
+            lds_sync();
         }
         __syncthreads();
         unsigned short *t = idx_a; idx_a = idx_b; idx_b = t;
