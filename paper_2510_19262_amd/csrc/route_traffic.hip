@@ -517,6 +517,13 @@ static int64_t rt_splits(int64_t tokens_per_gpu, int64_t G, int64_t pairs, int E
     while (splits > 1 && pairs * splits > 0x7FFFFFFFll) splits = (splits + 1) / 2;
     return splits;
 }
+
+// the same for rows of 9..32 logits, where two slices are one workgroup's two rounds: no slice counts, no second kernel
+static int64_t rt_list_splits(int64_t tokens_per_gpu, int64_t G, int64_t pairs, int E)
+{
+    const int64_t splits = rt_splits(tokens_per_gpu, G, pairs, E);
+    return splits == 2 ? 1 : splits;
+}
 }  // namespace rs
 
 extern "C" size_t railsched_route_traffic_workspace_bytes(int32_t batch, int64_t tokens_per_gpu, int32_t E, int32_t k,
@@ -531,7 +538,7 @@ extern "C" size_t railsched_route_traffic_workspace_bytes(int32_t batch, int64_t
         size_t need = railsched_traffic_matrix_workspace_bytes(batch, tokens_per_gpu, k, h_topo);
         const int rpg = 4 * (64 / rw_lanes(E));
         if (E <= 32 && k <= 8 && pairs > 0) {
-            const int64_t splits = rt_splits(tokens_per_gpu, G, pairs, E);
+            const int64_t splits = rt_list_splits(tokens_per_gpu, G, pairs, E);
             const size_t one = splits > 1 ? align_up(sizeof(uint32_t) * (size_t)(pairs * splits * G), 256) : 256;
             need = one > need ? one : need;
         }
@@ -593,7 +600,7 @@ extern "C" int railsched_route_traffic(const float *logits, int32_t batch, int64
         if (splits > 1) return launch_count_reduce(a.partial, D1, pairs * G, (int)G, (int)splits, payload_bytes, st);
         return RAILSCHED_OK;
     }
-    const int64_t list_splits = E > 8 && E <= 32 ? rt_splits(tokens_per_gpu, G, pairs, E) : 1;
+    const int64_t list_splits = E > 8 && E <= 32 ? rt_list_splits(tokens_per_gpu, G, pairs, E) : 1;
     // rows of 9..32 logits: one pass when the indices are wanted, k fits the lists, whole float4s load, and the workspace (if any
     // is needed) holds the slice counts.  3.1 M rows, both stages back to back against this: 16 logits top-4 80 -> 50 us, top-2 62 -> 49;
     // 32 logits top-4 145 -> 84, top-8 232 -> 110; 20 logits top-1 85 -> 73.
@@ -621,7 +628,7 @@ extern "C" int railsched_route_traffic(const float *logits, int32_t batch, int64
     a.table_in_lds = ((int64_t)E * R <= kRtTableMax && 4 * (a.copies * (int64_t)a.bin_stride + (int64_t)E * R) <= 64 * 1024) ? 1 : 0;
 
     a.wide_idx = reinterpret_cast<uintptr_t>(topk_idx) % 16 == 0 ? 1 : 0;
-    const int64_t splits = rt_splits(tokens_per_gpu, G, pairs, E);
+    const int64_t splits = list ? list_splits : rt_splits(tokens_per_gpu, G, pairs, E);
     if (pairs * splits > 0x7FFFFFFFll) return RAILSCHED_ERR_UNSUPPORTED;
     a.splits = (int32_t)splits;
     a.partial = static_cast<uint32_t *>(ws);
