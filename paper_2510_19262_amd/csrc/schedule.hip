@@ -296,10 +296,21 @@ __global__ __launch_bounds__(kSlThreads) void sl_recv_kernel(CsArgs a, SsArgs x)
     const int64_t out0 = a.chunk_off[inst];
     const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
     add_leading_run(a, x, fs, n_full, lead, sl_bins, tid, kSlThreads);
-    for (uint32_t p = lead + tid; p < n_all; p += kSlThreads) {
-        const unsigned r = x.rail[out0 + p];
-        const int node = ss_dst_node(a, x, a.chunk_flow[out0 + p]);
-        if (node < a.M && r < (unsigned)N) atomicAdd(&sl_bins[node * N + r], (unsigned long long)a.chunk_w[out0 + p]);
+    constexpr int U = 4;                                                 // records per thread and round, their loads in flight together (3904 instances of 3500: 75 -> 59 us)
+    const int n_late = (int)(n_all - lead);                              // fewer than N full chunks and one tail per flow
+    const int64_t late0 = out0 + lead;
+    for (int i0 = tid; i0 < n_late; i0 += U * kSlThreads) {
+        uint32_t w[U], f[U], r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = late0 + (i0 + u * kSlThreads < n_late ? i0 + u * kSlThreads : i0);
+            w[u] = a.chunk_w[i]; f[u] = a.chunk_flow[i]; r[u] = x.rail[i];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int node = ss_dst_node(a, x, f[u]);
+            if (i0 + u * kSlThreads < n_late && node < a.M && r[u] < (uint32_t)N) atomicAdd(&sl_bins[node * N + r[u]], (unsigned long long)w[u]);
+        }
     }
     __syncthreads();
     int64_t *slot = x.partial + (int64_t)inst * (a.G + 1);
