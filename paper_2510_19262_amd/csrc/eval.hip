@@ -211,10 +211,11 @@ __global__ __launch_bounds__(THREADS) void eval_reduce_kernel(EvArgs a)
 
 int launch_eval_reduce(const EvArgs &a, int batch, hipStream_t st)
 {
-    // a workgroup reads its matrix's slots alone: 256 threads while they are few (cheaper barriers), 1024 up to 64 Ki sums, and
+    // a workgroup reads its matrix's slots alone: 256 threads while they are few (cheaper barriers) or there are more matrices than the
+    // chip takes workgroups of 1024 (1024 matrices of 32 slots of 256 bins: 25 us by 256 threads, 37 by 1024), 1024 up to 64 Ki sums, and
     // beyond that the slots are summed by G / 64 workgroups per matrix first (128 slots of 1024
     // bins: 58 us by one workgroup as it was, 5 + 8 in two kernels)
-    if ((int64_t)a.slices * a.G <= 2048) {
+    if ((int64_t)a.slices * a.G <= 2048 || (batch > 512 && (int64_t)a.slices * a.G <= 16384 && a.M <= 256)) {
         hipLaunchKernelGGL((eval_reduce_kernel<256, true>), dim3((unsigned)batch), dim3(256), 0, st, a);
     } else if ((int64_t)a.slices * a.G <= 65536) {
         hipLaunchKernelGGL((eval_reduce_kernel<1024, true>), dim3((unsigned)batch), dim3(1024), 0, st, a);
