@@ -110,9 +110,10 @@ int railsched_traffic_matrix(const int32_t *topk_idx, int32_t batch, int64_t tok
  * Stages 1 and 2 in one call (Algorithm 1 steps 1-2: gate, then selection of input slices by gate
  * and expert assignment).  Same inputs, same rules and bit-identical outputs as
  * railsched_route_topk over all batch*G*tokens_per_gpu rows followed by railsched_traffic_matrix;
- * for E <= 8 both are produced in a single pass over the logits and the indices are never read back; so is D1 for
- * 32 < E <= 256 with k <= 8 when the indices are not wanted (topk_idx == NULL; 16-byte aligned logits, E a multiple
- * of 4, G <= 4096); everything else runs the two stages.
+ * for E <= 8 both are produced in a single pass over the logits and the indices are never read back; so they are for
+ * 8 < E <= 32 with k <= 8 when the indices are wanted, and so is D1 for 32 < E <= 256 with k <= 8 when they are not
+ * (topk_idx == NULL); both need 16-byte aligned logits, E a multiple of 4 and G <= 8192 and 4096.  Everything else runs the
+ * two stages.
  *   logits     [batch*G*tokens_per_gpu][E] fp32                     (in)
  *   expert_gpu [E][R] int32, values in [0,G)                        (in; out-of-range values are ignored)
  *   topk_idx   [batch*G*tokens_per_gpu][k] int32                    (out; may be NULL for the single-pass shapes:
@@ -218,8 +219,8 @@ int railsched_eval(const int64_t *chunk_off, const uint32_t *chunk_w, const uint
  * arguments, bit for bit, with less work: stage 3 knows that every instance starts with a run of full chunks,
  * whose allocation from empty rails is round robin, so their rails are written with the records, stage 4 only
  * runs behind them and stage 5 takes their receive loads in closed form.  Batches of at most 1024 instances
- * with N*G <= 2048 flows and capacity <= 32768 chunks per instance are served by one workgroup per instance
- * (two launches after the counts instead of eight).
+ * with N*G <= 2048 flows (256 with N*G <= 4096) and capacity <= 65536 chunks per instance are served by one workgroup per
+ * instance (two launches after the counts instead of six).
  *   D1 [batch][G][G] int64 (in);  chunk_off [batch*M+1];  chunk_w, chunk_flow, perm (perm may be NULL),
  *   rail: `capacity` records each;  S, R [batch][M][N] int64;  stats [batch][8] int64   (out)
  *   ws: railsched_schedule_workspace_bytes(batch, topo) bytes, 256-byte aligned.
