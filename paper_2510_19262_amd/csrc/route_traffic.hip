@@ -514,6 +514,9 @@ static int64_t rt_splits(int64_t tokens_per_gpu, int64_t G, int64_t pairs, int E
     const int64_t slice = kRtRound * (rounds < 1 ? 1 : rounds);
     int64_t splits = (tokens_per_gpu + slice - 1) / slice;
     if (splits < 1) splits = 1;
+    // few pairs of few tokens leave the chip idle either way: a workgroup takes a pair's rounds one after the other and the launch
+    // that sums slice counts is saved (a layer of 16 GPUs x 2048 tokens: 27.8 -> 24.7 us for the whole pass)
+    if (splits <= 4 && pairs <= 64) return 1;
     while (splits > 1 && pairs * splits > 0x7FFFFFFFll) splits = (splits + 1) / 2;
     return splits;
 }

@@ -149,6 +149,9 @@ static int64_t tm_splits(int64_t slots_per_gpu, int64_t G, int64_t pairs)
     // and writes its D1 row itself - no slice counts, no second kernel (a DeepSeek-V3-shaped layer: 512 pairs of 65 536 slots,
     // 0.038 -> 0.03 ms).
     if (pairs >= 512 && slots_per_gpu <= (int64_t)kTmThreadsWhole * 4 * 32) return 1;
+    // However few the pairs, what such a workgroup covers in one step is not cut: the sum over slices would be a launch more for
+    // nothing (seven layers of 30 GPUs, 6126 slots a pair: 9.1 us in two kernels, 5.2 in one).
+    if (slots_per_gpu <= (int64_t)kTmThreadsWhole * 4 * kTmUnroll) return 1;
     const int64_t unit = (int64_t)kTmThreads * kTmUnroll * 4;            // slots one workgroup covers per step
     int64_t slice = unit;
     while (slice < 32 * G) slice += unit;
@@ -194,7 +197,7 @@ extern "C" int railsched_traffic_matrix(const int32_t *topk_idx, int32_t batch, 
     const int64_t pairs = (int64_t)batch * G;
     const int64_t splits = tm_splits(a.slots_per_gpu, G, pairs);
     if (pairs * splits > 0x7FFFFFFFll) return RAILSCHED_ERR_UNSUPPORTED;
-    const bool whole = splits == 1 && pairs >= 512 && a.slots_per_gpu > (int64_t)kTmThreads * 4;   // see tm_splits
+    const bool whole = splits == 1 && a.slots_per_gpu > (int64_t)kTmThreads * 4;   // see tm_splits
     a.copies = 1;
     // as many copies as keep a workgroup's LDS (bins + table) within 20 KiB: eight workgroups of 256, all the wavefronts a CU
     // takes (two workgroups of 1024 have 80 KiB each, which the 8192-word bound keeps them far from)

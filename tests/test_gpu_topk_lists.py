@@ -85,3 +85,16 @@ def test_one_pass_routing_without_room_for_slice_counts():
     want = oracle.route_topk(x, k)
     assert np.array_equal(idx.cpu().numpy(), want)
     assert np.array_equal(D1.cpu().numpy(), oracle.traffic_matrix(want, B, tok, eg, 512, M, N))
+
+
+@pytest.mark.parametrize("E,tok", [(8, 512), (8, 513), (8, 2048), (8, 2049), (4, 1537), (60, 682), (60, 683), (60, 2730), (60, 2731)])
+def test_slices_of_few_pairs(E, tok):
+    # around the token counts where a pair's tokens become slices: one workgroup's rounds, or counts summed by a second kernel
+    rng = np.random.default_rng(E * 10_000 + tok)
+    M, N, k = 2, 3, 2 if E <= 8 else 6
+    x = rng.standard_normal((M * N * tok, E)).astype(np.float32)
+    eg = rng.integers(0, M * N, size=(E, 2)).astype(np.int32)
+    idx, D1 = rs.route_traffic(torch.from_numpy(x).to(DEV), k, 1, tok, torch.from_numpy(eg).to(DEV), 512, rs.Topo(M, N, 65536))
+    want = oracle.route_topk(x, k)
+    assert np.array_equal(idx.cpu().numpy(), want)
+    assert np.array_equal(D1.cpu().numpy(), oracle.traffic_matrix(want, 1, tok, eg, 512, M, N))
