@@ -30,6 +30,7 @@ typedef float rt_f32x4 __attribute__((ext_vector_type(4)));
 typedef int rt_i32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kRtThreads = 256;
+constexpr int kRtThreadsWhole = 1024;
 // rows per thread with their loads in flight together: 64 bytes of logits and more
 constexpr int rt_unroll(int vpl) { return vpl <= 16 ? 2 : 1; }
 constexpr int rt_round(int vpl) { return kRtThreads * rt_unroll(vpl); }   // tokens per workgroup and round
@@ -263,10 +264,11 @@ __device__ __forceinline__ void rt_store_row(const RtArgs &a, int64_t row, const
 }
 
 // L = 0: rows of at most 8 logits, picked in rounds.  L > 0: rows of 9..32 logits and k < L, picked from a list.
-template <int VPL, int L, bool VEC4, bool TABLE_LDS>
-__global__ __launch_bounds__(kRtThreads) void route_traffic_kernel(RtArgs a)
+// THREADS: kRtThreads, or kRtThreadsWhole where one workgroup takes a pair of a few rounds.
+template <int VPL, int L, bool VEC4, bool TABLE_LDS, int THREADS>
+__global__ __launch_bounds__(THREADS) void route_traffic_kernel(RtArgs a)
 {
-    constexpr int kRtUnroll = rt_unroll(VPL), kRtRound = rt_round(VPL);
+    constexpr int kRtUnroll = rt_unroll(VPL), kRtRound = THREADS * kRtUnroll;
     extern __shared__ unsigned rt_lds[];
     // [copies][G] counters; lanes that share a replica index - every lanes_per_period-th lane - would pile
     // onto the bins of the popular experts, so neighbouring periods count in different copies
@@ -290,14 +292,14 @@ __global__ __launch_bounds__(kRtThreads) void route_traffic_kernel(RtArgs a)
     // fetching the placement table do not delay them
 #pragma unroll
     for (int u = 0; u < kRtUnroll; ++u) {
-        const int64_t tu = t + (int64_t)u * kRtThreads;
-        if constexpr (L > 0) rt_load_rows<VPL>(a, row0, t_wave + (int64_t)u * kRtThreads, hi, lane, v[u]);
+        const int64_t tu = t + (int64_t)u * THREADS;
+        if constexpr (L > 0) rt_load_rows<VPL>(a, row0, t_wave + (int64_t)u * THREADS, hi, lane, v[u]);
         else rt_load_row<VPL, VEC4>(a, row0 + tu, tu < hi, v[u]);
     }
 
-    for (int i = threadIdx.x; i < a.bin_stride * a.copies; i += kRtThreads) all_bins[i] = 0;
+    for (int i = threadIdx.x; i < a.bin_stride * a.copies; i += THREADS) all_bins[i] = 0;
     if (TABLE_LDS)
-        for (int i = threadIdx.x; i < a.E * a.R; i += kRtThreads) lds_table[i] = a.expert_gpu[i];
+        for (int i = threadIdx.x; i < a.E * a.R; i += THREADS) lds_table[i] = a.expert_gpu[i];
     __syncthreads();
 
     if constexpr (L > 0) {
@@ -307,7 +309,7 @@ __global__ __launch_bounds__(kRtThreads) void route_traffic_kernel(RtArgs a)
             int win[kRtUnroll][L - 1];
 #pragma unroll
             for (int u = 0; u < kRtUnroll; ++u) {
-                const int64_t tu = t + (int64_t)u * kRtThreads;
+                const int64_t tu = t + (int64_t)u * THREADS;
                 rt_rows_to_lanes<VPL>(v[u], lane);
                 if (tu < hi) {
                     rt_pick_list<VPL, L>(a, v[u], win[u]);
@@ -322,20 +324,20 @@ __global__ __launch_bounds__(kRtThreads) void route_traffic_kernel(RtArgs a)
             }
 #pragma unroll
             for (int u = 0; u < kRtUnroll; ++u) {
-                const int64_t tu = t + (int64_t)u * kRtThreads;
+                const int64_t tu = t + (int64_t)u * THREADS;
                 if (tu < hi) rt_store_row<L - 1>(a, row0 + tu, win[u]);
             }
             t += round;
             if (tw + round >= hi) break;
 #pragma unroll
-            for (int u = 0; u < kRtUnroll; ++u) rt_load_rows<VPL>(a, row0, tw + round + (int64_t)u * kRtThreads, hi, lane, v[u]);
+            for (int u = 0; u < kRtUnroll; ++u) rt_load_rows<VPL>(a, row0, tw + round + (int64_t)u * THREADS, hi, lane, v[u]);
         }
     }
     while (L == 0 && t < hi) {
         rt_i32x2 pairs[kRtUnroll];
 #pragma unroll
         for (int u = 0; u < kRtUnroll; ++u) {
-            const int64_t tu = t + (int64_t)u * kRtThreads;
+            const int64_t tu = t + (int64_t)u * THREADS;
             pairs[u].x = 0; pairs[u].y = 0;
             // two calls, so that the table is read with LDS instructions where it is in LDS: through one pointer
             // that may be either, every lookup waited for all of the wavefront's memory traffic
@@ -347,7 +349,7 @@ __global__ __launch_bounds__(kRtThreads) void route_traffic_kernel(RtArgs a)
         if (a.topk_idx && a.k == 2) {
 #pragma unroll
             for (int u = 0; u < kRtUnroll; ++u) {
-                const int64_t tu = t + (int64_t)u * kRtThreads;
+                const int64_t tu = t + (int64_t)u * THREADS;
                 if (tu < hi) __builtin_nontemporal_store(pairs[u], reinterpret_cast<rt_i32x2 *>(a.topk_idx + (row0 + tu) * 2));
             }
         }
@@ -355,14 +357,14 @@ __global__ __launch_bounds__(kRtThreads) void route_traffic_kernel(RtArgs a)
         if (t >= hi) break;
 #pragma unroll
         for (int u = 0; u < kRtUnroll; ++u) {
-            const int64_t tu = t + (int64_t)u * kRtThreads;
+            const int64_t tu = t + (int64_t)u * THREADS;
             rt_load_row<VPL, VEC4>(a, row0 + tu, tu < hi, v[u]);
         }
     }
     __syncthreads();
 
     int64_t *dst = a.D1 + pair * a.G;
-    for (int i = threadIdx.x; i < a.G; i += kRtThreads) {
+    for (int i = threadIdx.x; i < a.G; i += THREADS) {
         unsigned cnt = 0;
         for (int c = 0; c < a.copies; ++c) cnt += all_bins[(size_t)c * a.bin_stride + i];
         if (a.splits == 1) dst[i] = (int64_t)cnt * a.payload;    // sole owner of the pair
@@ -370,18 +372,28 @@ __global__ __launch_bounds__(kRtThreads) void route_traffic_kernel(RtArgs a)
     }
 }
 
-template <int VPL, int L>
-static int launch_route_traffic(const RtArgs &a, int64_t pairs, size_t lds, hipStream_t st)
+template <int VPL, int L, int THREADS>
+static int launch_route_traffic_t(const RtArgs &a, int64_t pairs, size_t lds, hipStream_t st)
 {
     const bool vec4 = (a.E % 4 == 0) && (reinterpret_cast<uintptr_t>(a.logits) % 16 == 0);
     const dim3 grid((unsigned)(pairs * a.splits));
-    if (vec4 && a.table_in_lds) hipLaunchKernelGGL((route_traffic_kernel<VPL, L, true, true>), grid, dim3(kRtThreads), lds, st, a);
-    else if (vec4) hipLaunchKernelGGL((route_traffic_kernel<VPL, L, true, false>), grid, dim3(kRtThreads), lds, st, a);
+    if (vec4 && a.table_in_lds) hipLaunchKernelGGL((route_traffic_kernel<VPL, L, true, true, THREADS>), grid, dim3(THREADS), lds, st, a);
+    else if (vec4) hipLaunchKernelGGL((route_traffic_kernel<VPL, L, true, false, THREADS>), grid, dim3(THREADS), lds, st, a);
     else if constexpr (L == 0) {
-        if (a.table_in_lds) hipLaunchKernelGGL((route_traffic_kernel<VPL, L, false, true>), grid, dim3(kRtThreads), lds, st, a);
-        else hipLaunchKernelGGL((route_traffic_kernel<VPL, L, false, false>), grid, dim3(kRtThreads), lds, st, a);
+        if (a.table_in_lds) hipLaunchKernelGGL((route_traffic_kernel<VPL, L, false, true, THREADS>), grid, dim3(THREADS), lds, st, a);
+        else hipLaunchKernelGGL((route_traffic_kernel<VPL, L, false, false, THREADS>), grid, dim3(THREADS), lds, st, a);
     }
     return launch_status();
+}
+
+template <int VPL, int L>
+static int launch_route_traffic(const RtArgs &a, int64_t pairs, size_t lds, hipStream_t st)
+{
+    if constexpr (L == 0) {
+        // a pair that was not cut although it is more than one round: the round of a workgroup of 1024 covers it
+        if (a.splits == 1 && a.tokens_per_gpu > rt_round(VPL)) return launch_route_traffic_t<VPL, L, kRtThreadsWhole>(a, pairs, lds, st);
+    }
+    return launch_route_traffic_t<VPL, L, kRtThreads>(a, pairs, lds, st);
 }
 
 // ---------------------------------------------------------------------------------------------- rows of 33..256 logits
