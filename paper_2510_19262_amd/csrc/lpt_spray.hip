@@ -502,7 +502,7 @@ __device__ __forceinline__ void rows_steps(unsigned &t, unsigned &won, unsigned 
         RS_ROW_STEP("%2", "%1", "5") RS_ROW_STEP("%1", "%2", "6") RS_ROW_STEP("%2", "%1", "7") RS_ROW_STEP("%1", "%2", "8")
         RS_ROW_STEP("%2", "%1", "9") RS_ROW_STEP("%1", "%2", "10") RS_ROW_STEP("%2", "%1", "11") RS_ROW_STEP("%1", "%2", "12")
         RS_ROW_STEP("%2", "%1", "13") RS_ROW_STEP("%1", "%2", "14") RS_ROW_STEP("%2", "%1", "15") RS_ROW_STEP("%1", "%2", "15")
-        : "+v"(t), "+v"(won), "=&v"(y), "=&v"(w), "=&v"(nb)
+        : "+&v"(t), "+&v"(won), "=&v"(y), "=&v"(w), "=&v"(nb)   // wS is read to the end: no other operand may share its register
         : "v"(wS));
 }
 #undef RS_ROW_STEP
