@@ -102,11 +102,12 @@ template <int VPL, int L, int J>
 __device__ __forceinline__ void rt_insert(const float (&v)[VPL], int E, int (&lst)[L], unsigned &bits)
 {
     if constexpr (J < VPL) {
+        if constexpr (J % 4 == 0 && J > VPL / 2 && J >= L) {             // E > VPL / 2
+            if (J >= E) return;                     // uniform
+        }
         const unsigned c = __float_as_uint(v[J] + 0.0f);
-        int key = make_ikey<~((unsigned)VPL - 1u) | (unsigned)J>(c, ~((unsigned)VPL - 1u));
-        if (J >= VPL / 2) key = J < E ? key : kNoKey;             // E > VPL / 2; uniform
-        bits |= (J < VPL / 2 || J < E) ? c : 0u;
-        list_insert<L, (J < L ? J : L)>(lst, key);
+        bits |= c;
+        list_insert<L, (J < L ? J : L)>(lst, make_ikey<~((unsigned)VPL - 1u) | (unsigned)J>(c, ~((unsigned)VPL - 1u)));
         rt_insert<VPL, L, J + 1>(v, E, lst, bits);
     }
 }
@@ -190,7 +191,7 @@ __device__ __forceinline__ void rt_load_rows(const RtArgs &a, int64_t row0, int6
 #pragma unroll
     for (int i = 0; i < LPR; ++i) {
         const int64_t t = first + i * (64 / LPR) + p;
-        rt_f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+        rt_f32x4 x = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};   // logits that do not exist, as in row_load
         if (t < hi && 4 * q < a.E) x = __builtin_nontemporal_load(reinterpret_cast<const rt_f32x4 *>(a.logits + (row0 + t) * a.E + 4 * q));
         v[4 * i + 0] = x.x; v[4 * i + 1] = x.y; v[4 * i + 2] = x.z; v[4 * i + 3] = x.w;
     }
@@ -224,7 +225,7 @@ __device__ __forceinline__ void rt_pick_list(const RtArgs &a, const float (&v)[V
     if (close < MASK && (bits & MASK) != 0u) {
         float x[VPL];
 #pragma unroll
-        for (int j = 0; j < VPL; ++j) x[j] = j < a.E ? v[j] : -INFINITY;
+        for (int j = 0; j < VPL; ++j) x[j] = v[j];
 #pragma unroll
         for (int sel = 0; sel < L - 1; ++sel) {
             if (sel >= a.k) break;
@@ -243,7 +244,7 @@ __device__ __forceinline__ void rt_pick_list(const RtArgs &a, const float (&v)[V
     }
 }
 
-// the row's indices: whole 16-byte groups where k and the array's alignment allow
+// the row's indices, in the widest pieces that k and the array's alignment allow
 template <int KM>
 __device__ __forceinline__ void rt_store_row(const RtArgs &a, int64_t row, const int (&win)[KM])
 {
@@ -448,11 +449,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
                 if ((unsigned)d < (unsigned)a.G) atomicAdd(&bins[d], 1u);
             }
         };
-        int own[L];
+        int keys[VPL], own[L];
         unsigned bits;
-        lane_best<LANES, VPL, L, FULL>(x, a.E, q, own, bits);
-        // the next row group's logits are requested as soon as this one's are consumed
+        lane_keys<LANES, VPL>(x, q, keys, bits);
+        // the next row group's logits are on the way while this one's keys are worked on
         if (it + 1 < a.iters) row_load<LANES, VPL, FULL>(pair_logits + clamp_token(t + RPB) * a.E, a.E, q, x);
+        list_of_keys<LANES, VPL, L, FULL>(keys, a.E, own);
         unsigned u[8];
         const bool bad = row_best<LANES, VPL, L, 8>(own, bits, a.k, u);
         if (__ballot(live && bad) == 0ull) {

@@ -54,6 +54,26 @@ __device__ __forceinline__ void group_argmax(float &bv, int &bi)
     if constexpr (LANES >= 64) argmax_step<32>(bv, bi);
 }
 
+// largest value / smallest index of a group of LANES lanes, in all of them
+template <int LANES>
+__device__ __forceinline__ float group_max(float v)
+{
+    if constexpr (LANES >= 2) v = fmaxf(v, xlane<1>(v));
+    if constexpr (LANES >= 4) v = fmaxf(v, xlane<2>(v));
+    if constexpr (LANES >= 8) v = fmaxf(v, xlane<4>(v));
+    if constexpr (LANES >= 16) v = fmaxf(v, xlane<8>(v));
+    return v;
+}
+template <int LANES>
+__device__ __forceinline__ int group_min(int v)
+{
+    if constexpr (LANES >= 2) v = min(v, xlane<1>(v));
+    if constexpr (LANES >= 4) v = min(v, xlane<2>(v));
+    if constexpr (LANES >= 8) v = min(v, xlane<4>(v));
+    if constexpr (LANES >= 16) v = min(v, xlane<8>(v));
+    return v;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Insertion kernels for rows of 33..1024 logits and k <= KM (8 or 16): no rounds and no sorting networks.
 //
@@ -150,20 +170,21 @@ __device__ __forceinline__ int make_ikey(unsigned c, unsigned lane_field)
 template <unsigned MASK>
 __device__ __forceinline__ unsigned key_index(unsigned u) { return ~u & MASK; }
 
-// has(C): the row has logits at float4 C of this lane (false only where E < LANES * VPL)
+// float4s that no lane of the row has (E < LANES * VPL; E > LANES * VPL / 2) are left out: 132 logits in 8 lanes are 20 places a lane, not 32
 template <int LANES, int VPL, int L, unsigned MASK, bool FULL, int C, int J>
-__device__ __forceinline__ void insert_loaded(const float4 (&x)[VPL / 4], unsigned lane_field, int E, int q, int (&lst)[L], unsigned &bits)
+__device__ __forceinline__ void insert_loaded(const float4 (&x)[VPL / 4], unsigned lane_field, int E, int (&lst)[L], unsigned &bits)
 {
     if constexpr (C < VPL / 4) {
+        if constexpr (!FULL && J == 0 && C >= VPL / 8) {
+            if (4 * LANES * C >= E) return;         // uniform
+        }
         constexpr unsigned SLOT = ~MASK | (unsigned)(4 * LANES * C + J);
         const float v = J == 0 ? x[C].x : J == 1 ? x[C].y : J == 2 ? x[C].z : x[C].w;
         const unsigned c = __float_as_uint(v + 0.0f);
         bits |= c;
-        int key = make_ikey<SLOT>(c, lane_field);
-        if constexpr (!FULL) key = 4 * (q + LANES * C) < E ? key : kNoKey;
-        list_insert<L, (4 * C + J < L ? 4 * C + J : L)>(lst, key);
+        list_insert<L, (4 * C + J < L ? 4 * C + J : L)>(lst, make_ikey<SLOT>(c, lane_field));
         if constexpr (J == 3 && VPL >= 32) __builtin_amdgcn_sched_barrier(0);   // keys of later logits made early would only take registers
-        insert_loaded<LANES, VPL, L, MASK, FULL, (J == 3 ? C + 1 : C), (J == 3 ? 0 : J + 1)>(x, lane_field, E, q, lst, bits);
+        insert_loaded<LANES, VPL, L, MASK, FULL, (J == 3 ? C + 1 : C), (J == 3 ? 0 : J + 1)>(x, lane_field, E, lst, bits);
     }
 }
 
@@ -175,6 +196,8 @@ __device__ __forceinline__ unsigned min_xor_dist(unsigned m, unsigned a, unsigne
 
 // This lane's VPL logits of the row at `row_logits` (LANES lanes per row, float4s interleaved over the lanes).
 // FULL: E == LANES * VPL, every load is in range.
+// Logits that do not exist (E < LANES * VPL) read as -infinity: a cut value of its own below every finite one, with zeros in the bits that
+// the cut drops, so neither the order of the keys nor the union of the bits needs to know of them.
 template <int LANES, int VPL, bool FULL>
 __device__ __forceinline__ void row_load(const float *__restrict__ row_logits, int E, int q, float4 (&x)[VPL / 4])
 {
@@ -182,7 +205,7 @@ __device__ __forceinline__ void row_load(const float *__restrict__ row_logits, i
     for (int c = 0; c < VPL / 4; ++c) {
         const int e0 = 4 * (q + LANES * c);
         if constexpr (FULL) x[c] = load_stream4(row_logits + e0);
-        else x[c] = e0 < E ? load_stream4(row_logits + e0) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // their keys become kNoKey
+        else x[c] = e0 < E ? load_stream4(row_logits + e0) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
     }
 }
 
@@ -191,9 +214,42 @@ template <int LANES, int VPL, int L, bool FULL>
 __device__ __forceinline__ void lane_best(const float4 (&x)[VPL / 4], int E, int q, int (&own)[L], unsigned &bits)
 {
     constexpr unsigned MASK = (unsigned)(LANES * VPL) - 1u;   // expert index bits of a key
-    static_assert(VPL % 4 == 0 && VPL >= 8 && LANES >= 2 && LANES <= 16 && L >= 4 && L <= VPL, "shape");
+    static_assert(VPL % 4 == 0 && VPL >= 8 && LANES >= 2 && LANES <= 16 && L >= 4 && L <= VPL / 2, "shape");
     bits = 0;
-    insert_loaded<LANES, VPL, L, MASK, FULL, 0, 0>(x, ~MASK | (unsigned)(4 * q), E, q, own, bits);
+    insert_loaded<LANES, VPL, L, MASK, FULL, 0, 0>(x, ~MASK | (unsigned)(4 * q), E, own, bits);
+}
+
+// The same in two halves, so that a kernel that walks over rows can ask for its next logits between them: the keys take the logits' registers,
+// and the list is made while the loads are on the way.
+template <int LANES, int VPL, unsigned MASK, int C, int J>
+__device__ __forceinline__ void make_keys(const float4 (&x)[VPL / 4], unsigned lane_field, int (&keys)[VPL], unsigned &bits)
+{
+    if constexpr (C < VPL / 4) {
+        constexpr unsigned SLOT = ~MASK | (unsigned)(4 * LANES * C + J);
+        const float v = J == 0 ? x[C].x : J == 1 ? x[C].y : J == 2 ? x[C].z : x[C].w;
+        const unsigned c = __float_as_uint(v + 0.0f);
+        bits |= c;
+        keys[4 * C + J] = make_ikey<SLOT>(c, lane_field);
+        make_keys<LANES, VPL, MASK, (J == 3 ? C + 1 : C), (J == 3 ? 0 : J + 1)>(x, lane_field, keys, bits);
+    }
+}
+template <int LANES, int VPL>
+__device__ __forceinline__ void lane_keys(const float4 (&x)[VPL / 4], int q, int (&keys)[VPL], unsigned &bits)
+{
+    constexpr unsigned MASK = (unsigned)(LANES * VPL) - 1u;
+    bits = 0;
+    make_keys<LANES, VPL, MASK, 0, 0>(x, ~MASK | (unsigned)(4 * q), keys, bits);
+}
+template <int LANES, int VPL, int L, bool FULL, int I = 0>
+__device__ __forceinline__ void list_of_keys(const int (&keys)[VPL], int E, int (&own)[L])
+{
+    if constexpr (I < VPL) {
+        if constexpr (!FULL && I % 4 == 0 && I >= VPL / 2) {
+            if (LANES * I >= E) return;             // uniform; as in insert_loaded
+        }
+        list_insert<L, (I < L ? I : L)>(own, keys[I]);
+        list_of_keys<LANES, VPL, L, FULL, I + 1>(keys, E, own);
+    }
 }
 
 // The KM largest keys of the row from the lists of its LANES lanes, as bit patterns in u[0..KM), the same in all lanes of the
@@ -239,7 +295,8 @@ __device__ __forceinline__ bool row_best(const int (&own)[L], unsigned bits, int
     return bad || own[L - 1] >= kth;                // ... or every key this lane kept is a winner
 }
 
-// expert indices of the row's k winners to topk_idx[row][0..k); streaming stores (4 194 304 rows of 64 logits, top-6: 0.209 ms, plain 0.227)
+// expert indices of the row's k winners to topk_idx[row][0..k); streaming stores (4 194 304 rows of 64 logits, top-6: 0.209 ms, plain 0.227),
+// but not of single indices, a sixteenth of a line per row and more (262 144 x 256 top-1: 46 us streaming, 43 plain)
 template <int LANES, unsigned MASK, int KM>
 __device__ __forceinline__ void store_best(int32_t *__restrict__ topk_idx, int64_t row, int k, int q, bool live, int wide_store,
                                            const unsigned (&u)[KM])
@@ -259,7 +316,11 @@ __device__ __forceinline__ void store_best(int32_t *__restrict__ topk_idx, int64
             unsigned sel = 0;
 #pragma unroll
             for (int j = r * LANES; j < KM && j < (r + 1) * LANES; ++j) sel = (j == q + r * LANES) ? u[j] : sel;
-            if (live && q + r * LANES < k) __builtin_nontemporal_store((int)key_index<MASK>(sel), topk_idx + row * k + q + r * LANES);
+            if (live && q + r * LANES < k) {
+                int32_t *dst = topk_idx + row * k + q + r * LANES;
+                if (k == 1) *dst = (int)key_index<MASK>(sel);
+                else __builtin_nontemporal_store((int)key_index<MASK>(sel), dst);
+            }
         }
     }
 }
@@ -277,19 +338,19 @@ __device__ __forceinline__ void row_exact(const float *__restrict__ row_logits, 
         v[4 * c + 0] = cur.x; v[4 * c + 1] = cur.y; v[4 * c + 2] = cur.z; v[4 * c + 3] = cur.w;
     }
     for (int sel = 0; sel < k; ++sel) {
-        // places inside the lane (constants) while scanning and removing: expert indices of all VPL places would be kept in registers
-        float bv = -INFINITY;
-        int bj = -1;
+        // the row's largest value first, then the lowest index that holds it: no branches (one such wavefront is what a small launch waits
+        // for: 2048 x 512 top-8 10.0 -> 6.9 us, 8192 x 64 top-8 6.0 -> 5.0), and places inside the lane (constants)
+        // while scanning and removing - expert indices of all VPL places would be kept in registers
+        float bv = v[0];
 #pragma unroll
-        for (int j = 0; j < VPL; ++j) {
-            const bool better = v[j] > bv;
-            bv = better ? v[j] : bv;
-            bj = better ? j : bj;
-        }
-        int bi = bj < 0 ? INT_MAX : 4 * (q + LANES * (bj >> 2)) + (bj & 3);
-        const int mine = bi;
-        group_argmax<LANES>(bv, bi);
-        const int gone = bi == mine ? bj : -1;      // only the winner's lane loses an entry
+        for (int j = 1; j < VPL; ++j) bv = fmaxf(bv, v[j]);
+        bv = group_max<LANES>(bv);
+        int bj = VPL;
+#pragma unroll
+        for (int j = VPL - 1; j >= 0; --j) bj = v[j] == bv ? j : bj;
+        const int mine = bj < VPL && bv > -INFINITY ? 4 * (q + LANES * (bj >> 2)) + (bj & 3) : INT_MAX;
+        const int bi = group_min<LANES>(mine);
+        const int gone = bi == mine ? bj : VPL;     // only the winner's lane loses an entry
 #pragma unroll
         for (int j = 0; j < VPL; ++j) v[j] = (j == gone) ? -INFINITY : v[j];
         emit(sel, bi);
