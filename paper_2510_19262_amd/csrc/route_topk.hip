@@ -311,6 +311,17 @@ static int launch_topk(const float *logits, int64_t rows, int E, int k, int32_t 
     return launch_status();
 }
 
+// Rows of more than 256 logits that the rounds pick faster than the lists.  A round is a pass over the row by all 64 lanes, a list sees 32 or 64
+// logits per lane first: with few rows that latency is the time, and one or two rounds cost no more than the reads of the row.  us by
+// rounds / lists: 2048 x 512 top-1 2.5 / 2.8, top-8 6.5 / 6.8, 8192 x 512 top-1 3.7 / 4.3, top-4 7.0 / 5.7; 2048 x 1024 top-8 7.6 / 12.3,
+// 8192 x 1024 top-4 9.2 / 10.2, top-16 28.6 / 26.6, 16384 x 1024 top-2 11.1 / 13.2, top-4 16.0 / 15.6; 384 000 x 1024 top-1 225 / 236, top-2
+// 224 / 239, top-4 329 / 246; 762 046 x 516 top-1 255 / 282, top-2 358 / 296.
+static bool few_rows(int64_t rows, int E, int k)
+{
+    if (E <= 512) return rows <= (k == 1 ? 8192 : 4096);
+    return k == 1 || (k == 2 && E > 896) || rows <= (k <= 3 ? 16384 : k <= 10 ? 8192 : 4096);
+}
+
 }  // namespace rs
 
 extern "C" int railsched_route_topk(const float *logits, int64_t rows, int32_t E, int32_t k, int32_t *topk_idx,
@@ -328,16 +339,21 @@ extern "C" int railsched_route_topk(const float *logits, int64_t rows, int32_t E
     // is all winners rare (under one row in a thousand on shuffled logits).  us for 8 388 608 x 128 top-8: 843 with 32 logits per lane, 716
     // with 16, 1000 with 8; 4 194 304 x 256 top-8: 745 / 704; 524 288 x 512 top-10: 640 by rounds, 210 with 64 per lane, 198 with 32;
     // top-8 540 / 190 / 179; top-16 990 / 263 / 247; 262 144 x 1024 top-10: 457 by rounds, 207.  Larger k stays with the rounds.
+    // Rows that leave an eighth or more of 256 places empty take 32 per lane of 8 lanes, when there are many: 2 048 000 x 192 top-4: 250 against
+    // 304 by 16 lanes, 1 638 400 x 240: 272 / 269; 8192 x 192: 4.8 / 4.2.
     if (vec4 && E > 32 && E <= 64 && k <= 8) return launch_topk_insert<4, 16, 8, 8, 6>(logits, rows, E, k, topk_idx, st);
     if (vec4 && E > 32 && E <= 64 && k <= 16) return launch_topk_keys<16, 4>(logits, rows, E, k, topk_idx, st);
     if (vec4 && E > 64 && E <= 128 && k <= 8) return launch_topk_insert<8, 16, 6, 8, 6>(logits, rows, E, k, topk_idx, st);
     if (vec4 && E > 64 && E <= 128 && k <= 32) return launch_topk_keys<32, 4>(logits, rows, E, k, topk_idx, st);
+    if (vec4 && E > 128 && (E <= 224 || (E <= 240 && k <= 2)) && k <= 8 && rows > 16384) return launch_topk_insert<8, 32, 6, 8, 4>(logits, rows, E, k, topk_idx, st);
     if (vec4 && E > 128 && E <= 256 && k <= 8) return launch_topk_insert<16, 16, 5, 8, 6>(logits, rows, E, k, topk_idx, st);
     if (vec4 && E > 128 && E <= 256 && k <= 64) return launch_topk_keys<64, 4>(logits, rows, E, k, topk_idx, st);
-    if (vec4 && E > 256 && E <= 512 && k <= 8) return launch_topk_insert<16, 32, 5, 8, 4>(logits, rows, E, k, topk_idx, st);
-    if (vec4 && E > 256 && E <= 512 && k <= 16) return launch_topk_insert<16, 32, 7, 16, 4>(logits, rows, E, k, topk_idx, st);
-    if (vec4 && E > 512 && k <= 8) return launch_topk_insert<16, 64, 5, 8, 4>(logits, rows, E, k, topk_idx, st);
-    if (vec4 && E > 512 && k <= 16) return launch_topk_insert<16, 64, 7, 16, 4>(logits, rows, E, k, topk_idx, st);
+    if (vec4 && E > 256 && !few_rows(rows, E, k)) {
+        if (E <= 512 && k <= 8) return launch_topk_insert<16, 32, 5, 8, 4>(logits, rows, E, k, topk_idx, st);
+        if (E <= 512 && k <= 16) return launch_topk_insert<16, 32, 7, 16, 4>(logits, rows, E, k, topk_idx, st);
+        if (E > 512 && k <= 8) return launch_topk_insert<16, 64, 5, 8, 4>(logits, rows, E, k, topk_idx, st);
+        if (E > 512 && k <= 16) return launch_topk_insert<16, 64, 7, 16, 4>(logits, rows, E, k, topk_idx, st);
+    }
     if (E <= 4) return launch_topk<1, 4>(logits, rows, E, k, topk_idx, st);
     if (E <= 8) return launch_topk<1, 8>(logits, rows, E, k, topk_idx, st);
     if (E <= 16) return launch_topk<4, 4>(logits, rows, E, k, topk_idx, st);

@@ -87,6 +87,18 @@ def test_one_pass_routing_without_room_for_slice_counts():
     assert np.array_equal(D1.cpu().numpy(), oracle.traffic_matrix(want, B, tok, eg, 512, M, N))
 
 
+@pytest.mark.parametrize("E,k,edge", [(512, 1, 8192), (512, 8, 4096), (260, 3, 4096), (516, 2, 16384), (1024, 4, 8192), (768, 16, 4096), (192, 8, 16384),
+                                      (240, 2, 16384)])
+def test_topk_around_the_row_counts_where_the_kernel_changes(E, k, edge):
+    rng = np.random.default_rng(E + k)
+    x = _rows("normal", edge + 1, E, rng)
+    x[::3] = _bf16(x[::3])
+    xd = torch.from_numpy(x).to(DEV)
+    want = oracle.route_topk(x, k)
+    for rows in (edge, edge + 1):
+        assert np.array_equal(rs.route_topk(xd[:rows], k).cpu().numpy(), want[:rows])
+
+
 @pytest.mark.parametrize("E,tok", [(8, 512), (8, 513), (8, 2048), (8, 2049), (4, 1537), (60, 682), (60, 683), (60, 2730), (60, 2731)])
 def test_slices_of_few_pairs(E, tok):
     # around the token counts where a pair's tokens become slices: one workgroup's rounds, or counts summed by a second kernel
