@@ -480,12 +480,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
     }
 }
 
-// row groups per workgroup: enough tokens that the G counts a workgroup leaves behind are under a two-hundredth of the logits it read (twice that share: 2-6 % slower)
-static int rw_iters(int64_t tokens_per_gpu, int64_t G, int E, int rows_per_group)
+// Row groups per workgroup: at least 64 rows (32 of more than 128 logits), and so many tokens that the G counts a workgroup leaves behind are
+// under a hundredth of the logits it read, or under a two-hundredth where that still leaves 2048 workgroups (64 GPUs x 4096 tokens of 128
+// logits, top-2: 28.3 -> 26.4 us; where it leaves 256 of them, 256 GPUs x 1024 tokens of 64 logits, top-8: 23.2 -> 28.7).  No more than 128
+// slices a pair: one thread of the second kernel sums a count over all of them (16 GPUs x 16384 tokens of 256 logits: 512 slices 62 us,
+// 128 slices 54; 4 GPUs: 35 and 22).
+constexpr int kRwMaxSplits = 128;
+// `longer`: the longer slices in any case, for a caller whose workspace holds no more.
+static int rw_iters(int64_t tokens_per_gpu, int64_t G, int64_t pairs, int E, int rows_per_group, bool longer)
 {
-    int64_t it = 1;
-    while (it * rows_per_group * E < 256 * G && it * rows_per_group < tokens_per_gpu) it *= 2;
-    return (int)it;
+    const int64_t least = E <= 128 ? 64 : 32;
+    int64_t rows = rows_per_group;
+    auto splits = [&](int64_t r) { return (tokens_per_gpu + r - 1) / r; };
+    while ((rows < least || rows * E < 128 * G || splits(rows) > kRwMaxSplits) && rows < tokens_per_gpu) rows *= 2;
+    if (rows * E < 256 * G && (longer || pairs * splits(2 * rows) >= 2048)) rows *= 2;
+    // slices of one length: three thousand tokens are two slices of 1536, not one of 2048 and the rest
+    const int64_t groups = (tokens_per_gpu + rows_per_group - 1) / rows_per_group;
+    return (int)((groups + splits(rows) - 1) / splits(rows));
 }
 
 template <int LANES, int VPL, int L, int WAVES>
@@ -503,8 +514,10 @@ static int launch_route_traffic_insert(RwArgs a, int64_t pairs, hipStream_t st)
     return launch_status();
 }
 
-// lanes per row of the one-pass kernel: 16 logits per lane, as in stage 1
-static int rw_lanes(int E) { return E <= 64 ? 4 : E <= 128 ? 8 : 16; }
+// Lanes per row of the one-pass kernel: 16 logits per lane up to 128, as in stage 1, and 32 above, where stage 1 takes 16 lanes of 16: a
+// workgroup here lives long enough to have its next rows' loads in flight (64 GPUs x 16384 tokens of 256 logits, top-2 / top-8: 167 / 174 us,
+// 178 / 186 by 16 lanes; 512 GPUs x 256 tokens: 24.4 / 33.9 and 27.6 / 33.0).
+static int rw_lanes(int E) { return E <= 64 ? 4 : 8; }
 
 // shape of the one-pass kernel for rows of 33..256 logits; false: the two stages run back to back
 static bool rw_shape(const float *logits, int32_t E, int32_t k, int64_t G, int *lanes)
@@ -519,7 +532,15 @@ static bool rw_shape(const float *logits, int32_t E, int32_t k, int64_t G, int *
 }  // namespace rs
 
 namespace rs {
-// slices per pair: one round of tokens per slice while that keeps the slice counts (4*G bytes per slice)
+// the workspace holds the counts of `splits` slices per pair (one slice needs none)
+static bool rt_ws_holds(const void *ws, size_t ws_bytes, int64_t pairs, int64_t splits, int64_t G)
+{
+    return splits <= 1 || (ws && reinterpret_cast<uintptr_t>(ws) % 4 == 0 && ws_bytes >= sizeof(uint32_t) * (size_t)(pairs * splits * G));
+}
+
+static bool rt_may_stay_whole(int64_t tokens_per_gpu, int64_t pairs, int round) { return pairs <= 64 && tokens_per_gpu <= 4 * round; }
+
+// slices per pair, rows of at most 8 logits: one round of tokens per slice while that keeps the slice counts (4*G bytes per slice)
 // a small fraction of the logits, more rounds per slice for large G
 static int64_t rt_splits(int64_t tokens_per_gpu, int64_t G, int64_t pairs, int E)
 {
@@ -560,7 +581,7 @@ extern "C" size_t railsched_route_traffic_workspace_bytes(int32_t batch, int64_t
             need = one > need ? one : need;
         }
         if (E > 32 && E <= 256 && k <= 8 && pairs > 0 && 4 * G <= 16 * 1024) {
-            const int64_t rb = (int64_t)rw_iters(tokens_per_gpu, G, E, rpg) * rpg;
+            const int64_t rb = (int64_t)rw_iters(tokens_per_gpu, G, pairs, E, rpg, false) * rpg;
             const int64_t splits = (tokens_per_gpu + rb - 1) / rb;
             const size_t one = splits > 1 ? align_up(sizeof(uint32_t) * (size_t)(pairs * splits * G), 256) : 256;
             need = one > need ? one : need;
@@ -597,22 +618,23 @@ extern "C" int railsched_route_traffic(const float *logits, int32_t batch, int64
         a.E = E; a.k = k; a.R = R; a.rmask = is_pow2(R) ? R - 1 : -1;
         a.G = (int32_t)G;
         const int rpg = 4 * (64 / lanes);
-        a.iters = rw_iters(tokens_per_gpu, G, E, rpg);
-        const int64_t rb = (int64_t)a.iters * rpg;
-        const int64_t splits = (tokens_per_gpu + rb - 1) / rb;
+        auto slices = [&](bool longer) {
+            a.iters = rw_iters(tokens_per_gpu, G, pairs, E, rpg, longer);
+            const int64_t rb = (int64_t)a.iters * rpg;
+            return (tokens_per_gpu + rb - 1) / rb;
+        };
+        int64_t splits = slices(false);
+        if (!rt_ws_holds(ws, ws_bytes, pairs, splits, G)) splits = slices(true);
         if (pairs * splits > 0x7FFFFFFFll) return RAILSCHED_ERR_UNSUPPORTED;
+        if (!rt_ws_holds(ws, ws_bytes, pairs, splits, G)) return RAILSCHED_ERR_WORKSPACE;
         a.splits = (int32_t)splits;
         a.partial = static_cast<uint32_t *>(ws);
-        if (splits > 1) {
-            const size_t need = sizeof(uint32_t) * (size_t)(pairs * splits * G);
-            if (!ws || ws_bytes < need || reinterpret_cast<uintptr_t>(ws) % 4 != 0) return RAILSCHED_ERR_WORKSPACE;
-        }
         a.table_in_lds = ((int64_t)E * R <= kRtTableMax && 4 * (G + (int64_t)E * R) <= 16 * 1024) ? 1 : 0;
         hipStream_t st = static_cast<hipStream_t>(stream);
         int rc;
-        if (E <= 64) rc = launch_route_traffic_insert<4, 16, 8, 6>(a, pairs, st);
+        if (E <= 64) rc = launch_route_traffic_insert<4, 16, 8, 5>(a, pairs, st);
         else if (E <= 128) rc = launch_route_traffic_insert<8, 16, 6, 6>(a, pairs, st);
-        else rc = launch_route_traffic_insert<16, 16, 5, 6>(a, pairs, st);
+        else rc = launch_route_traffic_insert<8, 32, 6, 4>(a, pairs, st);
         if (rc) return rc;
         if (splits > 1) return launch_count_reduce(a.partial, D1, pairs * G, (int)G, (int)splits, payload_bytes, st);
         return RAILSCHED_OK;

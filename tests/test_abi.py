@@ -121,6 +121,24 @@ def test_route_traffic_validation():
     assert f(FAKE, 0, 10, 8, 2, FAKE, 2, 1024, C.byref(t), FAKE, FAKE, FAKE, need, None) == 0
 
 
+@pytest.mark.parametrize("E", [36, 64, 96, 128, 132, 192, 256])
+def test_route_traffic_slices_are_at_least_as_long_as_the_first_rule(E):
+    # a workspace for slices of 64 rows (32 of more than 128 logits), or of 128 * G logits where that is more, has always been enough
+    lib = rs.load()
+    for M, N in ((2, 2), (4, 4), (8, 8), (32, 8), (64, 16)):
+        G = M * N
+        t = _topo(M=M, N=N)
+        for tokens in (1, 33, 65, 300, 1500, 3072, 16384, 100_000):
+            for batch in (1, 3, 60):
+                rows = 64 if E <= 128 else 32
+                while rows * E < 128 * G and rows < tokens:
+                    rows *= 2
+                slices = -(-tokens // rows)
+                enough = max(256, -(-4 * batch * G * slices * G // 256) * 256 if slices > 1 else 256,
+                             lib.railsched_traffic_matrix_workspace_bytes(batch, tokens, 2, C.byref(t)))
+                assert lib.railsched_route_traffic_workspace_bytes(batch, tokens, E, 2, C.byref(t)) <= enough, (G, tokens, batch)
+
+
 def test_chunk_sort_and_eval_validation():
     lib = rs.load()
     t = _topo()

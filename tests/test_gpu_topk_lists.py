@@ -87,6 +87,27 @@ def test_one_pass_routing_without_room_for_slice_counts():
     assert np.array_equal(D1.cpu().numpy(), oracle.traffic_matrix(want, B, tok, eg, 512, M, N))
 
 
+def _routed(E, k, M, N, B, tok, R=1, ws=None, want_idx=True, x=None, seed=5):
+    """One call of route_traffic and the oracle's two stages on the same rows."""
+    rng = np.random.default_rng(seed)
+    if x is None:
+        x = rng.standard_normal((B * M * N * tok, E)).astype(np.float32)
+    eg = rng.integers(0, M * N, size=(E, R)).astype(np.int32)
+    idx, D1 = rs.route_traffic(torch.from_numpy(x).to(DEV), k, B, tok, torch.from_numpy(eg).to(DEV), 512, rs.Topo(M, N, 65536), ws=ws,
+                               want_idx=want_idx)
+    want = oracle.route_topk(x, k)
+    if want_idx:
+        assert np.array_equal(idx.cpu().numpy(), want)
+    assert np.array_equal(D1.cpu().numpy(), oracle.traffic_matrix(want, B, tok, eg, 512, M, N))
+
+
+@pytest.mark.parametrize("E,k,M,N,B,tok", [(64, 2, 2, 2, 1, 20_000), (128, 8, 2, 2, 1, 8300), (256, 2, 2, 2, 1, 4200), (192, 8, 2, 3, 1, 700),
+                                           (64, 6, 16, 16, 1, 1537), (96, 4, 8, 8, 2, 1500), (256, 8, 8, 8, 40, 65), (36, 1, 3, 3, 2, 129)])
+def test_one_pass_without_indices(E, k, M, N, B, tok):
+    # more rows than 128 slices of the shortest length, slices that do not divide the tokens, longer slices for many pairs
+    _routed(E, k, M, N, B, tok, want_idx=False)
+
+
 @pytest.mark.parametrize("E,k,edge", [(512, 1, 8192), (512, 8, 4096), (260, 3, 4096), (516, 2, 16384), (1024, 4, 8192), (768, 16, 4096), (192, 8, 16384),
                                       (240, 2, 16384)])
 def test_topk_around_the_row_counts_where_the_kernel_changes(E, k, edge):
