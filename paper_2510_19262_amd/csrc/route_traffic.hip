@@ -30,7 +30,8 @@ typedef float rt_f32x4 __attribute__((ext_vector_type(4)));
 typedef int rt_i32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kRtThreads = 256;
-constexpr int kRtThreadsWhole = 1024;
+constexpr int kRtThreadsWhole = 1024; // rows of at most 8 logits: see rt_whole
+constexpr int kRtThreadsTwo = 512;    // rows of 9..32 logits: see rt_list_splits
 // rows per thread with their loads in flight together: 64 bytes of logits and more
 constexpr int rt_unroll(int vpl) { return vpl <= 16 ? 2 : 1; }
 constexpr int rt_round(int vpl) { return kRtThreads * rt_unroll(vpl); }   // tokens per workgroup and round
@@ -50,7 +51,7 @@ struct RtArgs {
     int32_t copies, lanes_per_period;
     int32_t bin_stride;      // words between histogram copies: odd, so that a bin's copies lie in different LDS banks
     int32_t table_in_lds;
-    int32_t wide_idx;        // topk_idx aligned for 16-byte stores
+    int32_t wide_idx;        // bytes topk_idx is aligned to: 4, 8 or 16 (or more)
 };
 
 // D1[pair][d] = payload * sum of the pair's slice counts
@@ -213,6 +214,18 @@ template <int VPL, int L>
 __device__ __forceinline__ void rt_pick_list(const RtArgs &a, const float (&v)[VPL], int (&win)[L - 1])
 {
     constexpr unsigned MASK = (unsigned)VPL - 1u;
+    if constexpr (L == 2) {                         // the largest logit alone: compared as it is
+        float bv = -INFINITY;
+        int bi = INT_MAX;
+#pragma unroll
+        for (int j = 0; j < VPL; ++j) {
+            const bool better = v[j] > bv;
+            bv = better ? v[j] : bv;
+            bi = better ? j : bi;
+        }
+        win[0] = bi;
+        return;
+    }
     int lst[L];
     unsigned bits = 0;
     rt_insert<VPL, L, 0>(v, a.E, lst, bits);
@@ -249,13 +262,21 @@ template <int KM>
 __device__ __forceinline__ void rt_store_row(const RtArgs &a, int64_t row, const int (&win)[KM])
 {
     int32_t *dst = a.topk_idx + row * a.k;
-    if (a.wide_idx && (a.k & 3) == 0) {
+    if (a.wide_idx >= 16 && (a.k & 3) == 0) {
 #pragma unroll
         for (int j = 0; j + 4 <= KM; j += 4)
             if (j < a.k) {
                 i32x4 x;
                 x.x = win[j]; x.y = win[j + 1]; x.z = win[j + 2]; x.w = win[j + 3];
                 __builtin_nontemporal_store(x, reinterpret_cast<i32x4 *>(dst + j));
+            }
+    } else if (a.wide_idx >= 8 && (a.k & 1) == 0) {
+#pragma unroll
+        for (int j = 0; j + 2 <= KM; j += 2)
+            if (j < a.k) {
+                i32x2 x;
+                x.x = win[j]; x.y = win[j + 1];
+                __builtin_nontemporal_store(x, reinterpret_cast<i32x2 *>(dst + j));
             }
     } else {
 #pragma unroll
@@ -265,7 +286,7 @@ __device__ __forceinline__ void rt_store_row(const RtArgs &a, int64_t row, const
 }
 
 // L = 0: rows of at most 8 logits, picked in rounds.  L > 0: rows of 9..32 logits and k < L, picked from a list.
-// THREADS: kRtThreads, or kRtThreadsWhole where one workgroup takes a pair of a few rounds.
+// THREADS: kRtThreads, or more where a workgroup's tokens are several of its rounds (kRtThreadsWhole for L = 0, kRtThreadsTwo otherwise).
 template <int VPL, int L, bool VEC4, bool TABLE_LDS, int THREADS>
 __global__ __launch_bounds__(THREADS) void route_traffic_kernel(RtArgs a)
 {
@@ -387,12 +408,21 @@ static int launch_route_traffic_t(const RtArgs &a, int64_t pairs, size_t lds, hi
     return launch_status();
 }
 
+// An uncut pair of more than one round takes 1024 threads instead of 256 while the chip has room for its wavefronts: up to 256 pairs (a CU
+// holds two such workgroups) always - 256 GPUs x 2048 tokens, 8 logits: top-2 8.0 -> 4.8 us, top-8 22.7 -> 15.1 - and up to 512 from three rounds on
+// (512 GPUs, top-2: 1024 tokens 5.9 / 6.2, 2048 tokens 10.5 / 9.5, 4096 tokens 19.0 / 15.8); 1024 pairs lose (4096 tokens: 26.9 / 33.1).
+static bool rt_whole(int64_t tokens, int64_t pairs, int64_t splits, int round)
+{
+    return splits == 1 && tokens > round && (pairs <= 256 || (pairs <= 512 && tokens > 2 * round));
+}
+
 template <int VPL, int L>
-static int launch_route_traffic(const RtArgs &a, int64_t pairs, size_t lds, hipStream_t st)
+static int launch_route_traffic(const RtArgs &a, int64_t pairs, int64_t slice, size_t lds, hipStream_t st)
 {
     if constexpr (L == 0) {
-        // a pair that was not cut although it is more than one round: the round of a workgroup of 1024 covers it
-        if (a.splits == 1 && a.tokens_per_gpu > rt_round(VPL)) return launch_route_traffic_t<VPL, L, kRtThreadsWhole>(a, pairs, lds, st);
+        if (rt_whole(a.tokens_per_gpu, pairs, a.splits, rt_round(VPL))) return launch_route_traffic_t<VPL, L, kRtThreadsWhole>(a, pairs, lds, st);
+    } else {
+        if ((a.splits == 1 ? a.tokens_per_gpu : slice) > rt_round(VPL)) return launch_route_traffic_t<VPL, L, kRtThreadsTwo>(a, pairs, lds, st);
     }
     return launch_route_traffic_t<VPL, L, kRtThreads>(a, pairs, lds, st);
 }
@@ -542,25 +572,31 @@ static bool rt_may_stay_whole(int64_t tokens_per_gpu, int64_t pairs, int round) 
 
 // slices per pair, rows of at most 8 logits: one round of tokens per slice while that keeps the slice counts (4*G bytes per slice)
 // a small fraction of the logits, more rounds per slice for large G
-static int64_t rt_splits(int64_t tokens_per_gpu, int64_t G, int64_t pairs, int E)
+static int64_t rt_splits(int64_t tokens_per_gpu, int64_t G, int64_t pairs, int E, int k)
 {
     const int kRtRound = rt_round(rt_vpl(E));
     const int64_t rounds = (8 * G + kRtRound - 1) / kRtRound;
     const int64_t slice = kRtRound * (rounds < 1 ? 1 : rounds);
     int64_t splits = (tokens_per_gpu + slice - 1) / slice;
     if (splits < 1) splits = 1;
-    // few pairs of few tokens leave the chip idle either way: a workgroup takes a pair's rounds one after the other and the launch
-    // that sums slice counts is saved (a layer of 16 GPUs x 2048 tokens: 27.8 -> 24.7 us for the whole pass)
-    if (splits <= 4 && pairs <= 64) return 1;
+    // Few pairs of few tokens leave the chip idle either way: a workgroup of 1024 threads takes a pair of up to 2048 tokens in one of its
+    // rounds and the launch that sums slice counts is saved, as long as the picks of one round are not the longer part (16 GPUs, 8
+    // logits, us cut / uncut: 2048 tokens top-2 5.2 / 4.1, top-4 6.5 / 5.7, top-8 8.4 / 10.2; 1024 tokens top-8 8.1 / 6.3).
+    if (rt_may_stay_whole(tokens_per_gpu, pairs, kRtRound) && tokens_per_gpu * k <= 8192) return 1;
     while (splits > 1 && pairs * splits > 0x7FFFFFFFll) splits = (splits + 1) / 2;
     return splits;
 }
 
-// the same for rows of 9..32 logits, where two slices are one workgroup's two rounds: no slice counts, no second kernel
-static int64_t rt_list_splits(int64_t tokens_per_gpu, int64_t G, int64_t pairs, int E)
+// Slices per pair, rows of 9..32 logits, and the tokens of a slice: one round of 256 threads, more where the slice counts would be more than
+// a sixty-fourth of the logits.  Two rounds are one round of 512 threads: a pair that is no longer is not cut, which saves the second kernel.
+static int64_t rt_list_splits(int64_t tokens_per_gpu, int64_t G, int E, int64_t *slice_out)
 {
-    const int64_t splits = rt_splits(tokens_per_gpu, G, pairs, E);
-    return splits == 2 ? 1 : splits;
+    const int round = rt_round(rt_vpl(E));
+    const int64_t rounds = (64 * G / E + round - 1) / round;
+    const int64_t slice = round * (rounds < 1 ? 1 : rounds);
+    const int64_t splits = (tokens_per_gpu + slice - 1) / slice;
+    *slice_out = slice;
+    return splits < 1 || tokens_per_gpu <= 2 * round ? 1 : splits;
 }
 }  // namespace rs
 
@@ -576,7 +612,8 @@ extern "C" size_t railsched_route_traffic_workspace_bytes(int32_t batch, int64_t
         size_t need = railsched_traffic_matrix_workspace_bytes(batch, tokens_per_gpu, k, h_topo);
         const int rpg = 4 * (64 / rw_lanes(E));
         if (E <= 32 && k <= 8 && pairs > 0) {
-            const int64_t splits = rt_list_splits(tokens_per_gpu, G, pairs, E);
+            int64_t slice;
+            const int64_t splits = rt_list_splits(tokens_per_gpu, G, E, &slice);
             const size_t one = splits > 1 ? align_up(sizeof(uint32_t) * (size_t)(pairs * splits * G), 256) : 256;
             need = one > need ? one : need;
         }
@@ -589,7 +626,7 @@ extern "C" size_t railsched_route_traffic_workspace_bytes(int32_t batch, int64_t
         return need;
     }
     if (pairs == 0) return 256;
-    const int64_t splits = rt_splits(tokens_per_gpu, G, pairs, E);
+    const int64_t splits = rt_splits(tokens_per_gpu, G, pairs, E, k);
     return splits > 1 ? align_up(sizeof(uint32_t) * (size_t)(pairs * splits * G), 256) : 256;
 }
 
@@ -639,14 +676,13 @@ extern "C" int railsched_route_traffic(const float *logits, int32_t batch, int64
         if (splits > 1) return launch_count_reduce(a.partial, D1, pairs * G, (int)G, (int)splits, payload_bytes, st);
         return RAILSCHED_OK;
     }
-    const int64_t list_splits = E > 8 && E <= 32 ? rt_list_splits(tokens_per_gpu, G, pairs, E) : 1;
+    int64_t slice = 0;
+    const int64_t list_splits = E > 8 && E <= 32 ? rt_list_splits(tokens_per_gpu, G, E, &slice) : 1;
     // rows of 9..32 logits: one pass when the indices are wanted, k fits the lists, whole float4s load, and the workspace (if any
     // is needed) holds the slice counts.  3.1 M rows, both stages back to back against this: 16 logits top-4 80 -> 50 us, top-2 62 -> 49;
     // 32 logits top-4 145 -> 84, top-8 232 -> 110; 20 logits top-1 85 -> 73.
     const bool list = E > 8 && E <= 32 && k <= 8 && topk_idx && rows > 0 && E % 4 == 0 && reinterpret_cast<uintptr_t>(logits) % 16 == 0 &&
-                      pairs * list_splits <= 0x7FFFFFFFll && G <= 8192 &&
-                      (list_splits == 1 || (ws && reinterpret_cast<uintptr_t>(ws) % 4 == 0 &&
-                                            ws_bytes >= sizeof(uint32_t) * (size_t)(pairs * list_splits * G)));
+                      pairs * list_splits <= 0x7FFFFFFFll && G <= 8192 && rt_ws_holds(ws, ws_bytes, pairs, list_splits, G);
     if (E > 8 && !list) {
         // other shapes: the two stages run one after the other through the index array
         if (!topk_idx && rows > 0) return RAILSCHED_ERR_NULL_PTR;
@@ -666,19 +702,19 @@ extern "C" int railsched_route_traffic(const float *logits, int32_t batch, int64
     a.bin_stride = (int32_t)(a.copies > 1 ? (G | 1) : G);
     a.table_in_lds = ((int64_t)E * R <= kRtTableMax && 4 * (a.copies * (int64_t)a.bin_stride + (int64_t)E * R) <= 64 * 1024) ? 1 : 0;
 
-    a.wide_idx = reinterpret_cast<uintptr_t>(topk_idx) % 16 == 0 ? 1 : 0;
-    const int64_t splits = list ? list_splits : rt_splits(tokens_per_gpu, G, pairs, E);
+    const uintptr_t at = reinterpret_cast<uintptr_t>(topk_idx);
+    a.wide_idx = at % 16 == 0 ? 16 : at % 8 == 0 ? 8 : 4;
+    int64_t splits = list ? list_splits : rt_splits(tokens_per_gpu, G, pairs, E, k);
+    // a pair that may stay whole does so for a caller without room for its slices
+    if (!list && !rt_ws_holds(ws, ws_bytes, pairs, splits, G) && rt_may_stay_whole(tokens_per_gpu, pairs, rt_round(rt_vpl(E)))) splits = 1;
     if (pairs * splits > 0x7FFFFFFFll) return RAILSCHED_ERR_UNSUPPORTED;
+    if (!rt_ws_holds(ws, ws_bytes, pairs, splits, G)) return RAILSCHED_ERR_WORKSPACE;
     a.splits = (int32_t)splits;
     a.partial = static_cast<uint32_t *>(ws);
-    if (splits > 1) {
-        const size_t need = sizeof(uint32_t) * (size_t)(pairs * splits * G);
-        if (!ws || ws_bytes < need || reinterpret_cast<uintptr_t>(ws) % 4 != 0) return RAILSCHED_ERR_WORKSPACE;
-    }
     const size_t lds = sizeof(unsigned) * (size_t)a.bin_stride * a.copies + (a.table_in_lds ? sizeof(int32_t) * (size_t)E * R : 0);
-    const int rc = E <= 4 ? launch_route_traffic<4, 0>(a, pairs, lds, st) : E <= 8 ? launch_route_traffic<8, 0>(a, pairs, lds, st)
-                 : E <= 16 ? (k <= 4 ? launch_route_traffic<16, 5>(a, pairs, lds, st) : launch_route_traffic<16, 9>(a, pairs, lds, st))
-                           : (k <= 4 ? launch_route_traffic<32, 5>(a, pairs, lds, st) : launch_route_traffic<32, 9>(a, pairs, lds, st));
+    const int rc = E <= 4 ? launch_route_traffic<4, 0>(a, pairs, slice, lds, st) : E <= 8 ? launch_route_traffic<8, 0>(a, pairs, slice, lds, st)
+                 : E <= 16 ? (k == 1 ? launch_route_traffic<16, 2>(a, pairs, slice, lds, st) : k <= 4 ? launch_route_traffic<16, 5>(a, pairs, slice, lds, st) : launch_route_traffic<16, 9>(a, pairs, slice, lds, st))
+                           : (k == 1 ? launch_route_traffic<32, 2>(a, pairs, slice, lds, st) : k <= 4 ? launch_route_traffic<32, 5>(a, pairs, slice, lds, st) : launch_route_traffic<32, 9>(a, pairs, slice, lds, st));
     if (rc) return rc;
     if (splits > 1) return launch_count_reduce(a.partial, D1, pairs * G, (int)G, (int)splits, payload_bytes, st);
     return RAILSCHED_OK;

@@ -73,20 +73,6 @@ def test_one_pass_routing_of_short_rows(E, k, kind):
         assert np.array_equal(D1.cpu().numpy(), oracle.traffic_matrix(want, B, tok, eg, 512, M, N))
 
 
-def test_one_pass_routing_without_room_for_slice_counts():
-    # rows of 16 logits with a workspace that only the two stages fit: the same outputs
-    rng = np.random.default_rng(5)
-    M, N, B, E, k, tok = 2, 2, 1, 16, 2, 1100
-    topo = rs.Topo(M, N, 65536)
-    x = rng.standard_normal((B * M * N * tok, E)).astype(np.float32)
-    eg = rng.integers(0, M * N, size=(E, 1)).astype(np.int32)
-    ws = torch.empty(16, dtype=torch.uint8, device=DEV)
-    idx, D1 = rs.route_traffic(torch.from_numpy(x).to(DEV), k, B, tok, torch.from_numpy(eg).to(DEV), 512, topo, ws=ws)
-    want = oracle.route_topk(x, k)
-    assert np.array_equal(idx.cpu().numpy(), want)
-    assert np.array_equal(D1.cpu().numpy(), oracle.traffic_matrix(want, B, tok, eg, 512, M, N))
-
-
 def _routed(E, k, M, N, B, tok, R=1, ws=None, want_idx=True, x=None, seed=5):
     """One call of route_traffic and the oracle's two stages on the same rows."""
     rng = np.random.default_rng(seed)
@@ -99,6 +85,70 @@ def _routed(E, k, M, N, B, tok, R=1, ws=None, want_idx=True, x=None, seed=5):
     if want_idx:
         assert np.array_equal(idx.cpu().numpy(), want)
     assert np.array_equal(D1.cpu().numpy(), oracle.traffic_matrix(want, B, tok, eg, 512, M, N))
+
+
+def test_one_pass_routing_without_room_for_slice_counts():
+    # rows of 16 logits with a workspace that only the two stages fit: the same outputs
+    M, N, B, E, k, tok = 2, 2, 1, 16, 2, 2100
+    topo = rs.Topo(M, N, 65536)
+    ws = torch.empty(16, dtype=torch.uint8, device=DEV)
+    assert rs.route_traffic_workspace_bytes(B, tok, E, k, topo) > 256 > ws.numel()           # the one pass takes slices here ...
+    assert rs.traffic_matrix_workspace_bytes(B, tok, k, topo) == 256                         # ... and the two stages one
+    _routed(E, k, M, N, B, tok, ws=ws)
+
+
+def test_routing_with_room_for_longer_slices_only():
+    # rows of 64 logits without indices: half the workspace of the query still holds the counts of slices twice as long, less does not
+    M, N, E, k, tok = 8, 8, 64, 6, 512
+    need = rs.route_traffic_workspace_bytes(1, tok, E, k, rs.Topo(M, N, 65536))
+    assert need == 4 * 64 * 4 * 64                                                           # 64 pairs, 4 slices, 64 counts
+    _routed(E, k, M, N, 1, tok, ws=torch.empty(need // 2, dtype=torch.uint8, device=DEV), want_idx=False)
+    with pytest.raises(rs.RailschedError):
+        _routed(E, k, M, N, 1, tok, ws=torch.empty(need // 2 - 4, dtype=torch.uint8, device=DEV), want_idx=False)
+    # rows of 8 logits: few pairs of up to 2048 tokens may stay whole
+    assert rs.route_traffic_workspace_bytes(1, 2048, 8, 8, rs.Topo(4, 4, 65536)) > 256
+    _routed(8, 8, 4, 4, 1, 2048, ws=torch.empty(256, dtype=torch.uint8, device=DEV))
+
+
+@pytest.mark.parametrize("E,k,M,N,tok", [(16, 1, 2, 3, 512), (16, 3, 2, 3, 513), (12, 2, 2, 3, 1024), (16, 6, 2, 3, 1025), (12, 8, 2, 2, 2100),
+                                         (16, 4, 16, 16, 1025), (16, 7, 16, 16, 2049), (32, 1, 2, 3, 256), (32, 5, 2, 3, 257), (28, 6, 2, 3, 512),
+                                         (20, 1, 2, 3, 513), (32, 2, 8, 8, 300), (32, 4, 16, 16, 700)])
+def test_slices_of_short_rows(E, k, M, N, tok):
+    # rounds of 256 and of 512 threads, one slice and several, one round a slice and more (large G); every width of index stores
+    _routed(E, k, M, N, 1, tok, R=2)
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 6, 8])
+@pytest.mark.parametrize("shift", [1, 2])
+def test_index_arrays_at_any_alignment(k, shift):
+    # indices behind the first `shift` words of an allocation: 4 and 8 bytes off a 16-byte boundary
+    rng = np.random.default_rng(k)
+    M, N, E, tok = 2, 2, 16, 600
+    rows = M * N * tok
+    x = rng.standard_normal((rows, E)).astype(np.float32)
+    eg = rng.integers(0, M * N, size=(E, 1)).astype(np.int32)
+    room = torch.full((rows * k + 8,), -7, dtype=torch.int32, device=DEV)
+    idx = room[shift:shift + rows * k].view(rows, k)
+    D1 = torch.empty((1, M * N, M * N), dtype=torch.int64, device=DEV)
+    rs.route_traffic(torch.from_numpy(x).to(DEV), k, 1, tok, torch.from_numpy(eg).to(DEV), 512, rs.Topo(M, N, 65536), out=(idx, D1))
+    want = oracle.route_topk(x, k)
+    assert np.array_equal(idx.cpu().numpy(), want)
+    assert (room[:shift] == -7).all() and (room[shift + rows * k:] == -7).all()
+    assert np.array_equal(D1.cpu().numpy(), oracle.traffic_matrix(want, 1, tok, eg, 512, M, N))
+
+
+@pytest.mark.parametrize("E,k,R,tok", [(16, 4, 600, 700), (16, 1, 1000, 1100), (32, 8, 300, 300), (32, 3, 513, 600), (8, 2, 1500, 513), (8, 2, 1500, 2048),
+                                       (4, 1, 3000, 1999)])
+def test_placement_tables_in_global_memory(E, k, R, tok):
+    # more than 8192 entries: the one-pass kernels of up to 8 and of 9..32 logits read the table where it is
+    _routed(E, k, 2, 3, 1, tok, R=R)
+
+
+@pytest.mark.parametrize("E,k,M,N,tok", [(8, 4, 2, 3, 2048), (8, 5, 2, 3, 2048), (8, 8, 2, 3, 1024), (8, 8, 2, 3, 1025), (8, 2, 16, 16, 600), (4, 2, 16, 32, 1100),
+                                         (8, 1, 13, 40, 1100)])
+def test_whole_pairs_of_rows_of_eight(E, k, M, N, tok):
+    # cut or whole by tokens and picks, 256 or 1024 threads by pairs (256, 512 and 520 of them)
+    _routed(E, k, M, N, 1, tok)
 
 
 @pytest.mark.parametrize("E,k,M,N,B,tok", [(64, 2, 2, 2, 1, 20_000), (128, 8, 2, 2, 1, 8300), (256, 2, 2, 2, 1, 4200), (192, 8, 2, 3, 1, 700),
