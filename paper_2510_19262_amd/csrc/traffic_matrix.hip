@@ -197,7 +197,9 @@ extern "C" int railsched_traffic_matrix(const int32_t *topk_idx, int32_t batch, 
     const int64_t pairs = (int64_t)batch * G;
     const int64_t splits = tm_splits(a.slots_per_gpu, G, pairs);
     if (pairs * splits > 0x7FFFFFFFll) return RAILSCHED_ERR_UNSUPPORTED;
-    const bool whole = splits == 1 && a.slots_per_gpu > (int64_t)kTmThreads * 4;   // see tm_splits
+    // 1024 threads from the second step of 256 on (16 pairs of 4096 slots, one step of 256: 3.6 us, 4.1 by 1024), or, where all CUs hold
+    // several pairs, from the slots of one step without unrolling on; see tm_splits
+    const bool whole = splits == 1 && a.slots_per_gpu > (int64_t)kTmThreads * 4 * (pairs >= 512 ? 1 : kTmUnroll);
     a.copies = 1;
     // as many copies as keep a workgroup's LDS (bins + table) within 20 KiB: eight workgroups of 256, all the wavefronts a CU
     // takes (two workgroups of 1024 have 80 KiB each, which the 8192-word bound keeps them far from)

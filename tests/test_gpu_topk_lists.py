@@ -46,7 +46,7 @@ def test_topk_lists(E, k, kind):
         assert np.array_equal(got, oracle.route_topk(x, k))
 
 
-@pytest.mark.parametrize("k,R,tok", [(6, 1, 4096), (6, 4, 1021), (3, 3, 1000), (10, 1, 77), (5, 2, 4099), (8, 1, 512), (8, 5, 300)])
+@pytest.mark.parametrize("k,R,tok", [(6, 1, 4096), (6, 4, 1021), (3, 3, 1000), (10, 1, 77), (5, 2, 4099), (8, 1, 512), (8, 5, 300), (8, 2, 513)])
 def test_traffic_matrix_replicas(k, R, tok):
     # slots whose token index needs a division, whose replica index does not, and both
     rng = np.random.default_rng(k * 100 + R)
