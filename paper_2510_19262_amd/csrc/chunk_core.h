@@ -110,12 +110,16 @@ constexpr int kTailLoads = 4;       // flows per thread and round of the flow sc
 // LDS words tail_sort_block needs beside rem[NF], hist[] and the two index arrays
 template <int T> constexpr int tail_hist_words() { return 256 * (T / 64); }
 constexpr int kTailShared = 64 + 2 + 16;
-constexpr int kRankTails = 256;     // tails up to which places are counted instead of sorted for (a 16-GPU instance: one pass over its neighbours in LDS, no histogram)
+// Tails whose places are counted (one pass over the others in LDS, no histogram) instead of sorted for: what a wavefront by itself counts in one
+// round, or a quarter of a thousand for several.  Flows up to which even the empty ones are counted along, without gathering the tails first.
+// One wavefront each, 3840 instances of 256 tails of 16 differing bits: 56 us counted, 16 sorted.
+template <int T> constexpr int rank_tails() { return T == 64 ? 64 : 256; }
+template <int T> constexpr int rank_flows() { return T == 64 ? 96 : 256; }
 
 // Tails (B mod C > 0) of the flows of one instance, sorted by weight descending, ties in canonical (flow) order:
 // stable LSD radix sort by one workgroup of T threads in LDS, 8-bit digits over the span of key bits that differ at all.
 // A wavefront owns a contiguous share of the order and a histogram of its own, so ranks inside a share need no workgroup
-// barrier (ballot matching in batches of 64); a pass has three.  rem[NF] receives every flow's tail bytes,
+// barrier (ballot matching in batches of 64); a pass has four.  rem[NF] receives every flow's tail bytes,
 // hist[tail_hist_words<T>()] and sh[kTailShared] are scratch, idx_a/idx_b[NF] are ping-pong arrays of flow ids; returns the
 // array that holds the sorted ids and their number in nt.  Latency bound: one wavefront took 32 us for the 4096 flows of a
 // 512-GPU instance, and four of them per CU (its LDS) 364 us for 3904 such instances; a workgroup of 1024 takes 14 us for 128 instances of 8192 flows (67 before),
@@ -130,9 +134,51 @@ __device__ __forceinline__ unsigned short *tail_sort_block(const CsArgs &a, cons
     unsigned *sh_cnt = sh, *sh_bits = sh + 64, *sh_tot = sh + 66;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const unsigned long long lt = (1ull << lane) - 1ull;
+    int nt = 0;
+    if (a.NF <= rank_flows<T>()) {
+        // few flows: a tail's place is the number of tails that go before it, counted over all flows by the P neighbouring threads of its own
+        constexpr int R = T == 64 ? 2 : 1, P = T >= 512 ? T / 256 : 1;   // rounds of loads, threads per flow
+        const int quads = (a.NF + 3) >> 2;
+        int64_t bytes[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) bytes[u] = u * T + tid < a.NF ? flow_bytes(a, rows, k, u * T + tid) : 0;
+        stage();
+        unsigned tails = 0;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int f = u * T + tid;
+            uint32_t q = 0, r = 0;
+            split_bytes(a, bytes[u], q, r);
+            if (f < 4 * quads) rem[f] = r;                               // nothing behind the last flow: zeros
+            tails += (unsigned)__popcll(__ballot(r != 0));
+        }
+        if (lane == 0) sh_cnt[wave] = tails;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < (W < 4 ? W : 4); ++w) nt += (int)sh_cnt[w];  // 256 flows are in four wavefronts
+        for (int base = 0; base < a.NF; base += T / P) {
+            const int f = base + tid / P;
+            const unsigned w = f < a.NF ? rem[f] : 0u;
+            unsigned rank = 0;
+            if (w)
+                for (int g = tid % P; g < quads; g += P) {
+                    const uint4 o = *reinterpret_cast<const uint4 *>(rem + 4 * g);
+                    const int j = 4 * g;
+                    rank += (o.x > w || (o.x == w && j + 0 < f)) ? 1u : 0u;
+                    rank += (o.y > w || (o.y == w && j + 1 < f)) ? 1u : 0u;
+                    rank += (o.z > w || (o.z == w && j + 2 < f)) ? 1u : 0u;
+                    rank += (o.w > w || (o.w == w && j + 3 < f)) ? 1u : 0u;
+                }
+#pragma unroll
+            for (int d = 1; d < P; d <<= 1) rank += (unsigned)__shfl_xor((int)rank, d);
+            if (w && tid % P == 0) idx_b[rank] = (unsigned short)f;
+        }
+        __syncthreads();
+        nt_out = nt;
+        return idx_b;
+    }
     if (tid == 0) { sh_bits[0] = 0u; sh_bits[1] = 0xFFFFFFFFu; }
     // tails in canonical order; which key bits differ at all between them
-    int nt = 0;
     unsigned any1 = 0u, all1 = 0xFFFFFFFFu;
     for (int f0 = 0; f0 < a.NF; f0 += U * T) {
         int64_t bytes[U];
@@ -166,13 +212,13 @@ __device__ __forceinline__ unsigned short *tail_sort_block(const CsArgs &a, cons
         __syncthreads();                            // sh_cnt has been read
     }
     nt_out = nt;
-    if (nt <= kRankTails) {
+    if (nt <= rank_tails<T>()) {
         // few tails: a tail's place is the number of tails that go before it.  Keys side by side in hist, read four at a time;
         // with T / 256 threads per tail each counts a share of them.
         constexpr int P = T >= 256 ? T / 256 : 1, STEP = T >= 256 ? 256 : T;
         const int quads = (nt + 3) >> 2;
         for (int i = tid; i < 4 * quads; i += T) hist[i] = i < nt ? rem[idx_a[i]] : 0u;   // a tail is at least one byte
-        if constexpr (P > 1) { if (tid < kRankTails) hist[kRankTails + tid] = 0u; }
+        if constexpr (P > 1) { if (tid < 256) hist[256 + tid] = 0u; }
         __syncthreads();
         const int part = tid / 256;
         for (int i = tid % 256; i < nt; i += STEP) {
@@ -186,12 +232,12 @@ __device__ __forceinline__ unsigned short *tail_sort_block(const CsArgs &a, cons
                 rank += (o.z > w || (o.z == w && j + 2 < i)) ? 1u : 0u;
                 rank += (o.w > w || (o.w == w && j + 3 < i)) ? 1u : 0u;
             }
-            if constexpr (P > 1) atomicAdd(&hist[kRankTails + i], rank);
+            if constexpr (P > 1) atomicAdd(&hist[256 + i], rank);
             else idx_b[rank] = idx_a[i];
         }
         __syncthreads();
         if constexpr (P > 1) {
-            if (tid < nt) idx_b[hist[kRankTails + tid]] = idx_a[tid];
+            if (tid < nt) idx_b[hist[256 + tid]] = idx_a[tid];
             __syncthreads();
         }
         return idx_b;
