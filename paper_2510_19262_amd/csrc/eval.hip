@@ -129,8 +129,8 @@ __global__ __launch_bounds__(THREADS) void eval_reduce_kernel(EvArgs a)
         int64_t s = 0, r = 0;
         if (tid < nb) s = Sb[base + tid];
         if constexpr (SUM) {
-            int width = 64;                           // threads per slot row: the power of two >= nb
-            while (width < nb) width *= 2;            // nb <= THREADS, a multiple of 64 that is a power of two
+            int width = 16;                           // threads per slot row: the power of two >= nb (1024 slots of 16 bins: 6 us more for the evaluation with 64 threads a row)
+            while (width < nb) width *= 2;            // nb <= THREADS, a power of two
             const int groups = THREADS / width, g = tid / width, i = tid & (width - 1);
             int64_t acc = 0;
             if (i < nb) {
@@ -211,13 +211,15 @@ __global__ __launch_bounds__(THREADS) void eval_reduce_kernel(EvArgs a)
 
 int launch_eval_reduce(const EvArgs &a, int batch, hipStream_t st)
 {
-    // a workgroup reads its matrix's slots alone: 256 threads while they are few (cheaper barriers) or there are more matrices than the
-    // chip takes workgroups of 1024 (1024 matrices of 32 slots of 256 bins: 25 us by 256 threads, 37 by 1024), 1024 up to 64 Ki sums, and
-    // beyond that the slots are summed by G / 64 workgroups per matrix first (128 slots of 1024
-    // bins: 58 us by one workgroup as it was, 5 + 8 in two kernels)
-    if ((int64_t)a.slices * a.G <= 2048 || (batch > 512 && (int64_t)a.slices * a.G <= 16384 && a.M <= 256)) {
+    // A workgroup reads its matrix's slots alone.  256 threads up to 16 Ki sums: cheaper barriers, and 1024 matrices would wait for each other in workgroups
+    // of 1024 (32 slots of 256 bins: one matrix 36 / 39 us for the whole schedule, 1024 matrices 25 / 37 for this kernel).  1024 threads up to 64 Ki sums, or any
+    // number of up to 128 bins, whose slots are read side by side (2048 slots of 64 bins: 35 us for the evaluation, 57 in two kernels; of 128 bins: 52 / 63,
+    // of 144: 68 / 63).  Beyond that the slots are summed by G / 64 workgroups per matrix first (128 slots of 1024 bins: 58 us by one workgroup as it
+    // was, 5 + 8 in two kernels).
+    const int64_t sums = (int64_t)a.slices * a.G;
+    if (sums <= 16384 && a.M <= 256) {
         hipLaunchKernelGGL((eval_reduce_kernel<256, true>), dim3((unsigned)batch), dim3(256), 0, st, a);
-    } else if ((int64_t)a.slices * a.G <= 65536) {
+    } else if (sums <= 65536 || a.G <= 128) {
         hipLaunchKernelGGL((eval_reduce_kernel<1024, true>), dim3((unsigned)batch), dim3(1024), 0, st, a);
     } else {
         hipLaunchKernelGGL(eval_sum_kernel, dim3((unsigned)((a.G + 63) / 64), (unsigned)batch), dim3(256), 0, st, a);
