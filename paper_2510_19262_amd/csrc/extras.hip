@@ -154,8 +154,8 @@ __global__ __launch_bounds__(kPolThreads) void policy_kernel(PolArgs a)
 
 // ------------------------------------------------------------------------------------ port round robin
 // Algorithm 2 step 4.  port[i] = (how many earlier chunks of the same instance went to the same rail) mod P.
-// Instances are cut into tiles of kPortTile chunks that start at multiples of 16 of the record index; (1) tile offsets per
-// instance, (2) per-tile per-rail counts, (3) per instance an exclusive scan of the counts over its tiles, (4) per tile the running
+// Instances are cut into as many tiles as kPortTile chunks each would be; they start at multiples of 16 of the record index, the first up to 15
+// chunks early, and the last takes up to 15 chunks more; (1) tile offsets per instance, (2) per-tile per-rail counts, (3) per instance an exclusive scan of the counts over its tiles, (4) per tile the running
 // counts.  Both tile kernels give a wavefront a tile.
 //   packed (N <= 16, P a power of two up to 128, rail and port 16-byte aligned): a lane takes 16 consecutive chunks per 16-byte load
 //     and keeps the N counts as bytes of one or two 64-bit registers; P <= 128 leaves a byte room for a start below P and 16
@@ -199,15 +199,16 @@ __device__ __forceinline__ void port_widen(const unsigned long long (&c)[NW], un
 template <bool ASSIGN, int NW>
 __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a)
 {
-    constexpr int STEPS = kPortTile / 1024;         // 16-byte loads per lane and tile, all in flight together
+    constexpr int STEPS = kPortTile / 1024 + 1;     // 16-byte loads per lane and tile, all in flight together; the last for the last tile's up to 15 chunks more
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (a.chunk_off[a.n_inst] > a.capacity) return;                 // more chunks than rail and port hold: touch neither
     int64_t n_tiles = a.tile_off[a.n_inst];
     if (n_tiles > a.max_tiles) n_tiles = a.max_tiles;               // workspace sized for fewer chunks: never write past it
     for (int64_t u = (int64_t)blockIdx.x * kPortWaves + wv; u < n_tiles; u += (int64_t)gridDim.x * kPortWaves) {
         const int inst = wave_last_le<int64_t>(a.tile_off, a.n_inst, u);
-        const int64_t lo = a.chunk_off[inst], hi = a.chunk_off[inst + 1];
+        const int64_t lo = a.chunk_off[inst];
         const int64_t beg = port_base(lo) + (u - a.tile_off[inst]) * kPortTile;
+        const int64_t hi = u + 1 == a.tile_off[inst + 1] ? a.chunk_off[inst + 1] : beg + kPortTile;   // this tile's end
         uint4 x[STEPS];
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
@@ -232,9 +233,10 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a
         }
         uint32_t *c = a.cnt + u * a.N;
         if constexpr (!ASSIGN) {
-            unsigned long long ctr[NW] = {};                        // at most 64 per byte
+            unsigned long long ctr[NW] = {};                        // at most 80 per byte
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) {
+                if (beg + s * 1024 >= hi) break;                    // wavefront-uniform: an instance's last tile may be short, a small instance has no other
                 const uint32_t w[4] = {x[s].x, x[s].y, x[s].z, x[s].w};
 #pragma unroll
                 for (int j = 0; j < 16; ++j) {
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a
                 }
             }
             unsigned f[4 * NW];
-            port_widen<NW>(ctr, f);                                 // at most 4096 per field
+            port_widen<NW>(ctr, f);                                 // at most 4111 per field, summed over the lanes
 #pragma unroll
             for (int q = 0; q < 4 * NW; ++q) {
                 unsigned v = f[q];
@@ -264,6 +266,7 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a
             }
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) {
+                if (beg + s * 1024 >= hi) break;
                 const uint32_t w[4] = {x[s].x, x[s].y, x[s].z, x[s].w};
                 unsigned long long ctr[NW] = {};
 #pragma unroll
@@ -330,7 +333,7 @@ __global__ __launch_bounds__(1024) void port_tiles_kernel(PortArgs a)
         int64_t v = 0;
         if (i < a.n_inst) {
             const int64_t lo = a.chunk_off[i], hi = a.chunk_off[i + 1];
-            v = hi > lo ? (hi - port_base(lo) + kPortTile - 1) / kPortTile : 0;
+            v = (hi - lo + kPortTile - 1) / kPortTile;
         }
         sh[tid] = v;
         __syncthreads();
@@ -362,7 +365,7 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_tile_kernel(PortArgs a)
         const int inst = wave_last_le<int64_t>(a.tile_off, a.n_inst, u);
         const int64_t from = port_base(a.chunk_off[inst]) + (u - a.tile_off[inst]) * kPortTile;
         const int64_t beg = from > a.chunk_off[inst] ? from : a.chunk_off[inst];
-        const int64_t end = (from + kPortTile < a.chunk_off[inst + 1]) ? from + kPortTile : a.chunk_off[inst + 1];
+        const int64_t end = u + 1 == a.tile_off[inst + 1] ? a.chunk_off[inst + 1] : from + kPortTile;
         uint32_t *c = a.cnt + u * a.N;
         if (lane < a.N) mine[lane] = ASSIGN ? c[lane] : 0u;
         __builtin_amdgcn_wave_barrier();
@@ -418,8 +421,8 @@ __global__ __launch_bounds__(64) void port_scan_kernel(PortArgs a)
     }
 }
 
-// most tiles an instance list of `capacity` chunks is cut into: a tile starts at a multiple of 16, up to 15 chunks early
-static int64_t port_max_tiles(int64_t capacity, int64_t n_inst) { return capacity / kPortTile + n_inst + n_inst / 256 + 2; }
+// most tiles an instance list of `capacity` chunks is cut into
+static int64_t port_max_tiles(int64_t capacity, int64_t n_inst) { return capacity / kPortTile + n_inst + 1; }
 
 static void port_ws_layout(int64_t n_inst, int64_t max_tiles, int N, size_t off[3])
 {

@@ -209,6 +209,19 @@ def test_port_round_robin_validation():
     assert f(FAKE, FAKE, 0, C.byref(t), 4, 10, FAKE, FAKE, need, None) == 0
 
 
+def test_port_round_robin_workspace_is_one_count_row_per_4096_chunks_and_instance():
+    # what a caller that keeps the size of an earlier query has always had
+    lib = rs.load()
+    up = lambda n: -(-n // 256) * 256
+    for M, N in ((4, 4), (64, 8), (128, 16)):
+        t = _topo(M=M, N=N)
+        for batch in (1, 9, 64):
+            for capacity in (0, 10, 100_000, 50_000_000):
+                inst = batch * M
+                want = up(8 * (inst + 1)) + up(4 * (capacity // 4096 + inst + 1) * N)
+                assert lib.railsched_port_round_robin_workspace_bytes(batch, C.byref(t), capacity) == want
+
+
 def test_binding_rejects_host_tensors():
     import torch
     with pytest.raises(ValueError):

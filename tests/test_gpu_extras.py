@@ -188,6 +188,24 @@ def test_port_round_robin_long_instances():
         assert np.array_equal(port.cpu().numpy()[:n], oracle.port_round_robin(off.cpu().numpy(), rail.cpu().numpy()[:n], B, M, N, P))
 
 
+@pytest.mark.parametrize("N,P,shift", [(8, 8, 0), (8, 1, 0), (4, 128, 0), (16, 4, 0), (13, 2, 0), (8, 3, 0), (17, 8, 0), (8, 8, 1)])
+def test_port_round_robin_at_the_edges_of_tiles(N, P, shift):
+    # instances that start at any place of a 16-chunk group and end within 15 chunks of a tile, empty ones, ones shorter than a group
+    sizes = [0, 1, 15, 16, 17, 3, 4080, 4081, 4095, 4096, 4097, 4111, 4112, 0, 8191, 8193, 12288 + 15, 12288 + 16, 7, 20_000]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n, M = int(off[-1]), len(sizes)
+    rng = np.random.default_rng(N * 100 + P)
+    rail = rng.integers(0, N, size=n).astype(np.uint8)
+    want = oracle.port_round_robin(off, rail, 1, M, N, P)
+    topo = rs.Topo(M, N, 4096)
+    d_rail = torch.empty(n + 32, dtype=torch.uint8, device=DEV)[shift:n + shift]
+    d_rail.copy_(torch.from_numpy(rail))
+    room = torch.full((n + 64,), 255, dtype=torch.uint8, device=DEV)
+    rs.port_round_robin(torch.from_numpy(off).to(DEV), d_rail, 1, topo, P, capacity=n, out=room[16:16 + n])
+    assert np.array_equal(room[16:16 + n].cpu().numpy(), want)
+    assert (room[:16] == 255).all() and (room[16 + n:] == 255).all()
+
+
 @pytest.mark.parametrize("fused", [False, True])
 def test_whole_path_replays_from_a_hip_graph(fused):
     # the library enqueues kernels only (no allocation, no host synchronisation, no memset nodes), so a caller
