@@ -514,7 +514,8 @@ extern "C" int railsched_port_round_robin(const int64_t *chunk_off, const uint8_
     a.rail_bits = a.N > 1 ? ilog2(a.N - 1) + 1 : 0;
     hipLaunchKernelGGL(port_tiles_kernel, dim3(1), dim3(1024), 0, st, a);
     if (int rc = launch_status()) return rc;
-    const bool packed = a.N <= 16 && is_pow2(ports) && ports <= 128 && reinterpret_cast<uintptr_t>(rail) % 16 == 0 &&
+    // a few hundred chunks are all first and last ones of their instances, which the packed kernels take byte by byte (161 chunks: 12 us, 9 by ballot)
+    const bool packed = capacity >= 1024 && a.N <= 16 && is_pow2(ports) && ports <= 128 && reinterpret_cast<uintptr_t>(rail) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(port) % 16 == 0;
     auto tiles = [&](auto by_ballot, auto one, auto two) {
         hipLaunchKernelGGL(packed ? (a.N <= 8 ? one : two) : by_ballot, dim3(kPortBlocks), dim3(64 * kPortWaves), 0, st, a);
