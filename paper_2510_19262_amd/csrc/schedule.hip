@@ -52,6 +52,7 @@ void cs_ws_layout(int64_t n_inst, int64_t NF, size_t off[6]);  // chunk_sort.hip
 
 constexpr int kSlThreads = 256;         // closed-form receive loads of large batches
 constexpr int kSsRun = 24;              // late chunks per run of one weight from which the chain goes run by run (lpt_runs_body)
+constexpr int kSsLateAlone = 128;       // late chunks up to which the chain's wavefront also finishes them, beside the others' records
 constexpr int kSsMaxInst = 1024;        // instances whose counts one workgroup adds up
 constexpr int kSsMaxFlows = 4096;       // N*G of an instance held in LDS
 constexpr int kSsWideFlows = 1024;      // N*G above which an instance's workgroup has 1024 threads instead of 512: 16 flows a thread of the sort at most
@@ -179,6 +180,15 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
         wave_exscan(starts, total_starts);
         if (lane == 0 && total_starts) atomicAdd(&sh_runs, total_starts);
     }
+    // rails of the late chunks to memory, and their bytes to the receive bins
+    auto finish_late = [&](int first, int step) {
+        for (int i = first; i < n_late; i += step) {
+            const unsigned r = late_rail[i];
+            x.rail[out0 + skip + i] = (uint8_t)r;
+            const uint32_t f = i < (int)late_full ? (uint32_t)last_le<uint32_t>(st_fs, a.NF, skip + i) : (uint32_t)sorted[i - late_full];
+            atomicAdd(&bins[ss_dst_node(a, x, f) * N + r], (unsigned long long)late_w[i]);
+        }
+    };
     __syncthreads();
     if (wave == 0) {
         // ---- the serial chain over [late full chunks | sorted tails]; the others write the records
@@ -192,6 +202,7 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
         }
         if (!runs) lpt_wide_body<GW, true>(late_w, late_rail, n_late, base, N, S_row, late_w);
         __builtin_amdgcn_s_setprio(0);
+        if (n_late <= kSsLateAlone) { lds_sync(); finish_late(lane, 64); }
     } else {
         // ---- full chunks: records, rails of the leading run, receive loads of the leading run
         const int t = tid - 64;
@@ -268,14 +279,10 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
         add_leading_run(a, x, st_fs, n_full, skip, bins, t, T);
     }
     __syncthreads();
-    // rails of the late chunks to memory, and their bytes to the receive bins
-    for (int i = tid; i < n_late; i += kSsThreads) {
-        const unsigned r = late_rail[i];
-        x.rail[out0 + skip + i] = (uint8_t)r;
-        const uint32_t f = i < (int)late_full ? (uint32_t)last_le<uint32_t>(st_fs, a.NF, skip + i) : (uint32_t)sorted[i - late_full];
-        atomicAdd(&bins[ss_dst_node(a, x, f) * N + r], (unsigned long long)late_w[i]);
+    if (n_late > kSsLateAlone) {
+        finish_late(tid, kSsThreads);
+        __syncthreads();
     }
-    __syncthreads();
     int64_t *slot = x.partial + (int64_t)inst * (a.G + 1);               // [b][k][G + 1]
     for (int i = tid; i < a.G; i += kSsThreads) slot[i] = (int64_t)bins[i];
     if (tid == 0) slot[a.G] = n_full ? (int64_t)cw : nt ? (int64_t)late_w[0] : 0;   // no full chunk: the first tail is the largest
@@ -335,7 +342,10 @@ static int launch_ss_t(const CsArgs &a, const SsArgs &x, hipStream_t st)
 template <int GW>
 static int launch_ss(const CsArgs &a, const SsArgs &x, hipStream_t st)
 {
-    return a.NF > kSsWideFlows ? launch_ss_t<GW, 1024>(a, x, st) : launch_ss_t<GW, 512>(a, x, st);
+    // more instances than fit the chip together: half the threads each, so that more of them overlap (1024 instances of 64 flows: 30 -> 26 us, of
+    // 1024: 53 -> 41; 384 of 2048: 66 -> 47, 1024 of them: 120 -> 77 by 512 threads and 90 by 256)
+    if (a.NF > kSsWideFlows) return a.n_inst > 256 ? launch_ss_t<GW, 512>(a, x, st) : launch_ss_t<GW, 1024>(a, x, st);
+    return a.n_inst > 512 ? launch_ss_t<GW, 256>(a, x, st) : launch_ss_t<GW, 512>(a, x, st);
 }
 
 }  // namespace rs
