@@ -7,13 +7,14 @@
 // form behind Theorem 4's premise of equal granularity).  So the fill kernel writes those rails with the records,
 // stage 4's streaming scan for the leading runs is skipped (its serial kernels start behind them), and stage 5 gets
 // the leading runs' receive loads flow by flow in closed form and reads only the few chunks behind them - 13 bytes
-// of HBM traffic per chunk in all instead of 27.  Small ones - up to 1024 instances of a few thousand chunks, the
+// of HBM traffic per chunk in all instead of 27.  Small ones - up to 1024 instances of up to 64 K chunks on average, the
 // shape of one training step's MoE layers - are bound by the latency of nine dependent launches, so they take
 // three: the per-instance counts (stage 3's count kernel), then ONE workgroup per instance that does everything
 // the instance needs, then the per-matrix reduction of stage 5.  Inside the workgroup all wavefronts sort the
 // tails; then wavefront 0 runs the serial LPT chain on them - weights and rails in LDS, the chain being what bounds the
 // time - while the other wavefronts write the full-chunk records, the round-robin rails of the leading run (closed
-// form: from empty rails a run of one weight is rail = i mod N) and the receive loads those imply.
+// form: from empty rails a run of one weight is rail = i mod N) and the receive loads those imply.  The average is all
+// the host knows; an instance far longer than it leaves the rest of its full chunks to further workgroups of the launch.
 #include "chunk_core.h"
 #include "eval_core.h"
 #include "lpt_core.h"
@@ -54,15 +55,31 @@ constexpr int kSlThreads = 256;         // closed-form receive loads of large ba
 constexpr int kSsRun = 24;              // late chunks per run of one weight from which the chain goes run by run (lpt_runs_body)
 constexpr int kSsLateAlone = 128;       // late chunks up to which the chain's wavefront also finishes them, beside the others' records
 constexpr int kSsMaxInst = 1024;        // instances whose counts one workgroup adds up
-constexpr int kSsMaxFlows = 4096;       // N*G of an instance held in LDS
+// N*G of an instance held in LDS: 105 KB of a CU's 160 at 4096.  No limit of speed: up to 5760 flows still fit, and 80 nodes of 8 rails, 4.9 M chunks, take
+// 87 us by one workgroup each where the separate kernels take 146.
+constexpr int kSsMaxFlows = 4096;
 constexpr int kSsWideFlows = 1024;      // N*G above which an instance's workgroup has 1024 threads instead of 512: 16 flows a thread of the sort at most
-constexpr int kSsMaxInstWide = 256;     // instances of more than 2048 flows: one workgroup per CU, one round of them
-constexpr int kSsMaxAvg = 65536;        // chunks per instance (capacity / instances) above which one workgroup is too few
+// Instances of more than 2048 flows: one workgroup per CU, one round of them.  512 of 4096 flows and 61 K chunks even / skewed 145 / 241 us, by the separate
+// kernels 209 / 224; 256 78 / 118 and 147 / 160.
+constexpr int kSsMaxInstWide = 256;
+// Full chunks an instance's workgroup writes itself; what a longer one has over is spread over further workgroups (ss_help).  us without / with that and
+// by the separate kernels: 64 nodes x 8 rails, transposed Zipf 1.1, 3.9 M chunks, 751 K of them one instance's 187 / 79 / 134; 32 x 8, 15.1 M, 466 K
+// 146 / 92 / 114; 16 x 8, 0.9 M, 214 K 97 / 36 / 53; even instances of 61 K on 64 x 8 75.6 / 76.9 / 124, of 57 K on 16 x 8 42 / 36 / 53.
+constexpr int64_t kSsOwn = 8192;
+constexpr int64_t kSsOwnWide = 32768;   // where thousands of tails are scheduled meanwhile
+constexpr int64_t kSsOwnBusy = 65536;   // where no CU is idle
+constexpr uint32_t kSsHelpTile = 4096;  // full chunks in a tile of those it leaves over
+// Chunks per instance (capacity / instances) up to which one workgroup an instance, with helpers, is faster than the separate kernels.  us even / skewed,
+// against the separate kernels: 256 instances of 4096 flows and 120 K chunks 156 / 170 against 195 / 205, 248 K 266 / 310 against 255 / 262; 1024 of 2048
+// flows and 59 K 200 / 219 against 269 / 275, 117 K 541 / 540 against 372 / 372; 800 of 512 flows and 53 K 146 / 170 against 160 / 160.
+constexpr int64_t kSsMaxAvg = 131072, kSsMaxAvgBusy = 65536;
 
 struct SsArgs {
     uint8_t *rail;
     int64_t *S;
     int64_t *partial;       // stage 5 workspace: [batch][M][G + 1]
+    int64_t own;            // full chunks from which an instance leaves its records to the helping workgroups
+    int32_t helpers;        // how many of them there are
     int32_t vec_ok;
     int32_t nshift, gmask;  // >= 0 when N / G are powers of two
 };
@@ -103,6 +120,155 @@ __host__ __device__ constexpr int ss_hist_words(int NF) { return tail_hist_words
 template <int T>
 __host__ __device__ constexpr int ss_rem_words(int NF) { return 256 * (T / 64 - 1) > NF ? 256 * (T / 64 - 1) : (NF + 3) / 4 * 4; }
 
+// Records of the full chunks p_lo .. p_hi - 1 of one instance, and the rails of those in the leading run (below `skip`), by the wavefronts 1 .. of
+// a workgroup that has the instance's flow starts in LDS.  marks: 256 words for each of them.
+template <int kSsThreads>
+__device__ __forceinline__ void fill_full(const CsArgs &a, const SsArgs &x, const unsigned *st_fs, const unsigned *st_cs, unsigned *marks, int64_t out0,
+                                          uint32_t skip, uint32_t p_lo, uint32_t p_hi)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int t = (int)threadIdx.x - 64, N = a.N;
+    constexpr int T = kSsThreads - 64;
+    const uint32_t cw = (uint32_t)a.C;
+    if (!x.vec_ok) {
+        for (uint32_t p = p_lo + t; p < p_hi; p += T) {
+            const int j = last_le<uint32_t>(st_fs, a.NF, p);
+            a.chunk_w[out0 + p] = cw;
+            a.chunk_flow[out0 + p] = (uint32_t)j;
+            if (a.perm) a.perm[out0 + p] = st_cs[j] + (p - st_fs[j]);
+            if (p < skip) x.rail[out0 + p] = (uint8_t)(p % (uint32_t)N);
+        }
+        return;
+    }
+    const uint32_t head = (uint32_t)((4 - ((out0 + p_lo) & 3)) & 3);      // scalar positions before the first aligned group
+    const uint32_t pa = p_hi - p_lo < head ? p_hi : p_lo + head;
+    const uint32_t groups = (p_hi - pa) / 4;
+    const uint32_t pb = pa + groups * 4;
+    // A wavefront streams a contiguous share of the groups, 64 at a time: shares and steps end where the global group index is
+    // a multiple of 64, so the 64 lanes store one whole kilobyte on a 1 KiB boundary of each record array.
+    constexpr int kFill = kSsThreads / 64 - 1;
+    const uint32_t G0 = (uint32_t)(((out0 + pa) >> 2) & 63);             // global group index of group 0, mod 64
+    auto share = [&](int w) {
+        if (w <= 0) return 0u;
+        if (w >= kFill) return groups;
+        const uint32_t cut = ((G0 + (uint32_t)((uint64_t)groups * w / kFill)) & ~63u);
+        return cut > G0 ? cut - G0 : 0u;
+    };
+    const uint32_t g0 = share(wave - 1), g1 = share(wave);
+    unsigned *mark = marks + (wave - 1) * 256;
+    int j_lo = g0 < g1 ? last_le<uint32_t>(st_fs, a.NF, pa + 4 * g0) : 0;
+    uint32_t cnt = 0;
+    for (uint32_t gb = g0; gb < g1; gb += cnt) {
+        cnt = 64u - ((G0 + gb) & 63u);
+        cnt = cnt < g1 - gb ? cnt : g1 - gb;
+        const uint32_t p = pa + 4 * (gb + lane);
+        uint32_t fl[4], pm[4], rr = 0;
+        j_lo = window_flows(st_fs, a.NF, j_lo, pa + 4 * gb, pa + 4 * (gb + cnt) - 1, mark, fl);
+        if ((uint32_t)lane >= cnt) continue;
+        uint32_t r = x.nshift >= 0 ? (p & ((1u << x.nshift) - 1u)) : p % (uint32_t)N;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (a.perm) pm[e] = st_cs[fl[e]] - st_fs[fl[e]] + p + e;
+            rr |= r << (8 * e);
+            r = (r + 1 == (uint32_t)N) ? 0u : r + 1;
+        }
+        *reinterpret_cast<uint4 *>(a.chunk_w + out0 + p) = make_uint4(cw, cw, cw, cw);
+        *reinterpret_cast<uint4 *>(a.chunk_flow + out0 + p) = make_uint4(fl[0], fl[1], fl[2], fl[3]);
+        if (a.perm) *reinterpret_cast<uint4 *>(a.perm + out0 + p) = make_uint4(pm[0], pm[1], pm[2], pm[3]);
+        if (p + 4 <= skip) {
+            *reinterpret_cast<uint32_t *>(x.rail + out0 + p) = rr;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) if (p + e < skip) x.rail[out0 + p + e] = (uint8_t)(rr >> (8 * e));
+        }
+    }
+    const uint32_t n_edge = (pa - p_lo) + (p_hi - pb);                    // at most 6 positions outside the aligned groups
+    if ((uint32_t)t < n_edge) {
+        const uint32_t p = (uint32_t)t < pa - p_lo ? p_lo + (uint32_t)t : pb + ((uint32_t)t - (pa - p_lo));
+        const int j = last_le<uint32_t>(st_fs, a.NF, p);
+        a.chunk_w[out0 + p] = cw;
+        a.chunk_flow[out0 + p] = (uint32_t)j;
+        if (a.perm) a.perm[out0 + p] = st_cs[j] + (p - st_fs[j]);
+        if (p < skip) x.rail[out0 + p] = (uint8_t)(p % (uint32_t)N);
+    }
+}
+
+// Full chunks that an instance's own workgroup writes: x.own of them and up to a 1 KiB boundary of the record arrays.
+__device__ __forceinline__ uint32_t ss_own_end(const SsArgs &x, int64_t out0, uint32_t n_full)
+{
+    const int64_t end = ((out0 + x.own + 255) & ~(int64_t)255) - out0;
+    return end < (int64_t)n_full ? (uint32_t)end : n_full;
+}
+
+// The workgroups behind the instances' write what the long instances leave over, in tiles of kSsHelpTile chunks, every one a run of consecutive
+// tiles.  Which instances are long is known here only: the host sees the sum of their chunks at most (capacity), and the counts' kernel has just
+// ended.  They read the counts, 64 instances at a time, and end at once when there is nothing over (or no room for the records).
+template <int kSsThreads>
+__device__ __forceinline__ void ss_help(const CsArgs &a, const SsArgs &x, unsigned *lds)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    unsigned *st_fs = lds, *st_cs = st_fs + a.NF + 1, *marks = lds + (2 * a.NF + 1 + 3) / 4 * 4;
+    // tiles of instance base + lane, its first record and its full chunks; `before` counts the records of the instances before `base`
+    auto tiles_of = [&](int base, int64_t before, int64_t &out0, uint32_t &n_full, unsigned &tiles) {
+        const int i = base + lane;
+        const int64_t c = i < a.n_inst ? a.cnt_all[i] : 0;
+        n_full = i < a.n_inst ? (uint32_t)a.cnt_full[i] : 0u;
+        int64_t inc = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int64_t o = __shfl_up(inc, d);
+            inc += lane >= d ? o : 0;
+        }
+        out0 = before + inc - c;
+        tiles = (n_full - ss_own_end(x, out0, n_full) + kSsHelpTile - 1) / kSsHelpTile;
+        return before + __shfl(inc, 63);            // records up to base + 64
+    };
+    bool over = false;
+#pragma unroll
+    for (int u = 0; u < kSsMaxInst / kSsThreads; ++u) {                  // all loads in flight together: mostly this is all there is to do
+        const int i = u * kSsThreads + tid;
+        over |= i < a.n_inst && a.cnt_full[i] > x.own;
+    }
+    if (!__syncthreads_or(over)) return;
+    int64_t out0, records = 0;
+    uint32_t n_full;
+    unsigned tiles, all = 0, sum;
+    for (int base = 0; base < a.n_inst; base += 64) {
+        records = tiles_of(base, records, out0, n_full, tiles);
+        wave_exscan(tiles, sum);
+        all += sum;
+    }
+    if (all == 0 || records > a.capacity) return;
+    const unsigned h = blockIdx.x - (unsigned)a.n_inst, H = gridDim.x - (unsigned)a.n_inst;
+    unsigned u = (unsigned)((uint64_t)all * h / H);
+    const unsigned u1 = (unsigned)((uint64_t)all * (h + 1) / H);
+    unsigned seen = 0;                              // tiles before `base`
+    records = 0;
+    for (int base = 0; base < a.n_inst && u < u1; base += 64) {          // the same in all wavefronts
+        records = tiles_of(base, records, out0, n_full, tiles);
+        const unsigned first = seen + wave_exscan(tiles, sum);           // first tile of this lane's instance
+        seen += sum;
+        while (u < u1 && u < seen) {
+            const int l = 63 - __clzll((long long)__ballot(tiles != 0 && first <= u));
+            const int inst = base + l;
+            const int64_t o = __shfl(out0, l);
+            const uint32_t nf = (uint32_t)__shfl((int)n_full, l);
+            const unsigned t0 = (unsigned)__shfl((int)first, l), tn = (unsigned)__shfl((int)tiles, l);
+            const unsigned to = t0 + tn < u1 ? t0 + tn : u1;             // this workgroup's tiles of the instance: u .. to - 1
+            __syncthreads();                                             // the instance before is done with the starts
+            const uint32_t *fs = a.full_start + (int64_t)inst * a.NF, *cs = a.canon_start + (int64_t)inst * a.NF;
+            for (int i = tid; i < a.NF; i += kSsThreads) { st_fs[i] = fs[i]; st_cs[i] = cs[i]; }
+            if (tid == 0) st_fs[a.NF] = 0xFFFFFFFFu;
+            __syncthreads();
+            const uint32_t own = ss_own_end(x, o, nf);
+            const uint32_t p_lo = own + (u - t0) * kSsHelpTile;
+            const uint32_t left = nf - p_lo, run = (to - u) * kSsHelpTile;
+            if (tid >= 64) fill_full<kSsThreads>(a, x, st_fs, st_cs, marks, o, nf - nf % (uint32_t)a.N, p_lo, p_lo + (left < run ? left : run));
+            u = to;
+        }
+    }
+}
+
 template <int GW, int kSsThreads>
 __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArgs x)
 {
@@ -121,6 +287,10 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
     unsigned short *idx_b = idx_a + a.NF;
     uint8_t *late_rail = reinterpret_cast<uint8_t *>(idx_b + a.NF);
 
+    if ((int)blockIdx.x >= a.n_inst) {
+        ss_help<kSsThreads>(a, x, hist);
+        return;
+    }
     const int inst = blockIdx.x;
     const int b = inst / a.M, k = inst % a.M;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -215,67 +385,7 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
             // the tail is its flow's last chunk: one before the canonical start of the next flow
             if (a.perm) a.perm[tail0 + i] = (f + 1 < a.NF ? st_cs[f + 1] : n_all) - 1u;
         }
-        if (x.vec_ok) {
-            const uint32_t head = (uint32_t)((4 - (out0 & 3)) & 3);      // scalar positions before the first aligned group
-            const uint32_t pa = n_full < head ? n_full : head;
-            const uint32_t groups = (n_full - pa) / 4;
-            const uint32_t pb = pa + groups * 4;
-            // A wavefront streams a contiguous share of the groups, 64 at a time: shares and steps end where the global group index is
-            // a multiple of 64, so the 64 lanes store one whole kilobyte on a 1 KiB boundary of each record array.
-            constexpr int kFill = kSsThreads / 64 - 1;
-            const uint32_t G0 = (uint32_t)(((out0 + pa) >> 2) & 63);      // global group index of group 0, mod 64
-            auto share = [&](int w) {
-                if (w <= 0) return 0u;
-                if (w >= kFill) return groups;
-                const uint32_t cut = ((G0 + (uint32_t)((uint64_t)groups * w / kFill)) & ~63u);
-                return cut > G0 ? cut - G0 : 0u;
-            };
-            const uint32_t g0 = share(wave - 1), g1 = share(wave);
-            unsigned *mark = rem + (wave - 1) * 256;                      // the tails' bytes are in late_w by now
-            int j_lo = g0 < g1 ? last_le<uint32_t>(st_fs, a.NF, pa + 4 * g0) : 0;
-            uint32_t cnt = 0;
-            for (uint32_t gb = g0; gb < g1; gb += cnt) {
-                cnt = 64u - ((G0 + gb) & 63u);
-                cnt = cnt < g1 - gb ? cnt : g1 - gb;
-                const uint32_t p = pa + 4 * (gb + lane);
-                uint32_t fl[4], pm[4], rr = 0;
-                j_lo = window_flows(st_fs, a.NF, j_lo, pa + 4 * gb, pa + 4 * (gb + cnt) - 1, mark, fl);
-                if ((uint32_t)lane >= cnt) continue;
-                uint32_t r = x.nshift >= 0 ? (p & ((1u << x.nshift) - 1u)) : p % (uint32_t)N;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (a.perm) pm[e] = st_cs[fl[e]] - st_fs[fl[e]] + p + e;
-                    rr |= r << (8 * e);
-                    r = (r + 1 == (uint32_t)N) ? 0u : r + 1;
-                }
-                *reinterpret_cast<uint4 *>(a.chunk_w + out0 + p) = make_uint4(cw, cw, cw, cw);
-                *reinterpret_cast<uint4 *>(a.chunk_flow + out0 + p) = make_uint4(fl[0], fl[1], fl[2], fl[3]);
-                if (a.perm) *reinterpret_cast<uint4 *>(a.perm + out0 + p) = make_uint4(pm[0], pm[1], pm[2], pm[3]);
-                if (p + 4 <= skip) {
-                    *reinterpret_cast<uint32_t *>(x.rail + out0 + p) = rr;
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) if (p + e < skip) x.rail[out0 + p + e] = (uint8_t)(rr >> (8 * e));
-                }
-            }
-            const uint32_t n_edge = pa + (n_full - pb);                  // at most 6 positions outside the aligned groups
-            if ((uint32_t)t < n_edge) {
-                const uint32_t p = (uint32_t)t < pa ? (uint32_t)t : pb + ((uint32_t)t - pa);
-                const int j = last_le<uint32_t>(st_fs, a.NF, p);
-                a.chunk_w[out0 + p] = cw;
-                a.chunk_flow[out0 + p] = (uint32_t)j;
-                if (a.perm) a.perm[out0 + p] = st_cs[j] + (p - st_fs[j]);
-                if (p < skip) x.rail[out0 + p] = (uint8_t)(p % (uint32_t)N);
-            }
-        } else {
-            for (uint32_t p = t; p < n_full; p += T) {
-                const int j = last_le<uint32_t>(st_fs, a.NF, p);
-                a.chunk_w[out0 + p] = cw;
-                a.chunk_flow[out0 + p] = (uint32_t)j;
-                if (a.perm) a.perm[out0 + p] = st_cs[j] + (p - st_fs[j]);
-                if (p < skip) x.rail[out0 + p] = (uint8_t)(p % (uint32_t)N);
-            }
-        }
+        fill_full<kSsThreads>(a, x, st_fs, st_cs, rem, out0, skip, 0u, ss_own_end(x, out0, n_full));
         add_leading_run(a, x, st_fs, n_full, skip, bins, t, T);
     }
     __syncthreads();
@@ -335,7 +445,7 @@ static int launch_ss_t(const CsArgs &a, const SsArgs &x, hipStream_t st)
                                 (int)lds) != hipSuccess)
             return RAILSCHED_ERR_HIP;
     }
-    hipLaunchKernelGGL((ss_instance_kernel<GW, T>), dim3((unsigned)a.n_inst), dim3(T), lds, st, a, x);
+    hipLaunchKernelGGL((ss_instance_kernel<GW, T>), dim3((unsigned)(a.n_inst + x.helpers)), dim3(T), lds, st, a, x);
     return launch_status();
 }
 
@@ -382,11 +492,11 @@ static int schedule_run(const int64_t *D1, int32_t batch, const railsched_topo_t
     const int GW = N <= 4 ? 4 : N <= 8 ? 8 : N <= 16 ? 16 : N <= 32 ? 32 : 64;
     const unsigned w_limit = GW == 4 ? WideLimit<4>::value : GW == 8 ? WideLimit<8>::value : GW == 16 ? WideLimit<16>::value
                            : GW == 32 ? WideLimit<32>::value : WideLimit<64>::value;
-    const bool small = n_inst <= (NF <= 2048 ? kSsMaxInst : kSsMaxInstWide) && NF <= kSsMaxFlows && capacity <= n_inst * (int64_t)kSsMaxAvg &&
+    const bool small = n_inst <= (NF <= 2048 ? kSsMaxInst : kSsMaxInstWide) && NF <= kSsMaxFlows && capacity <= n_inst * (n_inst <= 256 ? kSsMaxAvg : kSsMaxAvgBusy) &&
                        (uint64_t)h_topo->chunk_bytes <= (uint64_t)w_limit;
     SsArgs x;
     x.rail = rail; x.S = S; x.partial = reinterpret_cast<int64_t *>(w8 + ws_sort);
-    x.vec_ok = 0;
+    x.vec_ok = 0; x.own = 0; x.helpers = 0;
     x.nshift = is_pow2(N) ? ilog2(N) : -1;
     x.gmask = is_pow2(G) ? (int32_t)G - 1 : -1;
     EvArgs e;
@@ -434,6 +544,15 @@ static int schedule_run(const int64_t *D1, int32_t batch, const railsched_topo_t
 
     x.vec_ok = (reinterpret_cast<uintptr_t>(chunk_w) % 16 == 0 && reinterpret_cast<uintptr_t>(chunk_flow) % 16 == 0 &&
                 reinterpret_cast<uintptr_t>(perm) % 16 == 0 && reinterpret_cast<uintptr_t>(rail) % 4 == 0) ? 1 : 0;
+    // One instance may hold as many chunks as there are records.  Up to 256 instances, or 128 of more than kSsWideFlows flows, which take a CU each, leave
+    // CUs idle, and sharing starts early; beyond that an instance of the mean length writes all its records itself (960 instances of 29 K chunks: 101 us,
+    // 129 when they shared theirs) and helpers come last.  64 / 256 of them, 1024 instances of 2048 flows, 59 K chunks each: even 201 / 200, skewed 304 / 219;
+    // 960 of 1024 flows 174 / 173 and 290 / 193.  Of the wide instances the helpers would wait for a CU as long as the rest: only what one round holds, or 64.
+    const bool wide = NF > kSsWideFlows, idle = n_inst <= (wide ? 128 : 256);
+    x.own = !idle ? kSsOwnBusy : wide ? kSsOwnWide : kSsOwn;
+    const int64_t room = !wide || idle ? 256 : n_inst <= 192 ? 256 - n_inst : 64;
+    const int64_t over = (capacity - x.own + kSsHelpTile - 1) / kSsHelpTile;
+    x.helpers = (int32_t)(over <= 0 ? 0 : over < room ? over : room);
     int rc = GW == 4 ? launch_ss<4>(a, x, st) : GW == 8 ? launch_ss<8>(a, x, st) : GW == 16 ? launch_ss<16>(a, x, st)
            : GW == 32 ? launch_ss<32>(a, x, st) : launch_ss<64>(a, x, st);
     if (rc) return rc;

@@ -68,3 +68,45 @@ def test_instances(M, N, B, C, kind):
         out = rs.schedule(D1, topo, n - 1)
         assert (out[5].cpu().numpy() == -1).all() and (out[6].cpu().numpy() == -1).all() and (out[7].cpu().numpy() == -1).all()
         assert np.array_equal(out[0].cpu().numpy(), off)
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("M,N,full", [(4, 4, [32768, 1, 0, 5]),                      # as many as a workgroup writes itself
+                                      (4, 4, [33023, 32769, 33025, 40000]),          # around the boundary of the record arrays behind them
+                                      (2, 5, [36864 + 32768, 50_001]),               # one tile and a ragged one, 5 rails
+                                      (16, 16, [100_000] + [3] * 14 + [36_900]),     # 4096 flows
+                                      (70, 2, [70] * 35 + [300_000] + [70] * 33 + [33_100])])   # the long ones among more than 64 instances
+def test_long_instances_share_their_records(M, N, full, shift):
+    # instances longer than the mean: further workgroups write part of their records
+    G, C, B = M * N, 4096, 2
+    rng = np.random.default_rng(M + N)
+    D1n = rng.integers(0, C, size=(B, G, G)) * (rng.random((B, G, G)) < 0.5)          # tails
+    for b in range(B):
+        for k in range(M):                                                             # full chunks of node k over its flows to other nodes
+            cols = np.r_[0:k * N, k * N + N:G]
+            share = rng.multinomial(full[(k + b) % M], np.full(N * cols.size, 1.0 / (N * cols.size)))
+            share[rng.random(share.size) < 0.3] = 0
+            share[0] += full[(k + b) % M] - share.sum()
+            D1n[b, k * N:k * N + N, cols] += (share.reshape(N, cols.size) * C).T
+    D1n = D1n.astype(np.int64)
+    topo = rs.Topo(M, N, C)
+    off, w, flow, perm = oracle.chunk_sort_batch(D1n, M, N, C)
+    rail, S = oracle.lpt_batch(off, w, B, M, N)
+    _, R, stats = oracle.eval_batch(off, w, flow, rail, B, M, N)
+    n = int(off[-1])
+    D1 = torch.from_numpy(D1n).to(DEV)
+    arrays = [torch.full((n + 8,), 77, dtype=dt, device=DEV) for dt in (torch.int32, torch.int32, torch.int32, torch.uint8)]
+    lead = 4 - shift                                                                   # 1: off the 16-byte boundary, scalar stores
+    gw, gf, gp, gr = (t[lead:lead + n] for t in arrays)
+    out = (torch.empty(B * M + 1, dtype=torch.int64, device=DEV), gw, gf, gp, gr, torch.empty((B, M, N), dtype=torch.int64, device=DEV),
+           torch.empty((B, M, N), dtype=torch.int64, device=DEV), torch.empty((B, 8), dtype=torch.int64, device=DEV))
+    rs.schedule(D1, topo, n, out=out)
+    u32 = lambda t: t.cpu().numpy().view(np.uint32)
+    for name, got, want in (("off", out[0].cpu().numpy(), off), ("w", u32(gw), w), ("flow", u32(gf), flow), ("perm", u32(gp), perm),
+                            ("rail", gr.cpu().numpy(), rail), ("S", out[5].cpu().numpy(), S), ("R", out[6].cpu().numpy(), R),
+                            ("stats", out[7].cpu().numpy(), stats)):
+        assert np.array_equal(got, want), name
+    for t in arrays:
+        assert (t[:lead] == 77).all() and (t[lead + n:] == 77).all()
+    short = rs.schedule(D1, topo, n - 1)                                               # too little room: nobody writes records
+    assert (short[5].cpu().numpy() == -1).all()
