@@ -1,5 +1,6 @@
 #!/usr/bin/env python3
-"""Benchmark of the rail-spraying path on one MI355X.  Prints ONE JSON line.
+"""Benchmark of the rail-spraying path on one MI355X.  Prints ONE JSON line: the headline and one short entry per larger workload
+(headline()).  The whole record, described below, goes to the file named by --details.
 
 Headline (metric, value, ms_per_step): the Mixtral-8x7B-shaped workload c2 - 8 nodes x 8 rails, 8 experts
 top-2, 16384 tokens per GPU, 8 KiB tokens, 256 KiB chunks, 32 layers = 32 traffic matrices of 64x64 - with its
@@ -8,13 +9,13 @@ top-2, 16384 tokens per GPU, 8 KiB tokens, 256 KiB chunks, 32 layers = 32 traffi
 (stages 1-2 in one pass over the logits) and railsched_schedule (stages 3-5).  Both write the same bytes as
 the five separate calls - asserted here on every output array; the five calls are timed too ("staged").
 
-Beside it, under "workloads", one record for each larger workload, each with the rooflines of its calls, the
+In the whole record beside it, under "workloads", one record for each larger workload, each with the rooflines of its calls, the
 per-chunk LPT kernel against the VALU issue rate, and the CPU oracle timed in the same run on a stated sample:
   c3  sparse synthetic flows, 32 x 8, 1024 matrices of 256x256 resident (3.9e9 chunks, 32 768 instances): stages 3-5
   c4  DeepSeek-V3-shaped, 64 x 8, 256 experts top-8, 61 layers of 4 194 304 rows: whole path, one layer's 4 GiB of
       logits resident at a time (regenerated between layers, untimed)
   c5  stress, 128 x 8, all 256 matrices of 1024x1024, one matrix (3.9e9 chunks) resident at a time: stages 3-5
---config c1|c2|c3|c4|c5 runs that workload alone (its record is the whole line); used for the profiles.
+--config c1|c2|c3|c4|c5 runs that workload alone and prints its whole record as the line; used for the profiles.
 Stage times are medians over the repetitions (hipEvents on the stream the calls are enqueued on).
 """
 import argparse
@@ -50,6 +51,8 @@ def parse():
                          "average duration is that of the timed region)")
     ap.add_argument("--copy-probe", action="store_true",
                     help="also run one 1 GiB device copy first: a kernel of known traffic to scale profiler byte counters by")
+    ap.add_argument("--details", default=os.path.join(ROOT, "bench_details.json"),
+                    help="--config all: the file the whole record is written to (empty: none)")
     return ap.parse_args()
 
 
@@ -931,6 +934,35 @@ def _name_the_cpu(rec, model):
                 _name_the_cpu(v, model)
 
 
+HEADLINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype",
+                 "data", "config")
+HEADLINE_BYTES = 1600                       # whoever keeps only the last 2000 characters of the output still has the line whole
+
+
+def headline(out, details):
+    """The printed line: the fixed keys as they are, of everything else one number each (six digits), the rest in `details`."""
+    def num(v):
+        return float(f"{v:.6g}") if isinstance(v, float) else v
+
+    def short(rec):
+        if "error" in rec:
+            return {"error": rec["error"][:60]}
+        roof, cpu, lb = (rec.get(k) or {} for k in ("roofline", "cpu_baseline", "makespan_over_lower_bound"))
+        d = {"frac_of_hbm_peak": num(roof.get("frac")), "makespan_over_lb_max": num(lb.get("max")), "matches_cpu_oracle": cpu.get("matches_gpu"),
+             "gpu_over_cpu": num(cpu.get("gpu_over_cpu"))}
+        return {k: v for k, v in d.items() if v is not None}
+
+    line = {k: out[k] for k in HEADLINE_KEYS}
+    line["value"], line["ms_per_step"] = num(line["value"]), num(line["ms_per_step"])
+    line["roofline"] = {k: num(out["roofline"][k]) for k in ("bound", "achieved", "peak", "unit", "frac", "traffic") if k in out["roofline"]}
+    line.update(short(out))
+    line["cpu_cores"] = (out.get("cpu_baseline") or {}).get("cores")
+    line["workloads"] = {n: {**({"chunks_per_s": num(r["value"]), "ms": num(r["ms_per_step"])} if "value" in r else {}), **short(r)}
+                         for n, r in out["workloads"].items()}
+    line["details"] = os.path.basename(details) if details else None
+    return line
+
+
 def main():
     args = parse()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
@@ -968,7 +1000,14 @@ def main():
         out["workloads"][name] = rec
         print(f"bench: {name} done in {rec['wall_s']:.1f} s", file=sys.stderr, flush=True)
     _name_the_cpu(out, _cpu_model())
-    print(json.dumps(out))
+    if args.details:
+        try:
+            with open(args.details, "w") as f:
+                json.dump(out, f, indent=1)
+        except OSError as exc:                          # the line below does not need the file
+            print(f"bench: {args.details} not written: {exc}", file=sys.stderr, flush=True)
+            args.details = ""
+    print(json.dumps(headline(out, args.details)), flush=True)
 
 
 if __name__ == "__main__":
