@@ -219,8 +219,9 @@ int railsched_eval(const int64_t *chunk_off, const uint32_t *chunk_w, const uint
  * arguments, bit for bit, with less work: stage 3 knows that every instance starts with a run of full chunks,
  * whose allocation from empty rails is round robin, so their rails are written with the records, stage 4 only
  * runs behind them and stage 5 takes their receive loads in closed form.  Batches of at most 1024 instances
- * with N*G <= 2048 flows (256 with N*G <= 4096) and capacity <= 65536 chunks per instance are served by one workgroup per
- * instance (two launches after the counts instead of six).
+ * with N*G <= 2048 flows (256 with N*G <= 4096) and capacity <= 65536 chunks per instance (131072 for at most 256
+ * instances) are served by one workgroup per instance (two launches after the counts instead of six), which leaves the
+ * full chunks of instances far longer than the rest to further workgroups of its launch.
  *   D1 [batch][G][G] int64 (in);  chunk_off [batch*M+1];  chunk_w, chunk_flow, perm (perm may be NULL),
  *   rail: `capacity` records each;  S, R [batch][M][N] int64;  stats [batch][8] int64   (out)
  *   ws: railsched_schedule_workspace_bytes(batch, topo) bytes, 256-byte aligned.

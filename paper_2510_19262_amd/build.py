@@ -19,8 +19,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 
 
-# Sources that order floats with v_min/v_max/v_med3 on bit patterns they built themselves: the inputs are finite by
-# contract, and without this the compiler quiets a possible signalling NaN in front of every min and max.
+# Sources that take maxima of logits, which are finite by contract (or the -inf of a place without one): without this the
+# compiler quiets a possible signalling NaN in front of every maximum and keeps compare-and-select pairs as they stand.
 EXTRA_FLAGS = {"route_topk.hip": ["-fno-honor-nans"], "route_traffic.hip": ["-fno-honor-nans"]}
 
 

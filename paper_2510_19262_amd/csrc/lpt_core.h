@@ -262,7 +262,7 @@ __device__ __forceinline__ void lpt_wide_body_sorted(const uint32_t *__restrict_
     const int place_of_chunk = lane % N;                                        // list place that takes chunk `lane` of a closed period
     const int after_closed = (ROW ? (lane & ~15) : 0) | (int)((r + extra) % (unsigned)N);   // lane whose entry moves here when the list rotates by `extra`
 
-    // Weights move in requests of kWideDepth periods, as in the rail-indexed form above.
+    // Weights move in requests of kWideDepth periods: one request is in flight while the chain works on the one before.
     auto weight_at = [&](int64_t i) { const uint32_t *src = (i < len) ? wsrc + i : spare; return *src; };
     unsigned cur[kWideDepth], nxt[kWideDepth], held[kWideDepth];
     auto store_rails = [&](int64_t i0) {
@@ -352,8 +352,9 @@ __device__ __forceinline__ void lpt_wide_body_sorted(const uint32_t *__restrict_
 // The same function for `n` chunks in LDS that are mostly runs of one weight (N <= 16; no weight above WideLimit; the 64 words behind the
 // last weight are readable).  The chain goes from run to run: with all loads within one weight of each other the rest of the
 // run, up to 64 chunks, is closed form (see closed_period: the list is visited front to back, round after round, and then
-// rotated by the run's length mod N); 16 ordinary steps when they are further apart or the run is shorter than that.  After N steps of
-// one weight from loads a little over it apart - what the heavier run before leaves - they are within it.
+// rotated by the run's length mod N).  Loads further apart first get as many ordinary steps as there are rails that stay at or below the
+// fullest with one more chunk, at most N - 1, which brings them within one weight; a run shorter than 16 gets 16 ordinary steps.  Steps come
+// in blocks of 16, those not wanted with weight 0.
 // An iteration is about 700 cycles where a step of the plain chain is 33, so runs have to hold about 24 chunks on average: decode layer
 // of 512 GPUs, 966 tails of 9 values: 33 iterations, the instance kernel 29 -> 24 us; 867 tails of 16 values: 28 -> 21.
 template <int GW>
