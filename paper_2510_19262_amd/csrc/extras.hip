@@ -257,6 +257,10 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a
                 if (lane == 2 * q + 1 && lane < a.N) c[lane] = v >> 16;
             }
         } else {
+            // A 64-bit shift by the last register a wavefront has goes wrong when others share its SIMD: 88 registers, amount in v87, and one chunk of
+            // sixteen got a wrong port in one tile of twenty.  Taking v95 makes 96 of them, still five wavefronts a SIMD; the shifts below stay under it
+            // (by 32-bit halves instead, without such shifts: 850 us for three stages and ports of 120 M chunks, 820 so).
+            asm volatile("; v95 is not used" ::: "v95");
             const unsigned pm = (unsigned)a.P - 1u, pm2 = pm | (pm << 16);
             unsigned start[4 * NW];                                 // counts before the step modulo P, 16-bit fields
 #pragma unroll

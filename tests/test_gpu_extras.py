@@ -206,6 +206,26 @@ def test_port_round_robin_at_the_edges_of_tiles(N, P, shift):
     assert (room[:16] == 255).all() and (room[16 + n:] == 255).all()
 
 
+@pytest.mark.parametrize("N,P", [(8, 8), (16, 128), (8, 3)])
+def test_port_round_robin_with_the_chip_full(N, P):
+    # thousands of tiles: every SIMD holds several wavefronts, each with neighbours' registers behind its own last one
+    M, B = 8, 8
+    gen = torch.Generator(device=DEV).manual_seed(N + P)
+    sizes = torch.randint(350_000, 450_000, (M * B,), generator=torch.Generator().manual_seed(N))
+    off = torch.cat([torch.zeros(1, dtype=torch.int64), sizes.cumsum(0)])
+    n = int(off[-1])
+    rail = torch.empty(n, dtype=torch.uint8, device=DEV)
+    want = torch.empty_like(rail)
+    for i, (lo, hi) in enumerate(zip(off[:-1].tolist(), off[1:].tolist())):
+        r = torch.randint(0, N, (hi - lo,), generator=gen, device=DEV)
+        r[: hi - lo - 4000] = torch.arange(hi - lo - 4000, device=DEV) % N        # as a schedule: one after the other, then in no order
+        before = torch.nn.functional.one_hot(r, N).to(torch.int32).cumsum(0).gather(1, r[:, None])[:, 0] - 1
+        rail[lo:hi], want[lo:hi] = r.to(torch.uint8), (before % P).to(torch.uint8)
+    d_off, topo = off.to(DEV), rs.Topo(M, N, 4096)
+    for _ in range(3):
+        assert torch.equal(rs.port_round_robin(d_off, rail, B, topo, P, capacity=n), want)
+
+
 @pytest.mark.parametrize("fused", [False, True])
 def test_whole_path_replays_from_a_hip_graph(fused):
     # the library enqueues kernels only (no allocation, no host synchronisation, no memset nodes), so a caller
