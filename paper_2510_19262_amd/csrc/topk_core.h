@@ -296,7 +296,8 @@ __device__ __forceinline__ bool row_best(const int (&own)[L], unsigned bits, int
 }
 
 // expert indices of the row's k winners to topk_idx[row][0..k); streaming stores (4 194 304 rows of 64 logits, top-6: 0.209 ms, plain 0.227),
-// but not of single indices, a sixteenth of a line per row and more (262 144 x 256 top-1: 46 us streaming, 43 plain)
+// but not of single indices, a sixteenth of a line per row and more (262 144 x 256 top-1: 46 us streaming, 43 plain).  Those have a branch of
+// their own: two stores to one address under one condition become one store, and a plain one
 template <int LANES, unsigned MASK, int KM>
 __device__ __forceinline__ void store_best(int32_t *__restrict__ topk_idx, int64_t row, int k, int q, bool live, int wide_store,
                                            const unsigned (&u)[KM])
@@ -310,17 +311,15 @@ __device__ __forceinline__ void store_best(int32_t *__restrict__ topk_idx, int64
             __builtin_nontemporal_store(lo, dst);
             __builtin_nontemporal_store(hi, dst + 1);
         }
+    } else if (k == 1) {
+        if (live && q == 0) topk_idx[row] = (int)key_index<MASK>(u[0]);
     } else {
 #pragma unroll
         for (int r = 0; r < (KM + LANES - 1) / LANES; ++r) {         // winners q, q+LANES, ... of this lane
             unsigned sel = 0;
 #pragma unroll
             for (int j = r * LANES; j < KM && j < (r + 1) * LANES; ++j) sel = (j == q + r * LANES) ? u[j] : sel;
-            if (live && q + r * LANES < k) {
-                int32_t *dst = topk_idx + row * k + q + r * LANES;
-                if (k == 1) *dst = (int)key_index<MASK>(sel);
-                else __builtin_nontemporal_store((int)key_index<MASK>(sel), dst);
-            }
+            if (live && q + r * LANES < k) __builtin_nontemporal_store((int)key_index<MASK>(sel), topk_idx + row * k + q + r * LANES);
         }
     }
 }
