@@ -211,13 +211,14 @@ __global__ __launch_bounds__(THREADS) void eval_reduce_kernel(EvArgs a)
 
 int launch_eval_reduce(const EvArgs &a, int batch, hipStream_t st)
 {
-    // A workgroup reads its matrix's slots alone.  256 threads up to 16 Ki sums: cheaper barriers, and 1024 matrices would wait for each other in workgroups
-    // of 1024 (32 slots of 256 bins: one matrix 36 / 39 us for the whole schedule, 1024 matrices 25 / 37 for this kernel).  1024 threads up to 64 Ki sums, or any
+    // A workgroup reads its matrix's slots alone.  256 threads up to 16 Ki sums, or 9 Ki of more bins than that: cheaper barriers, and 1024 matrices would
+    // wait for each other in workgroups of 1024 (us by 256 / 1024, 32 slots of 256 bins: one matrix 36.1 / 38.6 for the whole schedule, 1024 matrices 25 / 37
+    // for this kernel; 64 of 256 30.8 / 32.6, 33 of 264 38.9 / 40.0, 9 of 288 152 / 154; but 47 of 282 47.5 / 47.0, 44 of 352 47.2 / 46.8).  1024 threads up to 64 Ki sums, or any
     // number of up to 128 bins, whose slots are read side by side (2048 slots of 64 bins: 35 us for the evaluation, 57 in two kernels; of 128 bins: 52 / 63,
     // of 144: 68 / 63).  Beyond that the slots are summed by G / 64 workgroups per matrix first (128 slots of 1024 bins: 58 us by one workgroup as it
     // was, 5 + 8 in two kernels).
     const int64_t sums = (int64_t)a.slices * a.G;
-    if (sums <= 16384 && a.M <= 256) {
+    if (sums <= (a.G <= 256 ? 16384 : 9216) && a.M <= 256) {
         hipLaunchKernelGGL((eval_reduce_kernel<256, true>), dim3((unsigned)batch), dim3(256), 0, st, a);
     } else if (sums <= 65536 || a.G <= 128) {
         hipLaunchKernelGGL((eval_reduce_kernel<1024, true>), dim3((unsigned)batch), dim3(1024), 0, st, a);
