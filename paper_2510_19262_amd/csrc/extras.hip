@@ -159,8 +159,8 @@ __global__ __launch_bounds__(kPolThreads) void policy_kernel(PolArgs a)
 // counts.  Both tile kernels give a wavefront a tile.
 //   packed (N <= 16, P a power of two up to 128, rail and port 16-byte aligned): a lane takes 16 consecutive chunks per 16-byte load
 //     and keeps the N counts as bytes of one or two 64-bit registers; P <= 128 leaves a byte room for a start below P and 16
-//     increments, and all sums modulo P come out right in wider fields.  120 M chunks, N = 8, P = 8: 41 us for the
-//     counts and 67 for the ports
+//     increments, and all sums modulo P come out right in wider fields.  120 M chunks, N = 8, P = 8: 40 us for the
+//     counts and 68 for the ports
 //   by ballot (everything else): 64 chunks at a time, lanes with the same rail find each other by ballot matching, rank = running
 //     count + number of lower lanes with that rail: 130 us for the counts and 200 for the ports of the same chunks.
 constexpr int kPortTile = 4096;

@@ -13,9 +13,9 @@
 // insertion kernel of stage 1 with the same addition - once the lanes of a row hold its winners, lane j looks up
 // the destination of winner j and bumps its bin.  A workgroup walks a few hundred consecutive tokens of one pair
 // so that its G counts are a small share of the logits it read.  When the indices are wanted the two stages run
-// back to back instead: measured on 4 194 304 rows of 256 logits, top-8, the one-pass kernel takes 0.72 ms without
-// and 0.80 ms with the index stores (its workgroups live eight times longer than stage 1's, which ends the launch
-// on a longer tail), the two separate kernels 0.70 + 0.03 ms.  Other shapes always run the two stages.
+// back to back instead: 4 194 304 rows of 256 logits, top-8, take 0.70 ms in one pass without and 0.71 in two kernels with the
+// indices, and the index stores cost the one-pass kernel 0.08 ms more (its workgroups live eight times longer than stage 1's,
+// which ends the launch on a longer tail).  Other shapes always run the two stages.
 //
 // Short-lived workgroups of one or a few rounds of 512 tokens stream best, so a pair's tokens are cut
 // into many slices; each slice leaves its G counts in the workspace with plain stores and a second,
