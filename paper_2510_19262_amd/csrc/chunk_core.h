@@ -113,8 +113,10 @@ constexpr int kTailShared = 64 + 2 + 16;
 // Tails whose places are counted (one pass over the others in LDS, no histogram) instead of sorted for: what a wavefront by itself counts in one
 // round, or a quarter of a thousand for several.  Flows up to which even the empty ones are counted along, without gathering the tails first.
 // One wavefront each, 3840 instances of 256 tails of 16 differing bits: 56 us counted, 16 sorted.
+// Workgroups, whole schedule, us along / gathered first: 4 instances of 64 flows 13.9 / 14.4, 80 of 64 16.8 / 17.6; 20 of 128, all tails 17.1 / 16.7, a third of them
+// 16.9 / 14.9; 600 of 256, a third 25.3 / 19.7.
 template <int T> constexpr int rank_tails() { return T == 64 ? 64 : 256; }
-template <int T> constexpr int rank_flows() { return T == 64 ? 96 : 256; }
+template <int T> constexpr int rank_flows() { return T == 64 ? 96 : 64; }
 
 // Tails (B mod C > 0) of the flows of one instance, sorted by weight descending, ties in canonical (flow) order:
 // stable LSD radix sort by one workgroup of T threads in LDS, 8-bit digits over the span of key bits that differ at all.

@@ -200,6 +200,11 @@ __device__ __forceinline__ uint32_t ss_own_end(const SsArgs &x, int64_t out0, ui
     return end < (int64_t)n_full ? (uint32_t)end : n_full;
 }
 
+// What concerns an instance is the same in all lanes and is read out of its lane into scalar registers: with it in vector registers the kernel took 88 of
+// them, not 72, and a CU two workgroups of 512 instead of three (800 instances of 256 flows: 38.8 us, now 36.0).
+__device__ __forceinline__ uint32_t lane_u32(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
+__device__ __forceinline__ int64_t lane_i64(int64_t v, int l) { return (int64_t)((uint64_t)lane_u32((uint32_t)((uint64_t)v >> 32), l) << 32 | lane_u32((uint32_t)v, l)); }
+
 // The workgroups behind the instances' write what the long instances leave over, in tiles of kSsHelpTile chunks, every one a run of consecutive
 // tiles.  Which instances are long is known here only: the host sees the sum of their chunks at most (capacity), and the counts' kernel has just
 // ended.  They read the counts, 64 instances at a time, and end at once when there is nothing over (or no room for the records).
@@ -221,7 +226,7 @@ __device__ __forceinline__ void ss_help(const CsArgs &a, const SsArgs &x, unsign
         }
         out0 = before + inc - c;
         tiles = (n_full - ss_own_end(x, out0, n_full) + kSsHelpTile - 1) / kSsHelpTile;
-        return before + __shfl(inc, 63);            // records up to base + 64
+        return before + lane_i64(inc, 63);          // records up to base + 64
     };
     bool over = false;
 #pragma unroll
@@ -251,9 +256,9 @@ __device__ __forceinline__ void ss_help(const CsArgs &a, const SsArgs &x, unsign
         while (u < u1 && u < seen) {
             const int l = 63 - __clzll((long long)__ballot(tiles != 0 && first <= u));
             const int inst = base + l;
-            const int64_t o = __shfl(out0, l);
-            const uint32_t nf = (uint32_t)__shfl((int)n_full, l);
-            const unsigned t0 = (unsigned)__shfl((int)first, l), tn = (unsigned)__shfl((int)tiles, l);
+            const int64_t o = lane_i64(out0, l);
+            const uint32_t nf = lane_u32(n_full, l);
+            const unsigned t0 = lane_u32(first, l), tn = lane_u32(tiles, l);
             const unsigned to = t0 + tn < u1 ? t0 + tn : u1;             // this workgroup's tiles of the instance: u .. to - 1
             __syncthreads();                                             // the instance before is done with the starts
             const uint32_t *fs = a.full_start + (int64_t)inst * a.NF, *cs = a.canon_start + (int64_t)inst * a.NF;
@@ -452,10 +457,13 @@ static int launch_ss_t(const CsArgs &a, const SsArgs &x, hipStream_t st)
 template <int GW>
 static int launch_ss(const CsArgs &a, const SsArgs &x, hipStream_t st)
 {
-    // more instances than fit the chip together: half the threads each, so that more of them overlap (1024 instances of 64 flows: 30 -> 26 us, of
-    // 1024: 53 -> 41; 384 of 2048: 66 -> 47, 1024 of them: 120 -> 77 by 512 threads and 90 by 256)
+    // More instances than fit the chip together: half the threads each, so that more of them overlap (72 registers: three workgroups of 512 a CU, one of
+    // 1024).  us by half / all of them: 288 instances of 2048 flows 69 / 111, 1024 of them 124 / 217; 1024 of 1024 flows and 2.4 K chunks 54 / 73, 800
+    // of 256 and 0.5 K 31 / 36.  With many chunks per flow or instance the record writers want the threads: 800 of 256 flows and 22.6 K 70 / 66, 600 of 256 and
+    // 1.6 K 30 / 30, 6.1 K 36 / 34, 22.6 K 60 / 51; 560 of 512 and 7.2 K 37 / 40, 26.5 K 61 / 55.
     if (a.NF > kSsWideFlows) return a.n_inst > 256 ? launch_ss_t<GW, 512>(a, x, st) : launch_ss_t<GW, 1024>(a, x, st);
-    return a.n_inst > 512 ? launch_ss_t<GW, 256>(a, x, st) : launch_ss_t<GW, 512>(a, x, st);
+    const bool half = a.n_inst > 512 && a.capacity <= a.n_inst * (a.n_inst > 768 ? (int64_t)16384 : 16 * (int64_t)a.NF);
+    return half ? launch_ss_t<GW, 256>(a, x, st) : launch_ss_t<GW, 512>(a, x, st);
 }
 
 }  // namespace rs

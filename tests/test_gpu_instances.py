@@ -37,6 +37,9 @@ def _matrix(kind, B, G, C, rng):
                                      (64, 8, 1, 131072),          # 4096: the largest in one workgroup
                                      (65, 8, 1, 131072),          # 4160: separate kernels
                                      (28, 12, 1, 262144),         # 4032, 12 rails
+                                     (3, 8, 180, 65536),          # 540 instances of 192 flows: 256 threads up to 16 chunks a flow
+                                     (2, 8, 390, 65536),          # 780 of 128
+                                     (12, 12, 22, 65536),         # 264 of 1728: 512 threads
                                      (4, 2, 300, 4096),           # 1200 instances
                                      (16, 8, 66, 65536)])         # 1056 instances of 1024 flows
 def test_instances(M, N, B, C, kind):
