@@ -167,7 +167,7 @@ __global__ __launch_bounds__(T) void cs_tail_kernel(CsArgs a)
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
 
     int nt = 0;
-    const unsigned short *sorted = tail_sort_block<T>(a, rows, k, rem, hist, idx_a, idx_b, sh, nt, [] {});
+    const unsigned short *sorted = tail_sort_block<T, T == 64>(a, rows, k, rem, hist, idx_a, idx_b, sh, nt, [] {});
 
     const int64_t out0 = a.chunk_off[inst] + a.cnt_full[inst];
     const uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;

@@ -71,7 +71,7 @@ constexpr int64_t kSsOwnBusy = 65536;   // where no CU is idle
 constexpr uint32_t kSsHelpTile = 4096;  // full chunks in a tile of those it leaves over
 // Chunks per instance (capacity / instances) up to which one workgroup an instance, with helpers, is faster than the separate kernels.  us even / skewed,
 // against the separate kernels: 256 instances of 4096 flows and 120 K chunks 156 / 170 against 195 / 205, 248 K 266 / 310 against 255 / 262; 1024 of 2048
-// flows and 59 K 200 / 219 against 269 / 275, 117 K 541 / 540 against 372 / 372; 800 of 512 flows and 53 K 146 / 170 against 160 / 160.
+// flows and 59 K 214 / 226 against 269 / 275, 117 K 541 / 540 against 372 / 372; 800 of 512 flows and 53 K 141 / 158 against 160 / 160.
 constexpr int64_t kSsMaxAvg = 131072, kSsMaxAvgBusy = 65536;
 
 struct SsArgs {
@@ -293,7 +293,20 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
     uint8_t *late_rail = reinterpret_cast<uint8_t *>(idx_b + a.NF);
 
     if ((int)blockIdx.x >= a.n_inst) {
-        ss_help<kSsThreads>(a, x, hist);
+        // with arguments read anew: those of the instances' path, kept for both, would not fit its scalar registers (75 of them parked in vector lanes, 10 so)
+        typedef const __attribute__((address_space(4))) uint64_t *Words;
+        constexpr size_t A = sizeof(CsArgs) / 8, X = sizeof(SsArgs) / 8;
+        static_assert(sizeof(CsArgs) % 8 == 0 && sizeof(SsArgs) % 8 == 0 && alignof(SsArgs) == 8, "both are whole words, one behind the other");
+        Words args = (Words)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));
+        uint64_t words[A + X];
+#pragma unroll
+        for (size_t i = 0; i < A + X; ++i) words[i] = args[i];
+        CsArgs ha;
+        SsArgs hx;
+        __builtin_memcpy(&ha, words, sizeof(CsArgs));
+        __builtin_memcpy(&hx, words + A, sizeof(SsArgs));
+        ss_help<kSsThreads>(ha, hx, hist);
         return;
     }
     const int inst = blockIdx.x;
@@ -307,7 +320,7 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
     uint32_t n_full = 0, n_all = 0;
     int nt = 0;
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
-    const unsigned short *sorted = tail_sort_block<kSsThreads>(a, rows, k, rem, hist, idx_a, idx_b, sh_sort, nt, [&] {
+    const unsigned short *sorted = tail_sort_block<kSsThreads, true>(a, rows, k, rem, hist, idx_a, idx_b, sh_sort, nt, [&] {
         for (int i = tid; i < a.n_inst; i += kSsThreads) {
             const int64_t c = a.cnt_all[i];
             total += c;
@@ -554,11 +567,11 @@ static int schedule_run(const int64_t *D1, int32_t batch, const railsched_topo_t
                 reinterpret_cast<uintptr_t>(perm) % 16 == 0 && reinterpret_cast<uintptr_t>(rail) % 4 == 0) ? 1 : 0;
     // One instance may hold as many chunks as there are records.  Up to 256 instances, or 128 of more than kSsWideFlows flows, which take a CU each, leave
     // CUs idle, and sharing starts early; beyond that an instance of the mean length writes all its records itself (960 instances of 29 K chunks: 101 us,
-    // 129 when they shared theirs) and helpers come last.  64 / 256 of them, 1024 instances of 2048 flows, 59 K chunks each: even 201 / 200, skewed 304 / 219;
-    // 960 of 1024 flows 174 / 173 and 290 / 193.  Of the wide instances the helpers would wait for a CU as long as the rest: only what one round holds, or 64.
+    // 129 when they shared theirs) and helpers come last.  64 / 256 of them, 1024 instances of 2048 flows, 59 K chunks each: even 213 / 214, skewed 337 / 226;
+    // 960 of 1024 flows 174 / 174 and 290 / 199.  Beyond 2048 flows helpers would wait for a CU as long as the rest: only what one round holds, or 64.
     const bool wide = NF > kSsWideFlows, idle = n_inst <= (wide ? 128 : 256);
     x.own = !idle ? kSsOwnBusy : wide ? kSsOwnWide : kSsOwn;
-    const int64_t room = !wide || idle ? 256 : n_inst <= 192 ? 256 - n_inst : 64;
+    const int64_t room = NF <= 2048 || idle ? 256 : n_inst <= 192 ? 256 - n_inst : 64;
     const int64_t over = (capacity - x.own + kSsHelpTile - 1) / kSsHelpTile;
     x.helpers = (int32_t)(over <= 0 ? 0 : over < room ? over : room);
     int rc = GW == 4 ? launch_ss<4>(a, x, st) : GW == 8 ? launch_ss<8>(a, x, st) : GW == 16 ? launch_ss<16>(a, x, st)
