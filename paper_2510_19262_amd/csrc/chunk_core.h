@@ -11,15 +11,17 @@ struct CsArgs {
     int64_t *chunk_off;
     uint32_t *chunk_w, *chunk_flow, *perm;
     int64_t capacity;
-    int64_t *cnt_all, *cnt_full, *tile_off;
-    uint32_t *full_start, *canon_start;
+    int64_t *cnt_all, *cnt_full;
+    uint32_t *full_start;        // [n_inst][NF] full chunks of the instance before flow f
+    uint16_t *tails_before;      // [n_inst][NF] tails before flow f (at most NF <= 16384); canonical start of the flow = the two together
+    uint2 *entries;              // [n_entries] (instance, flow) at every 2^s-th record, where the record fill starts its searches (fill_entry_shift)
+    int64_t n_entries;
     int64_t C;
     int32_t cshift;      // >= 0 when C is a power of two
     int32_t M, N, G, NF, intra;
     int32_t n_inst;
-    int32_t tile;        // full-chunk positions per fill tile
-    uint8_t *rail;       // when set, the fill also writes the rails of every instance's leading run (see cs_fill_kernel)
     int32_t nmask;       // N - 1 when N is a power of two, else -1
+    uint8_t *rail;       // when set, the fill also writes the rails of every instance's leading run (see cs_fill_kernel)
     int32_t gmask, nshift;   // G - 1 and log2 N when G / N are powers of two, else -1
     int64_t *run_end;    // when set, run_end[inst * N] receives the length of every instance's leading run of full chunks
 };
@@ -73,6 +75,20 @@ __device__ __forceinline__ unsigned wave_exscan(unsigned v, unsigned &total)
 // for the wavefront's own LDS operations is enough (LDS executes a wavefront's operations in order) and
 // the asm statement keeps the compiler from moving LDS accesses across it.
 __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Maximum over the lanes before the caller's, and `first` (a lower bound of all) for lane 0.
+__device__ __forceinline__ unsigned wave_max_before(unsigned inc, unsigned first)
+{
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xF, 0xF, false));   // row_shr:1
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xF, 0xF, false));   // row_shr:2
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x114, 0xF, 0xF, false));   // row_shr:4
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xF, 0xF, false));   // row_shr:8
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x142, 0xA, 0xF, false));   // row_bcast15 into rows 1 and 3
+    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x143, 0xC, 0xF, false));   // row_bcast31 into rows 2 and 3
+    return (unsigned)__builtin_amdgcn_update_dpp((int)first, (int)inc, 0x138, 0xF, 0xF, false);   // wave_shr:1; lane 0 keeps `first`
+}
 
 // Flows of the 256 positions first .. first + 255, four per lane, for a wavefront that knows the flow j_lo of position `first` or of one
 // before it (the same in all lanes): every flow that starts in the window, or between j_lo and it, leaves its number where it

@@ -17,11 +17,12 @@
 
 namespace rs {
 
-constexpr int kTileMin = 1024;      // full-chunk positions per fill tile: a power of two between these two, chosen per call
-constexpr int kTileMax = 16384;     // so that small batches still spread over a few thousand workgroups
-constexpr int kFillThreads = 256;
-constexpr int kFillStage = 1536;    // flow boundaries staged in LDS per span (16 KiB with the canonical starts and the marks: 8 workgroups per CU)
-constexpr int kFillBlocks = 16384;  // most workgroups of one fill launch: several rounds of the chip, which evens out their ends
+// Record fill.  us of the whole call by 128 / 256 / 512 / 1024 threads a workgroup: 4096 instances, 480 M records of 13 bytes 1147 / 1118 / 1122 / 1100..1150, one
+// matrix of 3.9 G records of 9 bytes 5820 / 5510 / 5400 / 5450.  Neighbouring tiles on one XCD: a bare writer of 13 bytes a record with one read in front of its stores
+// 5.6 TB/s when tiles go round robin over the XCDs, 5.8 / 6.0 / 6.1 when an XCD has 64 / 128 / 512 KiB of an array in a row.
+constexpr int kFillThreads = 512;
+constexpr int kFillGranule = 7;     // log2 of the neighbouring tiles that the workgroups of one XCD write: 1 MiB of an array
+constexpr int64_t kFillTiles = 1 << 22;   // most tiles of one launch: 2^31 threads
 
 // ---- A: per-instance chunk counts and the two exclusive scans over its flows -----------------
 // One workgroup of T threads per instance, T * kTailLoads flows per round.  Latency bound (a few dependent trips to memory and
@@ -32,15 +33,16 @@ __global__ __launch_bounds__(T) void cs_count_kernel(CsArgs a)
     constexpr int W = T / 64, U = kTailLoads;
     static_assert(U * W <= 64, "one lane per (round, wavefront)");
     __shared__ unsigned sh_q[64], sh_c[64];
-    __shared__ int64_t sh_n[2][W];
+    __shared__ int64_t sh_n[W];
     const int inst = blockIdx.x;
     const int b = inst / a.M, k = inst % a.M;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
     uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
-    uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;
+    uint16_t *tb = a.tails_before + (int64_t)inst * a.NF;
+    const unsigned long long lt = (1ull << lane) - 1ull;
     unsigned carry_q = 0, carry_c = 0;
-    int64_t n_full = 0, n_all = 0;
+    int64_t n_full = 0;
     for (int f0 = 0; f0 < a.NF; f0 += U * T) {
         int64_t bytes[U];                           // all of a round's loads in flight before the scans, which chain
 #pragma unroll
@@ -53,18 +55,19 @@ __global__ __launch_bounds__(T) void cs_count_kernel(CsArgs a)
         for (int u = 0; u < U; ++u) {
             uint32_t q = 0, r = 0;
             split_bytes(a, bytes[u], q, r);
-            const unsigned c = q + (r ? 1u : 0u);
-            unsigned tq, tc;
+            unsigned tq;
             eq[u] = wave_exscan(q, tq);
-            ec[u] = wave_exscan(c, tc);
+            const unsigned long long tails = __ballot(r != 0);
+            const unsigned tc = (unsigned)__popcll(tails);
+            ec[u] = (unsigned)__popcll(tails & lt);
             if constexpr (W == 1) {                 // a wavefront by itself carries its totals along
                 const int f = f0 + u * T + tid;
-                if (f < a.NF) { fs[f] = carry_q + eq[u]; cs[f] = carry_c + ec[u]; }
+                if (f < a.NF) { fs[f] = carry_q + eq[u]; tb[f] = (uint16_t)(carry_c + ec[u]); }
                 carry_q += tq; carry_c += tc;
             } else if (lane == 0) {
                 sh_q[u * W + wave] = tq; sh_c[u * W + wave] = tc;
             }
-            n_full += q; n_all += c;
+            n_full += q;
         }
         if constexpr (W == 1) continue;
         __syncthreads();
@@ -76,21 +79,21 @@ __global__ __launch_bounds__(T) void cs_count_kernel(CsArgs a)
             const int f = f0 + u * T + tid;
             const unsigned oq = carry_q + (unsigned)__shfl((int)bq, u * W + wave) + eq[u];
             const unsigned oc = carry_c + (unsigned)__shfl((int)bc, u * W + wave) + ec[u];
-            if (f < a.NF) { fs[f] = oq; cs[f] = oc; }
+            if (f < a.NF) { fs[f] = oq; tb[f] = (uint16_t)oc; }
         }
         carry_q += total_q; carry_c += total_c;
         __syncthreads();                            // the totals have been read
     }
-    // exact 64-bit totals
+    // exact 64-bit total
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) { n_full += __shfl_xor(n_full, d); n_all += __shfl_xor(n_all, d); }
+    for (int d = 32; d >= 1; d >>= 1) n_full += __shfl_xor(n_full, d);
     if constexpr (W > 1) {
-        if (lane == 0) { sh_n[0][wave] = n_full; sh_n[1][wave] = n_all; }
+        if (lane == 0) sh_n[wave] = n_full;
         __syncthreads();
     }
     if (tid == 0) {
-        for (int w = 1; w < W; ++w) { n_full += sh_n[0][w]; n_all += sh_n[1][w]; }
-        a.cnt_all[inst] = n_all; a.cnt_full[inst] = n_full;
+        for (int w = 1; w < W; ++w) n_full += sh_n[w];
+        a.cnt_all[inst] = n_full + carry_c; a.cnt_full[inst] = n_full;
         if (a.run_end) a.run_end[(int64_t)inst * a.N] = n_full;
     }
 }
@@ -105,79 +108,134 @@ static int flow_threads(int64_t n_inst, int64_t NF)
     return 1024;
 }
 
-// ---- B: chunk_off = exclusive scan of instance sizes; tile_off = exclusive scan of fill tiles --
+// ---- B: chunk_off = exclusive scan of instance sizes --------------------------------------------
 __global__ __launch_bounds__(1024) void cs_scan_kernel(CsArgs a)
 {
     constexpr int PER = 4;                            // consecutive instances per thread and round
-    __shared__ int64_t sh_a[16], sh_t[16];
+    __shared__ int64_t sh_a[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tile_shift = __builtin_ctz((unsigned)a.tile);   // the tile is a power of two
-    int64_t carry_a = 0, carry_t = 0;                 // the same in every thread
+    int64_t carry = 0;                                // the same in every thread
     for (int base = 0; base < a.n_inst; base += 1024 * PER) {
-        int64_t va[PER], vt[PER], sa = 0, st = 0;
+        int64_t va[PER], sa = 0;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int i = base + tid * PER + u;
             va[u] = i < a.n_inst ? a.cnt_all[i] : 0;
-            vt[u] = i < a.n_inst ? (a.cnt_full[i] + a.tile - 1) >> tile_shift : 0;
-            sa += va[u]; st += vt[u];
+            sa += va[u];
         }
-        int64_t ia = sa, it = st;                     // inclusive scans of the thread sums inside the wavefront
+        int64_t ia = sa;                              // inclusive scan of the thread sums inside the wavefront
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
-            const int64_t xa = __shfl_up(ia, d), xt = __shfl_up(it, d);
-            if (lane >= d) { ia += xa; it += xt; }
+            const int64_t xa = __shfl_up(ia, d);
+            if (lane >= d) ia += xa;
         }
-        __syncthreads();                              // the round before is done with sh_a / sh_t
-        if (lane == 63) { sh_a[wave] = ia; sh_t[wave] = it; }
+        __syncthreads();                              // the round before is done with sh_a
+        if (lane == 63) sh_a[wave] = ia;
         __syncthreads();
-        int64_t before_a = 0, before_t = 0, tot_a = 0, tot_t = 0;
+        int64_t before = 0, total = 0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) {
-            const int64_t xa = sh_a[w], xt = sh_t[w];
-            if (w < wave) { before_a += xa; before_t += xt; }
-            tot_a += xa; tot_t += xt;
+            const int64_t xa = sh_a[w];
+            if (w < wave) before += xa;
+            total += xa;
         }
-        int64_t oa = carry_a + before_a + ia - sa, ot = carry_t + before_t + it - st;
+        int64_t oa = carry + before + ia - sa;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int i = base + tid * PER + u;
-            if (i < a.n_inst) { a.chunk_off[i] = oa; a.tile_off[i] = ot; }
-            oa += va[u]; ot += vt[u];
+            if (i < a.n_inst) a.chunk_off[i] = oa;
+            oa += va[u];
         }
-        carry_a += tot_a; carry_t += tot_t;
+        carry += total;
     }
-    if (tid == 0) { a.chunk_off[a.n_inst] = carry_a; a.tile_off[a.n_inst] = carry_t; }
+    if (tid == 0) a.chunk_off[a.n_inst] = carry;
 }
 
-// ---- C: tails of one instance: stable descending radix sort in LDS, one workgroup per instance ----
+// ---- C: tails of one instance: stable descending radix sort in LDS, one workgroup per instance; beside it the entries of the fill ----
+// Every 2^s-th record's instance and flow (NF where it is a tail), for the fill's wavefronts to start from: the smallest s from kEntryShift on for which
+// the room behind the workspace's other arrays is enough (two bytes a flow, so about four flows lie between two entries at most, on average).
+// One for every wavefront of the fill where there is room: 61 layers of 512 GPUs, 220 M records, 933 us the call with an entry every 256 records, 952 with
+// one every 512, 975 every 1024 (the scan from an entry to the window is as long as the window's own).
+constexpr int kEntryShift = 8;
+__host__ __device__ __forceinline__ int fill_entry_shift(int64_t total, int64_t n_entries)
+{
+    int s = kEntryShift;
+    while (((total - 1) >> s) >= n_entries) ++s;
+    return s;
+}
+
+// Entries u .. u + 63, one per lane.  The first and the last lane's instance and flow are searched for by the whole wavefront, the others' by
+// each lane between the two (a lane by itself from the start: a dozen dependent trips to memory).
+__device__ __forceinline__ void fill_entries(const CsArgs &a, int64_t u)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t total = a.chunk_off[a.n_inst];
+    if (total > a.capacity || total == 0) return;
+    const int s = fill_entry_shift(total, a.n_entries);
+    const int64_t end = (total - 1) >> s;                                // last entry
+    if (u > end) return;
+    const int64_t u_last = u + 63 < end ? u + 63 : end;
+    const int i_lo = wave_last_le<int64_t>(a.chunk_off, a.n_inst, u << s), i_hi = wave_last_le<int64_t>(a.chunk_off, a.n_inst, u_last << s);
+    const int64_t mine = u + lane < u_last ? u + lane : u_last;          // lanes behind the last entry repeat it
+    const int inst = i_lo + (i_hi > i_lo ? last_le<int64_t>(a.chunk_off + i_lo, i_hi - i_lo + 1, mine << s) : 0);
+    const int64_t p = (mine << s) - a.chunk_off[inst];
+    const bool full = p < a.cnt_full[inst];
+    const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
+    int j_lo = 0, j_hi = a.NF - 1;
+    if (i_lo == i_hi) {                                                  // flow starts ascend: all lanes' flows lie between these two
+        const uint32_t p0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p), p1 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)p, 63);
+        j_lo = wave_last_le<uint32_t>(fs, a.NF, p0);
+        j_hi = wave_last_le<uint32_t>(fs, a.NF, p1);
+    }
+    const int j = full ? j_lo + last_le<uint32_t>(fs + j_lo, j_hi - j_lo + 1, (uint32_t)p) : a.NF;
+    a.entries[mine] = make_uint2((unsigned)inst, (unsigned)j);
+}
+
 template <int T>
-__global__ __launch_bounds__(T) void cs_tail_kernel(CsArgs a)
+__global__ __launch_bounds__(T) void cs_tail_kernel(CsArgs a, unsigned entry_blocks)
 {
     extern __shared__ __align__(16) unsigned cs_lds[];
     __shared__ unsigned sh[kTailShared];
+    if (blockIdx.x < entry_blocks) {
+        fill_entries(a, ((int64_t)blockIdx.x * T + threadIdx.x) & ~(int64_t)63);
+        return;
+    }
     unsigned *hist = cs_lds;                                             // [tail_hist_words<T>()], read 16 bytes at a time
     unsigned *rem = hist + tail_hist_words<T>();                         // [NF] tail bytes per flow
     unsigned short *idx_a = reinterpret_cast<unsigned short *>(rem + a.NF);    // [NF] flow ids, ping
     unsigned short *idx_b = idx_a + a.NF;                                      // [NF] pong
     if (a.chunk_off[a.n_inst] > a.capacity) return;                      // record arrays too small: leave them alone
 
-    const int inst = blockIdx.x;
+    const int inst = (int)(blockIdx.x - entry_blocks);
     const int b = inst / a.M, k = inst % a.M;
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
 
     int nt = 0;
     const unsigned short *sorted = tail_sort_block<T, T == 64>(a, rows, k, rem, hist, idx_a, idx_b, sh, nt, [] {});
 
+    const uint32_t n_full = (uint32_t)a.cnt_full[inst];
     const int64_t out0 = a.chunk_off[inst] + a.cnt_full[inst];
-    const uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;
-    const uint32_t n_all = (uint32_t)a.cnt_all[inst];
-    for (int i = threadIdx.x; i < nt; i += T) {
-        const int f = sorted[i];
-        a.chunk_w[out0 + i] = rem[f];
-        a.chunk_flow[out0 + i] = (uint32_t)f;
-        // the tail is its flow's last chunk: one before the canonical start of the next flow
-        if (a.perm) a.perm[out0 + i] = (f + 1 < a.NF ? cs[f + 1] : n_all) - 1u;
+    const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
+    const uint16_t *tb = a.tails_before + (int64_t)inst * a.NF;
+    constexpr int U = 4;                                                 // the flows' starts are fetched for four tails at a time
+    for (int i0 = threadIdx.x; i0 < nt; i0 += U * T) {
+        int f[U];
+        uint32_t pm[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) f[u] = i0 + u * T < nt ? sorted[i0 + u * T] : sorted[i0];
+        if (a.perm) {
+            // the tail is its flow's last chunk: the full chunks up to the next flow and the tails before it come first
+#pragma unroll
+            for (int u = 0; u < U; ++u) pm[u] = (f[u] + 1 < a.NF ? fs[f[u] + 1] : n_full) + tb[f[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * T;
+            if (i >= nt) break;
+            a.chunk_w[out0 + i] = rem[f[u]];
+            a.chunk_flow[out0 + i] = (uint32_t)f[u];
+            if (a.perm) a.perm[out0 + i] = pm[u];
+        }
     }
 }
 
@@ -190,168 +248,151 @@ static int launch_cs_tail(const CsArgs &a, hipStream_t st)
                                 (int)lds) != hipSuccess)
             return RAILSCHED_ERR_HIP;
     }
-    hipLaunchKernelGGL(cs_tail_kernel<T>, dim3((unsigned)a.n_inst), dim3(T), lds, st, a);
+    int64_t entries = (a.capacity >> kEntryShift) + 1;
+    entries = entries < a.n_entries ? entries : a.n_entries;
+    const unsigned entry_blocks = (unsigned)((entries + T - 1) / T);
+    hipLaunchKernelGGL(cs_tail_kernel<T>, dim3(entry_blocks + (unsigned)a.n_inst), dim3(T), lds, st, a, entry_blocks);
     return launch_status();
 }
 
-// ---- D: full chunks: tiles of consecutive output positions ------------------------------------
-// Full-chunk region of the instances, cut into tiles of a.tile positions; a workgroup takes a contiguous run of
-// tiles, so the instance and the flow its next tile starts in carry over and only its first tile is searched for.
-// A tile is filled in spans: as many flow boundaries as fit are staged in LDS (in rounds of 512, until they reach
-// the tile's end), and the span ends where the staged flows end.  Inside a span positions are grouped by fours at
-// multiples of four of the global record index (16-byte stores); a wavefront walks a contiguous quarter of the
-// groups, 64 at a time, and finds the flows of its 256 positions from the starts that fall among them (window_flows).
-__global__ __launch_bounds__(kFillThreads) void cs_fill_kernel(CsArgs a, int vec_ok)
+// ---- D: full chunks ---------------------------------------------------------------------------
+// Write bound: 9 to 13 bytes a record.  A workgroup writes one tile of 4 T records at a multiple of that and exits, a wavefront its own kilobyte of
+// every array, on a 1 KiB boundary, with streaming stores.  What a writer reaches of the chip's 6.9 TB/s hangs on how many bytes wait behind
+// how long a chain of reads, and on what lies side by side in time: bare writers of 13 bytes a record, TB/s: no reads 6.1, two dependent trips in front
+// of the stores 5.2, the same with neighbouring tiles on one XCD 5.5, with streaming stores too 6.0; two and four tiles a workgroup are
+// slower throughout (5.2, 5.1).  So a wavefront makes two trips (its entry; then its instance's bounds and the flow starts from the entry's flow on), no
+// barrier, and finds the flows of its records from the starts that fall among them, as window_flows does.
+// Measured, as contiguous runs of tiles per workgroup with their flow starts staged in LDS / now: 4096 instances of 117 K records 1295 / 990 us (4.8 / 6.3 TB/s),
+// one matrix of 3.9 G records without perm 6720 / 5310 (5.3 / 6.7), 3904 instances of 57 K in flows of 14: 611 / 500.
+template <int T>
+__global__ __launch_bounds__(T) void cs_fill_kernel(CsArgs a, int vec_ok, int kshift, int64_t tile0)
 {
-    __shared__ uint32_t st_fs[kFillStage + 1];
-    __shared__ uint32_t st_cs[kFillStage];
-    __shared__ __align__(16) unsigned marks[kFillThreads / 64][256];
-    if (a.chunk_off[a.n_inst] > a.capacity) return;
-    const int64_t n_tiles = a.tile_off[a.n_inst];
-    const int64_t u0 = n_tiles * blockIdx.x / gridDim.x, u1 = n_tiles * (blockIdx.x + 1) / gridDim.x;
-    if (u0 >= u1) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    constexpr int kWaves = kFillThreads / 64;
+    constexpr int kWindow = 256;
+    __shared__ __align__(16) unsigned marks[T / 64][kWindow];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const unsigned b = blockIdx.x;
+    const int64_t tile = tile0 + ((int64_t)(b >> (3 + kshift)) << (3 + kshift)) + ((b & 7u) << kshift) + ((b >> 3) & ((1u << kshift) - 1u));
+    const int64_t w0 = tile * (T * 4) + wave * kWindow;                  // this wavefront's first record
+    const int64_t total = a.chunk_off[a.n_inst];
+    if (total > a.capacity || w0 >= total) return;
+    const uint2 entry = a.entries[w0 >> fill_entry_shift(total, a.n_entries)];
+    int inst = __builtin_amdgcn_readfirstlane((int)entry.x), j0 = __builtin_amdgcn_readfirstlane((int)entry.y);
+    unsigned *mark = marks[wave];
     const uint32_t cw = (uint32_t)a.C;
 
-    int inst = wave_last_le<int64_t>(a.tile_off, a.n_inst, u0);          // tile_off[inst] <= u0 < tile_off[inst+1]
-    int64_t t_end = a.tile_off[inst + 1];
-    int fb = -1;                                                         // flow that holds the position before the next span
-    for (int64_t u = u0; u < u1; ++u) {
-        if (u >= t_end) {
-            do { ++inst; t_end = a.tile_off[inst + 1]; } while (u >= t_end);
-            fb = -1;
-        }
+    int64_t out0 = a.chunk_off[inst], out1 = a.chunk_off[inst + 1];
+    while (out1 <= w0) {                                                 // the entry lies before the window, in another instance
+        const int i = inst + 1 + lane < a.n_inst ? inst + 1 + lane : a.n_inst;
+        inst += __popcll(__ballot(a.chunk_off[i] <= w0));                // chunk_off[n_inst] = total > w0
+        j0 = 0;
+        out0 = a.chunk_off[inst]; out1 = a.chunk_off[inst + 1];
+    }
+    while (true) {                                                       // the instances that have records in the window: one, but where one ends
         const uint32_t n_full = (uint32_t)a.cnt_full[inst];
-        const uint32_t t0 = (uint32_t)(u - a.tile_off[inst]) * (uint32_t)a.tile;
-        const uint32_t t1 = (n_full - t0 < (uint32_t)a.tile) ? n_full : t0 + (uint32_t)a.tile;
-        const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
-        const uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;
-        const int64_t out0 = a.chunk_off[inst];
-        const uint32_t lead = n_full - n_full % (uint32_t)a.N;          // positions below it go round robin (a.rail)
-        if (fb < 0) fb = wave_last_le<uint32_t>(fs, a.NF, t0);
-
-        uint32_t p0 = t0;
-        while (p0 < t1) {
-            // ---- stage flow starts fb.. until they pass the tile's end, the flows end or the stage is full
-            __syncthreads();                                             // the span before is done with the stage
-            int nf = 0;
-            bool covers = false;
-            while (true) {
-                int want = a.NF - fb - nf;
-                want = want < 512 ? want : 512;
-                want = want < kFillStage - nf ? want : kFillStage - nf;
-                for (int i = threadIdx.x; i < want; i += kFillThreads) {
-                    st_fs[nf + i] = fs[fb + nf + i];
-                    if (a.perm) st_cs[nf + i] = cs[fb + nf + i];
+        const int64_t first = w0 - out0;                                 // instance position of the window's first record; negative where the instance starts in it
+        if (n_full != 0 && first < (int64_t)n_full) {
+            const uint32_t last = first + kWindow <= (int64_t)n_full ? (uint32_t)(first + kWindow - 1) : n_full - 1u;
+            const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
+            const uint16_t *tb = a.tails_before + (int64_t)inst * a.NF;
+            *reinterpret_cast<uint4 *>(mark + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
+            lds_sync();
+            unsigned base = 0;                                           // flow << 16 | tails before it: both ascend together
+            for (int f = j0 + lane;; f += 64) {
+                const bool is = f < a.NF;
+                const uint32_t s = is ? fs[f] : 0xFFFFFFFFu;
+                const unsigned v = (unsigned)f << 16 | (is ? (unsigned)tb[f] : 0u);
+                const bool in = s <= last, before = in && (int64_t)s <= first;
+                const int n = __popcll(__ballot(before));
+                if (n) base = (unsigned)__builtin_amdgcn_readlane((int)v, n - 1);
+                if (in && !before) atomicMax(&mark[(uint32_t)((int64_t)s - first)], v);
+                if (__ballot(!in) != 0ull) break;
+            }
+            lds_sync();
+            const uint4 m = *reinterpret_cast<const uint4 *>(mark + 4 * lane);
+            const unsigned m1 = max(m.x, m.y), m2 = max(m1, m.z), m3 = max(m2, m.w);
+            const unsigned left = wave_max_before(max(m3, base), base);
+            const unsigned v[4] = {max(left, m.x), max(left, m1), max(left, m2), max(left, m3)};
+            const int64_t p = first + 4 * lane;
+            const uint32_t lead = n_full - n_full % (uint32_t)a.N;       // positions below it go round robin (a.rail)
+            const int64_t at = w0 + 4 * lane;
+            uint32_t rr = 0;
+            if (a.rail) {
+                uint32_t r = a.nmask >= 0 ? ((uint32_t)p & (uint32_t)a.nmask) : (uint32_t)p % (uint32_t)a.N;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    rr |= r << (8 * e);
+                    r = (r + 1 == (uint32_t)a.N) ? 0u : r + 1;
                 }
-                __syncthreads();
-                nf += want;
-                covers = (fb + nf >= a.NF) || (st_fs[nf - 1] >= t1);
-                if (covers || nf >= kFillStage) break;
             }
-            // the span ends at the tile's end, or where the last staged flow starts (it may continue unstaged)
-            uint32_t p1 = t1;
-            if (!covers) {
-                p1 = st_fs[nf - 1];
-                if (p1 <= p0) { fb += nf - 1; continue; }                // a stage full of empty flows: move on in the flows
-            }
-            __syncthreads();                                             // everyone has read st_fs[nf-1]
-            if (threadIdx.x == 0) st_fs[nf] = 0xFFFFFFFFu;               // nothing starts behind the staged flows
-            __syncthreads();
-
-            if (vec_ok) {
-                const uint32_t head = (uint32_t)((4 - ((out0 + p0) & 3)) & 3);   // scalar positions before the first aligned group
-                const uint32_t pa = (p1 - p0 < head) ? p1 : p0 + head;
-                const uint32_t groups = (p1 - pa) / 4;
-                const uint32_t pb = pa + groups * 4;                              // scalar positions from here on
-                // The wavefronts' shares and their steps end on 1 KiB boundaries of the record arrays (64 groups), so all
-                // steps but the span's first and last store whole, aligned kilobytes: 10 % more write rate than
-                // kilobytes that start 16 bytes off.
-                const uint32_t G0 = (uint32_t)(((out0 + pa) >> 2) & 63);           // global group index of group 0, mod 64
-                auto share = [&](int w) {
-                    if (w <= 0) return 0u;
-                    if (w >= kWaves) return groups;
-                    const uint32_t cut = ((G0 + (uint32_t)((uint64_t)groups * w / kWaves)) & ~63u);
-                    return cut > G0 ? cut - G0 : 0u;
-                };
-                const uint32_t g0 = share(wave), g1 = share(wave + 1);
-                if (g0 < g1) {
-                    int j_lo = last_le<uint32_t>(st_fs, nf, pa + 4 * g0);          // the same in every lane
-                    uint32_t cnt = 0;
-                    for (uint32_t gb = g0; gb < g1; gb += cnt) {
-                        cnt = 64u - ((G0 + gb) & 63u);
-                        cnt = cnt < g1 - gb ? cnt : g1 - gb;
-                        const bool active = (uint32_t)lane < cnt;
-                        const uint32_t p = pa + 4 * (gb + lane);
-                        const uint32_t p_last = pa + 4 * (gb + cnt) - 1;
-                        uint32_t fl[4], pm[4];
-                        j_lo = window_flows(st_fs, nf, j_lo, pa + 4 * gb, p_last, marks[wave], fl);
+            if (vec_ok && p >= 0 && p + 4 <= (int64_t)n_full) {
+                const uint32_t q = (uint32_t)p;
+                __builtin_nontemporal_store(u32x4{cw, cw, cw, cw}, reinterpret_cast<u32x4 *>(a.chunk_w + at));
+                __builtin_nontemporal_store(u32x4{v[0] >> 16, v[1] >> 16, v[2] >> 16, v[3] >> 16}, reinterpret_cast<u32x4 *>(a.chunk_flow + at));
+                if (a.perm)
+                    __builtin_nontemporal_store(u32x4{q + (v[0] & 0xFFFFu), q + 1 + (v[1] & 0xFFFFu), q + 2 + (v[2] & 0xFFFFu), q + 3 + (v[3] & 0xFFFFu)},
+                                                reinterpret_cast<u32x4 *>(a.perm + at));
+                if (a.rail) {
+                    if (q + 4 <= lead) {
+                        __builtin_nontemporal_store(rr, reinterpret_cast<uint32_t *>(a.rail + at));
+                    } else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            if (a.perm) pm[e] = st_cs[fl[e]] - st_fs[fl[e]] + p + e;
-                            fl[e] += (uint32_t)fb;
-                        }
-                        if (active && a.rail) {                      // leading run: rail = position mod N
-                            uint32_t r = a.nmask >= 0 ? (p & (uint32_t)a.nmask) : p % (uint32_t)a.N, rr = 0;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                rr |= r << (8 * e);
-                                r = (r + 1 == (uint32_t)a.N) ? 0u : r + 1;
-                            }
-                            if (p + 4 <= lead) {
-                                *reinterpret_cast<uint32_t *>(a.rail + out0 + p) = rr;
-                            } else {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) if (p + e < lead) a.rail[out0 + p + e] = (uint8_t)(rr >> (8 * e));
-                            }
-                        }
-                        if (active) {
-                            *reinterpret_cast<uint4 *>(a.chunk_w + out0 + p) = make_uint4(cw, cw, cw, cw);
-                            *reinterpret_cast<uint4 *>(a.chunk_flow + out0 + p) = make_uint4(fl[0], fl[1], fl[2], fl[3]);
-                            if (a.perm) *reinterpret_cast<uint4 *>(a.perm + out0 + p) = make_uint4(pm[0], pm[1], pm[2], pm[3]);
-                        }
+                        for (int e = 0; e < 4; ++e) if (q + e < lead) a.rail[at + e] = (uint8_t)(rr >> (8 * e));
                     }
                 }
-                // the few positions before the first and behind the last aligned group
-                const uint32_t n_edge = (pa - p0) + (p1 - pb);
-                if (threadIdx.x < n_edge) {
-                    const uint32_t p = threadIdx.x < pa - p0 ? p0 + threadIdx.x : pb + (threadIdx.x - (pa - p0));
-                    const int j = last_le<uint32_t>(st_fs, nf, p);
-                    a.chunk_w[out0 + p] = cw;
-                    a.chunk_flow[out0 + p] = (uint32_t)(fb + j);
-                    if (a.perm) a.perm[out0 + p] = st_cs[j] + (p - st_fs[j]);
-                    if (a.rail && p < lead) a.rail[out0 + p] = (uint8_t)(p % (uint32_t)a.N);
-                }
             } else {
-                for (uint32_t p = p0 + threadIdx.x; p < p1; p += kFillThreads) {
-                    const int j = last_le<uint32_t>(st_fs, nf, p);
-                    a.chunk_w[out0 + p] = cw;
-                    a.chunk_flow[out0 + p] = (uint32_t)(fb + j);
-                    if (a.perm) a.perm[out0 + p] = st_cs[j] + (p - st_fs[j]);
-                    if (a.rail && p < lead) a.rail[out0 + p] = (uint8_t)(p % (uint32_t)a.N);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (p + e < 0 || p + e >= (int64_t)n_full) continue;
+                    const uint32_t q = (uint32_t)(p + e);
+                    a.chunk_w[at + e] = cw;
+                    a.chunk_flow[at + e] = v[e] >> 16;
+                    if (a.perm) a.perm[at + e] = q + (v[e] & 0xFFFFu);
+                    if (a.rail && q < lead) a.rail[at + e] = (uint8_t)(q % (uint32_t)a.N);
                 }
             }
-            // the next span starts in the flow that holds position p1 - 1
-            fb += last_le<uint32_t>(st_fs, nf, p1 - 1);
-            p0 = p1;
         }
+        if (out1 >= w0 + kWindow || out1 >= total) return;
+        do { ++inst; out0 = out1; out1 = a.chunk_off[inst + 1]; } while (out1 == out0);
+        j0 = 0;
     }
 }
 
 static void ws_layout(int64_t n_inst, int64_t NF, size_t off[6])
 {
+    const size_t flows = (size_t)(n_inst * NF);
     size_t o = 0;
     off[0] = o; o += align_up(sizeof(int64_t) * (size_t)n_inst, 256);          // cnt_all
     off[1] = o; o += align_up(sizeof(int64_t) * (size_t)n_inst, 256);          // cnt_full
-    off[2] = o; o += align_up(sizeof(int64_t) * (size_t)(n_inst + 1), 256);    // tile_off
-    off[3] = o; o += align_up(sizeof(uint32_t) * (size_t)(n_inst * NF), 256);  // full_start
-    off[4] = o; o += align_up(sizeof(uint32_t) * (size_t)(n_inst * NF), 256);  // canon_start
-    off[5] = o;
+    off[2] = o; o += align_up(sizeof(uint32_t) * flows, 256);                  // full_start
+    off[3] = o; o += align_up(sizeof(uint16_t) * flows, 256);                  // tails_before
+    off[4] = o;                                                                // entries of the fill: two bytes a flow and 8 an instance, 256 or more
+    off[5] = off[2] + align_up(sizeof(int64_t) * (size_t)(n_inst + 1), 256) + 2 * align_up(sizeof(uint32_t) * flows, 256);
+}
+
+// pointers into the workspace, and what the kernels derive from the topology
+static void fill_args(CsArgs &a, const railsched_topo_t *h_topo, int64_t n_inst, void *ws)
+{
+    const int64_t M = h_topo->nodes, N = h_topo->rails, G = M * N, NF = N * G;
+    size_t off[6];
+    ws_layout(n_inst, NF, off);
+    char *w8 = static_cast<char *>(ws);
+    a.cnt_all = reinterpret_cast<int64_t *>(w8 + off[0]);
+    a.cnt_full = reinterpret_cast<int64_t *>(w8 + off[1]);
+    a.full_start = reinterpret_cast<uint32_t *>(w8 + off[2]);
+    a.tails_before = reinterpret_cast<uint16_t *>(w8 + off[3]);
+    a.entries = reinterpret_cast<uint2 *>(w8 + off[4]);
+    a.n_entries = (int64_t)((off[5] - off[4]) / sizeof(uint2));
+    a.C = h_topo->chunk_bytes;
+    a.cshift = is_pow2(a.C) ? ilog2(a.C) : -1;
+    a.M = (int32_t)M; a.N = (int32_t)N; a.G = (int32_t)G; a.NF = (int32_t)NF; a.intra = h_topo->include_intra_node;
+    a.n_inst = (int32_t)n_inst;
+    a.nmask = is_pow2(N) ? (int32_t)N - 1 : -1;
+    a.gmask = is_pow2(G) ? (int32_t)G - 1 : -1;
+    a.nshift = is_pow2(N) ? ilog2(N) : -1;
 }
 
 // entry points for the one-call scheduler (schedule.hip)
-void cs_ws_layout(int64_t n_inst, int64_t NF, size_t off[6]) { ws_layout(n_inst, NF, off); }
+void cs_fill_args(CsArgs &a, const railsched_topo_t *h_topo, int64_t n_inst, void *ws) { fill_args(a, h_topo, n_inst, ws); }
 void launch_cs_count(const CsArgs &a, hipStream_t st)
 {
     const int T = flow_threads(a.n_inst, a.NF);
@@ -390,26 +431,12 @@ int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int
     size_t off[6];
     ws_layout(n_inst, NF, off);
     if (!ws || ws_bytes < off[5] || reinterpret_cast<uintptr_t>(ws) % 256) return RAILSCHED_ERR_WORKSPACE;
-    char *w8 = static_cast<char *>(ws);
     CsArgs a;
     a.D1 = D1; a.chunk_off = chunk_off; a.chunk_w = chunk_w; a.chunk_flow = chunk_flow; a.perm = perm;
     a.capacity = capacity;
-    a.tile = kTileMin;
-    while (a.tile < kTileMax && capacity / a.tile > 8192) a.tile *= 2;
-    a.cnt_all = reinterpret_cast<int64_t *>(w8 + off[0]);
-    a.cnt_full = reinterpret_cast<int64_t *>(w8 + off[1]);
-    a.tile_off = reinterpret_cast<int64_t *>(w8 + off[2]);
-    a.full_start = reinterpret_cast<uint32_t *>(w8 + off[3]);
-    a.canon_start = reinterpret_cast<uint32_t *>(w8 + off[4]);
-    a.C = h_topo->chunk_bytes;
-    a.cshift = is_pow2(a.C) ? ilog2(a.C) : -1;
-    a.M = (int32_t)M; a.N = (int32_t)N; a.G = (int32_t)G; a.NF = (int32_t)NF; a.intra = h_topo->include_intra_node;
-    a.n_inst = (int32_t)n_inst;
     a.rail = rail;
     a.run_end = run_end;
-    a.nmask = is_pow2(N) ? (int32_t)N - 1 : -1;
-    a.gmask = is_pow2(G) ? (int32_t)G - 1 : -1;
-    a.nshift = is_pow2(N) ? ilog2(N) : -1;
+    fill_args(a, h_topo, n_inst, ws);
     if (args_out) *args_out = a;
 
     if (n_inst > 0) {
@@ -424,10 +451,14 @@ int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int
     if (int rc = T == 64 ? launch_cs_tail<64>(a, st) : T == 256 ? launch_cs_tail<256>(a, st) : launch_cs_tail<1024>(a, st)) return rc;
     const int vec_ok = (reinterpret_cast<uintptr_t>(chunk_w) % 16 == 0 && reinterpret_cast<uintptr_t>(chunk_flow) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(perm) % 16 == 0 && reinterpret_cast<uintptr_t>(rail) % 4 == 0) ? 1 : 0;
-    // no launch needs more workgroups than there can be tiles: capacity/tile full ones and one ragged one per instance
-    int64_t fill_blocks = capacity / a.tile + n_inst;
-    fill_blocks = fill_blocks < 1 ? 1 : fill_blocks > kFillBlocks ? kFillBlocks : fill_blocks;
-    hipLaunchKernelGGL(cs_fill_kernel, dim3((unsigned)fill_blocks), dim3(kFillThreads), 0, st, a, vec_ok);
+    int kshift = 0;
+    const int64_t tiles = (capacity + kFillThreads * 4 - 1) / (kFillThreads * 4);
+    while (kshift < kFillGranule && (tiles >> (kshift + 6)) > 0) ++kshift;
+    const int64_t group = (int64_t)8 << kshift;
+    for (int64_t tile0 = 0; tile0 < tiles; tile0 += kFillTiles) {
+        const int64_t n = tiles - tile0 < kFillTiles ? tiles - tile0 : kFillTiles;
+        hipLaunchKernelGGL(cs_fill_kernel<kFillThreads>, dim3((unsigned)((n + group - 1) / group * group)), dim3(kFillThreads), 0, st, a, vec_ok, kshift, tile0);
+    }
     return launch_status();
 }
 }  // namespace rs

@@ -40,7 +40,6 @@
 namespace rs {
 
 // ================================================================================ leading run
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kPfThreads = 256;
 constexpr int kPfTile = 16384;      // most chunk positions per workgroup iteration (16 x uint4 per thread)
 constexpr int kPfPass = kPfThreads * 4;   // positions one pass of the workgroup covers

@@ -49,7 +49,7 @@ static void *static_scratch()
 void launch_cs_count(const CsArgs &a, hipStream_t st);          // chunk_sort.hip
 int lpt_serial_after_leading_runs(const int64_t *chunk_off, const uint32_t *chunk_w, int64_t n_inst, int N, uint8_t *rail,
                                   int64_t *S, int64_t capacity, hipStream_t st);   // lpt_spray.hip
-void cs_ws_layout(int64_t n_inst, int64_t NF, size_t off[6]);  // chunk_sort.hip
+void cs_fill_args(CsArgs &a, const railsched_topo_t *h_topo, int64_t n_inst, void *ws);   // chunk_sort.hip
 
 constexpr int kSlThreads = 256;         // closed-form receive loads of large batches
 constexpr int kSsRun = 24;              // late chunks per run of one weight from which the chain goes run by run (lpt_runs_body)
@@ -123,7 +123,7 @@ __host__ __device__ constexpr int ss_rem_words(int NF) { return 256 * (T / 64 - 
 // Records of the full chunks p_lo .. p_hi - 1 of one instance, and the rails of those in the leading run (below `skip`), by the wavefronts 1 .. of
 // a workgroup that has the instance's flow starts in LDS.  marks: 256 words for each of them.
 template <int kSsThreads>
-__device__ __forceinline__ void fill_full(const CsArgs &a, const SsArgs &x, const unsigned *st_fs, const unsigned *st_cs, unsigned *marks, int64_t out0,
+__device__ __forceinline__ void fill_full(const CsArgs &a, const SsArgs &x, const unsigned *st_fs, const unsigned short *st_tb, unsigned *marks, int64_t out0,
                                           uint32_t skip, uint32_t p_lo, uint32_t p_hi)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -135,7 +135,7 @@ __device__ __forceinline__ void fill_full(const CsArgs &a, const SsArgs &x, cons
             const int j = last_le<uint32_t>(st_fs, a.NF, p);
             a.chunk_w[out0 + p] = cw;
             a.chunk_flow[out0 + p] = (uint32_t)j;
-            if (a.perm) a.perm[out0 + p] = st_cs[j] + (p - st_fs[j]);
+            if (a.perm) a.perm[out0 + p] = p + st_tb[j];
             if (p < skip) x.rail[out0 + p] = (uint8_t)(p % (uint32_t)N);
         }
         return;
@@ -168,7 +168,7 @@ __device__ __forceinline__ void fill_full(const CsArgs &a, const SsArgs &x, cons
         uint32_t r = x.nshift >= 0 ? (p & ((1u << x.nshift) - 1u)) : p % (uint32_t)N;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if (a.perm) pm[e] = st_cs[fl[e]] - st_fs[fl[e]] + p + e;
+            if (a.perm) pm[e] = p + e + st_tb[fl[e]];
             rr |= r << (8 * e);
             r = (r + 1 == (uint32_t)N) ? 0u : r + 1;
         }
@@ -188,7 +188,7 @@ __device__ __forceinline__ void fill_full(const CsArgs &a, const SsArgs &x, cons
         const int j = last_le<uint32_t>(st_fs, a.NF, p);
         a.chunk_w[out0 + p] = cw;
         a.chunk_flow[out0 + p] = (uint32_t)j;
-        if (a.perm) a.perm[out0 + p] = st_cs[j] + (p - st_fs[j]);
+        if (a.perm) a.perm[out0 + p] = p + st_tb[j];
         if (p < skip) x.rail[out0 + p] = (uint8_t)(p % (uint32_t)N);
     }
 }
@@ -212,7 +212,8 @@ template <int kSsThreads>
 __device__ __forceinline__ void ss_help(const CsArgs &a, const SsArgs &x, unsigned *lds)
 {
     const int tid = threadIdx.x, lane = tid & 63;
-    unsigned *st_fs = lds, *st_cs = st_fs + a.NF + 1, *marks = lds + (2 * a.NF + 1 + 3) / 4 * 4;
+    unsigned *st_fs = lds, *marks = lds + (a.NF + 1 + (a.NF + 1) / 2 + 3) / 4 * 4;
+    unsigned short *st_tb = reinterpret_cast<unsigned short *>(st_fs + a.NF + 1);
     // tiles of instance base + lane, its first record and its full chunks; `before` counts the records of the instances before `base`
     auto tiles_of = [&](int base, int64_t before, int64_t &out0, uint32_t &n_full, unsigned &tiles) {
         const int i = base + lane;
@@ -261,14 +262,15 @@ __device__ __forceinline__ void ss_help(const CsArgs &a, const SsArgs &x, unsign
             const unsigned t0 = lane_u32(first, l), tn = lane_u32(tiles, l);
             const unsigned to = t0 + tn < u1 ? t0 + tn : u1;             // this workgroup's tiles of the instance: u .. to - 1
             __syncthreads();                                             // the instance before is done with the starts
-            const uint32_t *fs = a.full_start + (int64_t)inst * a.NF, *cs = a.canon_start + (int64_t)inst * a.NF;
-            for (int i = tid; i < a.NF; i += kSsThreads) { st_fs[i] = fs[i]; st_cs[i] = cs[i]; }
+            const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
+            const uint16_t *tb = a.tails_before + (int64_t)inst * a.NF;
+            for (int i = tid; i < a.NF; i += kSsThreads) { st_fs[i] = fs[i]; st_tb[i] = tb[i]; }
             if (tid == 0) st_fs[a.NF] = 0xFFFFFFFFu;
             __syncthreads();
             const uint32_t own = ss_own_end(x, o, nf);
             const uint32_t p_lo = own + (u - t0) * kSsHelpTile;
             const uint32_t left = nf - p_lo, run = (to - u) * kSsHelpTile;
-            if (tid >= 64) fill_full<kSsThreads>(a, x, st_fs, st_cs, marks, o, nf - nf % (uint32_t)a.N, p_lo, p_lo + (left < run ? left : run));
+            if (tid >= 64) fill_full<kSsThreads>(a, x, st_fs, st_tb, marks, o, nf - nf % (uint32_t)a.N, p_lo, p_lo + (left < run ? left : run));
             u = to;
         }
     }
@@ -281,14 +283,14 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
     __shared__ int64_t sh_red[2][kSsThreads / 64];
     __shared__ unsigned sh_runs;
     __shared__ unsigned sh_sort[kTailShared];
-    // LDS: hist / late_w | rem[NF] / marks | bins[G] u64 | st_fs[NF+1] | st_cs[NF] | idx_a[NF] idx_b[NF] u16 | late_rail[NF+64] u8
+    // LDS: hist / late_w | rem[NF] / marks | bins[G] u64 | st_fs[NF+1] | st_tb[NF] idx_a[NF] idx_b[NF] u16 | late_rail[NF+64] u8
     unsigned *hist = reinterpret_cast<unsigned *>(ss_lds64);             // read 16 bytes at a time
     unsigned *late_w = hist;
     unsigned *rem = hist + ss_hist_words<kSsThreads>(a.NF);              // later the record writers' marks, 16-byte aligned
     unsigned long long *bins = reinterpret_cast<unsigned long long *>(rem + ss_rem_words<kSsThreads>(a.NF));
     unsigned *st_fs = reinterpret_cast<unsigned *>(bins + a.G);
-    unsigned *st_cs = st_fs + a.NF + 1;
-    unsigned short *idx_a = reinterpret_cast<unsigned short *>(st_cs + a.NF);
+    unsigned short *st_tb = reinterpret_cast<unsigned short *>(st_fs + a.NF + 1);
+    unsigned short *idx_a = st_tb + a.NF;
     unsigned short *idx_b = idx_a + a.NF;
     uint8_t *late_rail = reinterpret_cast<uint8_t *>(idx_b + a.NF);
 
@@ -317,7 +319,7 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
     // ---- the tails; while their flows are on the way, the offsets (chunks of the instances before this one, and of all) and this
     // instance's flow starts
     int64_t before = 0, total = 0;
-    uint32_t n_full = 0, n_all = 0;
+    uint32_t n_full = 0;
     int nt = 0;
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
     const unsigned short *sorted = tail_sort_block<kSsThreads, true>(a, rows, k, rem, hist, idx_a, idx_b, sh_sort, nt, [&] {
@@ -327,10 +329,9 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
             before += i < inst ? c : 0;
         }
         n_full = (uint32_t)a.cnt_full[inst];
-        n_all = (uint32_t)a.cnt_all[inst];
         const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
-        const uint32_t *cs = a.canon_start + (int64_t)inst * a.NF;
-        for (int i = tid; i < a.NF; i += kSsThreads) { st_fs[i] = fs[i]; st_cs[i] = cs[i]; }
+        const uint16_t *tb = a.tails_before + (int64_t)inst * a.NF;
+        for (int i = tid; i < a.NF; i += kSsThreads) { st_fs[i] = fs[i]; st_tb[i] = tb[i]; }
         for (int i = tid; i < a.G; i += kSsThreads) bins[i] = 0;
         if (tid == 0) { st_fs[a.NF] = 0xFFFFFFFFu; sh_runs = 0; }        // nothing starts behind the last flow
 #pragma unroll
@@ -400,10 +401,10 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
             const int f = sorted[i];
             a.chunk_w[tail0 + i] = late_w[late_full + i];
             a.chunk_flow[tail0 + i] = (uint32_t)f;
-            // the tail is its flow's last chunk: one before the canonical start of the next flow
-            if (a.perm) a.perm[tail0 + i] = (f + 1 < a.NF ? st_cs[f + 1] : n_all) - 1u;
+            // the tail is its flow's last chunk: the full chunks up to the next flow and the tails before it come first
+            if (a.perm) a.perm[tail0 + i] = (f + 1 < a.NF ? st_fs[f + 1] : n_full) + st_tb[f];
         }
-        fill_full<kSsThreads>(a, x, st_fs, st_cs, rem, out0, skip, 0u, ss_own_end(x, out0, n_full));
+        fill_full<kSsThreads>(a, x, st_fs, st_tb, rem, out0, skip, 0u, ss_own_end(x, out0, n_full));
         add_leading_run(a, x, st_fs, n_full, skip, bins, t, T);
     }
     __syncthreads();
@@ -456,8 +457,8 @@ __global__ __launch_bounds__(kSlThreads) void sl_recv_kernel(CsArgs a, SsArgs x)
 template <int GW, int T>
 static int launch_ss_t(const CsArgs &a, const SsArgs &x, hipStream_t st)
 {
-    const size_t lds = sizeof(unsigned long long) * (size_t)a.G + sizeof(unsigned) * (size_t)(2 * a.NF + 1 + ss_rem_words<T>(a.NF) + ss_hist_words<T>(a.NF)) +
-                       2 * sizeof(unsigned short) * (size_t)a.NF + (size_t)a.NF + 64 + 16;
+    const size_t lds = sizeof(unsigned long long) * (size_t)a.G + sizeof(unsigned) * (size_t)(a.NF + 1 + ss_rem_words<T>(a.NF) + ss_hist_words<T>(a.NF)) +
+                       3 * sizeof(unsigned short) * (size_t)a.NF + (size_t)a.NF + 64 + 16;
     if (lds > 48 * 1024) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(ss_instance_kernel<GW, T>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds) != hipSuccess)
@@ -542,24 +543,11 @@ static int schedule_run(const int64_t *D1, int32_t batch, const railsched_topo_t
         return launch_eval_reduce(e, batch, st);
     }
 
-    size_t off[6];
-    cs_ws_layout(n_inst, NF, off);
     CsArgs a;
     a.D1 = D1; a.chunk_off = chunk_off; a.chunk_w = chunk_w; a.chunk_flow = chunk_flow; a.perm = perm;
     a.capacity = capacity;
-    a.tile = 1024;                                  // unused here
-    a.cnt_all = reinterpret_cast<int64_t *>(w8 + off[0]);
-    a.cnt_full = reinterpret_cast<int64_t *>(w8 + off[1]);
-    a.tile_off = reinterpret_cast<int64_t *>(w8 + off[2]);
-    a.full_start = reinterpret_cast<uint32_t *>(w8 + off[3]);
-    a.canon_start = reinterpret_cast<uint32_t *>(w8 + off[4]);
-    a.C = h_topo->chunk_bytes;
-    a.cshift = is_pow2(a.C) ? ilog2(a.C) : -1;
-    a.M = (int32_t)M; a.N = (int32_t)N; a.G = (int32_t)G; a.NF = (int32_t)NF; a.intra = h_topo->include_intra_node;
-    a.n_inst = (int32_t)n_inst;
-    a.rail = nullptr; a.nmask = -1; a.run_end = nullptr;   // unused by the count kernel
-    a.gmask = is_pow2(G) ? (int32_t)G - 1 : -1;
-    a.nshift = is_pow2(N) ? ilog2(N) : -1;
+    a.rail = nullptr; a.run_end = nullptr;          // unused by the count kernel
+    cs_fill_args(a, h_topo, n_inst, w8);
     launch_cs_count(a, st);
     if (int rc = launch_status()) return rc;
 

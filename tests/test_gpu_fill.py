@@ -1,0 +1,60 @@
+"""The record fill at the edges of its windows of 256 records and of its entries, against the CPU oracle: whole numbers, compared exactly."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_19262_amd as rs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("M,N,B,C,kind", [
+    (2, 4, 700, 4096, "tiny"),          # dozens of instances in a window, some of tails only, some empty
+    (2, 2, 900, 4096, "tails"),         # no full chunk anywhere
+    (40, 2, 30, 4096, "empty"),         # most instances without a record
+    (2, 1, 1, 256, "long"),             # four flows, 60 000 records: entries far apart
+    (3, 3, 2, 1000, "long"),            # nothing a power of two
+    (16, 8, 1, 64, "dense"),            # a flow starts at every other record: several rounds of 64 starts in a window
+    (33, 5, 3, 4096, "gaps"),           # hundreds of flows without a full chunk between long ones
+    (130, 8, 2, 65536, "dense"),        # 8320 flows an instance
+])
+@pytest.mark.parametrize("shift", [0, 1])                            # record arrays on a 16-byte boundary and off it
+def test_fill(M, N, B, C, kind, shift):
+    G = M * N
+    rng = np.random.default_rng(M * 100 + N)
+    shape = (B, G, G)
+    if kind == "tiny":
+        D1n = np.where(rng.random(shape) < 0.6, 0, rng.integers(0, 3 * C, size=shape))
+        D1n[::7] = 0
+        D1n[3::7] %= C
+    elif kind == "tails":
+        D1n = rng.integers(0, C, size=shape)
+    elif kind == "empty":
+        D1n = np.where(rng.random((B, G, 1)) < 0.97, 0, rng.integers(0, 40 * C, size=shape))
+    elif kind == "long":
+        D1n = rng.integers(0, 60000 // max(1, G // 2) * C, size=shape)
+    elif kind == "dense":
+        D1n = rng.integers(0, 4 * C, size=shape)
+    else:
+        D1n = np.where(rng.random(shape) < 0.004, rng.integers(300 * C, 900 * C, size=shape), rng.integers(0, 2, size=shape) * (C - 1))
+    D1n = D1n.astype(np.int64)
+    off, w, flow, perm = oracle.chunk_sort_batch(D1n, M, N, C)
+    n = int(off[-1])
+    topo = rs.Topo(M, N, C)
+    D1 = torch.from_numpy(D1n).to(DEV)
+    for extra, want_perm in ((0, True), (5000, True), (3, False)):  # no room to spare, and some
+        cap = n + extra
+        recs = [torch.full((cap + 9,), -7, dtype=torch.int32, device=DEV) for _ in range(3)]
+        o = torch.empty(B * M + 1, dtype=torch.int64, device=DEV)
+        arrays = [r[shift:shift + cap] for r in recs]
+        rs.chunk_sort(D1, topo, capacity=cap, out=(o, arrays[0], arrays[1], arrays[2] if want_perm else None))
+        assert np.array_equal(o.cpu().numpy(), off)
+        for name, r, ref in zip(("w", "flow", "perm"), recs, (w, flow, perm)):
+            h = r.cpu().numpy()
+            if name == "perm" and not want_perm:
+                assert (h == -7).all()
+                continue
+            assert np.array_equal(h[shift:shift + n].view(np.uint32), ref), (name, cap)
+            assert (h[:shift] == -7).all() and (h[shift + n:] == -7).all(), name    # nothing outside the records
