@@ -15,8 +15,10 @@ struct CsArgs {
     uint32_t *full_start;        // [n_inst][NF] full chunks of the instance before flow f
     uint16_t *tails_before;      // [n_inst][NF] tails before flow f (at most NF <= 16384); canonical start of the flow = the two together
     uint2 *entries;              // [n_entries] (instance, flow) at every 2^s-th record, where the record fill starts its searches (fill_entry_shift)
-    int64_t n_entries;
+    int64_t n_entries;           // 0: none, the fill searches
     int64_t C;
+    uint64_t cinv;       // (2^64 - 1) / C
+    uint32_t ginv;       // 2^32 / G, rounded up (G > 1)
     int32_t cshift;      // >= 0 when C is a power of two
     int32_t M, N, G, NF, intra;
     int32_t n_inst;
@@ -47,6 +49,50 @@ __device__ __forceinline__ int64_t flow_bytes(const CsArgs &a, const int64_t *ro
         if (node == k) return 0;
     }
     return rows[f];
+}
+
+// The flows f0, f0 + step, ... (V of them) of instance (b, k), 0 behind the last flow and for destinations inside node k unless intra-node traffic is kept.
+// Without branches, so that all loads are in flight together: what does not count is read and dropped.
+template <int V>
+__device__ __forceinline__ void load_flows(const CsArgs &a, const int64_t *rows, int k, int f0, int step, int64_t (&bytes)[V])
+{
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        const int f = f0 + step * j;
+        bytes[j] = rows[f < a.NF ? f : a.NF - 1];
+    }
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        const unsigned f = (unsigned)(f0 + step * j);
+        // f / G by the reciprocal is exact: f and G are at most 2^14, so what rounding up adds stays below one part in G
+        const unsigned dst = f - (a.G > 1 ? __umulhi(f, a.ginv) : f) * (unsigned)a.G;
+        const bool inside = !a.intra && dst - (unsigned)(k * a.N) < (unsigned)a.N;
+        bytes[j] = (int)f < a.NF && !inside ? bytes[j] : 0;
+    }
+}
+
+template <int V>
+__device__ __forceinline__ void split_flows(const CsArgs &a, const int64_t (&bytes)[V], uint32_t (&q)[V], uint32_t (&r)[V])
+{
+    if (a.cshift >= 0) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const int64_t B = bytes[j] < 0 ? 0 : bytes[j];
+            q[j] = (uint32_t)(B >> a.cshift);
+            r[j] = (uint32_t)B & (uint32_t)(a.C - 1);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            // with the reciprocal rounded down the quotient comes out right or one too small
+            const uint64_t B = bytes[j] < 0 ? 0 : (uint64_t)bytes[j];
+            uint64_t qq = __umul64hi(B, a.cinv);
+            uint64_t rr = B - qq * (uint64_t)a.C;
+            if (rr >= (uint64_t)a.C) { rr -= (uint64_t)a.C; ++qq; }
+            q[j] = (uint32_t)qq;
+            r[j] = (uint32_t)rr;
+        }
+    }
 }
 
 // v of the lane the DPP control points at, 0 where there is none (or where row_mask switches the row off)

@@ -1,4 +1,4 @@
-"""The record fill at the edges of its windows of 256 records and of its entries, against the CPU oracle: whole numbers, compared exactly."""
+"""Tail sort and record fill at the edges of flows a thread, of windows of 256 records and of entries, against the CPU oracle: whole numbers, compared exactly."""
 import numpy as np
 import pytest
 import torch
@@ -18,7 +18,11 @@ DEV = "cuda:0"
     (3, 3, 2, 1000, "long"),            # nothing a power of two
     (16, 8, 1, 64, "dense"),            # a flow starts at every other record: several rounds of 64 starts in a window
     (33, 5, 3, 4096, "gaps"),           # hundreds of flows without a full chunk between long ones
-    (130, 8, 2, 65536, "dense"),        # 8320 flows an instance
+    (8, 8, 3, 4096, "dense"),           # 512 flows: the most of two a thread of the tail sort
+    (24, 8, 3, 100_000, "dense"),       # 1536, tails of 17 bits in three passes
+    (64, 8, 1, 65536, "dense"),         # 4096: the most of four a thread
+    (130, 8, 2, 65536, "dense"),        # 8320
+    (4, 64, 2, 1000, "dense"),          # 16384: the most there can be
 ])
 @pytest.mark.parametrize("shift", [0, 1])                            # record arrays on a 16-byte boundary and off it
 def test_fill(M, N, B, C, kind, shift):
@@ -44,7 +48,7 @@ def test_fill(M, N, B, C, kind, shift):
     n = int(off[-1])
     topo = rs.Topo(M, N, C)
     D1 = torch.from_numpy(D1n).to(DEV)
-    for extra, want_perm in ((0, True), (5000, True), (3, False)):  # no room to spare, and some
+    for extra, want_perm in ((0, True), (1 << 21, True), (3, False)):    # no room to spare, and so much that there are entries
         cap = n + extra
         recs = [torch.full((cap + 9,), -7, dtype=torch.int32, device=DEV) for _ in range(3)]
         o = torch.empty(B * M + 1, dtype=torch.int64, device=DEV)
