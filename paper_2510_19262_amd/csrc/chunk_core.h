@@ -122,8 +122,6 @@ __device__ __forceinline__ unsigned wave_exscan(unsigned v, unsigned &total)
 // the asm statement keeps the compiler from moving LDS accesses across it.
 __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 // Maximum over the lanes before the caller's, and `first` (a lower bound of all) for lane 0.
 __device__ __forceinline__ unsigned wave_max_before(unsigned inc, unsigned first)
 {

@@ -43,6 +43,8 @@ inline int ilog2(int64_t x)
 }
 
 #if defined(__HIPCC__)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // what the streaming loads and stores take
+
 // ---- cross-lane exchange: lane i reads the lane that differs from it at "distance" OFF.
 // 1 and 2 swap inside quads, 4 mirrors 8-lane halves, 8 mirrors 16-lane rows, 16 swaps rows through
 // the LDS crossbar, 32 swaps wave halves.  After steps 1..OFF every group of 2*OFF lanes that
