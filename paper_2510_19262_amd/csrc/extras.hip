@@ -159,13 +159,15 @@ __global__ __launch_bounds__(kPolThreads) void policy_kernel(PolArgs a)
 // counts.  Both tile kernels give a wavefront a tile.
 //   packed (N <= 16, P a power of two up to 128, rail and port 16-byte aligned): a lane takes 16 consecutive chunks per 16-byte load
 //     and keeps the N counts as bytes of one or two 64-bit registers; P <= 128 leaves a byte room for a start below P and 16
-//     increments, and all sums modulo P come out right in wider fields.  120 M chunks, N = 8, P = 8: 40 us for the
-//     counts and 68 for the ports
+//     increments, and all sums modulo P come out right in wider fields.  Steps of 1024 chunks whose rails go round and round need no
+//     counting.  120 M chunks, N = 8, P = 8: 32 us for the counts and 50 for the ports, 40 and 70 where everything is counted
 //   by ballot (everything else): 64 chunks at a time, lanes with the same rail find each other by ballot matching, rank = running
 //     count + number of lower lanes with that rail: 130 us for the counts and 200 for the ports of the same chunks.
 constexpr int kPortTile = 4096;
 constexpr int kPortWaves = 4;
-constexpr int kPortBlocks = 2048;
+// Most workgroups of a tile kernel: a tile a wavefront and exit up to 256 M chunks (2048 that go on: 86 us for the whole call on those 120 M chunks, 80 so; 991 M 725 / 620;
+// four consecutive tiles a wavefront with one search 95 / 829).
+constexpr int kPortBlocks = 16384;
 
 struct PortArgs {
     const int64_t *chunk_off;
@@ -176,6 +178,7 @@ struct PortArgs {
     int64_t max_tiles;
     int64_t capacity;           // records rail and port hold
     int32_t n_inst, N, P, pmask, rail_bits;
+    int32_t nmask;              // N - 1 when N is a power of two up to 16, else -1
 };
 
 // first position of an instance's first tile
@@ -193,6 +196,40 @@ __device__ __forceinline__ void port_widen(const unsigned long long (&c)[NW], un
         out[4 * w + 2] = (hi & 0xFFu) | ((hi << 8) & 0xFF0000u);
         out[4 * w + 3] = ((hi >> 16) & 0xFFu) | ((hi >> 8) & 0xFF0000u);
     }
+}
+
+// The rails of a leading run, and of any run of one weight from level loads, go round and round.  A lane whose 16 chunks do (N a power of two up to 16: every
+// rail 16 / N times, whichever comes first) needs no counting; `step` says that all lanes of a wavefront do.
+__device__ __forceinline__ bool port_cyclic(const uint4 &x, unsigned nmask)
+{
+    const unsigned all = nmask * 0x01010101u, r0 = x.x & 0xFFu;
+    auto want = [&](unsigned d) { return (0x03020100u + ((r0 + 4u * d) & nmask) * 0x01010101u) & all; };
+    return x.x == want(0) && x.y == want(1) && x.z == want(2) && x.w == want(3);
+}
+
+// Ports of 16 such chunks: run[r] = earlier chunks of rail r modulo P, a byte each; element j goes to rail (r0 + j) mod N and is that rail's (j / N)-th here.
+template <int NW>
+__device__ __forceinline__ void port_cyclic_out(const unsigned long long (&run)[NW], unsigned r0, int N, unsigned pm, uint32_t (&out)[4])
+{
+    unsigned e[4];                                  // the bytes of run, round and round
+    e[0] = (unsigned)run[0]; e[1] = (unsigned)(run[0] >> 32);
+    if constexpr (NW == 2) { e[2] = (unsigned)run[1]; e[3] = (unsigned)(run[1] >> 32); }
+    if (N < 8) {
+        if (N == 1) e[0] = (e[0] & 0xFFu) * 0x01010101u;
+        if (N == 2) e[0] = (e[0] & 0xFFFFu) * 0x00010001u;
+        e[1] = e[0];
+    }
+    if (N <= 8) { e[2] = e[0]; e[3] = e[1]; }
+    const unsigned k = r0 >> 2;
+    const unsigned a0 = k & 1 ? e[1] : e[0], a1 = k & 1 ? e[2] : e[1], a2 = k & 1 ? e[3] : e[2], a3 = k & 1 ? e[0] : e[3];
+    const unsigned b0 = k & 2 ? a2 : a0, b1 = k & 2 ? a3 : a1, b2 = k & 2 ? a0 : a2, b3 = k & 2 ? a1 : a3;
+    // turns before element 4 d + e, a byte each: bytes stay below 128 + 16
+    const unsigned t0 = N == 1 ? 0x03020100u : N == 2 ? 0x01010000u : 0u, td = N == 1 ? 4u : N == 2 ? 2u : N == 4 ? 1u : 0u;
+    const unsigned t2 = N == 8 ? 0x01010101u : 2u * td * 0x01010101u, t1 = td * 0x01010101u, p4 = pm * 0x01010101u;
+    out[0] = (__builtin_amdgcn_alignbyte(b1, b0, r0 & 3u) + t0) & p4;
+    out[1] = (__builtin_amdgcn_alignbyte(b2, b1, r0 & 3u) + t0 + t1) & p4;
+    out[2] = (__builtin_amdgcn_alignbyte(b3, b2, r0 & 3u) + t0 + t2) & p4;
+    out[3] = (__builtin_amdgcn_alignbyte(b0, b3, r0 & 3u) + t0 + t2 + t1) & p4;
 }
 
 // NW: 64-bit registers of byte counters (8 rails each)
@@ -234,9 +271,11 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a
         uint32_t *c = a.cnt + u * a.N;
         if constexpr (!ASSIGN) {
             unsigned long long ctr[NW] = {};                        // at most 80 per byte
+            unsigned turns = 0;                                     // steps that go round and round: 1024 / N of every rail
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) {
                 if (beg + s * 1024 >= hi) break;                    // wavefront-uniform: an instance's last tile may be short, a small instance has no other
+                if (a.nmask >= 0 && __ballot(!port_cyclic(x[s], (unsigned)a.nmask)) == 0ull) { ++turns; continue; }
                 const uint32_t w[4] = {x[s].x, x[s].y, x[s].z, x[s].w};
 #pragma unroll
                 for (int j = 0; j < 16; ++j) {
@@ -246,6 +285,10 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a
                     for (int q = 0; q < NW; ++q) ctr[q] += (NW == 1 || (r >> 3) == (uint32_t)q) ? one : 0ull;
                 }
             }
+            if (turns * 1024u == (unsigned)(hi - beg)) {            // nothing else in the tile
+                if (lane < a.N) c[lane] = turns * (1024u / (unsigned)a.N);
+                continue;
+            }
             unsigned f[4 * NW];
             port_widen<NW>(ctr, f);                                 // at most 4111 per field, summed over the lanes
 #pragma unroll
@@ -253,8 +296,8 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a
                 unsigned v = f[q];
 #pragma unroll
                 for (int d = 32; d >= 1; d >>= 1) v += (unsigned)__shfl_xor((int)v, d);
-                if (lane == 2 * q && lane < a.N) c[lane] = v & 0xFFFFu;
-                if (lane == 2 * q + 1 && lane < a.N) c[lane] = v >> 16;
+                if (lane == 2 * q && lane < a.N) c[lane] = (v & 0xFFFFu) + turns * (1024u / (unsigned)a.N);
+                if (lane == 2 * q + 1 && lane < a.N) c[lane] = (v >> 16) + turns * (1024u / (unsigned)a.N);
             }
         } else {
             // A 64-bit shift by the last register a wavefront has goes wrong when others share its SIMD: 88 registers, amount in v87, and one chunk of
@@ -262,6 +305,7 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a
             // (by 32-bit halves instead, without such shifts: 850 us for three stages and ports of 120 M chunks, 820 so).
             asm volatile("; v95 is not used" ::: "v95");
             const unsigned pm = (unsigned)a.P - 1u, pm2 = pm | (pm << 16);
+            const unsigned per_lane = a.nmask >= 0 ? 16u / (unsigned)a.N : 0u;          // of every rail, where rails go round and round
             unsigned start[4 * NW];                                 // counts before the step modulo P, 16-bit fields
 #pragma unroll
             for (int q = 0; q < 4 * NW; ++q) {
@@ -272,22 +316,32 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a
             for (int s = 0; s < STEPS; ++s) {
                 if (beg + s * 1024 >= hi) break;
                 const uint32_t w[4] = {x[s].x, x[s].y, x[s].z, x[s].w};
-                unsigned long long ctr[NW] = {};
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const uint32_t r = (w[j >> 2] >> (8 * (j & 3))) & 0xFFu;
-                    const unsigned long long one = (r < (uint32_t)a.N ? 1ull : 0ull) << ((r & 7u) * 8u);
-#pragma unroll
-                    for (int q = 0; q < NW; ++q) ctr[q] += (NW == 1 || (r >> 3) == (uint32_t)q) ? one : 0ull;
-                }
                 unsigned f[4 * NW];
-                port_widen<NW>(ctr, f);
+                const bool cyclic = a.nmask >= 0 && __ballot(!port_cyclic(x[s], (unsigned)a.nmask)) == 0ull;
+                if (cyclic) {
+                    const unsigned mine = (unsigned)lane * per_lane, total = 64u * per_lane;
 #pragma unroll
-                for (int q = 0; q < 4 * NW; ++q) {
-                    unsigned total;
-                    const unsigned before = wave_exscan(f[q], total);           // at most 1024 per field
-                    f[q] = (start[q] + before) & pm2;
-                    start[q] = (start[q] + total) & pm2;
+                    for (int q = 0; q < 4 * NW; ++q) {
+                        f[q] = (start[q] + (mine | mine << 16)) & pm2;
+                        start[q] = (start[q] + (total | total << 16)) & pm2;
+                    }
+                } else {
+                    unsigned long long ctr[NW] = {};
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) {
+                        const uint32_t r = (w[j >> 2] >> (8 * (j & 3))) & 0xFFu;
+                        const unsigned long long one = (r < (uint32_t)a.N ? 1ull : 0ull) << ((r & 7u) * 8u);
+#pragma unroll
+                        for (int q = 0; q < NW; ++q) ctr[q] += (NW == 1 || (r >> 3) == (uint32_t)q) ? one : 0ull;
+                    }
+                    port_widen<NW>(ctr, f);
+#pragma unroll
+                    for (int q = 0; q < 4 * NW; ++q) {
+                        unsigned total;
+                        const unsigned before = wave_exscan(f[q], total);       // at most 1024 per field
+                        f[q] = (start[q] + before) & pm2;
+                        start[q] = (start[q] + total) & pm2;
+                    }
                 }
                 unsigned long long run[NW];                         // the lane's counts modulo P, a byte each
 #pragma unroll
@@ -297,22 +351,26 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a
                     run[q] = (unsigned long long)l | ((unsigned long long)h << 32);
                 }
                 uint32_t out[4] = {0, 0, 0, 0};
+                if (cyclic) {
+                    port_cyclic_out<NW>(run, w[0] & 0xFFu, a.N, pm, out);
+                } else {
 #pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const uint32_t r = (w[j >> 2] >> (8 * (j & 3))) & 0xFFu;
-                    const bool ok = r < (uint32_t)a.N;
-                    const unsigned sh = (r & 7u) * 8u;
-                    const unsigned long long one = (ok ? 1ull : 0ull) << sh;
-                    unsigned long long cur = run[0];
-                    if constexpr (NW == 2) cur = (r >> 3) == 1u ? run[1] : run[0];
-                    const uint32_t port = ok ? (uint32_t)(cur >> sh) & pm : 0u;
-                    out[j >> 2] |= port << (8 * (j & 3));
+                    for (int j = 0; j < 16; ++j) {
+                        const uint32_t r = (w[j >> 2] >> (8 * (j & 3))) & 0xFFu;
+                        const bool ok = r < (uint32_t)a.N;
+                        const unsigned sh = (r & 7u) * 8u;
+                        const unsigned long long one = (ok ? 1ull : 0ull) << sh;
+                        unsigned long long cur = run[0];
+                        if constexpr (NW == 2) cur = (r >> 3) == 1u ? run[1] : run[0];
+                        const uint32_t port = ok ? (uint32_t)(cur >> sh) & pm : 0u;
+                        out[j >> 2] |= port << (8 * (j & 3));
 #pragma unroll
-                    for (int q = 0; q < NW; ++q) run[q] += (NW == 1 || (r >> 3) == (uint32_t)q) ? one : 0ull;
+                        for (int q = 0; q < NW; ++q) run[q] += (NW == 1 || (r >> 3) == (uint32_t)q) ? one : 0ull;
+                    }
                 }
                 const int64_t i = beg + s * 1024 + lane * 16;
                 if (i >= lo && i + 16 <= hi) {
-                    *reinterpret_cast<uint4 *>(a.port + i) = make_uint4(out[0], out[1], out[2], out[3]);
+                    __builtin_nontemporal_store(u32x4{out[0], out[1], out[2], out[3]}, reinterpret_cast<u32x4 *>(a.port + i));
                 } else if (i < hi && i + 16 > lo) {
 #pragma unroll
                     for (int j = 0; j < 16; ++j) {
@@ -516,13 +574,15 @@ extern "C" int railsched_port_round_robin(const int64_t *chunk_off, const uint8_
     a.max_tiles = max_tiles; a.capacity = capacity;
     a.n_inst = (int32_t)n_inst; a.N = h_topo->rails; a.P = ports; a.pmask = is_pow2(ports) ? ports - 1 : -1;
     a.rail_bits = a.N > 1 ? ilog2(a.N - 1) + 1 : 0;
+    a.nmask = a.N <= 16 && is_pow2(a.N) ? a.N - 1 : -1;
     hipLaunchKernelGGL(port_tiles_kernel, dim3(1), dim3(1024), 0, st, a);
     if (int rc = launch_status()) return rc;
     // a few hundred chunks are all first and last ones of their instances, which the packed kernels take byte by byte (161 chunks: 12 us, 9 by ballot)
     const bool packed = capacity >= 1024 && a.N <= 16 && is_pow2(ports) && ports <= 128 && reinterpret_cast<uintptr_t>(rail) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(port) % 16 == 0;
     auto tiles = [&](auto by_ballot, auto one, auto two) {
-        hipLaunchKernelGGL(packed ? (a.N <= 8 ? one : two) : by_ballot, dim3(kPortBlocks), dim3(64 * kPortWaves), 0, st, a);
+        const int64_t want = (max_tiles + kPortWaves - 1) / kPortWaves;
+        hipLaunchKernelGGL(packed ? (a.N <= 8 ? one : two) : by_ballot, dim3((unsigned)(want < kPortBlocks ? want : kPortBlocks)), dim3(64 * kPortWaves), 0, st, a);
         return launch_status();
     };
     if (int rc = tiles(port_tile_kernel<false>, port_packed_kernel<false, 1>, port_packed_kernel<false, 2>)) return rc;
