@@ -25,6 +25,7 @@ struct CsArgs {
     int32_t nmask;       // N - 1 when N is a power of two, else -1
     uint8_t *rail;       // when set, the fill also writes the rails of every instance's leading run (see cs_fill_kernel)
     int32_t gmask, nshift;   // G - 1 and log2 N when G / N are powers of two, else -1
+    int64_t *clear;      // when set, the counts' kernel clears clear[inst * N ..  + N - 1] (the receive loads that the instances then add to)
     int64_t *run_end;    // when set, run_end[inst * N] receives the length of every instance's leading run of full chunks
 };
 

@@ -43,6 +43,7 @@ __global__ __launch_bounds__(T) void cs_count_kernel(CsArgs a)
     const unsigned long long lt = (1ull << lane) - 1ull;
     unsigned carry_q = 0, carry_c = 0;
     int64_t n_full = 0;
+    if (a.clear && tid < a.N) a.clear[(int64_t)inst * a.N + tid] = 0;
     for (int f0 = 0; f0 < a.NF; f0 += U * T) {
         int64_t bytes[U];                           // all of a round's loads in flight before the scans, which chain
         uint32_t qs[U], rs[U];
@@ -683,6 +684,7 @@ int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int
     a.capacity = capacity;
     a.rail = rail;
     a.run_end = run_end;
+    a.clear = nullptr;
     fill_args(a, h_topo, n_inst, ws);
     // Few records of instances of few flows are written as fast by wavefronts that search for their instance and go through its flows (scan / fill in us
     // with entries and without, 1672 instances of 152 flows 7.2 / 9.4, 4.3 / 10.0; 1457 of 775 flows 10.7 / 3.2, 5.0 / 3.5); a count query needs none.

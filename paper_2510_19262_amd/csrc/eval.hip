@@ -10,7 +10,7 @@
 // the workgroups of one XCD (us for the evaluation, neither / streaming / both: 120 M records of 256 GPUs 198 / 179 / 178, one matrix of 1024
 // GPUs, 991 M records, 1665 / 1521 / 1364; 6.0 and 6.5 TB/s).  Copies, threads a workgroup and loads in flight do not matter.
 // Kernel 2: one workgroup per matrix adds the slots and derives the statistics from S (as produced by
-// stage 4) and R.  No global atomics anywhere; all sums are integer, so their order cannot matter.
+// stage 4) and R.  No global atomics here; all sums are integer, so their order cannot matter.
 #include "common.h"
 #include "eval_core.h"
 
@@ -99,10 +99,11 @@ __global__ __launch_bounds__(256) void eval_sum_kernel(EvArgs a)
     if (wave == 0 && i < a.G) a.R[(int64_t)b * a.G + i] = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
 }
 
-// SUM: the receive bins are summed here; otherwise eval_sum_kernel has already written R.
+// SUM: the receive bins are summed here; otherwise R is there (eval_sum_kernel, or the one-call scheduler's instances).
 // Latency bound (one workgroup per matrix): bins are taken in chunks of whole nodes, a chunk's slots are read with all
 // threads' loads in flight (groups of threads take every groups-th slot, eight at a time), and the per-node sums come
-// from LDS.  64 slots of 512 bins, one matrix: 20-26 us when 64 bins at a time were summed between two barriers and the
+// from LDS; the final maxima and the sum go through as many lanes as there are nodes or slots, and through LDS only beyond 64 (one matrix of 16 GPUs 4.1 -> 3.4 us,
+// of 512 with R there 7.1 -> 6.1).  64 slots of 512 bins, one matrix: 20-26 us when 64 bins at a time were summed between two barriers and the
 // nodes read back one load after the other, 12 now.
 template <int THREADS, bool SUM>
 __global__ __launch_bounds__(THREADS) void eval_reduce_kernel(EvArgs a)
@@ -115,6 +116,7 @@ __global__ __launch_bounds__(THREADS) void eval_reduce_kernel(EvArgs a)
     const int64_t *slots = a.partial + (int64_t)b * a.slices * (a.G + 1);
     int64_t *Rb = a.R + (int64_t)b * a.G;
     const int64_t *Sb = a.S + (int64_t)b * a.G;
+    const int64_t chunks = a.chunk_off[(int64_t)(b + 1) * a.M] - a.chunk_off[(int64_t)b * a.M];
     if (a.chunk_off[a.n_inst] > a.capacity) {         // more chunks than the record arrays hold: nothing was read, say so
         for (int i = tid; i < a.G; i += THREADS) Rb[i] = -1;
         if (tid < 8) a.stats[(int64_t)b * 8 + tid] = -1;
@@ -180,27 +182,34 @@ __global__ __launch_bounds__(THREADS) void eval_reduce_kernel(EvArgs a)
         }
         __syncthreads();                              // the nodes have been read
     }
-    // five maxima and one sum, together
+    // five maxima and one sum, together; nodes and slots sit in the first lanes, mostly of the first wavefront
+    const int used = a.M > a.slices ? a.M : a.slices;
+    int width = 1;
+    while (width < used && width < 64) width *= 2;
     int64_t v[6] = {max_s, max_r, lb, wmax, spread, total};
+    auto combine = [&](int from) {
+#pragma unroll 1
+        for (int d = from / 2; d >= 1; d >>= 1) {
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
+            for (int j = 0; j < 6; ++j) {
+                const int64_t o = __shfl_xor(v[j], d);
+                v[j] = j == 5 ? v[j] + o : (o > v[j] ? o : v[j]);
+            }
+        }
+    };
+    combine(width);
+    if (used > 64) {
+        if (lane == 0)
 #pragma unroll
-        for (int j = 0; j < 6; ++j) {
-            const int64_t o = __shfl_xor(v[j], d);
-            v[j] = j == 5 ? v[j] + o : (o > v[j] ? o : v[j]);
+            for (int j = 0; j < 6; ++j) sh[j][wave] = v[j];
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int j = 0; j < 6; ++j) v[j] = lane < WAVES ? sh[j][lane] : 0;   // none of them is below 0
+            combine(WAVES);
         }
     }
-    if (lane == 0)
-#pragma unroll
-        for (int j = 0; j < 6; ++j) sh[j][wave] = v[j];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int j = 0; j < 6; ++j) {
-            int64_t r = sh[j][0];
-            for (int w = 1; w < WAVES; ++w) r = j == 5 ? r + sh[j][w] : (sh[j][w] > r ? sh[j][w] : r);
-            v[j] = r;
-        }
+    if (tid == 0) {
         int64_t *st = a.stats + (int64_t)b * 8;
         st[0] = v[0] > v[1] ? v[0] : v[1];
         st[1] = v[0];
@@ -208,13 +217,18 @@ __global__ __launch_bounds__(THREADS) void eval_reduce_kernel(EvArgs a)
         st[3] = v[2] > v[3] ? v[2] : v[3];
         st[4] = v[5];
         st[5] = v[3];
-        st[6] = a.chunk_off[(int64_t)(b + 1) * a.M] - a.chunk_off[(int64_t)b * a.M];
+        st[6] = chunks;
         st[7] = v[4];
     }
 }
 
-int launch_eval_reduce(const EvArgs &a, int batch, hipStream_t st)
+int launch_eval_reduce(const EvArgs &a, int batch, hipStream_t st, bool summed)
 {
+    if (summed) {
+        if (a.G <= 256) hipLaunchKernelGGL((eval_reduce_kernel<256, false>), dim3((unsigned)batch), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((eval_reduce_kernel<1024, false>), dim3((unsigned)batch), dim3(1024), 0, st, a);
+        return launch_status();
+    }
     // A workgroup reads its matrix's slots alone.  256 threads up to 16 Ki sums, or 9 Ki of more bins than that: cheaper barriers, and 1024 matrices would
     // wait for each other in workgroups of 1024 (us by 256 / 1024, 32 slots of 256 bins: one matrix 36.1 / 38.6 for the whole schedule, 1024 matrices 25 / 37
     // for this kernel; 64 of 256 30.8 / 32.6, 33 of 264 38.9 / 40.0, 9 of 288 152 / 154; but 47 of 282 47.5 / 47.0, 44 of 352 47.2 / 46.8).  1024 threads up to 64 Ki sums, or any

@@ -30,7 +30,7 @@ __device__ __forceinline__ int dst_node(const EvArgs &a, uint32_t flow)
     return (int)((flow % (uint32_t)a.G) / (uint32_t)a.N);
 }
 
-// one workgroup per matrix: R = sum of the matrix's workspace slots, then the statistics (defined in eval.hip)
-int launch_eval_reduce(const EvArgs &a, int batch, hipStream_t st);
+// one workgroup per matrix: R = sum of the matrix's workspace slots (or summed: R is there, only the largest weights come from the slots), then the statistics (defined in eval.hip)
+int launch_eval_reduce(const EvArgs &a, int batch, hipStream_t st, bool summed = false);
 
 }  // namespace rs
