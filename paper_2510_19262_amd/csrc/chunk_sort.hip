@@ -17,11 +17,12 @@
 
 namespace rs {
 
-// Record fill.  us of the whole call by 128 / 256 / 512 / 1024 threads a workgroup: 4096 instances, 480 M records of 13 bytes 1147 / 1118 / 1122 / 1100..1150, one
-// matrix of 3.9 G records of 9 bytes 5820 / 5510 / 5400 / 5450.  Neighbouring tiles on one XCD: a bare writer of 13 bytes a record with one read in front of its stores
-// 5.6 TB/s when tiles go round robin over the XCDs, 5.8 / 6.0 / 6.1 when an XCD has 64 / 128 / 512 KiB of an array in a row.
-constexpr int kFillThreads = 512;
-constexpr int kFillGranule = 7;     // log2 of the neighbouring tiles that the workgroups of one XCD write: 1 MiB of an array
+// Record fill.  us of the whole call by 128 / 256 / 512 / 1024 threads a workgroup (a workgroup's room is free when its last wavefront is done, and a window in a stretch
+// of flows without full chunks takes long): 61 layers of 512 GPUs, 220 M records 955 / 788 / 815 / -, as routed 1.1 Zipf - / 730 / 805 / -; 4096 instances, 480 M records 1147 / 1118 / 1122 /
+// 1100..1150, one matrix of 3.9 G records 5820 / 5510 / 5400 / 5450 (boxes and placements differ by 8 %).  Neighbouring tiles on one XCD: a bare writer of 13 bytes
+// a record with one read in front of its stores 5.6 TB/s when tiles go round robin over the XCDs, 5.8 / 6.0 / 6.05 when an XCD has 256 / 512 / 1024 KiB of an array in a row.
+constexpr int kFillThreads = 256;
+constexpr int kFillGranule = 8;     // log2 of the neighbouring tiles that the workgroups of one XCD write: 1 MiB of an array
 constexpr int64_t kFillTiles = 1 << 22;   // most tiles of one launch: 2^31 threads
 
 // ---- A: per-instance chunk counts and the two exclusive scans over its flows -----------------
@@ -458,7 +459,7 @@ static int launch_tails(const CsArgs &a, hipStream_t st)
 // slower throughout (5.2, 5.1).  So a wavefront makes two trips (its entry; then its instance's bounds and the flow starts from the entry's flow on), no
 // barrier, and finds the flows of its records from the starts that fall among them, as window_flows does.
 // Measured, as contiguous runs of tiles per workgroup with their flow starts staged in LDS / now: 4096 instances of 117 K records 1295 / 990 us (4.8 / 6.3 TB/s),
-// one matrix of 3.9 G records without perm 6720 / 5310 (5.3 / 6.7), 3904 instances of 57 K in flows of 14: 611 / 500.
+// one matrix of 3.9 G records without perm 6720 / 5310 (5.3 / 6.7), 3904 instances of 57 K in flows of 14: 611 / 515 (5.3).
 // v of lane l, the same in all lanes
 __device__ __forceinline__ int64_t shfl_i64(int64_t v, int l)
 {
@@ -518,19 +519,20 @@ __device__ __forceinline__ void fill_window(const CsArgs &a, int vec_ok, unsigne
             };
             const int f = j0 + lane;
             bool on = take(f, f < a.NF ? fs[f] : 0xFFFFFFFFu, f < a.NF ? (unsigned)tb[f] : 0u);
-            // Many flows of no full chunk, or of one: four loads in flight (273 instances of 5616 flows, nearly all tails: 36 us one by one, 18 so)
-            for (int f0 = j0 + 64; on; f0 += 256) {
-                uint32_t s[4];
-                unsigned tails[4];
+            // Many flows of no full chunk: two loads in flight (273 instances of 5616 flows, nearly all tails: 36 us one by one, 23 so, 18 by four, but mostly one more
+            // is enough: 224 M records of 61 layers as routed, 1.1 Zipf, whole stage 725 us by four, 708 by two)
+            for (int f0 = j0 + 64; on; f0 += 128) {
+                uint32_t s[2];
+                unsigned tails[2];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < 2; ++u) {
                     const int fu = f0 + 64 * u + lane, fc = fu < a.NF ? fu : a.NF - 1;
                     s[u] = fs[fc];
                     tails[u] = tb[fc];
                     if (fu >= a.NF) s[u] = 0xFFFFFFFFu;
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) if (on) on = take(f0 + 64 * u + lane, s[u], tails[u]);
+                for (int u = 0; u < 2; ++u) if (on) on = take(f0 + 64 * u + lane, s[u], tails[u]);
             }
             lds_sync();
             const uint4 m = *reinterpret_cast<const uint4 *>(mark + 4 * lane);
