@@ -188,8 +188,7 @@ template <int T> constexpr int rank_flows() { return T == 64 ? 96 : 64; }
 // 512-GPU instance, and four of them per CU (its LDS) 364 us for 3904 such instances; a workgroup of 1024 takes 14 us for 128 instances of 8192 flows (67 before),
 // one of 256 155 us for the 3904.
 // stage() is called once with the first flows' loads in flight, for what the caller has to fetch as well.
-// FEW: the caller may have rank_flows<T>() flows or fewer (what it does not have costs the sort of 3416 instances of 1525 flows 58 us for 55).
-template <int T, bool FEW, typename F>
+template <int T, typename F>
 __device__ __forceinline__ unsigned short *tail_sort_block(const CsArgs &a, const int64_t *rows, int k, unsigned *rem, unsigned *hist,
                                                            unsigned short *idx_a, unsigned short *idx_b, unsigned *sh, int &nt_out, F stage)
 {
@@ -199,7 +198,7 @@ __device__ __forceinline__ unsigned short *tail_sort_block(const CsArgs &a, cons
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const unsigned long long lt = (1ull << lane) - 1ull;
     int nt = 0;
-    if (FEW && a.NF <= rank_flows<T>()) {
+    if (a.NF <= rank_flows<T>()) {
         // few flows: a tail's place is the number of tails that go before it, counted over all flows by the P neighbouring threads of its own
         constexpr int R = T == 64 ? 2 : 1, P = T >= 512 ? T / 256 : 1;   // rounds of loads, threads per flow
         const int quads = (a.NF + 3) >> 2;

@@ -23,7 +23,8 @@ namespace rs {
 // a record with one read in front of its stores 5.6 TB/s when tiles go round robin over the XCDs, 5.8 / 6.0 / 6.05 when an XCD has 256 / 512 / 1024 KiB of an array in a row.
 constexpr int kFillThreads = 256;
 constexpr int kFillGranule = 8;     // log2 of the neighbouring tiles that the workgroups of one XCD write: 1 MiB of an array
-constexpr int64_t kFillTiles = 1 << 22;   // most tiles of one launch: 2^31 threads
+constexpr int64_t kFillTiles = 1 << 22;   // most workgroups of the launch: 2^30 threads
+constexpr int64_t kFillTilesUnbounded = 1 << 16, kMostRecords = (int64_t)1 << 35;   // 9 bytes a record: 288 GB
 
 // ---- A: per-instance chunk counts and the two exclusive scans over its flows -----------------
 // One workgroup of T threads per instance, T * kTailLoads flows per round.  Latency bound (a few dependent trips to memory and
@@ -413,7 +414,7 @@ __global__ __launch_bounds__(64) void cs_tail_small_kernel(CsArgs a)
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
 
     int nt = 0;
-    const unsigned short *sorted = tail_sort_block<64, true>(a, rows, k, rem, hist, idx_a, idx_b, sh, nt, [] {});
+    const unsigned short *sorted = tail_sort_block<64>(a, rows, k, rem, hist, idx_a, idx_b, sh, nt, [] {});
 
     const int64_t out0 = a.chunk_off[inst] + a.cnt_full[inst];
     const uint32_t n_full = (uint32_t)a.cnt_full[inst];
@@ -466,13 +467,13 @@ __device__ __forceinline__ int64_t shfl_i64(int64_t v, int l)
     return (int64_t)((uint64_t)(unsigned)__builtin_amdgcn_readlane((int)((uint64_t)v >> 32), l) << 32 | (unsigned)__builtin_amdgcn_readlane((int)v, l));
 }
 
-// marks: 256 words of LDS for the calling wavefront, 16-byte aligned; w0: its first record, a multiple of 256
-__device__ __forceinline__ void fill_window(const CsArgs &a, int vec_ok, unsigned *mark, int64_t w0)
+// mark: 256 words of LDS for the calling wavefront, 16-byte aligned; w0: its first record, a multiple of 256.  False behind the last record.
+__device__ __forceinline__ bool fill_window(const CsArgs &a, int vec_ok, unsigned *mark, int64_t w0)
 {
     constexpr int kWindow = 256;
     const int lane = threadIdx.x & 63;
     const int64_t total = a.chunk_off[a.n_inst];
-    if (total > a.capacity || w0 >= total) return;
+    if (total > a.capacity || w0 >= total) return false;
     int inst, j0 = 0;
     if (a.n_entries == 0) {
         inst = wave_last_le<int64_t>(a.chunk_off, a.n_inst, w0);
@@ -578,7 +579,7 @@ __device__ __forceinline__ void fill_window(const CsArgs &a, int vec_ok, unsigne
                 }
             }
         }
-        if (out1 >= w0 + kWindow || out1 >= total) return;
+        if (out1 >= w0 + kWindow || out1 >= total) return true;
         do {                                                             // on to the next instance with records: there is one below `total`
             ++inst;
             out0 = out1;
@@ -595,14 +596,22 @@ __device__ __forceinline__ void fill_window(const CsArgs &a, int vec_ok, unsigne
     }
 }
 
-// Workgroup b, which the hardware deals to XCD b mod 8: every XCD takes 2^kshift neighbouring tiles in a row.
-__global__ __launch_bounds__(kFillThreads) void cs_fill_kernel(CsArgs a, int vec_ok, int kshift, int64_t tile0)
+// Workgroup b, which the hardware deals to XCD b mod 8: every XCD takes 2^kshift neighbouring tiles in a row.  The grid has a workgroup for every tile there is
+// room for, up to kFillTiles; what lies behind them is taken in further rounds (ROUNDS: a wavefront that has to look whether there are any stays
+// longer, 61 layers of 512 GPUs 1012 us the call, 837 without).
+template <bool ROUNDS>
+__global__ __launch_bounds__(kFillThreads) void cs_fill_kernel(CsArgs a, int vec_ok, int kshift)
 {
     __shared__ __align__(16) unsigned marks[kFillThreads / 64][256];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const unsigned b = blockIdx.x;
-    const int64_t tile = tile0 + ((int64_t)(b >> (3 + kshift)) << (3 + kshift)) + ((b & 7u) << kshift) + ((b >> 3) & ((1u << kshift) - 1u));
-    fill_window(a, vec_ok, marks[wave], tile * (kFillThreads * 4) + wave * 256);
+    const int64_t tile = ((int64_t)(b >> (3 + kshift)) << (3 + kshift)) + ((b & 7u) << kshift) + ((b >> 3) & ((1u << kshift) - 1u));
+    int64_t w0 = tile * (kFillThreads * 4) + wave * 256;
+    if constexpr (ROUNDS) {
+        while (fill_window(a, vec_ok, marks[wave], w0)) w0 += (int64_t)gridDim.x * (kFillThreads * 4);
+    } else {
+        fill_window(a, vec_ok, marks[wave], w0);
+    }
 }
 
 static void ws_layout(int64_t n_inst, int64_t NF, size_t off[6])
@@ -706,14 +715,16 @@ int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int
     const int vec_ok = (reinterpret_cast<uintptr_t>(chunk_w) % 16 == 0 && reinterpret_cast<uintptr_t>(chunk_flow) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(perm) % 16 == 0 && reinterpret_cast<uintptr_t>(rail) % 4 == 0) ? 1 : 0;
     if (int rc = launch_tails(a, st)) return rc;
+    // more records than the memory holds are no allocation but a caller who knows that the arrays are large enough
+    int64_t tiles = capacity / (kFillThreads * 4) + 1;
+    const bool rounds = tiles > kFillTiles;
+    if (rounds) tiles = capacity <= kMostRecords ? kFillTiles : kFillTilesUnbounded;
     int kshift = 0;
-    const int64_t tiles = (capacity + kFillThreads * 4 - 1) / (kFillThreads * 4);
     while (kshift < kFillGranule && (tiles >> (kshift + 6)) > 0) ++kshift;
     const int64_t group = (int64_t)8 << kshift;
-    for (int64_t tile0 = 0; tile0 < tiles; tile0 += kFillTiles) {
-        const int64_t n = tiles - tile0 < kFillTiles ? tiles - tile0 : kFillTiles;
-        hipLaunchKernelGGL(cs_fill_kernel, dim3((unsigned)((n + group - 1) / group * group)), dim3(kFillThreads), 0, st, a, vec_ok, kshift, tile0);
-    }
+    const dim3 grid((unsigned)((tiles + group - 1) / group * group));
+    if (rounds) hipLaunchKernelGGL(cs_fill_kernel<true>, grid, dim3(kFillThreads), 0, st, a, vec_ok, kshift);
+    else hipLaunchKernelGGL(cs_fill_kernel<false>, grid, dim3(kFillThreads), 0, st, a, vec_ok, kshift);
     return launch_status();
 }
 }  // namespace rs

@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kSsThreads) void ss_instance_kernel(CsArgs a, SsArg
     uint32_t n_full = 0;
     int nt = 0;
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
-    const unsigned short *sorted = tail_sort_block<kSsThreads, true>(a, rows, k, rem, hist, idx_a, idx_b, sh_sort, nt, [&] {
+    const unsigned short *sorted = tail_sort_block<kSsThreads>(a, rows, k, rem, hist, idx_a, idx_b, sh_sort, nt, [&] {
         for (int i = tid; i < a.n_inst; i += kSsThreads) {
             const int64_t c = a.cnt_all[i];
             total += c;

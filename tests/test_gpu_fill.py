@@ -62,3 +62,21 @@ def test_fill(M, N, B, C, kind, shift):
                 continue
             assert np.array_equal(h[shift:shift + n].view(np.uint32), ref), (name, cap)
             assert (h[:shift] == -7).all() and (h[shift + n:] == -7).all(), name    # nothing outside the records
+
+
+def test_fill_without_a_bound_on_capacity():
+    # a capacity beyond any memory says that the arrays are large enough: the records are written in rounds of a smaller grid
+    M, N, C = 4, 2, 64
+    G = M * N
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    D1 = torch.randint(0, 2 * 120_000_000 // (G * G) * C, (1, G, G), device=DEV, generator=gen)
+    topo = rs.Topo(M, N, C)
+    off, w, flow, perm = rs.chunk_sort(D1, topo)
+    n = int(off[-1].item())
+    assert n > (1 << 16) * 1024
+    got = [torch.zeros(n, dtype=torch.int32, device=DEV) for _ in range(3)]
+    o = torch.empty_like(off)
+    rs.chunk_sort(D1, topo, capacity=1 << 62, out=(o, *got))
+    assert torch.equal(o, off)
+    for a, b in zip(got, (w, flow, perm)):
+        assert torch.equal(a, b[:n])
