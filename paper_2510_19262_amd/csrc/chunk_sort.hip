@@ -22,9 +22,12 @@ namespace rs {
 // 1100..1150, one matrix of 3.9 G records 5820 / 5510 / 5400 / 5450 (boxes and placements differ by 8 %).  Neighbouring tiles on one XCD: a bare writer of 13 bytes
 // a record with one read in front of its stores 5.6 TB/s when tiles go round robin over the XCDs, 5.8 / 6.0 / 6.05 when an XCD has 256 / 512 / 1024 KiB of an array in a row.
 constexpr int kFillThreads = 256;
+constexpr int kFillWindow = 256;    // records of one wavefront
+constexpr int kFillTile = kFillThreads / 64 * kFillWindow;
 constexpr int kFillGranule = 8;     // log2 of the neighbouring tiles that the workgroups of one XCD write: 1 MiB of an array
 constexpr int64_t kFillTiles = 1 << 22;   // most workgroups of the launch: 2^30 threads
 constexpr int64_t kFillTilesUnbounded = 1 << 16, kMostRecords = (int64_t)1 << 35;   // 9 bytes a record: 288 GB
+constexpr int kFillInstWaves = 1 << 18;   // most wavefronts that look for instances of few full chunks
 
 // ---- A: per-instance chunk counts and the two exclusive scans over its flows -----------------
 // One workgroup of T threads per instance, T * kTailLoads flows per round.  Latency bound (a few dependent trips to memory and
@@ -453,164 +456,197 @@ static int launch_tails(const CsArgs &a, hipStream_t st)
 }
 
 // ---- D: full chunks ---------------------------------------------------------------------------
-// Write bound: 9 to 13 bytes a record.  A workgroup writes one tile of 4 T records at a multiple of that and exits, a wavefront its own kilobyte of
+// Write bound: 9 to 13 bytes a record.  A workgroup writes one tile of 1024 records at a multiple of that and exits, a wavefront its own kilobyte of
 // every array, on a 1 KiB boundary, with streaming stores.  What a writer reaches of the chip's 6.9 TB/s hangs on how many bytes wait behind
 // how long a chain of reads, and on what lies side by side in time: bare writers of 13 bytes a record, TB/s: no reads 6.1, two dependent trips in front
 // of the stores 5.2, the same with neighbouring tiles on one XCD 5.5, with streaming stores too 6.0; two and four tiles a workgroup are
-// slower throughout (5.2, 5.1).  So a wavefront makes two trips (its entry; then its instance's bounds and the flow starts from the entry's flow on), no
-// barrier, and finds the flows of its records from the starts that fall among them, as window_flows does.
+// slower throughout (5.2, 5.1), and so are two and four windows behind one chain of reads (226 M records of 512 GPUs, whole stage 600 us by one, 613, 625).  A wavefront
+// makes four trips (the number of records; its entry; its instance's bounds; the flow starts from the entry's flow on), the first three through the scalar cache,
+// no barrier, and finds the flows of its records from the starts that fall among them, as window_flows does.
 // Measured, as contiguous runs of tiles per workgroup with their flow starts staged in LDS / now: 4096 instances of 117 K records 1295 / 990 us (4.8 / 6.3 TB/s),
-// one matrix of 3.9 G records without perm 6720 / 5310 (5.3 / 6.7), 3904 instances of 57 K in flows of 14: 611 / 515 (5.3).
+// 3904 instances of 57 K in flows of 14: 611 / 515 (5.3).
+// Windows write the instances of kFillWindow full chunks and more.  Of these at most two have records in one: the one that holds the window's first record, and the one that
+// holds the record behind it.  The instances of fewer have a wavefront of their own (16 000 instances of two flows, 2000 records in all: 480 us when windows
+// went from instance to instance, 37 now; 1335 matrices of 24 GPUs, 12 500 records 95 and 20).
+
 // v of lane l, the same in all lanes
 __device__ __forceinline__ int64_t shfl_i64(int64_t v, int l)
 {
     return (int64_t)((uint64_t)(unsigned)__builtin_amdgcn_readlane((int)((uint64_t)v >> 32), l) << 32 | (unsigned)__builtin_amdgcn_readlane((int)v, l));
 }
 
-// mark: 256 words of LDS for the calling wavefront, 16-byte aligned; w0: its first record, a multiple of 256.  False behind the last record.
-__device__ __forceinline__ bool fill_window(const CsArgs &a, int vec_ok, unsigned *mark, int64_t w0)
+// p[i] through the scalar cache, i the same in all lanes, for what no workgroup of the launch writes: the compiler by itself takes a vector load once there are
+// stores in front (61 layers of 512 GPUs 743 us for 630)
+template <typename T>
+__device__ __forceinline__ T scalar_load(const T *p, int64_t i) { return ((const __attribute__((address_space(4))) T *)p)[i]; }
+
+// Full chunks of an instance (out0: its first record, n_full of them, at least one, fewer than 2^32) among the records w0 .. w0 + 255, w0 a multiple of 4.  j0: a flow that starts at
+// the first of them or before.  mark: 256 words of LDS for the calling wavefront, 16-byte aligned.  U: flow starts a lane has in flight, after one by itself where U = 2.
+template <int U>
+__device__ __forceinline__ void fill_part(const CsArgs &a, int vec_ok, unsigned *mark, int64_t w0, int inst, int64_t out0, uint32_t n_full, int j0)
 {
-    constexpr int kWindow = 256;
     const int lane = threadIdx.x & 63;
-    const int64_t total = a.chunk_off[a.n_inst];
-    if (total > a.capacity || w0 >= total) return false;
-    int inst, j0 = 0;
-    if (a.n_entries == 0) {
-        inst = wave_last_le<int64_t>(a.chunk_off, a.n_inst, w0);
-    } else {
-        const uint2 entry = a.entries[w0 >> fill_entry_shift(total, a.n_entries)];
-        inst = __builtin_amdgcn_readfirstlane((int)entry.x);
-        j0 = __builtin_amdgcn_readfirstlane((int)entry.y);
-    }
     const uint32_t cw = (uint32_t)a.C;
-    int64_t out0 = a.chunk_off[inst], out1 = a.chunk_off[inst + 1];
-    while (out1 <= w0) {                                                 // the entry lies before the window, in another instance
-        const int i = inst + 1 + lane < a.n_inst ? inst + 1 + lane : a.n_inst;
-        inst += __popcll(__ballot(a.chunk_off[i] <= w0));                // chunk_off[n_inst] = total > w0
-        j0 = 0;
-        out0 = a.chunk_off[inst]; out1 = a.chunk_off[inst + 1];
+    const int64_t first = w0 - out0;                                     // instance position of the window's first record; negative where the instance starts in it
+    const uint32_t last = first + kFillWindow <= (int64_t)n_full ? (uint32_t)(first + kFillWindow - 1) : n_full - 1u;
+    const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
+    const uint16_t *tb = a.tails_before + (int64_t)inst * a.NF;
+    *reinterpret_cast<uint4 *>(mark + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
+    lds_sync();
+    unsigned base = 0;                                                   // flow << 16 | tails before it: both ascend together
+    auto take = [&](int f, uint32_t s, unsigned tails) {                 // 64 flow starts; false when the window's end is among them
+        const unsigned v = (unsigned)f << 16 | tails;
+        const bool in = s <= last, before = in && (int64_t)s <= first;
+        const int n = __popcll(__ballot(before));
+        if (n) base = (unsigned)__builtin_amdgcn_readlane((int)v, n - 1);
+        // of flows that start at one place only the last can hold it: the others are empty
+        const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)s, 0x130, 0xF, 0xF, false);   // wave_shl:1
+        if (in && !before && (s != next || lane == 63)) atomicMax(&mark[(uint32_t)((int64_t)s - first)], v);
+        return __ballot(!in) == 0ull;
+    };
+    bool on = true;
+    int f0 = j0;
+    if constexpr (U == 2) {
+        const int f = j0 + lane;
+        on = take(f, f < a.NF ? fs[f] : 0xFFFFFFFFu, f < a.NF ? (unsigned)tb[f] : 0u);
+        f0 += 64;
     }
-    // the instances that have records in the window: mostly one; the bounds of the next 63 are fetched along with the first one's flows where it ends here
-    const int next0 = inst + 1;
-    int64_t offs = 0, fulls = 0;
-    if (out1 < w0 + kWindow && out1 < total) {
-        const int i = next0 + lane < a.n_inst ? next0 + lane : a.n_inst;
-        offs = a.chunk_off[i];
-        fulls = a.cnt_full[i < a.n_inst ? i : a.n_inst - 1];
+    // Many flows of no full chunk: two loads in flight (273 instances of 5616 flows, nearly all tails: 36 us one by one, 23 so, 18 by four, but mostly one more
+    // is enough: 224 M records of 61 layers as routed, 1.1 Zipf, whole stage 725 us by four, 708 by two)
+    for (; on; f0 += 64 * U) {
+        uint32_t s[U];
+        unsigned tails[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int fu = f0 + 64 * u + lane, fc = fu < a.NF ? fu : a.NF - 1;
+            s[u] = fs[fc];
+            tails[u] = tb[fc];
+            if (fu >= a.NF) s[u] = 0xFFFFFFFFu;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) if (on) on = take(f0 + 64 * u + lane, s[u], tails[u]);
     }
-    uint32_t n_full = (uint32_t)a.cnt_full[inst];
-    while (true) {
-        const int64_t first = w0 - out0;                                 // instance position of the window's first record; negative where the instance starts in it
-        if (n_full != 0 && first < (int64_t)n_full) {
-            const uint32_t last = first + kWindow <= (int64_t)n_full ? (uint32_t)(first + kWindow - 1) : n_full - 1u;
-            const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
-            const uint16_t *tb = a.tails_before + (int64_t)inst * a.NF;
-            *reinterpret_cast<uint4 *>(mark + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
-            lds_sync();
-            unsigned base = 0;                                           // flow << 16 | tails before it: both ascend together
-            auto take = [&](int f, uint32_t s, unsigned tails) {         // 64 flow starts; false when the window's end is among them
-                const unsigned v = (unsigned)f << 16 | tails;
-                const bool in = s <= last, before = in && (int64_t)s <= first;
-                const int n = __popcll(__ballot(before));
-                if (n) base = (unsigned)__builtin_amdgcn_readlane((int)v, n - 1);
-                // of flows that start at one place only the last can hold it: the others are empty
-                const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)s, 0x130, 0xF, 0xF, false);   // wave_shl:1
-                if (in && !before && (s != next || lane == 63)) atomicMax(&mark[(uint32_t)((int64_t)s - first)], v);
-                return __ballot(!in) == 0ull;
-            };
-            const int f = j0 + lane;
-            bool on = take(f, f < a.NF ? fs[f] : 0xFFFFFFFFu, f < a.NF ? (unsigned)tb[f] : 0u);
-            // Many flows of no full chunk: two loads in flight (273 instances of 5616 flows, nearly all tails: 36 us one by one, 23 so, 18 by four, but mostly one more
-            // is enough: 224 M records of 61 layers as routed, 1.1 Zipf, whole stage 725 us by four, 708 by two)
-            for (int f0 = j0 + 64; on; f0 += 128) {
-                uint32_t s[2];
-                unsigned tails[2];
+    lds_sync();
+    const uint4 m = *reinterpret_cast<const uint4 *>(mark + 4 * lane);
+    const unsigned m1 = max(m.x, m.y), m2 = max(m1, m.z), m3 = max(m2, m.w);
+    const unsigned left = wave_max_before(max(m3, base), base);
+    const unsigned v[4] = {max(left, m.x), max(left, m1), max(left, m2), max(left, m3)};
+    const int64_t p = first + 4 * lane;
+    const uint32_t lead = n_full - n_full % (uint32_t)a.N;               // positions below it go round robin (a.rail)
+    const int64_t at = w0 + 4 * lane;
+    uint32_t rr = 0;
+    if (a.rail) {
+        uint32_t r = a.nmask >= 0 ? ((uint32_t)p & (uint32_t)a.nmask) : (uint32_t)p % (uint32_t)a.N;
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int fu = f0 + 64 * u + lane, fc = fu < a.NF ? fu : a.NF - 1;
-                    s[u] = fs[fc];
-                    tails[u] = tb[fc];
-                    if (fu >= a.NF) s[u] = 0xFFFFFFFFu;
-                }
-#pragma unroll
-                for (int u = 0; u < 2; ++u) if (on) on = take(f0 + 64 * u + lane, s[u], tails[u]);
-            }
-            lds_sync();
-            const uint4 m = *reinterpret_cast<const uint4 *>(mark + 4 * lane);
-            const unsigned m1 = max(m.x, m.y), m2 = max(m1, m.z), m3 = max(m2, m.w);
-            const unsigned left = wave_max_before(max(m3, base), base);
-            const unsigned v[4] = {max(left, m.x), max(left, m1), max(left, m2), max(left, m3)};
-            const int64_t p = first + 4 * lane;
-            const uint32_t lead = n_full - n_full % (uint32_t)a.N;       // positions below it go round robin (a.rail)
-            const int64_t at = w0 + 4 * lane;
-            uint32_t rr = 0;
-            if (a.rail) {
-                uint32_t r = a.nmask >= 0 ? ((uint32_t)p & (uint32_t)a.nmask) : (uint32_t)p % (uint32_t)a.N;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    rr |= r << (8 * e);
-                    r = (r + 1 == (uint32_t)a.N) ? 0u : r + 1;
-                }
-            }
-            if (vec_ok && p >= 0 && p + 4 <= (int64_t)n_full) {
-                const uint32_t q = (uint32_t)p;
-                __builtin_nontemporal_store(u32x4{cw, cw, cw, cw}, reinterpret_cast<u32x4 *>(a.chunk_w + at));
-                __builtin_nontemporal_store(u32x4{v[0] >> 16, v[1] >> 16, v[2] >> 16, v[3] >> 16}, reinterpret_cast<u32x4 *>(a.chunk_flow + at));
-                if (a.perm)
-                    __builtin_nontemporal_store(u32x4{q + (v[0] & 0xFFFFu), q + 1 + (v[1] & 0xFFFFu), q + 2 + (v[2] & 0xFFFFu), q + 3 + (v[3] & 0xFFFFu)},
-                                                reinterpret_cast<u32x4 *>(a.perm + at));
-                if (a.rail) {
-                    if (q + 4 <= lead) {
-                        __builtin_nontemporal_store(rr, reinterpret_cast<uint32_t *>(a.rail + at));
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) if (q + e < lead) a.rail[at + e] = (uint8_t)(rr >> (8 * e));
-                    }
-                }
+        for (int e = 0; e < 4; ++e) {
+            rr |= r << (8 * e);
+            r = (r + 1 == (uint32_t)a.N) ? 0u : r + 1;
+        }
+    }
+    if (vec_ok && p >= 0 && p + 4 <= (int64_t)n_full) {
+        const uint32_t q = (uint32_t)p;
+        __builtin_nontemporal_store(u32x4{cw, cw, cw, cw}, reinterpret_cast<u32x4 *>(a.chunk_w + at));
+        __builtin_nontemporal_store(u32x4{v[0] >> 16, v[1] >> 16, v[2] >> 16, v[3] >> 16}, reinterpret_cast<u32x4 *>(a.chunk_flow + at));
+        if (a.perm)
+            __builtin_nontemporal_store(u32x4{q + (v[0] & 0xFFFFu), q + 1 + (v[1] & 0xFFFFu), q + 2 + (v[2] & 0xFFFFu), q + 3 + (v[3] & 0xFFFFu)},
+                                        reinterpret_cast<u32x4 *>(a.perm + at));
+        if (a.rail) {
+            if (q + 4 <= lead) {
+                __builtin_nontemporal_store(rr, reinterpret_cast<uint32_t *>(a.rail + at));
             } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (p + e < 0 || p + e >= (int64_t)n_full) continue;
-                    const uint32_t q = (uint32_t)(p + e);
-                    a.chunk_w[at + e] = cw;
-                    a.chunk_flow[at + e] = v[e] >> 16;
-                    if (a.perm) a.perm[at + e] = q + (v[e] & 0xFFFFu);
-                    if (a.rail && q < lead) a.rail[at + e] = (uint8_t)(q % (uint32_t)a.N);
-                }
+                for (int e = 0; e < 4; ++e) if (q + e < lead) a.rail[at + e] = (uint8_t)(rr >> (8 * e));
             }
         }
-        if (out1 >= w0 + kWindow || out1 >= total) return true;
-        do {                                                             // on to the next instance with records: there is one below `total`
-            ++inst;
-            out0 = out1;
-            const int l = inst - next0;
-            if (l < 63) {
-                out1 = shfl_i64(offs, l + 1);
-                n_full = (uint32_t)shfl_i64(fulls, l);
-            } else {
-                out1 = a.chunk_off[inst + 1];
-                n_full = (uint32_t)a.cnt_full[inst];
-            }
-        } while (out1 == out0);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (p + e < 0 || p + e >= (int64_t)n_full) continue;
+            const uint32_t q = (uint32_t)(p + e);
+            a.chunk_w[at + e] = cw;
+            a.chunk_flow[at + e] = v[e] >> 16;
+            if (a.perm) a.perm[at + e] = q + (v[e] & 0xFFFFu);
+            if (a.rail && q < lead) a.rail[at + e] = (uint8_t)(q % (uint32_t)a.N);
+        }
+    }
+}
+
+// Instance that holds record w, and a flow of it that starts before w's or is w's; its bounds and full chunks.
+__device__ __forceinline__ void find_instance(const CsArgs &a, int64_t w, int64_t total, int &inst, int &j0, int64_t &out0, int64_t &out1, int64_t &n_full)
+{
+    j0 = 0;
+    if (a.n_entries == 0) {
+        inst = wave_last_le<int64_t>(a.chunk_off, a.n_inst, w);
+    } else {
+        const uint64_t entry = scalar_load(reinterpret_cast<const uint64_t *>(a.entries), w >> fill_entry_shift(total, a.n_entries));
+        inst = (int)(uint32_t)entry;
+        j0 = (int)(entry >> 32);
+    }
+    while (true) {
+        out0 = scalar_load(a.chunk_off, inst);
+        out1 = scalar_load(a.chunk_off, inst + 1);
+        n_full = scalar_load(a.cnt_full, inst);
+        if (out1 > w) return;
+        const int i = inst + 1 + (threadIdx.x & 63) < a.n_inst ? inst + 1 + (threadIdx.x & 63) : a.n_inst;
+        inst += __popcll(__ballot(a.chunk_off[i] <= w));                 // the entry lies before w, in another instance; chunk_off[n_inst] = total > w
         j0 = 0;
     }
 }
 
-// Workgroup b, which the hardware deals to XCD b mod 8: every XCD takes 2^kshift neighbouring tiles in a row.  The grid has a workgroup for every tile there is
-// room for, up to kFillTiles; what lies behind them is taken in further rounds (ROUNDS: a wavefront that has to look whether there are any stays
-// longer, 61 layers of 512 GPUs 1012 us the call, 837 without).
-template <bool ROUNDS>
-__global__ __launch_bounds__(kFillThreads) void cs_fill_kernel(CsArgs a, int vec_ok, int kshift)
+__device__ __forceinline__ bool fill_windows_write(int64_t n_full) { return n_full >= kFillWindow; }
+
+// The records w0 .. w0 + 255 of instances of kFillWindow full chunks and more; w0, a multiple of 256, is below `total`.
+__device__ __forceinline__ void fill_window(const CsArgs &a, int vec_ok, unsigned *mark, int64_t w0, int64_t total)
 {
-    __shared__ __align__(16) unsigned marks[kFillThreads / 64][256];
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const unsigned b = blockIdx.x;
-    const int64_t tile = ((int64_t)(b >> (3 + kshift)) << (3 + kshift)) + ((b & 7u) << kshift) + ((b >> 3) & ((1u << kshift) - 1u));
-    int64_t w0 = tile * (kFillThreads * 4) + wave * 256;
+    const int64_t w1 = w0 + kFillWindow;
+    int inst, j0;
+    int64_t out0, out1, n_full;
+    find_instance(a, w0, total, inst, j0, out0, out1, n_full);
+    if (fill_windows_write(n_full) && w0 < out0 + n_full) fill_part<2>(a, vec_ok, mark, w0, inst, out0, (uint32_t)n_full, j0);
+    if (out1 >= w1 || w1 >= total) return;
+    find_instance(a, w1, total, inst, j0, out0, out1, n_full);                   // such an instance that starts behind w0 goes on behind the window
+    if (out0 >= w1) return;
+    if (fill_windows_write(n_full)) fill_part<2>(a, vec_ok, mark, w0, inst, out0, (uint32_t)n_full, 0);
+}
+
+// The first inst_blocks workgroups write the instances of few full chunks, the others the windows.  Workgroup b, which the hardware deals to XCD b mod 8: every XCD takes 2^kshift
+// neighbouring tiles in a row.  The grid has a workgroup for every tile there is room for, up to kFillTiles; what lies behind them is taken in further rounds (ROUNDS).
+template <bool ROUNDS>
+__global__ __launch_bounds__(kFillThreads) void cs_fill_kernel(CsArgs a, int vec_ok, int kshift, unsigned inst_blocks)
+{
+    __shared__ __align__(16) unsigned marks[kFillThreads / 64][kFillWindow];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    unsigned *mark = marks[wave];
+    const int64_t total = scalar_load(a.chunk_off, a.n_inst);
+    if (total > a.capacity) return;
+    if (blockIdx.x < inst_blocks) {
+        const int64_t waves = (int64_t)inst_blocks * (kFillThreads / 64), w = (int64_t)blockIdx.x * (kFillThreads / 64) + wave;
+        const int i0 = (int)(a.n_inst * w / waves), i1 = (int)(a.n_inst * (w + 1) / waves);
+        for (int base = i0; base < i1; base += 64) {
+            const int i = base + lane < i1 ? base + lane : i0;
+            const int64_t off = a.chunk_off[i], full = a.cnt_full[i];
+            unsigned long long few = __ballot(base + lane < i1 && full > 0 && full < kFillWindow);
+            while (few) {
+                const int l = __builtin_ctzll(few);
+                few &= few - 1;
+                const int64_t out0 = shfl_i64(off, l);
+                const uint32_t n_full = (uint32_t)shfl_i64(full, l);
+                for (int64_t w0 = out0 & ~(int64_t)3; w0 < out0 + n_full; w0 += kFillWindow)   // one round, or two
+                    fill_part<4>(a, vec_ok, mark, w0, base + l, out0, n_full, 0);
+            }
+        }
+        return;
+    }
+    const unsigned b = blockIdx.x - inst_blocks, blocks = gridDim.x - inst_blocks, in_granule = (1u << kshift) - 1u;
+    auto window_of = [&](unsigned v) {
+        const int64_t tile = ((int64_t)(v >> (3 + kshift)) << (3 + kshift)) + ((v & 7u) << kshift) + ((v >> 3) & in_granule);
+        return tile * kFillTile + wave * kFillWindow;
+    };
+    int64_t w0 = window_of(b);
     if constexpr (ROUNDS) {
-        while (fill_window(a, vec_ok, marks[wave], w0)) w0 += (int64_t)gridDim.x * (kFillThreads * 4);
+        for (; w0 < total; w0 += (int64_t)blocks * kFillTile) fill_window(a, vec_ok, mark, w0, total);
     } else {
-        fill_window(a, vec_ok, marks[wave], w0);
+        if (w0 < total) fill_window(a, vec_ok, mark, w0, total);
     }
 }
 
@@ -716,15 +752,16 @@ int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int
                         reinterpret_cast<uintptr_t>(perm) % 16 == 0 && reinterpret_cast<uintptr_t>(rail) % 4 == 0) ? 1 : 0;
     if (int rc = launch_tails(a, st)) return rc;
     // more records than the memory holds are no allocation but a caller who knows that the arrays are large enough
-    int64_t tiles = capacity / (kFillThreads * 4) + 1;
+    int64_t tiles = capacity / kFillTile + 1;
     const bool rounds = tiles > kFillTiles;
     if (rounds) tiles = capacity <= kMostRecords ? kFillTiles : kFillTilesUnbounded;
     int kshift = 0;
     while (kshift < kFillGranule && (tiles >> (kshift + 6)) > 0) ++kshift;
     const int64_t group = (int64_t)8 << kshift;
-    const dim3 grid((unsigned)((tiles + group - 1) / group * group));
-    if (rounds) hipLaunchKernelGGL(cs_fill_kernel<true>, grid, dim3(kFillThreads), 0, st, a, vec_ok, kshift);
-    else hipLaunchKernelGGL(cs_fill_kernel<false>, grid, dim3(kFillThreads), 0, st, a, vec_ok, kshift);
+    const int64_t inst_waves = n_inst < kFillInstWaves ? n_inst : kFillInstWaves;
+    const int64_t inst_blocks = (inst_waves + kFillThreads / 64 * 8 - 1) / (kFillThreads / 64 * 8) * 8;   // a whole number of rounds over the XCDs
+    const dim3 grid((unsigned)((tiles + group - 1) / group * group + inst_blocks));
+    hipLaunchKernelGGL(rounds ? cs_fill_kernel<true> : cs_fill_kernel<false>, grid, dim3(kFillThreads), 0, st, a, vec_ok, kshift, (unsigned)inst_blocks);
     return launch_status();
 }
 }  // namespace rs

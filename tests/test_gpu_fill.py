@@ -80,3 +80,25 @@ def test_fill_without_a_bound_on_capacity():
     assert torch.equal(o, off)
     for a, b in zip(got, (w, flow, perm)):
         assert torch.equal(a, b[:n])
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+def test_fill_instances_around_a_window(shift):
+    # one flow an instance, of as many full chunks as a window has, a few more or fewer, or hardly any, at every alignment
+    M, N, B, C = 2, 1, 400, 4096
+    rng = np.random.default_rng(3)
+    q = rng.choice([0, 0, 1, 2, 3, 7, 252, 253, 254, 255, 256, 257, 258, 259, 260, 511, 512, 513, 5000], size=(B, 2))
+    D1n = np.zeros((B, 2, 2), dtype=np.int64)
+    D1n[:, [0, 1], [1, 0]] = q * C + rng.integers(0, 2, size=(B, 2)) * rng.integers(1, C, size=(B, 2))
+    off, w, flow, perm = oracle.chunk_sort_batch(D1n, M, N, C)
+    n = int(off[-1])
+    D1 = torch.from_numpy(D1n).to(DEV)
+    for cap in (n, n + (1 << 21)):                                       # without entries and with them
+        recs = [torch.full((cap + 9,), -7, dtype=torch.int32, device=DEV) for _ in range(3)]
+        o = torch.empty(B * M + 1, dtype=torch.int64, device=DEV)
+        rs.chunk_sort(D1, rs.Topo(M, N, C), capacity=cap, out=(o, *[r[shift:shift + cap] for r in recs]))
+        assert np.array_equal(o.cpu().numpy(), off)
+        for name, r, ref in zip(("w", "flow", "perm"), recs, (w, flow, perm)):
+            h = r.cpu().numpy()
+            assert np.array_equal(h[shift:shift + n].view(np.uint32), ref), (name, cap)
+            assert (h[:shift] == -7).all() and (h[shift + n:] == -7).all(), name
