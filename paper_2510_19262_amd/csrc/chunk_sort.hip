@@ -25,8 +25,17 @@ constexpr int kFillThreads = 256;
 constexpr int kFillWindow = 256;    // records of one wavefront
 constexpr int kFillTile = kFillThreads / 64 * kFillWindow;
 constexpr int kFillGranule = 8;     // log2 of the neighbouring tiles that the workgroups of one XCD write: 1 MiB of an array
-constexpr int64_t kFillTiles = 1 << 22;   // most workgroups of the launch: 2^30 threads
-constexpr int64_t kFillTilesUnbounded = 1 << 16, kMostRecords = (int64_t)1 << 35;   // 9 bytes a record: 288 GB
+// Workgroups of the launch: a tile each for all records there is room for, because a wavefront that exits behind its stores is what writes fastest, up to a limit, because one that finds
+// nothing to do costs 0.21 ns (the chip starts a wavefront every 0.053 ns) and the host does not know how much of the room is used.  The limit is 2^15 (7 us in all, what the other
+// launches of a call cost) and one more for every 32 flows, 6.6 ps a flow beside the 10 to 25 that the rest of the call takes.  What lies behind it goes to the last kFillRounds
+// workgroups, which is what the chip holds, by tickets, so that what is being written stays close together.  us, chunk_sort, all tiles launched / 2^15 and tickets /
+// 2^15 workgroups that go round: 226 M records of 512 GPUs 597 / 626 / 640, 489 M of 256 GPUs 1045 / 1087 / 1200, 3.7 G of 1024 GPUs without perm 4620 / 5040 / 5500; the other
+// way round, 8.6 M records of 64 GPUs and room for 8.6 M / 430 M / 3.4 G 33 / 117 / 740 when all tiles are launched, 33 / 37 / 37 so.
+constexpr int64_t kFillTiles = 1 << 15, kFillTileFlows = 32, kFillTilesMost = 1 << 22;   // 2^22: the launch stays within 2^30 threads
+constexpr int kFillRounds = 2048;
+// Counters of tickets and the words from one to the next, a cache line.  A line takes 16 ns an addition: eight counters 7.4 ms for the 3.7 G records.  A batch of few flows has no room for
+// them; all its workgroups go round.
+constexpr int kFillCounters = 16, kTicketStep = 32;
 constexpr int kFillInstWaves = 1 << 18;   // most wavefronts that look for instances of few full chunks
 
 // ---- A: per-instance chunk counts and the two exclusive scans over its flows -----------------
@@ -212,6 +221,7 @@ __global__ __launch_bounds__(kScanThreads) void cs_scan_kernel(CsArgs a)
 #pragma unroll
     for (int w = 0; w < W; ++w) { before += sh[0][w]; total += sh[1][w]; }
     if (blockIdx.x == gridDim.x - 1 && tid == 0) a.chunk_off[a.n_inst] = total;
+    if (a.tickets && blockIdx.x == 0 && tid < kFillCounters) a.tickets[tid * kTicketStep] = 0u;
     const bool entries = a.n_entries != 0 && total <= a.capacity && total > 0;
     const int s = entries ? fill_entry_shift(total, a.n_entries) : 0;
     for (int base = i0; base < i1; base += 64) {                         // the same in every wavefront
@@ -610,8 +620,8 @@ __device__ __forceinline__ void fill_window(const CsArgs &a, int vec_ok, unsigne
 }
 
 // The first inst_blocks workgroups write the instances of few full chunks, the others the windows.  Workgroup b, which the hardware deals to XCD b mod 8: every XCD takes 2^kshift
-// neighbouring tiles in a row.  The grid has a workgroup for every tile there is room for, up to kFillTiles; what lies behind them is taken in further rounds (ROUNDS).
-template <bool ROUNDS>
+// neighbouring tiles in a row.
+template <bool BEYOND>
 __global__ __launch_bounds__(kFillThreads) void cs_fill_kernel(CsArgs a, int vec_ok, int kshift, unsigned inst_blocks)
 {
     __shared__ __align__(16) unsigned marks[kFillThreads / 64][kFillWindow];
@@ -643,9 +653,29 @@ __global__ __launch_bounds__(kFillThreads) void cs_fill_kernel(CsArgs a, int vec
         return tile * kFillTile + wave * kFillWindow;
     };
     int64_t w0 = window_of(b);
-    if constexpr (ROUNDS) {
-        for (; w0 < total; w0 += (int64_t)blocks * kFillTile) fill_window(a, vec_ok, mark, w0, total);
-    } else {
+    if (w0 < total) fill_window(a, vec_ok, mark, w0, total);
+    if (!BEYOND || (int64_t)blocks * kFillTile >= total || (a.tickets && b + kFillRounds < blocks)) return;
+    // Tiles behind the launch's: workgroup b draws on counter b mod kFillCounters, so that it stays with its XCD's.  The next ticket is on its way while a tile is written.
+    __shared__ unsigned sh_ticket[2];
+    const unsigned x = b & (kFillCounters - 1);
+    auto draw = [&] {
+        return a.tickets && threadIdx.x == 0 ? __hip_atomic_fetch_add(a.tickets + x * kTicketStep, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    };
+    unsigned ticket = draw();
+    int64_t v = b;
+    for (int k = 0;; k ^= 1) {                                           // the slot before is still being read
+        if (a.tickets) {
+            if (threadIdx.x == 0) sh_ticket[k] = ticket;
+            lds_sync();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            v = (int64_t)blocks + (int64_t)kFillCounters * (unsigned)__builtin_amdgcn_readfirstlane((int)sh_ticket[k]) + x;
+        } else {
+            v += blocks;
+        }
+        if ((v >> (3 + kshift) << (3 + kshift)) * kFillTile >= total) return;   // the same in all wavefronts
+        ticket = draw();
+        w0 = window_of((unsigned)v);
         if (w0 < total) fill_window(a, vec_ok, mark, w0, total);
     }
 }
@@ -675,6 +705,7 @@ static void fill_args(CsArgs &a, const railsched_topo_t *h_topo, int64_t n_inst,
     a.tails_before = reinterpret_cast<uint16_t *>(w8 + off[3]);
     a.entries = reinterpret_cast<uint2 *>(w8 + off[4]);
     a.n_entries = (int64_t)((off[5] - off[4]) / sizeof(uint2));
+    a.tickets = nullptr;
     a.C = h_topo->chunk_bytes;
     a.cinv = ~0ull / (uint64_t)a.C;
     a.ginv = G > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)G - 1) / (uint64_t)G) : 0u;
@@ -736,6 +767,14 @@ int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int
     // Few records of instances of few flows are written as fast by wavefronts that search for their instance and go through its flows (scan / fill in us
     // with entries and without, 1672 instances of 152 flows 7.2 / 9.4, 4.3 / 10.0; 1457 of 775 flows 10.7 / 3.2, 5.0 / 3.5); a count query needs none.
     if (!chunk_w || (NF <= kSearchFlows && capacity <= kSearchRecords)) a.n_entries = 0;
+    int64_t tiles = capacity / kFillTile + 1, most = kFillTiles + n_inst * NF / kFillTileFlows;
+    if (most > kFillTilesMost) most = kFillTilesMost;
+    const bool beyond = tiles > most;
+    if (beyond) tiles = most;
+    if (beyond && chunk_w && a.n_entries >= 2 * kFillCounters * kTicketStep) {   // at the end of the entries' room; few flows have too little
+        a.n_entries -= kFillCounters * kTicketStep / 2;
+        a.tickets = reinterpret_cast<unsigned *>(a.entries + a.n_entries);
+    }
     if (args_out) *args_out = a;
 
     if (n_inst > 0) {
@@ -751,17 +790,13 @@ int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int
     const int vec_ok = (reinterpret_cast<uintptr_t>(chunk_w) % 16 == 0 && reinterpret_cast<uintptr_t>(chunk_flow) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(perm) % 16 == 0 && reinterpret_cast<uintptr_t>(rail) % 4 == 0) ? 1 : 0;
     if (int rc = launch_tails(a, st)) return rc;
-    // more records than the memory holds are no allocation but a caller who knows that the arrays are large enough
-    int64_t tiles = capacity / kFillTile + 1;
-    const bool rounds = tiles > kFillTiles;
-    if (rounds) tiles = capacity <= kMostRecords ? kFillTiles : kFillTilesUnbounded;
     int kshift = 0;
     while (kshift < kFillGranule && (tiles >> (kshift + 6)) > 0) ++kshift;
     const int64_t group = (int64_t)8 << kshift;
     const int64_t inst_waves = n_inst < kFillInstWaves ? n_inst : kFillInstWaves;
     const int64_t inst_blocks = (inst_waves + kFillThreads / 64 * 8 - 1) / (kFillThreads / 64 * 8) * 8;   // a whole number of rounds over the XCDs
     const dim3 grid((unsigned)((tiles + group - 1) / group * group + inst_blocks));
-    hipLaunchKernelGGL(rounds ? cs_fill_kernel<true> : cs_fill_kernel<false>, grid, dim3(kFillThreads), 0, st, a, vec_ok, kshift, (unsigned)inst_blocks);
+    hipLaunchKernelGGL(beyond ? cs_fill_kernel<true> : cs_fill_kernel<false>, grid, dim3(kFillThreads), 0, st, a, vec_ok, kshift, (unsigned)inst_blocks);
     return launch_status();
 }
 }  // namespace rs

@@ -39,6 +39,16 @@ def _sort(D1, topo, n, capacity):
     return lambda: rs.chunk_sort(D1, topo, capacity=capacity, out=out, ws=ws)
 
 
+@pytest.mark.parametrize("M,N,B,mean", [(4, 4, 1, 20), (8, 8, 16, 150)])
+@pytest.mark.parametrize("capacity", [400_000_000, 4_200_000_000, 1 << 62])
+def test_room_that_is_not_used_costs_little(M, N, B, mean, capacity):
+    topo = rs.Topo(M, N, 65536)
+    D1 = _matrices(M, N, B, topo.chunk_bytes, mean)
+    n = rs.chunk_total(D1, topo)
+    tight, roomy = _us(_sort(D1, topo, n, n), _sort(D1, topo, n, capacity))
+    assert roomy < 1.5 * tight + 20, (tight, roomy)                      # 20 / 27 and 33 / 40 us; 880 us when 4.2 G records had a workgroup a tile
+
+
 @pytest.mark.parametrize("M,N,B,mean,zero", [(2, 1, 8000, 2, 0.95), (4, 4, 256, 2, 0.95), (3, 8, 1335, 2, 0.99), (11, 8, 87, 2, 0.99)])
 def test_instances_of_few_records_cost_no_more_than_of_many(M, N, B, mean, zero):
     topo = rs.Topo(M, N, 65536)

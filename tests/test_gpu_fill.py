@@ -102,3 +102,36 @@ def test_fill_instances_around_a_window(shift):
             h = r.cpu().numpy()
             assert np.array_equal(h[shift:shift + n].view(np.uint32), ref), (name, cap)
             assert (h[:shift] == -7).all() and (h[shift + n:] == -7).all(), name
+
+
+@pytest.mark.parametrize("M,N", [(2, 1), (8, 8)])                    # few flows, without room for counters, and many
+@pytest.mark.parametrize("capacity", [0, 1 << 40])
+def test_fill_beyond_the_launch(M, N, capacity):
+    # more records than the launch has workgroups for: its last ones draw the rest by tickets, or go round.  Matrix by matrix there are fewer, and the records are the same
+    B, C, G = 5, 4096, M * N
+    per = 2 * 12_000_000 // (G * (G - N))                                # twice the mean number of chunks of a flow
+    D1 = torch.randint(0, per * C, (B, G, G), device=DEV, generator=torch.Generator(device=DEV).manual_seed(M))
+    if M == 2:
+        D1[:, 0, 1] = 11_000_000 * C + 5
+        D1[:, 1, 0] = torch.arange(B, device=DEV) * C + 77
+    topo = rs.Topo(M, N, C)
+    off = rs.chunk_count(D1, topo)
+    n = int(off[-1].item())
+    assert n > (1 << 15) * 1024 + 2_000_000
+    out = (torch.empty_like(off), *[torch.full((n + 64,), -7, dtype=torch.int32, device=DEV) for _ in range(3)],
+           torch.full((n + 64,), 99, dtype=torch.uint8, device=DEV), *[torch.empty((B, M, N), dtype=torch.int64, device=DEV) for _ in range(2)],
+           torch.empty((B, 8), dtype=torch.int64, device=DEV))
+    for _ in range(2):                                                   # the second time on counters that have been drawn on
+        for t in out[1:5]:
+            t.fill_(99)
+        rs.schedule(D1, topo, capacity or n, out=out)
+        assert torch.equal(out[0], off)
+        for t in out[1:5]:
+            assert (t[n:] == 99).all()
+        for b in range(B):
+            lo, hi = int(off[b * M].item()), int(off[(b + 1) * M].item())
+            one = rs.schedule(D1[b:b + 1].contiguous(), topo, hi - lo)
+            for name, a, r in zip(("w", "flow", "perm", "rail"), out[1:5], one[1:5]):
+                assert torch.equal(a[lo:hi], r[:hi - lo]), (name, b)
+            for a, r in zip(out[5:], one[5:]):
+                assert torch.equal(a[b:b + 1], r)
