@@ -178,6 +178,10 @@ template <int T>
 __device__ __forceinline__ void instance_entries(const CsArgs &a, int inst, int64_t out0, int64_t n_all, int64_t n_full, int s, int tid)
 {
     if (n_all == 0) return;
+    if (n_full >> 32) {                             // more than an instance may have: flow starts do not fit, but every entry names an instance
+        for (int64_t e = ((out0 - 1) >> s) + 1 + tid; (e << s) < out0 + n_all; e += T) a.entries[e] = make_uint2((unsigned)inst, 0u);
+        return;
+    }
     // in 32 bits where positions, counted from the entry before the instance's first record, fit
     if (s < 31 && n_full < (int64_t)1 << 31) flow_entries<uint32_t, T>(a, inst, (uint32_t)n_full, out0, s, tid);
     else flow_entries<uint64_t, T>(a, inst, (uint32_t)n_full, out0, s, tid);
@@ -603,7 +607,7 @@ __device__ __forceinline__ void find_instance(const CsArgs &a, int64_t w, int64_
     }
 }
 
-__device__ __forceinline__ bool fill_windows_write(int64_t n_full) { return n_full >= kFillWindow; }
+__device__ __forceinline__ bool fill_windows_write(int64_t n_full) { return n_full >= kFillWindow && n_full <= 0xFFFFFFFFll; }
 
 // The records w0 .. w0 + 255 of instances of kFillWindow full chunks and more; w0, a multiple of 256, is below `total`.
 __device__ __forceinline__ void fill_window(const CsArgs &a, int vec_ok, unsigned *mark, int64_t w0, int64_t total)

@@ -135,3 +135,22 @@ def test_fill_beyond_the_launch(M, N, capacity):
                 assert torch.equal(a[lo:hi], r[:hi - lo]), (name, b)
             for a, r in zip(out[5:], one[5:]):
                 assert torch.equal(a[b:b + 1], r)
+
+
+def test_fill_positions_above_31_bits():
+    # one instance of more than 2^31 full chunks of one byte: entries are counted in 64 bits, positions go up to the last window
+    topo = rs.Topo(1, 2, 1, include_intra_node=1)
+    q = [(1 << 30) + 3, 5, (1 << 30) + 70_001, 1000]
+    n = sum(q)
+    assert n > 1 << 31
+    D1 = torch.tensor(q, dtype=torch.int64, device=DEV).view(1, 2, 2)
+    w = torch.zeros(n + 8, dtype=torch.int32, device=DEV)
+    flow = torch.full((n + 8,), -7, dtype=torch.int32, device=DEV)
+    off = torch.empty(2, dtype=torch.int64, device=DEV)
+    rs.chunk_sort(D1, topo, capacity=n, out=(off, w, flow, None))
+    assert off.tolist() == [0, n]
+    assert (w[:n] == 1).all() and (w[n:] == 0).all() and (flow[n:] == -7).all()
+    at = 0
+    for f, c in enumerate(q):
+        assert (flow[at:at + c] == f).all(), f
+        at += c
