@@ -6,7 +6,7 @@
 // "weight descending, ties in canonical order" all full chunks therefore come first, in canonical
 // order (their positions follow from an exclusive scan of floor(B/C) over the instance's flows), and
 // only the tails - at most one per flow, N*G per instance - need a real sort.  The tails of one
-// instance are sorted by one workgroup with a stable LSD radix sort held in registers (8-bit digits,
+// instance are sorted by one workgroup with a stable LSD radix sort, held in registers up to 8192 flows (8-bit digits,
 // ranks inside a 64-element batch from ballot matching).  Every chunk record is written to HBM
 // exactly once.
 //
@@ -249,8 +249,8 @@ __global__ __launch_bounds__(kScanThreads) void cs_scan_kernel(CsArgs a)
     }
 }
 
-// ---- C: tails of one instance: stable descending radix sort in LDS, one workgroup per instance ----
-// One workgroup of T threads per instance, V flows per thread, which stay in its registers: a wavefront owns 64 V consecutive flows, 64 at a time.  A pass
+// ---- C: tails of one instance: stable descending radix sort, one workgroup per instance ----
+// Up to kRegisterFlows flows: T threads, V flows per thread, which stay in its registers: a wavefront owns 64 V consecutive flows, 64 at a time.  A pass
 // (8 bits of the key; nearly always the only one, since tails are multiples of the token payload and only the span of bits that
 // differ at all counts) ranks a wavefront's elements among its own by ballots, batch after batch, the count of a digit so far in LDS; the scan of the
 // counts over (digit, wavefront) makes that the place; then the elements change places through LDS, one word each, keys first, then flows, at last
@@ -415,13 +415,17 @@ __global__ __launch_bounds__(T, V <= 4 ? 8 : 1) void cs_tail_kernel(CsArgs a)
     write_tails<T, V>(a, blockIdx.x, cs_lds, sh);
 }
 
-// Up to kSmallFlows flows: a wavefront by itself, which counts the tails before each instead of sorting where they are few.
-__global__ __launch_bounds__(64) void cs_tail_small_kernel(CsArgs a)
+// The sort of chunk_core.h, with flow ids and tail bytes in LDS: up to kSmallFlows flows by a wavefront, which counts the tails before each instead of sorting where they
+// are few, and beyond kRegisterFlows: sixteen flows a thread spill.  us of the whole stage, sixteen a thread / LDS, 256 instances of 16384 flows: all tails 112 / 80, a tenth 77 / 45,
+// 3 in a hundred 73 / 41; 520 of 8320 flows 166 / 128, 150 / 73, 140 / 64.  Canonical positions picked out in memory instead of LDS: 107 for the 80, but 1903 / 2076 the
+// other way round for 9001 instances of 9001 flows, two workgroups of 256 threads on a CU, and 41 / 45 for the 3 in a hundred.
+template <int T>
+__global__ __launch_bounds__(T) void cs_tail_lds_kernel(CsArgs a)
 {
     extern __shared__ __align__(16) unsigned cs_lds[];
     __shared__ unsigned sh[kTailShared];
-    unsigned *hist = cs_lds;                                             // [tail_hist_words<64>()], read 16 bytes at a time
-    unsigned *rem = hist + tail_hist_words<64>();                        // [NF] tail bytes per flow
+    unsigned *hist = cs_lds;                                             // [tail_hist_words<T>()], read 16 bytes at a time
+    unsigned *rem = hist + tail_hist_words<T>();                         // [NF] tail bytes per flow
     unsigned short *idx_a = reinterpret_cast<unsigned short *>(rem + a.NF);    // [NF] flow ids, ping
     unsigned short *idx_b = idx_a + a.NF;                                      // [NF] pong
     if (a.chunk_off[a.n_inst] > a.capacity) return;                      // record arrays too small: leave them alone
@@ -431,42 +435,52 @@ __global__ __launch_bounds__(64) void cs_tail_small_kernel(CsArgs a)
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
 
     int nt = 0;
-    const unsigned short *sorted = tail_sort_block<64>(a, rows, k, rem, hist, idx_a, idx_b, sh, nt, [] {});
+    const unsigned short *sorted = tail_sort_block<T>(a, rows, k, rem, hist, idx_a, idx_b, sh, nt, [] {});
 
     const int64_t out0 = a.chunk_off[inst] + a.cnt_full[inst];
     const uint32_t n_full = (uint32_t)a.cnt_full[inst];
     const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
     const uint16_t *tb = a.tails_before + (int64_t)inst * a.NF;
-    for (int i = threadIdx.x; i < nt; i += 64) {
+    auto canonical = [&](int f) { return (f + 1 < a.NF ? fs[f + 1] : n_full) + tb[f]; };
+    const bool through = T == 1024 && a.perm && 4 * nt > a.NF;           // canonical positions read in flow order and picked out in LDS
+    for (int i = threadIdx.x; i < nt; i += T) {
         const int f = sorted[i];
         a.chunk_w[out0 + i] = rem[f];
         a.chunk_flow[out0 + i] = (uint32_t)f;
-        if (a.perm) a.perm[out0 + i] = (f + 1 < a.NF ? fs[f + 1] : n_full) + tb[f];
+        if (!through && a.perm) a.perm[out0 + i] = canonical(f);
     }
+    if (!through) return;
+    __syncthreads();
+    for (int f = threadIdx.x; f < a.NF; f += T) rem[f] = canonical(f);
+    __syncthreads();
+    for (int i = threadIdx.x; i < nt; i += T) a.perm[out0 + i] = rem[sorted[i]];
 }
 
-template <int T, int V>
-static int launch_cs_tail(const CsArgs &a, hipStream_t st)
+static int launch_tail_kernel(void (*kernel)(CsArgs), int T, size_t lds, const CsArgs &a, hipStream_t st)
 {
-    const size_t lds = tail_lds<T>(a.NF);
     if (lds > 48 * 1024) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(cs_tail_kernel<T, V>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess)
-            return RAILSCHED_ERR_HIP;
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return RAILSCHED_ERR_HIP;
     }
-    hipLaunchKernelGGL((cs_tail_kernel<T, V>), dim3((unsigned)a.n_inst), dim3(T), lds, st, a);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)a.n_inst), dim3((unsigned)T), lds, st, a);
     return launch_status();
 }
 
+template <int T, int V>
+static int launch_cs_tail(const CsArgs &a, hipStream_t st) { return launch_tail_kernel(cs_tail_kernel<T, V>, T, tail_lds<T>(a.NF), a, st); }
+
+template <int T>
+static int launch_cs_tail_lds(const CsArgs &a, hipStream_t st)
+{
+    return launch_tail_kernel(cs_tail_lds_kernel<T>, T, sizeof(unsigned) * (size_t)(a.NF + tail_hist_words<T>()) + 2 * sizeof(unsigned short) * (size_t)a.NF, a, st);
+}
+
+constexpr int kRegisterFlows = 8192;
 static int launch_tails(const CsArgs &a, hipStream_t st)
 {
-    if (a.NF <= kSmallFlows) {
-        const size_t lds = sizeof(unsigned) * (size_t)(a.NF + tail_hist_words<64>()) + 2 * sizeof(unsigned short) * (size_t)a.NF;
-        hipLaunchKernelGGL(cs_tail_small_kernel, dim3((unsigned)a.n_inst), dim3(64), lds, st, a);
-        return launch_status();
-    }
+    if (a.NF <= kSmallFlows) return launch_cs_tail_lds<64>(a, st);
+    if (a.NF > kRegisterFlows) return flow_threads(a.n_inst, a.NF) == 256 ? launch_cs_tail_lds<256>(a, st) : launch_cs_tail_lds<1024>(a, st);
     return a.NF <= 512 ? launch_cs_tail<256, 2>(a, st) : a.NF <= 1024 ? launch_cs_tail<256, 4>(a, st) : a.NF <= 2048 ? launch_cs_tail<512, 4>(a, st)
-         : a.NF <= 4096 ? launch_cs_tail<1024, 4>(a, st) : a.NF <= 8192 ? launch_cs_tail<1024, 8>(a, st) : launch_cs_tail<1024, 16>(a, st);
+         : a.NF <= 4096 ? launch_cs_tail<1024, 4>(a, st) : launch_cs_tail<1024, 8>(a, st);
 }
 
 // ---- D: full chunks ---------------------------------------------------------------------------
