@@ -256,12 +256,13 @@ __global__ __launch_bounds__(kScanThreads) void cs_scan_kernel(CsArgs a)
 // counts over (digit, wavefront) makes that the place; then the elements change places through LDS, one word each, keys first, then flows, at last
 // the canonical positions, which are read in flow order.  LDS is four bytes a flow and a kilobyte a wavefront: twice the
 // workgroups on a CU of a sort that keeps flow ids and tail bytes in LDS, and no gathers from memory.
-template <int T> constexpr size_t tail_lds(int64_t NF) { return sizeof(unsigned) * (size_t)(NF + 256 * (T / 64)); }
+template <int T> constexpr size_t tail_lds(int64_t NF) { return sizeof(unsigned) * (size_t)(NF + 4 + 256 * (T / 64)); }
 
 // at[j] = place of element j (key[j], act bit) among all active elements by bits shift .. shift + bits - 1 of the keys, descending, stable.  `mine` is this
-// wavefront's histogram, hist all of them.
+// wavefront's histogram, hist all of them; the wavefront has elements in its first `batches` batches only.
 template <int T, int V>
-__device__ __forceinline__ void tail_places(const unsigned (&key)[V], const bool (&act)[V], unsigned (&at)[V], int shift, int bits, unsigned *hist, unsigned *sh_tot)
+__device__ __forceinline__ void tail_places(const unsigned (&key)[V], const bool (&act)[V], unsigned (&at)[V], int batches, int shift, int bits, unsigned *hist,
+                                            unsigned *sh_tot)
 {
     constexpr int W = T / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -270,6 +271,7 @@ __device__ __forceinline__ void tail_places(const unsigned (&key)[V], const bool
     *reinterpret_cast<uint4 *>(mine + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
     for (int j = 0; j < V; ++j) {                                        // batches in order keep the sort stable
+        if (j >= batches) break;
         const unsigned d = 255u - ((key[j] >> shift) & 255u);
         unsigned long long peers = __ballot(act[j]);
         for (int bit = 0; bit < bits; bit += 2) {   // one bit too many changes nothing: it is the same in all keys
@@ -302,7 +304,108 @@ __device__ __forceinline__ void tail_places(const unsigned (&key)[V], const bool
     __syncthreads();
     asm volatile("" : "+s"(shift));                 // the digits anew: kept from above they and their addresses would take V registers more
 #pragma unroll
-    for (int j = 0; j < V; ++j) at[j] += mine[255u - ((key[j] >> shift) & 255u)];
+    for (int j = 0; j < V; ++j) if (j < batches) at[j] += mine[255u - ((key[j] >> shift) & 255u)];
+}
+
+// Bits that differ at all between the tails of a workgroup, from every thread's any1 and all1; one barrier.
+template <int T>
+__device__ __forceinline__ unsigned tail_bits(unsigned any1, unsigned all1, unsigned *sh_bits)
+{
+    constexpr int W = T / 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) { any1 |= (unsigned)__shfl_xor((int)any1, d); all1 &= (unsigned)__shfl_xor((int)all1, d); }
+    if (lane == 0) { sh_bits[wave] = any1; sh_bits[W + wave] = all1; }
+    __syncthreads();
+    any1 = 0u; all1 = 0xFFFFFFFFu;
+#pragma unroll
+    for (int w = 0; w < W; ++w) { any1 |= sh_bits[w]; all1 &= sh_bits[W + w]; }
+    return (unsigned)__builtin_amdgcn_readfirstlane((int)(any1 ^ all1));
+}
+
+// Tails whose places are counted, one pass over the others in LDS, instead of sorted for (4000 instances of 224 tails of 512 flows 51 us counted, 35 sorted).
+template <int T> constexpr int few_tails() { return T >= 512 ? 256 : 128; }
+
+// The tails of an instance at most half of whose flows have one: brought together in LDS (where to is what tails_before says), then counted or sorted.
+template <int T, int V>
+__device__ __forceinline__ void write_few_tails(const CsArgs &a, int inst, int nt, int64_t n_full, const int64_t *rows, int k, unsigned *lds, unsigned *sh)
+{
+    constexpr int W = T / 64, C = (V + 1) / 2;
+    unsigned *hist = lds, *stage = lds + 256 * W, *ids = stage + ((a.NF + 1) / 2 + 3) / 4 * 4;
+    unsigned *sh_bits = sh, *sh_tot = sh + 2 * W;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t out0 = a.chunk_off[inst] + n_full;
+    const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
+    const uint16_t *tb = a.tails_before + (int64_t)inst * a.NF;
+    unsigned any1 = 0u, all1 = 0xFFFFFFFFu;
+    {
+        int64_t bytes[V];
+        uint32_t q[V], r[V];
+        unsigned to[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) { const int f = j * T + tid; to[j] = tb[f < a.NF ? f : a.NF - 1]; }
+        load_flows<V>(a, rows, k, tid, T, bytes);
+        split_flows<V>(a, bytes, q, r);
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            if (r[j] == 0) continue;
+            stage[to[j]] = r[j];
+            ids[to[j]] = (unsigned)(j * T + tid);
+            any1 |= r[j]; all1 &= r[j];
+        }
+    }
+    auto put = [&](int64_t i, unsigned w, unsigned f) {
+        a.chunk_w[i] = w;
+        a.chunk_flow[i] = f;
+        if (a.perm) a.perm[i] = ((int)f + 1 < a.NF ? fs[f + 1] : (uint32_t)n_full) + tb[f];
+    };
+    if (nt <= few_tails<T>()) {
+        constexpr int P = T >= 1024 ? 4 : T >= 512 ? 2 : 1;              // threads a tail
+        const int quads = (nt + 3) >> 2, i = tid / P;
+        if (tid < 4 * quads - nt) stage[nt + tid] = 0u;                  // behind the last: a tail is at least one byte
+        __syncthreads();
+        const unsigned w = i < nt ? stage[i] : 0u;
+        unsigned rank = 0;
+        if (w)
+            for (int g = tid % P; g < quads; g += P) {
+                const uint4 o = *reinterpret_cast<const uint4 *>(stage + 4 * g);
+                const int j = 4 * g;
+                rank += (o.x > w || (o.x == w && j + 0 < i)) ? 1u : 0u;
+                rank += (o.y > w || (o.y == w && j + 1 < i)) ? 1u : 0u;
+                rank += (o.z > w || (o.z == w && j + 2 < i)) ? 1u : 0u;
+                rank += (o.w > w || (o.w == w && j + 3 < i)) ? 1u : 0u;
+            }
+#pragma unroll
+        for (int d = 1; d < P; d <<= 1) rank += (unsigned)__shfl_xor((int)rank, d);
+        if (w && tid % P == 0) put(out0 + rank, w, ids[i]);
+        return;
+    }
+    const unsigned diff = tail_bits<T>(any1, all1, sh_bits);
+    const int lo_bit = diff ? __builtin_ctz(diff) : 0;
+    const int span = diff ? 32 - __builtin_clz(diff) - lo_bit : 0;
+    const int share = (nt + 64 * W - 1) / (64 * W), i0 = wave * 64 * share + lane;   // batches of a wavefront
+    unsigned key[C], id[C], at[C];
+    bool act[C];
+    auto take = [&] {
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            const int i = i0 + 64 * j;
+            act[j] = j < share && i < nt;
+            key[j] = act[j] ? stage[i] : 0u;
+            id[j] = act[j] ? ids[i] : 0u;
+        }
+        __syncthreads();
+    };
+    take();
+    for (int done = 0; done < span; done += 8) {
+        tail_places<T, C>(key, act, at, share, lo_bit + done, span - done < 8 ? span - done : 8, hist, sh_tot);
+#pragma unroll
+        for (int j = 0; j < C; ++j) if (act[j]) { stage[at[j]] = key[j]; ids[at[j]] = id[j]; }
+        __syncthreads();
+        take();
+    }
+#pragma unroll
+    for (int j = 0; j < C; ++j) if (act[j]) put(out0 + i0 + 64 * j, key[j], id[j]);
 }
 
 template <int T, int V>
@@ -311,42 +414,40 @@ __device__ __forceinline__ void write_tails(const CsArgs &a, int inst, unsigned 
     constexpr int W = T / 64;
     unsigned *hist = lds, *stage = lds + 256 * W;
     unsigned *sh_bits = sh, *sh_tot = sh + 2 * W;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = inst / a.M, k = inst % a.M;
     const int64_t *rows = a.D1 + ((int64_t)b * a.G + (int64_t)k * a.N) * a.G;
     const int64_t n_full = a.cnt_full[inst];
     const int nt = (int)(a.cnt_all[inst] - n_full);
     if (nt == 0) return;
+    if (2 * nt <= a.NF) {
+        write_few_tails<T, V>(a, inst, nt, n_full, rows, k, lds, sh);
+        return;
+    }
     const int64_t out0 = a.chunk_off[inst] + n_full;
     const uint32_t *fs = a.full_start + (int64_t)inst * a.NF;
     const uint16_t *tb = a.tails_before + (int64_t)inst * a.NF;
     const int i0 = wave * 64 * V + lane;            // this thread's elements: i0, i0 + 64, ...
+    const int batches = (a.NF - wave * 64 * V + 63) / 64;   // of this wavefront, V and more: all
     unsigned key[V], at[V];
     bool act[V];
+    unsigned any1 = 0u, all1 = 0xFFFFFFFFu;         // which key bits differ at all
     {
         int64_t bytes[V];
         uint32_t q[V];
         load_flows<V>(a, rows, k, i0, 64, bytes);
         split_flows<V>(a, bytes, q, key);
-        unsigned any1 = 0u, all1 = 0xFFFFFFFFu;     // which key bits differ at all
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             act[j] = key[j] != 0u;
             any1 |= key[j];
             all1 &= act[j] ? key[j] : 0xFFFFFFFFu;
         }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) { any1 |= (unsigned)__shfl_xor((int)any1, d); all1 &= (unsigned)__shfl_xor((int)all1, d); }
-        if (lane == 0) { sh_bits[wave] = any1; sh_bits[W + wave] = all1; }
     }
-    __syncthreads();
-    unsigned any1 = 0u, all1 = 0xFFFFFFFFu;
-#pragma unroll
-    for (int w = 0; w < W; ++w) { any1 |= sh_bits[w]; all1 &= sh_bits[W + w]; }
-    const unsigned diff = (unsigned)__builtin_amdgcn_readfirstlane((int)(any1 ^ all1));
+    const unsigned diff = tail_bits<T>(any1, all1, sh_bits);
     const int lo_bit = diff ? __builtin_ctz(diff) : 0;
     const int span = diff ? 32 - __builtin_clz(diff) - lo_bit : 0;
-    tail_places<T, V>(key, act, at, lo_bit, span < 8 ? span : 8, hist, sh_tot);
+    tail_places<T, V>(key, act, at, batches, lo_bit, span < 8 ? span : 8, hist, sh_tot);
     // a tail is its flow's last chunk: the full chunks up to the next flow and the tails before it come first
     if (span <= 8) {
         auto through = [&](auto value, uint32_t *to) {
@@ -391,7 +492,7 @@ __device__ __forceinline__ void write_tails(const CsArgs &a, int inst, unsigned 
         if (done >= span) break;
 #pragma unroll
         for (int j = 0; j < V; ++j) act[j] = i0 + 64 * j < nt;           // flows without a tail have left
-        tail_places<T, V>(key, act, at, lo_bit + done, span - done < 8 ? span - done : 8, hist, sh_tot);
+        tail_places<T, V>(key, act, at, (nt - wave * 64 * V + 63) / 64, lo_bit + done, span - done < 8 ? span - done : 8, hist, sh_tot);
     }
 #pragma unroll
     for (int j = 0; j < V; ++j) {
@@ -404,8 +505,10 @@ __device__ __forceinline__ void write_tails(const CsArgs &a, int inst, unsigned 
 }
 
 // V = 4 fits 64 registers, that is eight wavefronts on a SIMD.  us, 3904 instances of 4096 flows, 3074 tails of 64 values: by 256 threads with ids and tail bytes in LDS
-// 159, eight flows a thread 152, four 104 (its traffic 57); 4096 instances of 2048 flows 37 and 35; whole stage, every flow a 16-bit tail: 250 x 16 instances of 1024 flows
-// 66 / 57, 128 x 32 of 2048 105 / 94, 30 x 128 of 8192 583 / 412.
+// 159, eight flows a thread 152, four 104 (its traffic 57); whole stage, LDS / registers: all tails of 16 bits, 4000 instances of 1024 flows 66 / 55, 3600 of 2700 136 / 136,
+// 3904 of 4096 247 / 206, 3600 of 7680 666 / 504, 850 of 5440 123 / 108; a tenth of them 48 / 36, 88 / 88, 117 / 120, 367 / 251, 75 / 62; 30 in a thousand
+// 40 / 31, 75 / 65, 112 / 88, 367 / 200, 62 / 50 (45, 143, 164, 356, 93 when all flows went through the passes).  3600 instances of 2700 flows and 1700 of 1088 of which half have tails
+// are what loses: 113 / 122, 37 / 40.
 template <int T, int V>
 __global__ __launch_bounds__(T, V <= 4 ? 8 : 1) void cs_tail_kernel(CsArgs a)
 {
@@ -475,11 +578,14 @@ static int launch_cs_tail_lds(const CsArgs &a, hipStream_t st)
 }
 
 constexpr int kRegisterFlows = 8192;
+// Threads for four flows each: a wavefront without flows waits at every barrier and holds its room (1590 instances of 1080 flows 45 us by 512 threads, 40 by 320; 1200 of 2700 66
+// by 1024, 58 by 768).
 static int launch_tails(const CsArgs &a, hipStream_t st)
 {
     if (a.NF <= kSmallFlows) return launch_cs_tail_lds<64>(a, st);
     if (a.NF > kRegisterFlows) return flow_threads(a.n_inst, a.NF) == 256 ? launch_cs_tail_lds<256>(a, st) : launch_cs_tail_lds<1024>(a, st);
-    return a.NF <= 512 ? launch_cs_tail<256, 2>(a, st) : a.NF <= 1024 ? launch_cs_tail<256, 4>(a, st) : a.NF <= 2048 ? launch_cs_tail<512, 4>(a, st)
+    return a.NF <= 512 ? launch_cs_tail<256, 2>(a, st) : a.NF <= 1024 ? launch_cs_tail<256, 4>(a, st) : a.NF <= 1280 ? launch_cs_tail<320, 4>(a, st)
+         : a.NF <= 1536 ? launch_cs_tail<384, 4>(a, st) : a.NF <= 2048 ? launch_cs_tail<512, 4>(a, st) : a.NF <= 3072 ? launch_cs_tail<768, 4>(a, st)
          : a.NF <= 4096 ? launch_cs_tail<1024, 4>(a, st) : launch_cs_tail<1024, 8>(a, st);
 }
 

@@ -58,7 +58,7 @@ def test_instances_of_few_records_cost_no_more_than_of_many(M, N, B, mean, zero)
     assert few < 1.4 * many + 15, (few, many)                            # 2.5 to 15 times when a wavefront went from instance to instance
 
 
-@pytest.mark.parametrize("M,N,B", [(130, 8, 4), (64, 16, 4)])
+@pytest.mark.parametrize("M,N,B", [(130, 8, 4), (64, 8, 20), (30, 6, 130), (16, 8, 250)])
 def test_few_tails_cost_less_than_many(M, N, B):
     topo = rs.Topo(M, N, 65536)
     gen = torch.Generator(device=DEV).manual_seed(M)
@@ -66,4 +66,4 @@ def test_few_tails_cost_less_than_many(M, N, B):
     few = torch.where(torch.rand(many.shape, device=DEV, generator=gen) < 0.97, torch.zeros_like(many), many)
     counts = [rs.chunk_total(D, topo) for D in (few, many)]
     a, b = _us(*[_sort(D, topo, n, n) for D, n in zip((few, many), counts)])
-    assert a < 0.75 * b, (a, b)                                          # 0.5; 0.65 to 0.85 when sixteen flows a thread went through every pass
+    assert a < 0.75 * b, (a, b)                                          # 0.45 to 0.6; 0.75 to 0.95 when every flow went through every pass
