@@ -17,6 +17,7 @@ struct CsArgs {
     uint2 *entries;              // [n_entries] (instance, flow) at every 2^s-th record, where the record fill starts its searches (fill_entry_shift)
     int64_t n_entries;           // 0: none, the fill searches
     unsigned *tickets;           // when set, the counters that the fill's last workgroups draw further tiles on
+    int64_t *sums;               // when set, [workgroups of the scan] chunks of the instances of each
     int64_t C;
     uint64_t cinv;       // (2^64 - 1) / C
     uint32_t ginv;       // 2^32 / G, rounded up (G > 1)

@@ -189,32 +189,58 @@ __device__ __forceinline__ void instance_entries(const CsArgs &a, int inst, int6
         a.entries[e] = make_uint2((unsigned)inst, (unsigned)a.NF);
 }
 
-// Every workgroup takes a few consecutive instances and adds up all counts by itself (the counts are few and in L2; handing sums on would need another
-// launch).  It writes its instances' offsets and entries, those of instances of few flows by a wavefront each: 16 000 instances of 64 flows 18 us by a
-// wavefront, 36 by all threads (20 by one workgroup without entries); 3904 of 4096 flows 40 and 26.
+// Every workgroup takes a few consecutive instances and adds up all counts by itself, or, of more than kScanAlone instances, the sums that a launch before left,
+// one for the instances of each workgroup: what all workgroups read together grows with workgroups times instances otherwise.  us, count query alone / whole call, by
+// counts / by sums: 16 000 instances of 2 flows 16.7 / 17.5 and 31.0 / 31.5, 32 000 27 / 23 and 48 / 45, 131 072 165 / 60 and 260 / 155, 1 M 1249 / 359 and 1657 / 764, 4.2 M of
+// 64 flows 5170 / 1530 and 11 000 / 7520.  A workgroup writes its instances' offsets and entries, those of instances of few flows by a wavefront each: 16 000 instances of 64 flows
+// 18 us by a wavefront, 36 by all threads (20 by one workgroup without entries); 3904 of 4096 flows 40 and 26.
 constexpr int kScanThreads = 256, kScanBlocks = 2048;
+constexpr int64_t kScanAlone = 16384;   // at least kScanBlocks: the sums lie where entries of 8 bytes an instance would
+
+// the instances of workgroup b of the scan: first(b) .. first(b + 1) - 1
+__device__ __forceinline__ int scan_first(const CsArgs &a, unsigned b) { return (int)((int64_t)a.n_inst * b / gridDim.x); }
+
+__global__ __launch_bounds__(kScanThreads) void cs_sums_kernel(CsArgs a)
+{
+    constexpr int W = kScanThreads / 64;
+    __shared__ int64_t sh[W];
+    const int tid = threadIdx.x, i1 = scan_first(a, blockIdx.x + 1);
+    int64_t sum = 0;
+#pragma unroll 4
+    for (int i = scan_first(a, blockIdx.x) + tid; i < i1; i += kScanThreads) sum += a.cnt_all[i];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
+    if ((tid & 63) == 0) sh[tid >> 6] = sum;
+    __syncthreads();
+    if (tid != 0) return;
+    for (int w = 1; w < W; ++w) sum += sh[w];
+    a.sums[blockIdx.x] = sum;
+}
+
 __global__ __launch_bounds__(kScanThreads) void cs_scan_kernel(CsArgs a)
 {
     constexpr int W = kScanThreads / 64, U = 16;
     __shared__ int64_t sh[2][W];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int i0 = (int)((int64_t)a.n_inst * blockIdx.x / gridDim.x), i1 = (int)((int64_t)a.n_inst * (blockIdx.x + 1) / gridDim.x);
+    const int i0 = scan_first(a, blockIdx.x), i1 = scan_first(a, blockIdx.x + 1);
     // the counts of its instances, 64 at a time; the first ones are on their way while all are added up
     auto count = [&](const int64_t *of, int base) { return base + lane < i1 ? of[base + lane] : 0; };
     int64_t n_all = count(a.cnt_all, i0), n_full = count(a.cnt_full, i0);
     int64_t before = 0, total = 0;
-    for (int base = 0; base < a.n_inst; base += U * kScanThreads) {
+    const int64_t *of = a.sums ? a.sums : a.cnt_all;
+    const int n = a.sums ? (int)gridDim.x : a.n_inst, n0 = a.sums ? (int)blockIdx.x : i0;
+    for (int base = 0; base < n; base += U * kScanThreads) {
         int64_t c[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = base + u * kScanThreads + tid;
-            c[u] = a.cnt_all[i < a.n_inst ? i : a.n_inst - 1];
+            c[u] = of[i < n ? i : n - 1];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = base + u * kScanThreads + tid;
-            total += i < a.n_inst ? c[u] : 0;
-            before += i < i0 ? c[u] : 0;
+            total += i < n ? c[u] : 0;
+            before += i < n0 ? c[u] : 0;
         }
     }
 #pragma unroll
@@ -830,6 +856,7 @@ static void fill_args(CsArgs &a, const railsched_topo_t *h_topo, int64_t n_inst,
     a.entries = reinterpret_cast<uint2 *>(w8 + off[4]);
     a.n_entries = (int64_t)((off[5] - off[4]) / sizeof(uint2));
     a.tickets = nullptr;
+    a.sums = nullptr;
     a.C = h_topo->chunk_bytes;
     a.cinv = ~0ull / (uint64_t)a.C;
     a.ginv = G > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)G - 1) / (uint64_t)G) : 0u;
@@ -888,6 +915,10 @@ int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int
     a.run_end = run_end;
     a.clear = nullptr;
     fill_args(a, h_topo, n_inst, ws);
+    if (n_inst > kScanAlone) {
+        a.n_entries -= kScanBlocks;
+        a.sums = reinterpret_cast<int64_t *>(a.entries + a.n_entries);
+    }
     // Few records of instances of few flows are written as fast by wavefronts that search for their instance and go through its flows (scan / fill in us
     // with entries and without, 1672 instances of 152 flows 7.2 / 9.4, 4.3 / 10.0; 1457 of 775 flows 10.7 / 3.2, 5.0 / 3.5); a count query needs none.
     if (!chunk_w || (NF <= kSearchFlows && capacity <= kSearchRecords)) a.n_entries = 0;
@@ -907,6 +938,10 @@ int cs_run(const int64_t *D1, int32_t batch, const railsched_topo_t *h_topo, int
     }
     const int64_t scan_wants = a.n_entries ? n_inst : (n_inst + 63) / 64;       // workgroups: offsets alone are 64 lanes' work
     const int64_t scan_blocks = scan_wants < 1 ? 1 : scan_wants > kScanBlocks ? kScanBlocks : scan_wants;
+    if (a.sums) {
+        hipLaunchKernelGGL(cs_sums_kernel, dim3((unsigned)scan_blocks), dim3(kScanThreads), 0, st, a);
+        if (int rc = launch_status()) return rc;
+    }
     hipLaunchKernelGGL(cs_scan_kernel, dim3((unsigned)scan_blocks), dim3(kScanThreads), 0, st, a);
     if (int rc = launch_status()) return rc;
     if (!chunk_w || n_inst == 0) return RAILSCHED_OK;

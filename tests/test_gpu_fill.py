@@ -137,6 +137,31 @@ def test_fill_beyond_the_launch(M, N, capacity):
                 assert torch.equal(a[b:b + 1], r)
 
 
+@pytest.mark.parametrize("B", [8192, 8193, 16401])                   # the scan alone and with sums, of 2 nodes each
+@pytest.mark.parametrize("large", [0, 9_000_000])                    # and with more records than the launch has workgroups for, beside its tickets
+def test_offsets_of_many_instances(B, large):
+    M, N, C, parts = 2, 1, 4096, 5
+    rng = np.random.default_rng(B)
+    q = rng.integers(0, 4, size=(B, 2)) * (rng.random((B, 2)) < 0.7)
+    q[rng.choice(B, size=4, replace=False), 0] = 1000 + large
+    D1n = np.zeros((B, 2, 2), dtype=np.int64)
+    D1n[:, [0, 1], [1, 0]] = q * C + rng.integers(0, 2, size=(B, 2)) * rng.integers(1, C, size=(B, 2))
+    D1 = torch.from_numpy(D1n).to(DEV)
+    topo = rs.Topo(M, N, C)
+    ref = np.concatenate([[0], np.cumsum((D1n[:, [0, 1], [1, 0]] + C - 1) // C)])
+    assert np.array_equal(rs.chunk_count(D1, topo).cpu().numpy(), ref)
+    n = int(ref[-1])
+    for cap in (n, n + (1 << 21)):                                       # without entries and with them
+        off, *recs = rs.chunk_sort(D1, topo, capacity=cap)
+        assert np.array_equal(off.cpu().numpy(), ref)
+        for p in range(parts):                                           # few enough instances for the scan alone
+            b0, b1 = B * p // parts, B * (p + 1) // parts
+            lo, hi = int(ref[b0 * M]), int(ref[b1 * M])
+            _, *part = rs.chunk_sort(D1[b0:b1].contiguous(), topo, capacity=hi - lo)
+            for name, a, r in zip(("w", "flow", "perm"), recs, part):
+                assert torch.equal(a[lo:hi], r[:hi - lo]), (name, p, cap)
+
+
 def test_fill_positions_above_31_bits():
     # one instance of more than 2^31 full chunks of one byte: entries are counted in 64 bits, positions go up to the last window
     topo = rs.Topo(1, 2, 1, include_intra_node=1)
