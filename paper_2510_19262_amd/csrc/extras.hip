@@ -199,7 +199,7 @@ __device__ __forceinline__ void port_widen(const unsigned long long (&c)[NW], un
 }
 
 // The rails of a leading run, and of any run of one weight from level loads, go round and round.  A lane whose 16 chunks do (N a power of two up to 16: every
-// rail 16 / N times, whichever comes first) needs no counting; `step` says that all lanes of a wavefront do.
+// rail 16 / N times, whichever comes first) needs no counting.
 __device__ __forceinline__ bool port_cyclic(const uint4 &x, unsigned nmask)
 {
     const unsigned all = nmask * 0x01010101u, r0 = x.x & 0xFFu;
@@ -301,9 +301,10 @@ __global__ __launch_bounds__(64 * kPortWaves) void port_packed_kernel(PortArgs a
             }
         } else {
             // A 64-bit shift by the last register a wavefront has goes wrong when others share its SIMD: 88 registers, amount in v87, and one chunk of
-            // sixteen got a wrong port in one tile of twenty.  Taking v95 makes 96 of them, still five wavefronts a SIMD; the shifts below stay under it
-            // (by 32-bit halves instead, without such shifts: 850 us for three stages and ports of 120 M chunks, 820 so).
-            asm volatile("; v95 is not used" ::: "v95");
+            // sixteen got a wrong port in one tile of twenty.  Taking the last register of the granule, v95 of 96 and five wavefronts a SIMD up to 8 rails, v103 of 104 and
+            // four beyond, keeps the shifts below under it (by 32-bit halves instead, without such shifts: 850 us for three stages and ports of 120 M chunks, 820 so).
+            if constexpr (NW == 1) asm volatile("; v95 is not used" ::: "v95");
+            else asm volatile("; v103 is not used" ::: "v103");
             const unsigned pm = (unsigned)a.P - 1u, pm2 = pm | (pm << 16);
             const unsigned per_lane = a.nmask >= 0 ? 16u / (unsigned)a.N : 0u;          // of every rail, where rails go round and round
             unsigned start[4 * NW];                                 // counts before the step modulo P, 16-bit fields

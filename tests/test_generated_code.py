@@ -43,6 +43,16 @@ def test_no_64_bit_shift_by_the_last_register(src):
     assert not list(_shifts_by_the_last_register(text))
 
 
+@pytest.mark.parametrize("registers", [1, 2])
+def test_the_port_kernels_leave_their_last_register_alone(registers):
+    body, kernel = re.search(r"^_ZN2rs18port_packed_kernelILb1ELi%dEE\w+:\s*; @\w+\n(.*?)\.amdhsa_kernel (.*?)\.end_amdhsa_kernel" % registers, _assembly("extras.hip"), re.S | re.M).groups()
+    last = int(re.search(r"amdhsa_next_free_vgpr (\d+)", kernel)[1]) - 1
+    assert last % 8 == 7
+    instructions = re.sub(r";.*", "", body)
+    for lo, hi in re.findall(r"\bv(?:\[(\d+):)?(\d+)\b", instructions):
+        assert int(hi) < last
+
+
 def test_indices_of_the_list_kernels_are_streamed():
     # a plain store beside them under the same condition would make them plain: 4 194 304 rows of 64 logits, top-6: 209 us streaming, 222 plain
     bodies = re.findall(r"^(_ZN2rs24route_topk_insert_kernel\w+):\s*; @\1\n(.*?)\.amdhsa_kernel \1\n", _assembly("route_topk.hip"), re.S | re.M)
