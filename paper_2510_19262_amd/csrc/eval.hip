@@ -230,8 +230,9 @@ int launch_eval_reduce(const EvArgs &a, int batch, hipStream_t st, bool summed)
         return launch_status();
     }
     // A workgroup reads its matrix's slots alone.  256 threads up to 16 Ki sums, or 9 Ki of more bins than that: cheaper barriers, and 1024 matrices would
-    // wait for each other in workgroups of 1024 (us by 256 / 1024, 32 slots of 256 bins: one matrix 36.1 / 38.6 for the whole schedule, 1024 matrices 25 / 37
-    // for this kernel; 64 of 256 30.8 / 32.6, 33 of 264 38.9 / 40.0, 9 of 288 152 / 154; but 47 of 282 47.5 / 47.0, 44 of 352 47.2 / 46.8).  1024 threads up to 64 Ki sums, or any
+    // wait for each other in workgroups of 1024 (us of this kernel by 256 / 1024, slots of bins: 1024 matrices of 32 slots of 256 bins 16.9 / 28.8, 128 of them 6.6 / 7.6;
+    // 4096 of 8 of 64 14 / 54; 256 of 16 of 128 4.7 / 6.1; 64 of 64 of 256 8.1 / 8.3; 128 of 16 of 264 6.7 / 7.1, of 33 of 264 8.8 / 8.2; but 128 of 47 of 282 11.6 / 9.9, of
+    // 44 of 352 12.9 / 10.6).  1024 threads up to 64 Ki sums, or any
     // number of up to 128 bins, whose slots are read side by side (2048 slots of 64 bins: 35 us for the evaluation, 57 in two kernels; of 128 bins: 52 / 63,
     // of 144: 68 / 63).  Beyond that the slots are summed by G / 64 workgroups per matrix first (128 slots of 1024 bins: 58 us by one workgroup as it
     // was, 5 + 8 in two kernels).
