@@ -106,7 +106,8 @@ def test_fill_instances_around_a_window(shift):
 
 @pytest.mark.parametrize("M,N", [(2, 1), (8, 8)])                    # few flows, without room for counters, and many
 @pytest.mark.parametrize("capacity", [0, 1 << 40])
-def test_fill_beyond_the_launch(M, N, capacity):
+@pytest.mark.parametrize("perm", [True, False])                      # half of the workgroups draw, or all
+def test_fill_beyond_the_launch(M, N, capacity, perm):
     # more records than the launch has workgroups for: its last ones draw the rest by tickets, or go round.  Matrix by matrix there are fewer, and the records are the same
     B, C, G = 5, 4096, M * N
     per = 2 * 12_000_000 // (G * (G - N))                                # twice the mean number of chunks of a flow
@@ -121,18 +122,21 @@ def test_fill_beyond_the_launch(M, N, capacity):
     out = (torch.empty_like(off), *[torch.full((n + 64,), -7, dtype=torch.int32, device=DEV) for _ in range(3)],
            torch.full((n + 64,), 99, dtype=torch.uint8, device=DEV), *[torch.empty((B, M, N), dtype=torch.int64, device=DEV) for _ in range(2)],
            torch.empty((B, 8), dtype=torch.int64, device=DEV))
+    if not perm:
+        out = (*out[:3], None, *out[4:])
     for _ in range(2):                                                   # the second time on counters that have been drawn on
         for t in out[1:5]:
-            t.fill_(99)
+            if t is not None:
+                t.fill_(99)
         rs.schedule(D1, topo, capacity or n, out=out)
         assert torch.equal(out[0], off)
         for t in out[1:5]:
-            assert (t[n:] == 99).all()
+            assert t is None or (t[n:] == 99).all()
         for b in range(B):
             lo, hi = int(off[b * M].item()), int(off[(b + 1) * M].item())
             one = rs.schedule(D1[b:b + 1].contiguous(), topo, hi - lo)
             for name, a, r in zip(("w", "flow", "perm", "rail"), out[1:5], one[1:5]):
-                assert torch.equal(a[lo:hi], r[:hi - lo]), (name, b)
+                assert a is None or torch.equal(a[lo:hi], r[:hi - lo]), (name, b)
             for a, r in zip(out[5:], one[5:]):
                 assert torch.equal(a[b:b + 1], r)
 
