@@ -156,16 +156,9 @@ __device__ __forceinline__ int window_flows(const uint32_t *fs, int nf, int j_lo
     lds_sync();
     const uint4 m = *reinterpret_cast<const uint4 *>(mark + 4 * lane);
     const unsigned m1 = max(m.x, m.y), m2 = max(m1, m.z), m3 = max(m2, m.w);
-    unsigned inc = max(m3, (unsigned)j_lo);         // inclusive maximum over the lanes
-    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xF, 0xF, false));   // row_shr:1
-    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xF, 0xF, false));   // row_shr:2
-    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x114, 0xF, 0xF, false));   // row_shr:4
-    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xF, 0xF, false));   // row_shr:8
-    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x142, 0xA, 0xF, false));   // row_bcast15 into rows 1 and 3
-    inc = max(inc, (unsigned)__builtin_amdgcn_update_dpp(0, (int)inc, 0x143, 0xC, 0xF, false));   // row_bcast31 into rows 2 and 3
-    const unsigned left = (unsigned)__builtin_amdgcn_update_dpp(j_lo, (int)inc, 0x138, 0xF, 0xF, false);   // wave_shr:1; lane 0 keeps j_lo
+    const unsigned left = wave_max_before(max(m3, (unsigned)j_lo), (unsigned)j_lo);
     fl[0] = max(left, m.x); fl[1] = max(left, m1); fl[2] = max(left, m2); fl[3] = max(left, m3);
-    return __builtin_amdgcn_readlane((int)inc, 63);
+    return __builtin_amdgcn_readlane((int)fl[3], 63);
 }
 
 constexpr int kTailLoads = 4;       // flows per thread and round of the flow scans: their loads are in flight together
@@ -187,8 +180,7 @@ template <int T> constexpr int rank_flows() { return T == 64 ? 96 : 64; }
 // barrier (ballot matching in batches of 64); a pass has four.  rem[NF] receives every flow's tail bytes,
 // hist[tail_hist_words<T>()] and sh[kTailShared] are scratch, idx_a/idx_b[NF] are ping-pong arrays of flow ids; returns the
 // array that holds the sorted ids and their number in nt.  Latency bound: one wavefront took 32 us for the 4096 flows of a
-// 512-GPU instance, and four of them per CU (its LDS) 364 us for 3904 such instances; a workgroup of 1024 takes 14 us for 128 instances of 8192 flows (67 before),
-// one of 256 155 us for the 3904.
+// 512-GPU instance, a workgroup of 1024 takes 6.  Callers: the one-call scheduler's instances, and in stage 3 those of up to 256 flows and of more than 8192.
 // stage() is called once with the first flows' loads in flight, for what the caller has to fetch as well.
 template <int T, typename F>
 __device__ __forceinline__ unsigned short *tail_sort_block(const CsArgs &a, const int64_t *rows, int k, unsigned *rem, unsigned *hist,

@@ -55,8 +55,8 @@ constexpr int kSlThreads = 256;         // closed-form receive loads of large ba
 constexpr int kSsRun = 24;              // late chunks per run of one weight from which the chain goes run by run (lpt_runs_body)
 constexpr int kSsLateAlone = 128;       // late chunks up to which the chain's wavefront also finishes them, beside the others' records
 constexpr int kSsMaxInst = 1024;        // instances whose counts one workgroup adds up
-// N*G of an instance held in LDS, 21 bytes a flow and 8 a GPU: 90 KB of a CU's 160 at 4096 flows of 8 rails, 119 of one.  No limit of speed: up to 5376
-// fit for any N, 8192 for none, and 5120 of 8 rails (80 nodes, 4.9 M chunks) take 87 us by one workgroup each, 146 by the separate kernels.
+// N*G of an instance held in LDS, 19 bytes a flow and 8 a GPU: 82 KB of a CU's 160 at 4096 flows of 8 rails, 111 of one.  No limit of speed: up to 6000
+// fit for any N, 8192 from 16 rails on, and 5120 of 8 rails (80 nodes, 4.9 M chunks) take 87 us by one workgroup each, 146 by the separate kernels.
 constexpr int kSsMaxFlows = 4096;
 constexpr int kSsWideFlows = 1024;      // N*G above which an instance's workgroup has 1024 threads instead of 512: 16 flows a thread of the sort at most
 // Instances of more than 2048 flows: one workgroup per CU, one round of them.  512 of 4096 flows and 61 K chunks even / skewed 145 / 241 us, by the separate
