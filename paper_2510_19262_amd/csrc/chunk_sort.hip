@@ -27,13 +27,14 @@ constexpr int kFillTile = kFillThreads / 64 * kFillWindow;
 constexpr int kFillGranule = 8;     // log2 of the neighbouring tiles that the workgroups of one XCD write: 1 MiB of an array
 // Workgroups of the launch: a tile each for all records there is room for, because a wavefront that exits behind its stores is what writes fastest, up to a limit, because one that finds
 // nothing to do costs 0.21 ns (the chip starts a wavefront every 0.053 ns) and the host does not know how much of the room is used.  The limit is 2^15 (7 us in all, what the other
-// launches of a call cost) and one more for every 32 flows, 6.6 ps a flow beside the 10 to 25 that the rest of the call takes.  What lies behind it goes to the last workgroups
+// launches of a call cost) and one more for every 16 flows, 13 ps a flow beside the 10 to 25 that the rest of the call takes (for every 32, the fill of 3.86 G records of 32 768 instances
+// of 2048 flows took 10.4 ms for 9.2).  What lies behind it goes to the last workgroups
 // by tickets, so that what is being written stays close together: to as many as the chip holds, or half of them with perm, whose larger records fill the way to memory with fewer
 // (1024 / 2048, with perm 3.6 G records of 1024 GPUs 7050 / 7560, without 6400 / 4875).  us, chunk_sort, all tiles launched / 2^15 and tickets / 2^15 workgroups that go
 // round: 226 M records of 512 GPUs 597 / 626 / 640, 489 M of 256 GPUs 1045 / 1087 / 1200, 3.7 G of 1024 GPUs without perm 4620 / 5040 / 5500; the other way round, 8.6 M records of
 // 64 GPUs and room for 8.6 M / 430 M / 3.4 G 33 / 117 / 740 when all tiles are launched, 33 / 37 / 37 so.  The 5 to 18 % stay however the rest is cut: tickets of two and four tiles, 8 to
 // 64 counters, the next tile's instance fetched ahead, flow starts through the scalar cache, two windows side by side, waves of 2 to 64 windows launched for all of them.
-constexpr int64_t kFillTiles = 1 << 15, kFillTileFlows = 32, kFillTilesMost = 1 << 22;   // 2^22: the launch stays within 2^30 threads
+constexpr int64_t kFillTiles = 1 << 15, kFillTileFlows = 16, kFillTilesMost = 1 << 22;   // 2^22: the launch stays within 2^30 threads
 constexpr unsigned kFillRounds = 2048, kFillRoundsPerm = 1024;
 // Counters of tickets and the words from one to the next, a cache line.  A line takes 16 ns an addition: eight counters 7.4 ms for the 3.7 G records.  A batch of few flows has no room for
 // them; all its workgroups go round.
